@@ -1,58 +1,195 @@
-// fp32 path: the same pipeline for float inputs, built from one strided LDS-tiled contraction that
-// accumulates in fp64 plus two row-wise kernels over a materialised row chunk of logits.  It is the
-// accuracy path (small shapes, tolerance 1e-5), not the throughput path.
+// fp32 path: the same pipeline for float inputs, built from one strided contraction on the fp64 matrix
+// instruction plus two row-wise kernels over a materialised row chunk of logits.  It is the accuracy path
+// (tolerance 1e-5).
+#include <type_traits>
+
 #include "rapid_internal.h"
 
 namespace rapid {
 
 namespace {
 
-constexpr int TS = 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-__global__ void f32_gemm_kernel(F32Gemm g) {
-    __shared__ float As[TS][TS + 1];
-    __shared__ float Bs[TS][TS + 1];
+// One operand of a contraction: element (o, k) at p[omap(o) * so + kmap(k) * sk].
+struct F64Operand {
+    const float* p;
+    int64_t so, sk;
+    const int32_t *omap, *kmap;   // optional index maps, already offset
+};
+
+// C[i][j] (+)= alpha sum_k A(i, k) B(j, k) on the fp64 matrix instruction (v_mfma_f64_16x16x4_f64): the operands are
+// fp32 in memory and are widened on the way into LDS, the accumulators are fp64.  Bound by the fp64 matrix rate: the
+// instruction on its own, from registers, sustains 47 TFLOP/s; 4096 rows x V = 4096 x d = 256 run at 45 (logits), 48
+// (dHidden) and 40 (dW).  (A fused multiply-add per lane on a 16 x 16 tile, which this replaces, ran at 12: an LDS read
+// and a conversion per operand and product.)
+// A workgroup of 4 waves owns TI x TJ of C.  SPLIT: every wave works on the whole tile but on a quarter of the
+// contraction index (groups of 4 dealt round robin) and the four sums are added in wave order at the end; that is
+// for shapes with too few tiles to fill the chip.  Otherwise the waves share the tile 2 x 2 and each element is
+// summed in the order of k whatever the tile size, so the logits of a row do not depend on which size ran.
+// KA / KB: the operand is contiguous along k (else along its outer index); MA / MB: its k goes through the map.
+// These are template arguments because a branch around a load keeps the loads of a step from being in flight together.
+// Global loads run two steps ahead of the MFMAs (two register sets; a step's MFMAs take less than a trip to memory).
+// LDS rows are KS + 2 doubles apart (an odd multiple of 16 bytes): a fragment read is free of bank conflicts.
+template <int TI, int TJ, int KS, bool SPLIT, bool KA, bool KB, bool MA, bool MB>
+__global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand B, F32Gemm g) {
+    constexpr int WI = SPLIT ? TI / 16 : TI / 32, WJ = SPLIT ? TJ / 16 : TJ / 32, LD = KS + 2;
+    constexpr int QA = TI * KS / 256, QB = TJ * KS / 256;   // elements per thread and step
+    static_assert(KS <= 64 && 256 % KS == 0 && 256 % TI == 0 && 256 % TJ == 0, "thread layout of the loads");
+    __shared__ double As[2][TI * LD], Bs[2][TJ * LD];
     int64_t I = g.I, Kd = g.Kd;
     if (g.counts) {
-        int64_t lim = (int64_t)g.counts[CNT_M] - g.i0;
-        lim = lim < 0 ? 0 : lim;
-        if (g.limit_k) Kd = lim < Kd ? lim : Kd;
-        else I = lim < I ? lim : I;
+        const int64_t M = g.counts[CNT_M], left = M > g.i0 ? M - g.i0 : 0;
+        if (g.skip_last && left <= g.I) return;   // what this launch would form is still in C
+        if (g.limit_k) Kd = left < Kd ? left : Kd;
+        else I = left < I ? left : I;
     }
-    const int64_t ib = (int64_t)blockIdx.y * TS, jb = (int64_t)blockIdx.x * TS;
+    const int64_t ib = (int64_t)blockIdx.y * TI, jb = (int64_t)blockIdx.x * TJ;
     if (ib >= I) return;
     if (g.limit_k && Kd == 0 && g.beta) return;
-    const int ty = threadIdx.y, tx = threadIdx.x;
-    const int64_t i = ib + ty, j = jb + tx;
-    double acc = 0.0;
-    for (int64_t k0 = 0; k0 < Kd; k0 += TS) {
-        // A tile: element (i = ib + ty, k = k0 + tx)
-        {
-            const int64_t ai = ib + ty, ak = k0 + tx;
-            float v = 0.f;
-            if (ai < I && ak < Kd) {
-                const int64_t r = g.a_imap ? (int64_t)g.a_imap[g.i0 + ai] : ai;
-                const int64_t kk = g.a_kmap ? (int64_t)g.a_kmap[g.i0 + ak] : ak;
-                v = g.A[r * g.sa_i + kk * g.sa_k];
-            }
-            As[ty][tx] = v;
-        }
-        {
-            const int64_t bk = k0 + ty, bj = jb + tx;
-            float v = 0.f;
-            if (bk < Kd && bj < g.J) v = g.B[bk * g.sb_k + bj * g.sb_j];
-            Bs[ty][tx] = v;
-        }
-        __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+    // Thread's share of a step: consecutive threads along whichever index is contiguous in memory.  The outer index
+    // of a thread's element q stays the same over the steps, so its address is formed (and its map read) once and
+    // then advanced; rows past the end repeat the last one (their sums are not stored).
+    auto outer = [&](bool kc, int T, int q) { const int e = tid + 256 * q; return kc ? e / KS : e % T; };
+    auto inner = [&](bool kc, int T, int q) { const int e = tid + 256 * q; return kc ? e % KS : e / T; };
+    auto first = [&](const F64Operand& X, bool kc, bool map, int T, int q, int64_t base, int64_t limit) {
+        int64_t o = base + outer(kc, T, q);
+        o = o < limit ? o : limit - 1;
+        return X.p + (X.omap ? (int64_t)X.omap[o] : o) * X.so + (map ? 0 : inner(kc, T, q) * X.sk);
+    };
+    const float* pa[QA];
+    const float* pb[QB];
 #pragma unroll
-        for (int kk = 0; kk < TS; ++kk) acc += (double)As[ty][kk] * (double)Bs[kk][tx];
+    for (int q = 0; q < QA; ++q) pa[q] = first(A, KA, MA, TI, q, ib, I);
+#pragma unroll
+    for (int q = 0; q < QB; ++q) pb[q] = first(B, KB, MB, TJ, q, jb, g.J);
+    const int64_t step_a = KS * A.sk, step_b = KS * B.sk;
+    float ra[2][QA], rb[2][QB];
+    // mapped operand: the map's entries are read one step before the elements they lead to
+    int32_t next[MA ? QA : MB ? QB : 1];
+    auto fetch_map = [&](int64_t k0) {
+#pragma unroll
+        for (int q = 0; q < (MA ? QA : MB ? QB : 0); ++q) {
+            const int64_t k = k0 + (MA ? inner(KA, TI, q) : inner(KB, TJ, q));
+            next[q] = (MA ? A.kmap : B.kmap)[k < Kd ? k : Kd - 1];
+        }
+    };
+    auto fetch_whole = [&](auto set, int64_t k0) {
+#pragma unroll
+        for (int q = 0; q < QA; ++q) {
+            if constexpr (MA) ra[set][q] = pa[q][(int64_t)next[q] * A.sk];
+            else { ra[set][q] = *pa[q]; pa[q] += step_a; }
+        }
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+            if constexpr (MB) rb[set][q] = pb[q][(int64_t)next[q] * B.sk];
+            else { rb[set][q] = *pb[q]; pb[q] += step_b; }
+        }
+        fetch_map(k0 + KS);
+    };
+    auto fetch = [&](auto set, int64_t k0) {   // also the last step, which may be short, and steps that do not exist
+        if (k0 + KS <= Kd) { fetch_whole(set, k0); return; }
+        if (k0 >= Kd) return;
+#pragma unroll
+        for (int q = 0; q < QA; ++q) {
+            const int64_t k = k0 + inner(KA, TI, q);
+            ra[set][q] = k < Kd ? pa[q][MA ? (int64_t)next[q] * A.sk : 0] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+            const int64_t k = k0 + inner(KB, TJ, q);
+            rb[set][q] = k < Kd ? pb[q][MB ? (int64_t)next[q] * B.sk : 0] : 0.f;
+        }
+    };
+    auto stage = [&](auto set) {
+#pragma unroll
+        for (int q = 0; q < QA; ++q) As[set][outer(KA, TI, q) * LD + inner(KA, TI, q)] = (double)ra[set][q];
+#pragma unroll
+        for (int q = 0; q < QB; ++q) Bs[set][outer(KB, TJ, q) * LD + inner(KB, TJ, q)] = (double)rb[set][q];
+    };
+
+    f64x4 acc[WI][WJ];
+#pragma unroll
+    for (int x = 0; x < WI; ++x)
+#pragma unroll
+        for (int y = 0; y < WJ; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int wi = SPLIT ? 0 : (wave & 1) * (WI * 16), wj = SPLIT ? 0 : (wave >> 1) * (WJ * 16);
+    const int fo = lane & 15, fk = lane >> 4;   // fragment: row (or column) lane % 16, contraction index lane / 16
+    auto multiply = [&](auto set) {
+#pragma unroll
+        for (int kk = 0; kk < KS / 4; kk += SPLIT ? 4 : 1) {
+            const int k = (kk + (SPLIT ? wave : 0)) * 4 + fk;
+            double a[WI], b[WJ];
+#pragma unroll
+            for (int x = 0; x < WI; ++x) a[x] = As[set][(wi + x * 16 + fo) * LD + k];
+#pragma unroll
+            for (int y = 0; y < WJ; ++y) b[y] = Bs[set][(wj + y * 16 + fo) * LD + k];
+#pragma unroll
+            for (int x = 0; x < WI; ++x)
+#pragma unroll
+                for (int y = 0; y < WJ; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
+        }
+    };
+    const std::integral_constant<int, 0> s0;
+    const std::integral_constant<int, 1> s1;
+    if (Kd > 0) fetch_map(0);
+    fetch(s0, 0);
+    fetch(s1, KS);
+    if (Kd > 0) stage(s0);
+    __syncthreads();
+    // step k0 is in LDS, step k0 + KS in registers
+    int64_t k0 = 0;
+    for (; k0 + 4 * KS <= Kd; k0 += 2 * KS) {
+        fetch_whole(s0, k0 + 2 * KS);
+        multiply(s0);
+        stage(s1);
+        __syncthreads();
+        fetch_whole(s1, k0 + 3 * KS);
+        multiply(s1);
+        stage(s0);
         __syncthreads();
     }
-    if (i < I && j < g.J) {
+    for (; k0 < Kd; k0 += 2 * KS) {
+        fetch(s0, k0 + 2 * KS);
+        multiply(s0);
+        if (k0 + KS >= Kd) break;
+        stage(s1);
+        __syncthreads();
+        fetch(s1, k0 + 3 * KS);
+        multiply(s1);
+        if (k0 + 2 * KS >= Kd) break;
+        stage(s0);
+        __syncthreads();
+    }
+
+    // element (i, j) of a block sits in lane (i % 4) * 16 + j, register i / 4
+    auto write = [&](int64_t i, int64_t j, double sum) {
+        if (i >= I || j >= g.J) return;
         const int64_t r = g.c_rows ? (int64_t)g.c_rows[g.i0 + i] : i;
         float* p = g.C + r * g.sc_i + j * g.sc_j;
-        const double v = acc * (double)g.alpha;
+        const double v = sum * (double)g.alpha;
         *p = (float)(g.beta ? (double)*p + v : v);
+    };
+    if constexpr (SPLIT) {
+        __shared__ double sum[4][TI * TJ];
+#pragma unroll
+        for (int x = 0; x < WI; ++x)
+#pragma unroll
+            for (int y = 0; y < WJ; ++y)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[wave][(x * 16 + v * 4 + fk) * TJ + y * 16 + fo] = acc[x][y][v];
+        __syncthreads();
+        for (int e = tid; e < TI * TJ; e += 256)
+            write(ib + e / TJ, jb + e % TJ, (sum[0][e] + sum[1][e]) + (sum[2][e] + sum[3][e]));
+    } else {
+#pragma unroll
+        for (int x = 0; x < WI; ++x)
+#pragma unroll
+            for (int y = 0; y < WJ; ++y)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) write(ib + wi + x * 16 + v * 4 + fk, jb + wj + y * 16 + fo, acc[x][y][v]);
     }
 }
 
@@ -109,12 +246,34 @@ __global__ void f32_dz_kernel(float* __restrict__ z, int64_t V, int64_t m0, cons
     }
 }
 
+// Tile: 64 x 64 where that gives every CU two workgroups (a SIMD needs two waves at least to keep the instruction
+// going: 35 TFLOP/s with one, 46 with two), else 32 x 32, else (dHidden and dW of small shapes, fewer tiles than CUs)
+// 16 x 16 with the contraction shared out over the waves: 10 us for 640 rows x V = 1000 x d = 64, 31 us before.
+template <bool KA, bool KB, bool MA, bool MB>
+void launch_tiles(const F64Operand& A, const F64Operand& B, const F32Gemm& g, hipStream_t st) {
+    auto tiles = [&](int T) { return ((g.I + T - 1) / T) * ((g.J + T - 1) / T); };
+    auto grid = [&](int T) { return dim3((unsigned)((g.J + T - 1) / T), (unsigned)((g.I + T - 1) / T)); };
+    if (tiles(64) >= 512) f64_mfma_kernel<64, 64, 16, false, KA, KB, MA, MB><<<grid(64), 256, 0, st>>>(A, B, g);
+    else if (tiles(32) >= 256 || !g.may_split) f64_mfma_kernel<32, 32, 32, false, KA, KB, MA, MB><<<grid(32), 256, 0, st>>>(A, B, g);
+    else f64_mfma_kernel<16, 16, 64, true, KA, KB, MA, MB><<<grid(16), 256, 0, st>>>(A, B, g);
+}
+
 }  // namespace
 
-void launch_f32_gemm(const F32Gemm& g, hipStream_t st) {
-    if (g.I <= 0 || g.J <= 0) return;
-    dim3 grid((unsigned)((g.J + TS - 1) / TS), (unsigned)((g.I + TS - 1) / TS));
-    f32_gemm_kernel<<<grid, dim3(TS, TS), 0, st>>>(g);
+void launch_f32_gemm(const F32Gemm& in, hipStream_t st) {
+    if (in.I <= 0 || in.J <= 0) return;
+    F32Gemm g = in;
+    F64Operand A{g.A, g.sa_i, g.sa_k, g.a_imap ? g.a_imap + g.i0 : nullptr, g.a_kmap ? g.a_kmap + g.i0 : nullptr};
+    F64Operand B{g.B, g.sb_j, g.sb_k, nullptr, nullptr};
+    if (g.sc_i == 1 && g.limit_k) {   // C is contiguous along i: form its transpose, so that a store covers whole lines
+        const F64Operand t = A; A = B; B = t;
+        const int64_t n = g.I; g.I = g.J; g.J = n;
+        g.sc_i = g.sc_j; g.sc_j = 1;
+    }
+    if (A.kmap) launch_tiles<false, false, true, false>(A, B, g, st);        // dW: both operands contiguous along their outer index
+    else if (B.kmap) launch_tiles<false, false, false, true>(A, B, g, st);
+    else if (B.sk == 1) launch_tiles<true, true, false, false>(A, B, g, st);
+    else launch_tiles<true, false, false, false>(A, B, g, st);
 }
 
 void launch_f32_row_lse(const float* z, int64_t V, int64_t rows, int64_t m0, const int32_t* tokc,

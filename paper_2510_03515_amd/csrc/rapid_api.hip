@@ -1230,9 +1230,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         }
     } else {
         float* z = at<float>(ws, p.chunk0);
+        // Last chunk first: the forward went through the chunks in order, so the logits of the last one that holds tokens
+        // (known on the device only) are still in z and need not be formed again.
         int chunk = 0;
         Span sp(ST_F32, st);
-        for (int64_t m0 = 0; m0 < p.Mmax; m0 += p.Mc, ++chunk) {
+        for (int64_t m0 = (p.Mmax - 1) / p.Mc * p.Mc; m0 >= 0; m0 -= p.Mc, ++chunk) {
             const int64_t rows = (p.Mmax - m0) < p.Mc ? (p.Mmax - m0) : p.Mc;
             F32Gemm gz;
             memset(&gz, 0, sizeof(gz));
@@ -1240,7 +1242,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             gz.B = (const float*)W;
             if (o.w_layout == RAPID_W_DV) { gz.sb_k = V; gz.sb_j = 1; } else { gz.sb_k = 1; gz.sb_j = d; }
             gz.C = z; gz.sc_i = V; gz.sc_j = 1;
-            gz.I = rows; gz.J = V; gz.Kd = d; gz.beta = 0; gz.counts = counts; gz.i0 = m0; gz.alpha = inv_temp;
+            gz.I = rows; gz.J = V; gz.Kd = d; gz.beta = 0; gz.counts = counts; gz.i0 = m0; gz.alpha = inv_temp; gz.skip_last = 1;
             launch_f32_gemm(gz, st);
             launch_f32_dz(z, V, rows, m0, tokc, lse_c, rowg, inv_temp, counts, st);
             // dH[row] = dz[row, :] . W^T
@@ -1250,7 +1252,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             gh.B = (const float*)W;   // B(k = v, j = k') = W(k', v)
             if (o.w_layout == RAPID_W_DV) { gh.sb_k = 1; gh.sb_j = V; } else { gh.sb_k = d; gh.sb_j = 1; }
             gh.C = (float*)dhidden_out; gh.sc_i = d; gh.sc_j = 1; gh.c_rows = row_index;
-            gh.I = rows; gh.J = d; gh.Kd = V; gh.beta = 0; gh.counts = counts; gh.i0 = m0; gh.alpha = 1.f;
+            gh.I = rows; gh.J = d; gh.Kd = V; gh.beta = 0; gh.counts = counts; gh.i0 = m0; gh.alpha = 1.f; gh.may_split = 1;
             launch_f32_gemm(gh, st);
             // dW(k', v) += sum_rows H[row, k'] dz[row, v]
             F32Gemm gw;
@@ -1260,7 +1262,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             gw.C = dW32;
             if (o.w_layout == RAPID_W_DV) { gw.sc_i = V; gw.sc_j = 1; } else { gw.sc_i = 1; gw.sc_j = d; }
             gw.I = d; gw.J = V; gw.Kd = rows; gw.beta = (chunk > 0 || o.accumulate_dw) ? 1 : 0;
-            gw.counts = counts; gw.i0 = m0; gw.limit_k = 1; gw.alpha = 1.f;
+            gw.counts = counts; gw.i0 = m0; gw.limit_k = 1; gw.alpha = 1.f; gw.may_split = 1;
             launch_f32_gemm(gw, st);
         }
     }

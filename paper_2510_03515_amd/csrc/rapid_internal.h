@@ -301,6 +301,9 @@ struct F32Gemm {
     const int32_t* counts; int64_t i0;   // if counts: I (or Kd when limit_k) is clipped to M - i0
     int limit_k;
     float alpha;
+    int may_split;           // 1: the order of summation may depend on the shape (never for logits: two calls on one batch
+                             // have to agree in every bit)
+    int skip_last;           // 1: nothing to do if no row lies past this chunk (its C is still what this launch would form)
 };
 void launch_f32_gemm(const F32Gemm& g, hipStream_t st);
 // row-wise: lse, logp, gathered logit from a materialised logits chunk z [rows, V]
