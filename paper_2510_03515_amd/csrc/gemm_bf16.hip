@@ -1002,34 +1002,34 @@ __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
 
 // ------------------------------------------------------------------------------------------ dh
 // The tiles of dHidden are long (the contraction runs over the whole vocabulary) and few: a launch has
-// a handful of rounds of one tile per workgroup, and a last round that is only partly filled would
-// leave most of the chip idle for a whole tile.  So the last, partial round of an XCD's share is not
-// dealt out tile by tile: the contraction of each of its rem tiles is cut into S equal segments, and the
-// rem x S (tile, segment) units are dealt out in short rounds, segment by segment, so that the workgroups
-// of a short round are on the same K steps and share operand panels in the L2 as in a whole round.  A
-// workgroup leaves the fp32 accumulators of a unit in `part`, and dh_reduce_kernel adds the S pieces of a
-// tile in segment order and stores the result.  The last round then takes ceil(rem S / workgroups) / S of
-// a tile's time, and the result does not depend on timing.
-constexpr int DH_UNITS_PER_XCD = 64;   // partial tiles an XCD's last round may leave (dh_part_bytes)
-struct DhShare {       // an XCD's share of the order, and how its last round is cut
-    int total, per, wgs, mine, full_rounds, rem, segs;
+// a handful of rounds of one tile per workgroup (or, for a small batch, less than one), and a last round that is
+// only partly filled would leave most of the chip idle for a whole tile.  So the rem tiles of the last, partial round
+// are not dealt out tile by tile: the contraction of each is cut into S equal segments, and the rem x S (segment, tile)
+// units, in that order, are dealt to the XCDs in contiguous shares.  An XCD thus works on one or a few segments of
+// all those tiles and reads only those stretches of W and of the row chunk: both come from memory about once,
+// however small the batch.  A workgroup leaves the fp32 accumulators of a unit in `part`, and dh_reduce_kernel adds
+// the S pieces of a tile in segment order and stores the result, which does not depend on timing.
+// Measured, d = 1536, V = 151936, about 2200 rows: 1.73 ms when a launch had no more workgroups than tiles, 0.76 ms now
+// (d = 256, V = 4096, 1800 rows: 104 -> 21 us, and the second pass 28 -> 11 us).
+constexpr int DH_MAX_UNITS = 512;      // partial tiles a launch may leave (dh_part_bytes)
+struct DhShare {       // how a launch of `grid` workgroups works through `total` tiles
+    int wgs, full_rounds, rem, segs, unit_share;
     bool cut;
-    __device__ __forceinline__ DhShare(int tilesD, int tilesM, int grid, int x, int ktiles, bool can_cut) {
-        total = tilesD * tilesM; per = (total + 7) / 8; wgs = grid / 8;
-        mine = max(0, min(per, total - x * per));
-        full_rounds = mine / wgs; rem = mine - full_rounds * wgs;
-        // the number of segments that makes the last round shortest: rounds(S) / S with rounds(S) = ceil(rem S / wgs)
+    __device__ __forceinline__ DhShare(int total, int grid, int ktiles, bool can_cut) {
+        wgs = grid / 8; full_rounds = total / grid; rem = total - full_rounds * grid;
+        // S with the shortest last round, counted in K steps of a workgroup: the segments of its units, about 5 steps for
+        // filling the pipeline and storing the accumulators, and the second pass over 256 KiB per unit (1 / 25 step each)
         segs = 1;
-        int best_rounds = 1;
+        float best = (float)ktiles + 4.f;
         if (can_cut && rem > 0) {
-            for (int sg = 2; sg <= 8 && sg <= ktiles && rem * sg <= DH_UNITS_PER_XCD; ++sg) {
-                const int r = (rem * sg + wgs - 1) / wgs;
-                if (r * segs < best_rounds * sg) { segs = sg; best_rounds = r; }
+            for (int sg = 2; sg <= 64 && rem * sg <= DH_MAX_UNITS && sg * 4 <= ktiles; sg += sg < 8 ? 1 : sg / 4) {
+                const int rounds = (rem * sg + grid - 1) / grid;
+                const float cost = (float)rounds * ((float)ktiles / (float)sg + 5.f) + (float)(rem * sg) * 0.04f;
+                if (cost < best) { best = cost; segs = sg; }
             }
         }
-        // a cut costs a second pass over the partial tiles: it has to save a fifth of a tile's time at least
-        cut = segs > 1 && best_rounds * 5 <= segs * 4;
-        if (!cut) segs = 1;
+        cut = segs > 1;
+        unit_share = (rem * segs + 7) / 8;
     }
 };
 
@@ -1080,45 +1080,37 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
     // the order (and with it the split over the XCDs) covers the row tiles that hold tokens only: a
     // short last chunk would otherwise leave whole XCDs with nothing but empty tiles
     const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
-    const int x = blockIdx.x & 7, w = blockIdx.x >> 3;
+    const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
     const int ktiles = (int)(a.Vpad / K_TILE);
-    const DhShare sh(tilesD, tilesM, gridDim.x, x, ktiles, a.part != nullptr && a.pace == nullptr);
+    const DhShare sh(tilesD * tilesM, grid, ktiles, a.part != nullptr);
     const int gi = a.gi > 0 ? a.gi : tilesD;
-    // pacing of the launch's workgroups (see GridPace): with total = 8 * per tiles (or fewer in the last
-    // XCD shares) the workgroups of round r are those whose id is a valid tile
-    GridPace pace{a.pace, 0u, 0u, a.pace ? a.pace_every : 0};
-    unsigned before = 0;   // valid tiles of the rounds before this one, over all XCDs
-    // rounds dealt out tile by tile: uniform over the launch when pacing is on (nobody cuts then)
-    const int whole_rounds = sh.cut ? sh.full_rounds : (pace.every ? (sh.per + sh.wgs - 1) / sh.wgs : (sh.mine + sh.wgs - 1) / sh.wgs);
-    for (int round = 0; round < whole_rounds; ++round) {
-        const int pos = round * sh.wgs + w;
-        unsigned now = 0;
-        if (pace.every) {
-            for (int xx = 0; xx < 8; ++xx) {
-                const int mine = max(0, min(sh.per, sh.total - xx * sh.per));
-                now += (unsigned)max(0, min(sh.wgs, mine - round * sh.wgs));
-            }
-        }
-        if (pos >= sh.mine) { before += now; continue; }
-        const TileId t = tile_of_vid(x * sh.per + pos, tilesD, tilesM, gi);
+    GridPace pace{a.pace, 0u, (unsigned)grid, a.pace ? a.pace_every : 0};   // see GridPace
+    const unsigned meetings = (unsigned)(ktiles / (pace.every ? pace.every : 1));
+    for (int round = 0; round < sh.full_rounds; ++round) {
+        const TileId t = tile_of_vid((x * sh.full_rounds + round) * sh.wgs + w, tilesD, tilesM, gi);
         f32x16 acc[WI][WJ];
-        pace.n = now;
-        pace.base = (unsigned)(ktiles / (pace.every ? pace.every : 1)) * before;
-        before += now;
+        pace.base = meetings * (unsigned)(grid * round);
         dh_contract<S, GridPace>(a, t, 0, ktiles, lds, acc, pace);
         dh_store<S>(a, t, M, acc);
     }
-    if (!sh.cut) return;
-    // the last round: unit u = (segment u / rem, tile u % rem), dealt out in rounds of one unit per workgroup;
-    // its accumulators go to part[x * DH_UNITS_PER_XCD + u]
-    for (int u = w; u < sh.rem * sh.segs; u += sh.wgs) {
+    // the last round: unit u = (segment u / rem, tile u % rem); the accumulators of a cut tile go to part[u]
+    pace.base = meetings * (unsigned)(grid * sh.full_rounds);
+    pace.n = (unsigned)sh.rem;
+    for (int pos = w; pos < sh.unit_share; pos += sh.wgs) {
+        const int u = x * sh.unit_share + pos;
+        if (u >= sh.rem * sh.segs) break;
         const int seg = u / sh.rem, tpos = u - seg * sh.rem;
         const int k0 = (int)((int64_t)ktiles * seg / sh.segs), k1 = (int)((int64_t)ktiles * (seg + 1) / sh.segs);
-        const TileId t = tile_of_vid(x * sh.per + sh.full_rounds * sh.wgs + tpos, tilesD, tilesM, gi);
+        const TileId t = tile_of_vid(sh.full_rounds * grid + tpos, tilesD, tilesM, gi);
         f32x16 acc[WI][WJ];
+        if (!sh.cut) {
+            dh_contract<S, GridPace>(a, t, k0, k1, lds, acc, pace);
+            dh_store<S>(a, t, M, acc);
+            continue;
+        }
         dh_contract<S, NoPace>(a, t, k0, k1, lds, acc, NoPace());
-        // the accumulators as they are: register r of thread tid at part[unit slot][r][tid]
-        int64_t off = ((int64_t)x * DH_UNITS_PER_XCD + u) * (S::BI * S::BJ) + threadIdx.x;
+        // the accumulators as they are: register r of thread tid at part[u][r][tid]
+        int64_t off = (int64_t)u * (S::BI * S::BJ) + threadIdx.x;
 #pragma unroll
         for (int ib = 0; ib < WI; ++ib)
 #pragma unroll
@@ -1131,8 +1123,9 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
     }
 }
 
-// adds the pieces of the tiles that dh_kernel cut (same launch geometry: grid_of_dh says how many
-// workgroups that launch had) and stores them; one workgroup per (XCD, tile of its last round)
+// adds the pieces of the tiles that dh_kernel cut (grid_of_dh: the number of workgroups of that launch) and stores
+// them; workgroup (t, b) does the 32 x 32 block b of every wave of tile t of the last round.  The pieces are added in
+// segment order, 16 loads of a piece in flight together.
 template <class S>
 __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_dh) {
     constexpr int WI = S::WI, WJ = S::WJ;
@@ -1140,44 +1133,32 @@ __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.m0 >= Mr) return;
     const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
-    const int x = blockIdx.x & 7, tpos = blockIdx.x >> 3;
-    const int ktiles = (int)(a.Vpad / K_TILE);
-    const DhShare sh(tilesD, tilesM, grid_of_dh, x, ktiles, true);
+    const DhShare sh(tilesD * tilesM, grid_of_dh, (int)(a.Vpad / K_TILE), true);
+    const int tpos = blockIdx.x, ib = blockIdx.y / WJ, jb = blockIdx.y % WJ;
     if (!sh.cut || tpos >= sh.rem) return;
-    const TileId t = tile_of_vid(x * sh.per + sh.full_rounds * sh.wgs + tpos, tilesD, tilesM, a.gi > 0 ? a.gi : tilesD);
-    // One 32 x 32 block at a time, its pieces added in segment order (a fixed order of summation).  The 16
-    // loads of a piece are independent and in flight together; with all 256 accumulators of the tile live at
-    // once the loads went out one by one, each a trip to memory, and a tile with five pieces took 3 ms.
+    const TileId t = tile_of_vid(sh.full_rounds * grid_of_dh + tpos, tilesD, tilesM, a.gi > 0 ? a.gi : tilesD);
     const Lane<S> L;
-    const int64_t i_base = (int64_t)t.ti * S::BI + L.wave_i * (WI * 32);
+    const int64_t i_base = (int64_t)t.ti * S::BI + L.wave_i * (WI * 32) + ib * 32;
+    const int64_t j = a.m0 + (int64_t)t.tj * S::BJ + L.wave_j * (WJ * 32) + jb * 32 + L.lj;
+    if (j >= M) return;
+    float sum[16];
 #pragma unroll
-    for (int jb = 0; jb < WJ; ++jb) {
-        const int64_t j = a.m0 + (int64_t)t.tj * S::BJ + L.wave_j * (WJ * 32) + jb * 32 + L.lj;
-        const bool row_live = j < M;
-        bf16_t* out = a.dhidden + (row_live ? (int64_t)a.row_index[j] * a.d : 0);
-        const float cj = (a.rowc && row_live) ? a.rowc[j] : 1.f;
+    for (int v = 0; v < 16; ++v) sum[v] = 0.f;
+    const float* in = a.part + (int64_t)tpos * (S::BI * S::BJ) + threadIdx.x + (int64_t)((ib * WJ + jb) * 16) * S::NT;
+    for (int seg = 0; seg < sh.segs; ++seg, in += (int64_t)sh.rem * (S::BI * S::BJ)) {
+        float got[16];
 #pragma unroll
-        for (int ib = 0; ib < WI; ++ib) {
-            float sum[16];
+        for (int v = 0; v < 16; ++v) got[v] = in[v * S::NT];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-            for (int seg = 0; seg < sh.segs; ++seg) {
-                const float* in = a.part + ((int64_t)x * DH_UNITS_PER_XCD + seg * sh.rem + tpos) * (S::BI * S::BJ) + threadIdx.x +
-                                  (int64_t)((ib * WJ + jb) * 16) * S::NT;
-                float got[16];
+        for (int v = 0; v < 16; ++v) sum[v] += got[v];
+    }
+    bf16_t* out = a.dhidden + (int64_t)a.row_index[j] * a.d;
+    const float cj = a.rowc ? a.rowc[j] : 1.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) got[v] = in[v * S::NT];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) sum[v] += got[v];
-            }
-            if (!row_live) continue;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t i0 = i_base + ib * 32 + q * 8 + L.hi * 4;
-                if (i0 < a.d)
-                    *(uint2*)(out + i0) = pack_bf16x4(cj * sum[q * 4], cj * sum[q * 4 + 1], cj * sum[q * 4 + 2], cj * sum[q * 4 + 3]);
-            }
-        }
+    for (int q = 0; q < 4; ++q) {
+        const int64_t i0 = i_base + q * 8 + L.hi * 4;
+        if (i0 < a.d)
+            *(uint2*)(out + i0) = pack_bf16x4(cj * sum[q * 4], cj * sum[q * 4 + 1], cj * sum[q * 4 + 2], cj * sum[q * 4 + 3]);
     }
 }
 
@@ -1386,12 +1367,14 @@ void launch_dz_t(const DzArgs& a, hipStream_t st) {
 template <class S>
 void launch_dh_t(const DhArgs& a, hipStream_t st) {
     allow_lds<&dh_kernel<S>>(S::LDS_BYTES);
-    const unsigned grid = grid_for((int)(a.dpadR / S::BI), a.tilesM);
+    const int tilesD = (int)(a.dpadR / S::BI);
     DhArgs b = a;
-    // a cut last round needs DH_UNITS_PER_XCD tiles of fp32 scratch per XCD and whole XCD shares of workgroups
-    if (grid % 8 != 0 || grid < 16 || (size_t)8 * DH_UNITS_PER_XCD * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
+    if ((size_t)DH_MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
+    // with scratch for cut tiles a launch of few tiles takes the whole chip as well
+    const unsigned grid = b.part ? (unsigned)(g_num_cu.load() / 8 * 8) : grid_for(tilesD, a.tilesM);
     dh_kernel<S><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
-    if (b.part && !b.pace) dh_reduce_kernel<S><<<grid, S::NT, 0, st>>>(b, (int)grid);
+    const int64_t tiles = (int64_t)tilesD * a.tilesM;
+    if (b.part) dh_reduce_kernel<S><<<dim3((unsigned)(tiles < grid ? tiles : grid), S::WI * S::WJ), S::NT, 0, st>>>(b, (int)grid);
 }
 template <class S, bool DEEP = false>
 void launch_dw_t(const DwArgs& a, hipStream_t st) {
@@ -1401,8 +1384,7 @@ void launch_dw_t(const DwArgs& a, hipStream_t st) {
 
 }  // namespace
 
-// DH_UNITS_PER_XCD fp32 tiles of 256 x 256 for each of the 8 XCDs
-size_t dh_part_bytes() { return (size_t)8 * DH_UNITS_PER_XCD * 256 * 256 * 4; }
+size_t dh_part_bytes() { return (size_t)DH_MAX_UNITS * 256 * 256 * 4; }
 void set_waves_per_workgroup(int n) { g_waves = (n == 4 || n == 8 || n == 16) ? n : 0; }
 void set_cu_count(int n) { g_num_cu = n >= 8 ? n : 8; }
 

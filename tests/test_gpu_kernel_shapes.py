@@ -1,6 +1,7 @@
 """GPU parity at the sizes where the kernels' tiles, cuts and dispatch rules change over, against the float64 oracle with
 the bounds of test_gpu_parity."""
 import pytest
+import torch
 
 from paper_2510_03515_amd import workloads as wl
 from test_gpu_parity import _check_pair, _run_pair, rb  # noqa: F401  (rb is the library fixture)
@@ -21,3 +22,33 @@ def test_fp64_matrix_tiles(rb, d, V, prompts, length, layout, min_ws):
     spec = wl.small_spec("f64_tiles", "f32", d=d, V=V, prompts=prompts, G=3, len_lo=max(1, length - 3), len_hi=length, reward="uniform")
     w, out, ref = _run_pair(rb, spec, layout=layout, min_ws=min_ws)
     _check_pair(rb, spec, out, ref, layout)
+
+
+@pytest.mark.parametrize("d,V,prompts,length", [
+    (64, 2100, 1, 40),       # one tile of dHidden, its contraction cut into many segments
+    (640, 1300, 5, 60),      # d padded to 768: a few tiles, fewer than workgroups
+    (384, 3000, 2, 30),      # d padded to 384: tiles of 128 x 256
+    (136, 70, 2, 30),        # a contraction of two steps: nothing to cut
+])
+@pytest.mark.parametrize("cache", [False, True])
+def test_dhidden_of_few_tiles(rb, d, V, prompts, length, cache):
+    print(f"dHidden of few tiles d {d} V {V} rows {prompts * 3 * length} cache {cache}", flush=True)
+    spec = wl.small_spec("few_tiles", "bf16", d=d, V=V, prompts=prompts, G=3, len_lo=length - 3, len_hi=length, reward="uniform")
+    w, out, ref = _run_pair(rb, spec, logits_cache=cache)
+    _check_pair(rb, spec, out, ref)
+
+
+def test_dhidden_pacing_over_whole_rounds(rb):
+    """280 tiles on 256 workgroups: the whole round meets every 4 of its 12 K steps (tuning key 16), the cut last round
+    does not; same bits as unpaced."""
+    spec = wl.small_spec("pace_whole", "bf16", d=512, V=520, prompts=35, G=4, len_lo=256, len_hi=256, sigma=0.02, reward="uniform")
+    got = []
+    try:
+        for every in (4, 0):
+            rb.rapid_set_tuning(16, every)
+            w, out, ref = _run_pair(rb, spec)
+            _check_pair(rb, spec, out, ref)
+            got.append(out.dhidden.clone())
+    finally:
+        rb.rapid_set_tuning(16, 0)
+    assert torch.equal(got[0], got[1])
