@@ -1000,29 +1000,30 @@ __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
     }
 }
 
-// ------------------------------------------------------------------------------------------ dh
-// The tiles of dHidden are long (the contraction runs over the whole vocabulary) and few: a launch has
-// a handful of rounds of one tile per workgroup (or, for a small batch, less than one), and a last round that is
-// only partly filled would leave most of the chip idle for a whole tile.  So the rem tiles of the last, partial round
-// are not dealt out tile by tile: the contraction of each is cut into S equal segments, and the rem x S (segment, tile)
-// units, in that order, are dealt to the XCDs in contiguous shares.  An XCD thus works on one or a few segments of
-// all those tiles and reads only those stretches of W and of the row chunk: both come from memory about once,
-// however small the batch.  A workgroup leaves the fp32 accumulators of a unit in `part`, and dh_reduce_kernel adds
+// ------------------------------------------------------------------------------- sharing out tiles
+// The tiles of dHidden are long (the contraction runs over the whole vocabulary) and few, those of dW are few if the
+// head is small: a launch has a handful of rounds of one tile per workgroup, or less than one, and a last round that
+// is only partly filled would leave most of the chip idle for a whole tile.  So the rem tiles of the last, partial
+// round are not dealt out tile by tile: the contraction of each is cut into S equal segments, and the rem x S
+// (segment, tile) units, in that order, are dealt to the XCDs in contiguous shares.  An XCD thus works on one or a few
+// segments of all those tiles and reads only those stretches of the operands: they come from memory about once,
+// however few rows there are.  A workgroup leaves the fp32 accumulators of a unit in `part`, and a second kernel adds
 // the S pieces of a tile in segment order and stores the result, which does not depend on timing.
-// Measured, d = 1536, V = 151936, about 2200 rows: 1.73 ms when a launch had no more workgroups than tiles, 0.76 ms now
-// (d = 256, V = 4096, 1800 rows: 104 -> 21 us, and the second pass 28 -> 11 us).
-constexpr int DH_MAX_UNITS = 512;      // partial tiles a launch may leave (dh_part_bytes)
-struct DhShare {       // how a launch of `grid` workgroups works through `total` tiles
+// Measured, dHidden: d = 1536, V = 151936, about 2200 rows: 1.73 ms when a launch had no more workgroups than tiles,
+// 0.76 ms now; d = 256, V = 4096, 1800 rows: 104 -> 21 us, dW there 49 -> 29 us with the second pass; dW of d = 896, 73 000
+// rows, whose last round was a third full: 18.8 -> 17.1 ms.
+constexpr int MAX_UNITS = 512;      // partial tiles a launch may leave (part_bytes)
+struct TileShare {     // how a launch of `grid` workgroups works through `total` tiles
     int wgs, full_rounds, rem, segs, unit_share;
     bool cut;
-    __device__ __forceinline__ DhShare(int total, int grid, int ktiles, bool can_cut) {
+    __device__ __forceinline__ TileShare(int total, int grid, int ktiles, bool can_cut) {
         wgs = grid / 8; full_rounds = total / grid; rem = total - full_rounds * grid;
         // S with the shortest last round, counted in K steps of a workgroup: the segments of its units, about 5 steps for
         // filling the pipeline and storing the accumulators, and the second pass over 256 KiB per unit (1 / 25 step each)
         segs = 1;
         float best = (float)ktiles + 4.f;
         if (can_cut && rem > 0) {
-            for (int sg = 2; sg <= 64 && rem * sg <= DH_MAX_UNITS && sg * 4 <= ktiles; sg += sg < 8 ? 1 : sg / 4) {
+            for (int sg = 2; sg <= 64 && rem * sg <= MAX_UNITS && sg * 4 <= ktiles; sg += sg < 8 ? 1 : sg / 4) {
                 const int rounds = (rem * sg + grid - 1) / grid;
                 const float cost = (float)rounds * ((float)ktiles / (float)sg + 5.f) + (float)(rem * sg) * 0.04f;
                 if (cost < best) { best = cost; segs = sg; }
@@ -1033,6 +1034,36 @@ struct DhShare {       // how a launch of `grid` workgroups works through `total
     }
 };
 
+// the accumulators as they are: register r of thread tid at part[unit][r][tid]
+template <class S>
+__device__ __forceinline__ void store_unit(float* part, int unit, const f32x16 (&acc)[S::WI][S::WJ]) {
+    int64_t off = (int64_t)unit * (S::BI * S::BJ) + threadIdx.x;
+#pragma unroll
+    for (int ib = 0; ib < S::WI; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < S::WJ; ++jb) {
+            asm volatile("" : "+v"(off));   // one address per block of 16 stores, formed here and not ahead of the loops
+#pragma unroll
+            for (int v = 0; v < 16; ++v) part[off + v * S::NT] = acc[ib][jb][v];
+            off += 16 * S::NT;
+        }
+}
+// sum[16] = block (ib, jb) of tile tpos of the cut round, its pieces added in segment order (16 loads in flight together)
+template <class S>
+__device__ __forceinline__ void sum_units(const float* part, const TileShare& sh, int tpos, int ib, int jb, float (&sum)[16]) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[v] = 0.f;
+    const float* in = part + (int64_t)tpos * (S::BI * S::BJ) + threadIdx.x + (int64_t)((ib * S::WJ + jb) * 16) * S::NT;
+    for (int seg = 0; seg < sh.segs; ++seg, in += (int64_t)sh.rem * (S::BI * S::BJ)) {
+        float got[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) got[v] = in[v * S::NT];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum[v] += got[v];
+    }
+}
+
+// ------------------------------------------------------------------------------------------ dh
 // stores a tile of dHidden: accumulators times the row factor (if any), bf16, to the rows' positions
 template <class S>
 __device__ __forceinline__ void dh_store(const DhArgs& a, const TileId& t, int M, const f32x16 (&acc)[S::WI][S::WJ]) {
@@ -1082,7 +1113,7 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
     const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
     const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
     const int ktiles = (int)(a.Vpad / K_TILE);
-    const DhShare sh(tilesD * tilesM, grid, ktiles, a.part != nullptr);
+    const TileShare sh(tilesD * tilesM, grid, ktiles, a.part != nullptr);
     const int gi = a.gi > 0 ? a.gi : tilesD;
     GridPace pace{a.pace, 0u, (unsigned)grid, a.pace ? a.pace_every : 0};   // see GridPace
     const unsigned meetings = (unsigned)(ktiles / (pace.every ? pace.every : 1));
@@ -1109,23 +1140,12 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
             continue;
         }
         dh_contract<S, NoPace>(a, t, k0, k1, lds, acc, NoPace());
-        // the accumulators as they are: register r of thread tid at part[u][r][tid]
-        int64_t off = (int64_t)u * (S::BI * S::BJ) + threadIdx.x;
-#pragma unroll
-        for (int ib = 0; ib < WI; ++ib)
-#pragma unroll
-            for (int jb = 0; jb < WJ; ++jb) {
-                asm volatile("" : "+v"(off));   // one address per block of 16 stores, formed here and not ahead of the loops
-#pragma unroll
-                for (int v = 0; v < 16; ++v) a.part[off + v * S::NT] = acc[ib][jb][v];
-                off += 16 * S::NT;
-            }
+        store_unit<S>(a.part, u, acc);
     }
 }
 
 // adds the pieces of the tiles that dh_kernel cut (grid_of_dh: the number of workgroups of that launch) and stores
-// them; workgroup (t, b) does the 32 x 32 block b of every wave of tile t of the last round.  The pieces are added in
-// segment order, 16 loads of a piece in flight together.
+// them; workgroup (t, b) does the 32 x 32 block b of every wave of tile t of the last round
 template <class S>
 __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_dh) {
     constexpr int WI = S::WI, WJ = S::WJ;
@@ -1133,7 +1153,7 @@ __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.m0 >= Mr) return;
     const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
-    const DhShare sh(tilesD * tilesM, grid_of_dh, (int)(a.Vpad / K_TILE), true);
+    const TileShare sh(tilesD * tilesM, grid_of_dh, (int)(a.Vpad / K_TILE), true);
     const int tpos = blockIdx.x, ib = blockIdx.y / WJ, jb = blockIdx.y % WJ;
     if (!sh.cut || tpos >= sh.rem) return;
     const TileId t = tile_of_vid(sh.full_rounds * grid_of_dh + tpos, tilesD, tilesM, a.gi > 0 ? a.gi : tilesD);
@@ -1142,16 +1162,7 @@ __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_
     const int64_t j = a.m0 + (int64_t)t.tj * S::BJ + L.wave_j * (WJ * 32) + jb * 32 + L.lj;
     if (j >= M) return;
     float sum[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-    const float* in = a.part + (int64_t)tpos * (S::BI * S::BJ) + threadIdx.x + (int64_t)((ib * WJ + jb) * 16) * S::NT;
-    for (int seg = 0; seg < sh.segs; ++seg, in += (int64_t)sh.rem * (S::BI * S::BJ)) {
-        float got[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) got[v] = in[v * S::NT];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sum[v] += got[v];
-    }
+    sum_units<S>(a.part, sh, tpos, ib, jb, sum);
     bf16_t* out = a.dhidden + (int64_t)a.row_index[j] * a.d;
     const float cj = a.rowc ? a.rowc[j] : 1.f;
 #pragma unroll
@@ -1163,62 +1174,183 @@ __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_
 }
 
 // ------------------------------------------------------------------------------------------ dw
-template <class S, bool DEEP = false>
+// dW is stored [d, V] or [V, d]; i is the index that is contiguous in memory (VD: the hidden dimension, else the
+// vocabulary), so a lane's runs of 4 consecutive i are consecutive words of a row in either layout.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));      // rows need not start on 16 bytes
+typedef unsigned short u16x4u __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ u16x4u round4(const f32x4u& v) {
+    u16x4u h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = __builtin_bit_cast(unsigned short, (__bf16)v[r]);
+    return h;
+}
+// 4 consecutive elements at offset `off` = j ld + i of dW, the first `n` of which exist (n <= 0: none):
+// value = old * scale + sum if beta; to fp32 dW or, with a.dW16, rounded to it
+struct DwOut {
+    float* dW; bf16_t* dW16; int64_t ld; int nI, nJ; float scale; bool beta;
+    __device__ __forceinline__ DwOut(const DwArgs& a, bool vd)
+        : dW(a.dW), dW16(a.dW16), ld(vd ? a.d : a.V), nI((int)(vd ? a.d : a.V)), nJ((int)(vd ? a.V : a.d)),
+          scale((a.beta && a.beta_scale) ? a.beta_scale[0] : 1.f), beta(a.beta != 0) {}
+    __device__ __forceinline__ f32x4u old(int64_t off, int n) const {
+        f32x4u c = {0.f, 0.f, 0.f, 0.f};
+        if (!beta || n <= 0) return c;
+        const float* p = dW + off;
+        if (n >= 4) return *(const f32x4u*)p;
+        for (int r = 0; r < n; ++r) c[r] = p[r];
+        return c;
+    }
+    __device__ __forceinline__ void put(int64_t off, int n, const f32x4u& c, const f32x4u& sum) const {
+        if (n <= 0) return;
+        f32x4u o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = c[r] * scale + sum[r];
+        if (dW16) {
+            const u16x4u h = round4(o);
+            bf16_t* p = dW16 + off;
+            if (n >= 4) { *(u16x4u*)p = h; return; }
+            for (int r = 0; r < n; ++r) p[r] = h[r];
+            return;
+        }
+        float* p = dW + off;
+        if (n >= 4) { *(f32x4u*)p = o; return; }
+        for (int r = 0; r < n; ++r) p[r] = o[r];
+    }
+};
+
+// A tile of dW leaves through LDS: straight from the accumulators a store instruction would touch 32 rows, 32 bytes of
+// each, and a tile of 256 KiB is a third of this kernel's time when there are few rows to contract.  Each wave owns a
+// region of 32 rows j x IBW * 32 columns i.  Measured, d = 1536, V = 151936: added to a [V, d] gradient, about 2100 rows,
+// 1.67 -> 1.06 ms; [d, V] without the addition, 13 000 rows, 2 % faster.  All waves must be done with both LDS stages (barrier) before the call.
+template <class S>
+__device__ __forceinline__ void dw_store(char* lds, const DwOut& out, int64_t i_tile, int64_t j_tile, const f32x16 (&acc)[S::WI][S::WJ]) {
+    constexpr int fit = S::LDS_BYTES / S::NW / (32 * 128);                          // blocks of 32 x 32 floats per wave
+    constexpr int IBW = fit >= S::WI ? S::WI : fit >= S::WI / 2 ? S::WI / 2 : 1;
+    constexpr int C = IBW * 8, R = 64 / C, T = 32 / R;                              // 16-byte chunks per row; rows per access
+    static_assert(fit >= 1 && S::WI % IBW == 0 && C <= 64, "region");
+    const Lane<S> L;
+    constexpr int U = T < 8 ? T : 8;                                                // accesses in flight together
+    char* region = lds + L.wave * (IBW * 32 * 128);
+    const int c = L.lane % C, rr = L.lane / C;
+    const int64_t step = R * out.ld;
+    const bool inside = i_tile + S::BI <= out.nI && j_tile + S::BJ <= out.nJ;
+#pragma unroll
+    for (int jb = 0; jb < S::WJ; ++jb)
+#pragma unroll
+        for (int i0 = 0; i0 < S::WI; i0 += IBW) {
+            char* row = region + L.lj * (C * 16);
+#pragma unroll
+            for (int ib = 0; ib < IBW; ++ib)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *(float4*)(row + (((ib * 8 + q * 2 + L.hi) ^ (L.lj & (C - 1))) * 16)) =
+                        make_float4(acc[i0 + ib][jb][q * 4], acc[i0 + ib][jb][q * 4 + 1], acc[i0 + ib][jb][q * 4 + 2],
+                                    acc[i0 + ib][jb][q * 4 + 3]);
+            const int j = (int)j_tile + (L.wave_j * S::WJ + jb) * 32 + rr, i = (int)i_tile + (L.wave_i * S::WI + i0) * 32 + c * 4;
+            int64_t off = (int64_t)j * out.ld + i;
+            auto value = [&](int t) {
+                const int r = t * R + rr;
+                const float4 v = *(const float4*)(region + r * (C * 16) + ((c ^ (r & (C - 1))) * 16));
+                return f32x4u{v.x, v.y, v.z, v.w};
+            };
+            // rolled: the accumulators of the other blocks leave no registers for all of a region's rows at once
+            if (inside) {   // no branch between the accesses of a batch, so that they are in flight together
+#pragma unroll 1
+                for (int t0 = 0; t0 < T; t0 += U, off += U * step) {
+                    f32x4u cur[U];
+                    if (out.beta) {
+#pragma unroll
+                        for (int t = 0; t < U; ++t) cur[t] = *(const f32x4u*)(out.dW + off + t * step);
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < U; ++t) cur[t] = f32x4u{0.f, 0.f, 0.f, 0.f};
+                    }
+#pragma unroll
+                    for (int t = 0; t < U; ++t) cur[t] = cur[t] * out.scale + value(t0 + t);
+                    if (out.dW16) {
+#pragma unroll
+                        for (int t = 0; t < U; ++t) __builtin_nontemporal_store(round4(cur[t]), (u16x4u*)(out.dW16 + off + t * step));
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < U; ++t) __builtin_nontemporal_store(cur[t], (f32x4u*)(out.dW + off + t * step));
+                    }
+                }
+            } else {
+#pragma unroll 1
+                for (int t = 0; t < T; ++t, off += step) {
+                    const int n = j + t * R < out.nJ ? out.nI - i : 0;
+                    const f32x4u cur = out.old(off, n);
+                    out.put(off, n, cur, value(t));
+                }
+            }
+        }
+}
+
+template <class S, bool VD, bool DEEP = false>
 __global__ __launch_bounds__(S::NT) void dw_kernel(DwArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
-    const int tilesV = (int)(a.Vpad / S::BI), tilesD = (int)(a.dpadR / S::BJ);
+    const int tilesV = (int)(a.Vpad / (VD ? S::BJ : S::BI)), tilesD = (int)(a.dpadR / (VD ? S::BI : S::BJ));
     const int Mr = a.counts[CNT_MR];
     int64_t rows = (int64_t)Mr - a.m0;
     rows = rows < 0 ? 0 : (rows > a.Mc ? a.Mc : rows);
-    if (rows == 0 && a.beta) return;   // nothing to add
-    for (int pid = blockIdx.x, ids = ids_for(tilesV, tilesD); pid < ids; pid += gridDim.x) {
-    const TileId t = map_tile(pid, tilesV, tilesD, a.gi);
-    if (!t.valid) continue;
-    f32x16 acc[WI][WJ];
-    if constexpr (DEEP)
-        mainloop_kmajor32<S, 4>(a.dz + (int64_t)t.ti * S::BI, a.ldz, a.Hc + (int64_t)t.tj * S::BJ, a.ldH, (int)(rows / 32), lds, acc);
-    else
-        mainloop_kmajor<S>(a.dz + (int64_t)t.ti * S::BI, a.ldz, a.Hc + (int64_t)t.tj * S::BJ, a.ldH,
-                           (int)(rows / K_TILE), lds, acc);
+    if (rows == 0 && a.beta && !a.dW16) return;   // nothing to add
+    const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
+    const int ktiles = (int)(rows / K_TILE);
+    const TileShare sh(tilesV * tilesD, grid, ktiles, a.part != nullptr);
+    const DwOut out(a, VD);
+    auto contract = [&](const TileId& t, int k0, int k1, f32x16 (&acc)[WI][WJ]) {
+        const bf16_t* z = a.dz + (int64_t)t.ti * (VD ? S::BJ : S::BI) + (int64_t)k0 * K_TILE * a.ldz;
+        const bf16_t* h = a.Hc + (int64_t)t.tj * (VD ? S::BI : S::BJ) + (int64_t)k0 * K_TILE * a.ldH;
+        if constexpr (VD) mainloop_kmajor<S>(h, a.ldH, z, a.ldz, k1 - k0, lds, acc);
+        else if constexpr (DEEP) mainloop_kmajor32<S, 4>(z, a.ldz, h, a.ldH, (k1 - k0) * 2, lds, acc);
+        else mainloop_kmajor<S>(z, a.ldz, h, a.ldH, k1 - k0, lds, acc);
+    };
+    auto finish = [&](const TileId& t, const f32x16 (&acc)[WI][WJ]) {
+        lds_barrier();   // every wave is done with both stages
+        dw_store<S>(lds, out, (int64_t)(VD ? t.tj : t.ti) * S::BI, (int64_t)(VD ? t.ti : t.tj) * S::BJ, acc);
+    };
+    for (int round = 0; round < sh.full_rounds; ++round) {
+        const TileId t = tile_of_vid((x * sh.full_rounds + round) * sh.wgs + w, tilesV, tilesD, a.gi);
+        f32x16 acc[WI][WJ];
+        contract(t, 0, ktiles, acc);
+        finish(t, acc);
+    }
+    for (int pos = w; pos < sh.unit_share; pos += sh.wgs) {   // the last round (see TileShare)
+        const int u = x * sh.unit_share + pos;
+        if (u >= sh.rem * sh.segs) break;
+        const int seg = u / sh.rem, tpos = u - seg * sh.rem;
+        const TileId t = tile_of_vid(sh.full_rounds * grid + tpos, tilesV, tilesD, a.gi);
+        f32x16 acc[WI][WJ];
+        contract(t, (int)((int64_t)ktiles * seg / sh.segs), (int)((int64_t)ktiles * (seg + 1) / sh.segs), acc);
+        if (sh.cut) store_unit<S>(a.part, u, acc); else finish(t, acc);
+    }
+}
+
+// adds the pieces of the tiles that dw_kernel cut and stores them (see dh_reduce_kernel)
+template <class S, bool VD>
+__global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_dw) {
+    const int tilesV = (int)(a.Vpad / (VD ? S::BJ : S::BI)), tilesD = (int)(a.dpadR / (VD ? S::BI : S::BJ));
+    const int Mr = a.counts[CNT_MR];
+    int64_t rows = (int64_t)Mr - a.m0;
+    rows = rows < 0 ? 0 : (rows > a.Mc ? a.Mc : rows);
+    const TileShare sh(tilesV * tilesD, grid_of_dw, (int)(rows / K_TILE), true);
+    const int tpos = blockIdx.x, ib = blockIdx.y / S::WJ, jb = blockIdx.y % S::WJ;
+    if (!sh.cut || tpos >= sh.rem) return;
+    const TileId t = tile_of_vid(sh.full_rounds * grid_of_dw + tpos, tilesV, tilesD, a.gi);
+    const DwOut out(a, VD);
     const Lane<S> L;
-    const int64_t i_base = (int64_t)t.ti * S::BI + L.wave_i * (WI * 32);
-    const bool vec = (a.V % 4) == 0;
-    const float bs = (a.beta && a.beta_scale) ? a.beta_scale[0] : 1.f;   // what the sum so far is multiplied by
+    const int i = (VD ? t.tj : t.ti) * S::BI + (L.wave_i * S::WI + ib) * 32 + L.hi * 4;
+    const int j = (VD ? t.ti : t.tj) * S::BJ + (L.wave_j * S::WJ + jb) * 32 + L.lj;
+    const int64_t off = (int64_t)j * out.ld + i;
+    const int left = j < out.nJ ? out.nI - i : 0;
+    f32x4u cur[4];
 #pragma unroll
-    for (int jb = 0; jb < WJ; ++jb) {
-        const int64_t jd = (int64_t)t.tj * S::BJ + L.wave_j * (WJ * 32) + jb * 32 + L.lj;
-        if (jd >= a.d) continue;
+    for (int q = 0; q < 4; ++q) cur[q] = out.old(off + q * 8, left - q * 8);
+    float sum[16];
+    sum_units<S>(a.part, sh, tpos, ib, jb, sum);
 #pragma unroll
-        for (int ib = 0; ib < WI; ++ib)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t i0 = i_base + ib * 32 + q * 8 + L.hi * 4;
-                if (i0 >= a.V) continue;
-                float o[4] = {acc[ib][jb][q * 4], acc[ib][jb][q * 4 + 1], acc[ib][jb][q * 4 + 2],
-                              acc[ib][jb][q * 4 + 3]};
-                if (a.w_layout == RAPID_W_DV) {
-                    float* p = a.dW + jd * a.V + i0;
-                    if (vec) {
-                        float4 cur = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (a.beta) cur = *(const float4*)p;
-                        *(float4*)p = make_float4(cur.x * bs + o[0], cur.y * bs + o[1], cur.z * bs + o[2], cur.w * bs + o[3]);
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (i0 + r < a.V) p[r] = (a.beta ? p[r] * bs : 0.f) + o[r];
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (i0 + r < a.V) {
-                            float* p = a.dW + (i0 + r) * a.d + jd;
-                            *p = (a.beta ? *p * bs : 0.f) + o[r];
-                        }
-                }
-            }
-    }
-    }
+    for (int q = 0; q < 4; ++q)
+        out.put(off + q * 8, left - q * 8, cur[q], f32x4u{sum[q * 4], sum[q * 4 + 1], sum[q * 4 + 2], sum[q * 4 + 3]});
 }
 
 // Logit of the sampled token: zy[j] = inv_temp * <Hc[j, :], Wvd[tok_j, :]>, one wave per token row
@@ -1369,22 +1501,28 @@ void launch_dh_t(const DhArgs& a, hipStream_t st) {
     allow_lds<&dh_kernel<S>>(S::LDS_BYTES);
     const int tilesD = (int)(a.dpadR / S::BI);
     DhArgs b = a;
-    if ((size_t)DH_MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
+    if ((size_t)MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
     // with scratch for cut tiles a launch of few tiles takes the whole chip as well
     const unsigned grid = b.part ? (unsigned)(g_num_cu.load() / 8 * 8) : grid_for(tilesD, a.tilesM);
     dh_kernel<S><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
     const int64_t tiles = (int64_t)tilesD * a.tilesM;
     if (b.part) dh_reduce_kernel<S><<<dim3((unsigned)(tiles < grid ? tiles : grid), S::WI * S::WJ), S::NT, 0, st>>>(b, (int)grid);
 }
-template <class S, bool DEEP = false>
+template <class S, bool VD, bool DEEP = false>
 void launch_dw_t(const DwArgs& a, hipStream_t st) {
-    allow_lds<&dw_kernel<S, DEEP>>(S::LDS_BYTES);
-    dw_kernel<S, DEEP><<<grid_for((int)(a.Vpad / S::BI), (int)(a.dpadR / S::BJ)), S::NT, S::LDS_BYTES, st>>>(a);
+    allow_lds<&dw_kernel<S, VD, DEEP>>(S::LDS_BYTES);
+    const int64_t tilesV = a.Vpad / (VD ? S::BJ : S::BI), tilesD = a.dpadR / (VD ? S::BI : S::BJ), tiles = tilesV * tilesD;
+    DwArgs b = a;
+    if ((size_t)MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
+    const unsigned grid = b.part ? (unsigned)(g_num_cu.load() / 8 * 8) : grid_for((int)tilesV, (int)tilesD);
+    dw_kernel<S, VD, DEEP><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
+    if (b.part && tiles % grid != 0)
+        dw_reduce_kernel<S, VD><<<dim3((unsigned)(tiles % grid), S::WI * S::WJ), S::NT, 0, st>>>(b, (int)grid);
 }
 
 }  // namespace
 
-size_t dh_part_bytes() { return (size_t)DH_MAX_UNITS * 256 * 256 * 4; }
+size_t dh_part_bytes() { return (size_t)MAX_UNITS * 256 * 256 * 4; }
 void set_waves_per_workgroup(int n) { g_waves = (n == 4 || n == 8 || n == 16) ? n : 0; }
 void set_cu_count(int n) { g_num_cu = n >= 8 ? n : 8; }
 
@@ -1468,15 +1606,20 @@ std::atomic<int> g_dw_deep{0};
 void set_dw_deep(int on) { g_dw_deep = on ? 1 : 0; }
 void launch_dw(const DwArgs& a, hipStream_t st) {
     const int w = waves_for(8);
-    if (g_dw_deep.load() && w == 8) {   // K steps of 32 rows, requests three steps ahead
-        if (a.dpadR % 256 == 0) launch_dw_t<G8, true>(a, st); else launch_dw_t<G8_J128, true>(a, st);
+    const bool d256 = a.dpadR % 256 == 0;   // else d is padded to a multiple of 128 only
+    if (a.w_layout == RAPID_W_VD) {
+        if (w == 16) d256 ? launch_dw_t<G16, true>(a, st) : launch_dw_t<G16_I128, true>(a, st);
+        else if (w == 8) d256 ? launch_dw_t<G8, true>(a, st) : launch_dw_t<G8_I128, true>(a, st);
+        else d256 ? launch_dw_t<G4, true>(a, st) : launch_dw_t<G4_I128, true>(a, st);
         return;
     }
-    if (a.dpadR % 256 == 0) {
-        if (w == 16) launch_dw_t<G16>(a, st); else if (w == 8) launch_dw_t<G8>(a, st); else launch_dw_t<G4>(a, st);
-    } else {   // d padded to a multiple of 128 only
-        if (w == 16) launch_dw_t<G16_J128>(a, st); else if (w == 8) launch_dw_t<G8_J128>(a, st); else launch_dw_t<G4_J128>(a, st);
+    if (g_dw_deep.load() && w == 8) {   // K steps of 32 rows, requests three steps ahead
+        d256 ? launch_dw_t<G8, false, true>(a, st) : launch_dw_t<G8_J128, false, true>(a, st);
+        return;
     }
+    if (w == 16) d256 ? launch_dw_t<G16, false>(a, st) : launch_dw_t<G16_J128, false>(a, st);
+    else if (w == 8) d256 ? launch_dw_t<G8, false>(a, st) : launch_dw_t<G8_J128, false>(a, st);
+    else d256 ? launch_dw_t<G4, false>(a, st) : launch_dw_t<G4_J128, false>(a, st);
 }
 
 }  // namespace rapid

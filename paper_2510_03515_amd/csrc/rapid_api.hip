@@ -980,7 +980,8 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         float* beta_scale = at<float>(ws, p.beta_scale);
         // a normalised gradient that is added to the caller's dW goes through a buffer of its own: the
         // running rescaling of the sum must not touch what the caller had in dW
-        const bool dw_staged = o.dw_dtype == RAPID_DTYPE_BF16 || (o.accumulate_dw && o.normalized_grads && p.Cmax > 1);
+        const bool dw_bf16 = o.dw_dtype == RAPID_DTYPE_BF16;
+        const bool dw_staged = dw_bf16 || (o.accumulate_dw && o.normalized_grads && p.Cmax > 1);
         float* dW32 = dw_staged ? at<float>(ws, p.dw32) : (float*)dW_out;
         const bool dw_adds_to_caller = o.accumulate_dw && !dw_staged;
         io.zc = cache;
@@ -1082,6 +1083,9 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 wa.beta = (c > 0 || piece > 0 || dw_adds_to_caller) ? 1 : 0;
                 // the sum over the earlier chunks is brought to this chunk's scale, once, by its first piece
                 wa.beta_scale = (c > 0 && piece == 0 && o.normalized_grads && !dw_adds_to_caller) ? beta_scale : nullptr;
+                // the last launch rounds a bf16 gradient on its way out
+                if (dw_bf16 && c == p.Cmax - 1 && r0 + wstep >= p.Rcap) wa.dW16 = (bf16_t*)dW_out;
+                wa.part = g_dh_split.load() ? at<float>(ws, p.dh_part) : nullptr; wa.part_bytes = dh_part_bytes();
                 Span sp(ST_DW, st);
                 launch_dw(wa, st);
             }
@@ -1112,10 +1116,9 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                                         part ? part + (int64_t)c * blocks_per_region * d : nullptr, st);
             if (part) launch_rmsnorm_dweight_reduce(part, d, p.rms_blocks, o.drms_weight_out, st);
         }
-        if (dw_staged) {
+        if (dw_staged && !dw_bf16) {
             Span sp(ST_CONVERT, st);
-            if (o.dw_dtype == RAPID_DTYPE_BF16) launch_f32_to_bf16(dW32, (bf16_t*)dW_out, d * V, st);
-            else launch_f32_add(dW32, (float*)dW_out, d * V, st);
+            launch_f32_add(dW32, (float*)dW_out, d * V, st);
         }
         return check_launch(name);
     }
@@ -1215,6 +1218,8 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             wa.dz = dz; wa.Hc = Hc + m0 * p.ldk; wa.Mc = step; wa.ldz = p.ldv; wa.ldH = p.ldk;
             wa.d = p.d; wa.dpadR = p.dpadR; wa.V = p.V; wa.Vpad = p.Vpad; wa.m0 = m0; wa.counts = bwd_counts;
             wa.dW = dW32; wa.w_layout = o.w_layout; wa.beta = (chunk > 0 || o.accumulate_dw) ? 1 : 0; wa.gi = g_gi_dw;
+            if (dw_staged && m0 + step >= p.Mmax_pad) wa.dW16 = (bf16_t*)dW_out;   // the last launch rounds it on its way out
+            wa.part = ha.part; wa.part_bytes = ha.part_bytes;
             {
                 Span sp(ST_DW, st);
                 launch_dw(wa, st);
@@ -1266,7 +1271,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             launch_f32_gemm(gw, st);
         }
     }
-    if (dw_staged) {
+    if (dw_staged && dtype == RAPID_DTYPE_F32) {
         Span sp(ST_CONVERT, st);
         launch_f32_to_bf16(dW32, (bf16_t*)dW_out, d * V, st);
     }

@@ -253,11 +253,11 @@ struct DhArgs {           // dH[row, :] = dz[row, :] . Wdv^T
     int pace_every;       // K steps between meetings (power of two)
     bf16_t* dhidden;      // [N*T, d]
     int gi;               // tiles along i that share one j before the order moves on (L2 blocking)
-    float* part = nullptr;    // NULL, or scratch of part_bytes: lets the kernel cut a partly filled last round of tiles
-    size_t part_bytes = 0;    // along the contraction (needs 512 KiB per workgroup of the launch)
+    float* part = nullptr;    // NULL, or scratch of part_bytes (128 MiB): lets the kernel cut a partly filled last round of
+    size_t part_bytes = 0;    // tiles along the contraction
 };
 void launch_dh(const DhArgs& a, hipStream_t st);
-size_t dh_part_bytes();   // scratch that lets every dHidden launch cut its last round
+size_t dh_part_bytes();   // scratch that lets a dHidden or dW launch cut its last round
 
 struct DwArgs {           // dW (+)= Hc^T . dz over the chunk's rows
     const bf16_t* dz;     // [Mc, Vpad] chunk (rows = tokens)
@@ -268,10 +268,13 @@ struct DwArgs {           // dW (+)= Hc^T . dz over the chunk's rows
     int64_t m0;
     const int32_t* counts;
     float* dW;            // fp32, layout per w_layout
+    bf16_t* dW16 = nullptr;   // if set the result goes here, rounded once (the old value of beta = 1 still comes from dW)
     int w_layout;
     int beta;             // 0 overwrite, 1 accumulate
     const float* beta_scale = nullptr;   // NULL, or device: with beta = 1 the old value is multiplied by beta_scale[0] first
-    int gi;               // tiles along i that share one j before the order moves on (L2 blocking)
+    int gi;               // vocabulary tiles that share one tile of d before the order moves on (L2 blocking)
+    float* part = nullptr;    // as in DhArgs
+    size_t part_bytes = 0;
 };
 void launch_dw(const DwArgs& a, hipStream_t st);
 void set_waves_per_workgroup(int n);   // 4, 8 or 16 waves per contraction workgroup

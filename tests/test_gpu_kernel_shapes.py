@@ -52,3 +52,27 @@ def test_dhidden_pacing_over_whole_rounds(rb):
     finally:
         rb.rapid_set_tuning(16, 0)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("d,V", [(256, 1024), (264, 1027), (72, 259)])     # whole tiles; rows off 16 bytes and ragged tiles
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("cache", [False, True])
+def test_dw_leaves_in_every_form(rb, d, V, layout, cache):
+    """dW as fp32, rounded to bf16, and added to what is there, from one launch and (smallest workspace) from several."""
+    spec = wl.small_spec("dw_store", "bf16", d=d, V=V, prompts=6, G=3, len_lo=20, len_hi=60, reward="uniform")
+    for min_ws in (False, True):
+        print(f"dW forms d {d} V {V} {layout} cache {cache} min_ws {min_ws}", flush=True)
+        w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache, min_ws=min_ws)
+        _check_pair(rb, spec, out, ref, layout)
+        w, half, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache, min_ws=min_ws, dw_dtype=torch.bfloat16)
+        assert torch.equal(half.dW, out.dW.to(torch.bfloat16))              # one rounding of the same sum
+    g = {k: (v.cuda() if torch.is_tensor(v) else v) for k, v in w.items()}
+    lay = rb.W_DV if layout == "dv" else rb.W_VD
+    W = g["W"] if layout == "dv" else g["W"].t().contiguous()
+    args = (g["hidden"], W, g["tokens"], g["mask"], None, g["rewards"], g["group_ids"], w["K"])
+    base = rb.rapid_iw_pg_loss_fwd_bwd(*args, w_layout=lay, logits_cache=cache).dW
+    buf = rb.IwPgBuffers(g["hidden"], W, w["K"], lay, logits_cache=cache)
+    old = torch.randn_like(buf.dW)
+    buf.dW.copy_(old)
+    added = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=buf, w_layout=lay, logits_cache=cache, accumulate_dw=True).dW
+    assert torch.equal(added, old + base)
