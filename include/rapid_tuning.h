@@ -19,7 +19,8 @@ extern "C" {
  * key 1: per-stage event timing on (1) / off (0, default); see rapid_profile_read.
  * key 2: waves per workgroup of the contraction kernels: 0 (default) = each kernel's own choice (8,
  *        i.e. 2 x 4 waves of 128 x 64, for the logits kernels and dW; 4, i.e. 2 x 2 waves of 128 x 128,
- *        for dHidden), or 4 / 8 / 16 for all of them.  Same 256 x 256 tile and same results either way.
+ *        for dHidden), or 4 / 8 / 16 for all of them.  Same 256 x 256 tile and same results either way.  A value other than 0
+ *        also makes them read W from its packed copies always, not in place as a small batch otherwise does.
  * keys 10, 11, 12: tile-order blocking (tiles along the first tile dimension that share one tile of
  *        the second before the order moves on) of the logits kernels, the dHidden kernel (0 = all)
  *        and the dW kernel; defaults 4, 0, 2 were measured best on MI355X.  Results are identical.

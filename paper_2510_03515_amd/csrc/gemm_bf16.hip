@@ -67,20 +67,6 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// Requests one K step (64 columns) of a tile with ROWS rows: direct memory -> LDS loads, 16 bytes
-// per lane.  `gwave` is the wave-uniform address of the wave's first row of round 0 (scalar
-// registers), `voff` the lane's byte offset from it (row lane/8 of the 8-row band, swizzled chunk),
-// `round_bytes` the uniform distance between rounds (8 rows per wave); lane l's chunk lands at
-// lds_wave + 16 l of each round.
-template <int ROWS, int NW>
-__device__ __forceinline__ void issue_tile_load(const char* __restrict__ gwave, uint32_t voff, int64_t round_bytes,
-                                                char* lds_wave) {
-#pragma unroll
-    for (int t = 0; t < ROWS / (8 * NW); ++t)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gwave + t * round_bytes + voff),
-                                         (__attribute__((address_space(3))) void*)(lds_wave + t * (8 * NW * 128)), 16, 0, 0);
-}
-
 template <int WI, int WJ>
 struct Frags {
     bf16x8 a[WI], b[WJ];
@@ -114,18 +100,6 @@ __device__ __forceinline__ void wait_frags(Frags<WI, WJ>& f) {
     for (int ib = 0; ib < WI; ++ib) asm volatile("" : "+v"(f.a[ib]));
 #pragma unroll
     for (int jb = 0; jb < WJ; ++jb) asm volatile("" : "+v"(f.b[jb]));
-}
-
-template <int WI, int WJ, int... IB, int... JB>
-__device__ __forceinline__ void load_frags_seq(Frags<WI, WJ>& f, uint32_t a_addr, uint32_t b_addr,
-                                               std::integer_sequence<int, IB...>, std::integer_sequence<int, JB...>) {
-    ((f.a[IB] = ds_read128<IB * (32 * 128)>(a_addr)), ...);
-    ((f.b[JB] = ds_read128<JB * (32 * 128)>(b_addr)), ...);
-}
-// a_addr / b_addr: LDS byte addresses of this lane's chunk in block 0 of each operand
-template <int WI, int WJ>
-__device__ __forceinline__ void load_frags(Frags<WI, WJ>& f, uint32_t a_addr, uint32_t b_addr) {
-    load_frags_seq<WI, WJ>(f, a_addr, b_addr, std::make_integer_sequence<int, WI>{}, std::make_integer_sequence<int, WJ>{});
 }
 
 template <int WI, int WJ>
@@ -212,122 +186,6 @@ struct GridPace {
     }
 };
 
-// acc += A_tile . B_tile^T over `ktiles` steps of 64.  A / B point at the tile's first row, k = 0.
-template <class S, class Pace = NoPace>
-__device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B,
-                                         int64_t ldb, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ],
-                                         int step_a = 128, int step_b = 128, Pace pace = Pace()) {
-    constexpr int WI = S::WI, WJ = S::WJ;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave_i = wave % S::NWI, wave_j = wave / S::NWI;
-
-    // global side of the tile loads: lane l of a wave covers row l/8 of the wave's 8-row band and
-    // the chunk that belongs at slot l%8 of that row; a wave's bands are 8 * (waves that share the
-    // tile) rows apart.
-    const int gchunk = (lane & 7) ^ ((((wave & 1) << 2) + (lane >> 4)) & 7);
-    const uint32_t voff_a = (uint32_t)(((int64_t)(lane >> 3) * lda + gchunk * 8) * 2);
-    const uint32_t voff_b = (uint32_t)(((int64_t)(lane >> 3) * ldb + gchunk * 8) * 2);
-    const char* ga = (const char*)(A + (int64_t)(wave * 8) * lda);
-    const char* gb = (const char*)(B + (int64_t)(wave * 8) * ldb);
-    const int lds_wave_off = wave * 8 * 128;
-
-    // LDS side of the fragment reads
-    const int frow = lane & 31, fhi = lane >> 5;
-    int xo[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) xo[ks] = (((ks * 2 + fhi) ^ ((lane >> 1) & 7)) * 16);
-    const int a_off = (wave_i * (WI * 32) + frow) * 128;
-    const int b_off = S::BI * 128 + (wave_j * (WJ * 32) + frow) * 128;
-
-#pragma unroll
-    for (int ib = 0; ib < WI; ++ib)
-#pragma unroll
-        for (int jb = 0; jb < WJ; ++jb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[ib][jb][v] = 0.f;
-
-    if (ktiles <= 0) return;
-
-    // A workgroup runs tile after tile: everybody must be done with the LDS stages of the tile before
-    // (its last reads, its trailing requests, a staged epilogue) before they are filled again.
-    lds_barrier();
-    issue_tile_load<S::BI, S::NW>(ga, voff_a, (int64_t)(8 * S::NW) * lda * 2, lds + lds_wave_off);
-    issue_tile_load<S::BJ, S::NW>(gb, voff_b, (int64_t)(8 * S::NW) * ldb * 2, lds + S::BI * 128 + lds_wave_off);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    lds_barrier();
-
-    // One K step on stage `cur` = kt % 2 (its first fragments f0 were read at the end of the step before,
-    // and the first half of tile kt+1 was requested there too):
-    //   read f1 (sub-step 1) | MFMA f0 + second half of the requests for tile kt+1
-    //   read f0 (sub-step 2) | MFMA f1
-    //   read f1 (sub-step 3) | MFMA f0
-    //   wait: own requests landed, own reads of `cur` done; barrier
-    //   read f0 of tile kt+1 | MFMA f1 + first half of the requests for tile kt+2 (into `cur`)
-    // After the barrier tile kt+1 is complete and nobody reads `cur` any more.  Steps past the last
-    // tile re-request the last tile into the idle stage, which keeps the loop free of branches and
-    // every address in bounds.  (Skipping those requests with a uniform branch each was tried: the logits
-    // kernels, where they are 6 % of the memory -> LDS traffic, got 2 % slower and dHidden 5 %.)
-    Frags<WI, WJ> f0, f1;
-    constexpr int NR = WI + WJ;   // LDS reads per sub-step
-    constexpr int RA = S::BI / (8 * S::NW), RB = S::BJ / (8 * S::NW), SR = 8 * S::NW;
-    char* dst = lds + S::STAGE_BYTES;   // stage the requests go to
-    auto request = [&](int r) {
-        if (r < RA)
-            load_to_lds_16(ga + (int64_t)(r * SR) * lda * 2 + voff_a, dst + lds_wave_off + r * (SR * 128));
-        else
-            load_to_lds_16(gb + (int64_t)((r - RA) * SR) * ldb * 2 + voff_b,
-                           dst + S::BI * 128 + lds_wave_off + (r - RA) * (SR * 128));
-    };
-    {
-        const uint32_t la = lds_addr(lds) + a_off, lb = lds_addr(lds) + b_off;
-        load_frags<WI, WJ>(f0, la + xo[0], lb + xo[0]);
-        ga += ktiles > 1 ? step_a : 0;
-        gb += ktiles > 1 ? step_b : 0;
-        request_first_half<S, RA + RB>(request);   // of tile 1
-        // A register that an LDS read (issued from inline assembly) is still writing must not meet
-        // a compiler-made copy, and copies appear where control flow splits or joins: every read is
-        // therefore waited for in the block that issued it.
-        wait_frags<0>(f0);
-    }
-    for (int kt = 0; kt < ktiles; ++kt) {
-        char* cur = lds + (kt & 1) * S::STAGE_BYTES;
-        char* nxt = lds + ((kt + 1) & 1) * S::STAGE_BYTES;
-        const uint32_t la = lds_addr(cur) + a_off, lb = lds_addr(cur) + b_off;
-        const uint32_t na = lds_addr(nxt) + a_off, nb = lds_addr(nxt) + b_off;
-        fence();
-        load_frags<WI, WJ>(f1, la + xo[1], lb + xo[1]);
-        fence();
-        dst = nxt;
-        mma_block_requesting<S, 1, RA + RB>(f0, acc, request);
-        fence();
-        load_frags<WI, WJ>(f0, la + xo[2], lb + xo[2]);
-        wait_frags<NR>(f1);
-        fence();
-        mma_block<WI, WJ>(f1, acc);
-        fence();
-        load_frags<WI, WJ>(f1, la + xo[3], lb + xo[3]);
-        wait_frags<NR>(f0);
-        fence();
-        mma_block<WI, WJ>(f0, acc);
-        fence();
-        wait_frags<0>(f1);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        lds_barrier();
-        pace(kt);   // no LDS read or tile request is in flight here
-        load_frags<WI, WJ>(f0, na + xo[0], nb + xo[0]);
-        fence();
-        ga += (kt + 2 < ktiles) ? step_a : 0;
-        gb += (kt + 2 < ktiles) ? step_b : 0;
-        dst = cur;
-        mma_block_requesting<S, 0, RA + RB>(f1, acc, request);
-        fence();
-        wait_frags<0>(f0);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests for steps that do not exist
-}
-
 // ---- contraction index major operands ("k-major") ---------------------------------------------
 // For dW = H^T dz both operands are stored with the contraction index (the token row) as the slow
 // dimension: A(k, i) = dz[row k][column i], B(k, j) = H[row k][column j].  A K step is 64 rows of
@@ -350,19 +208,6 @@ struct KMajor {
     static constexpr int TILE_BYTES = STEP * ROW_BYTES;
 };
 
-template <int COLS, int NW>
-__device__ __forceinline__ void issue_kmajor_load(const char* __restrict__ gwave, uint32_t voff, int64_t round_bytes,
-                                                  char* lds_wave) {
-    using KM = KMajor<COLS, NW>;
-#pragma unroll
-    for (int t = 0; t < KM::ROUNDS; ++t) {
-        const char* gp = gwave + t * round_bytes + voff;
-        char* lp = lds_wave + t * (KM::ROUND_ROWS * KM::ROW_BYTES);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
-                                         (__attribute__((address_space(3))) void*)lp, 16, 0, 0);
-    }
-}
-
 template <int OFF>
 __device__ __forceinline__ bf16x8 read_tr_frag(uint32_t a0, uint32_t a1) {
     const s16x4 lo = ds_read_tr64<OFF>(a0);
@@ -382,59 +227,131 @@ __device__ __forceinline__ void load_frags_kmajor(Frags<S::WI, S::WJ>& f, uint32
     for (int jb = 0; jb < S::WJ; ++jb) f.b[jb] = read_tr_frag<OB>(cur + xb[jb][0], cur + xb[jb][1]);
 }
 
-// acc[i-block][j-block] += sum over `ktiles` steps of 64 rows of A(k, i) B(k, j).
-// A points at (row 0, first column of the i tile), B likewise; lda / ldb are row strides in elements.
-template <class S>
-__device__ __forceinline__ void mainloop_kmajor(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B,
-                                                int64_t ldb, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ]) {
-    constexpr int WI = S::WI, WJ = S::WJ;
-    using KA = KMajor<S::BI, S::NW>;
-    using KB = KMajor<S::BJ, S::NW>;
+// One operand of a contraction, seen from a tile: element (outer index o, contraction index k) at p[o * ld + k], or, if
+// the contraction index is the slow one ("k-major"), at p[k * ld + o].  `step` is the distance of two K steps in bytes.
+// outer_left, k_left: how many outer and contraction indices exist from here on (both >= 1; looked at only for an
+// operand that is read in place, not from a zero-padded copy).
+struct Operand {
+    const bf16_t* p;
+    int64_t ld, step;
+    int outer_left = 0;
+    int64_t k_left = 0;
+};
+
+// How a wave requests one K step of a tile with EXT outer indices from an operand, and where in the LDS it goes.
+// CLAMP: requests past the end of a matrix that is read in place repeat its last row or chunk instead.  What a
+// repeated outer index contributes is dropped by the epilogues; a repeated contraction index meets a zero of the other
+// operand (packed hidden rows and dz are zero there).
+template <class S, int EXT, bool KM, bool CLAMP>
+struct Loader {
+    using K = KMajor<EXT, S::NW>;
+    static constexpr int ROUNDS = KM ? K::ROUNDS : EXT / (8 * S::NW);           // requests per wave and step
+    static constexpr int ROUND = KM ? K::ROUND_ROWS : 8 * S::NW;                // rows between two of them
+    static constexpr int LDS_ROUND = KM ? K::ROUND_ROWS * K::ROW_BYTES : 8 * S::NW * 128;
+    static constexpr int NV = CLAMP ? ROUNDS : 1;
+    const char* g;          // wave-uniform (scalar registers)
+    int64_t ld2;            // bytes
+    uint32_t voff[NV];      // lane's offset from g (CLAMP: for every request; else of the first one)
+    int row0, col;          // CLAMP: lane's row of round 0, and its first element within a row
+    int lds_wave;           // byte offset of the wave's first request within the operand's stage
+    int64_t k_left;
+    __device__ __forceinline__ Loader(const Operand& o, int wave, int lane) {
+        ld2 = o.ld * 2; k_left = o.k_left;
+        if (KM) {       // lane l of a request covers chunk slot l % CPR of row l / CPR of its band
+            const int lrow = lane / K::CPR, pos = lane % K::CPR, row = wave * K::RPI + lrow;
+            col = (((pos >> 2) ^ (row & (K::SEGS - 1))) * 4 + (pos & 3)) * 8;
+            lds_wave = wave * K::RPI * K::ROW_BYTES;
+            row0 = row;
+            if (CLAMP) { g = (const char*)o.p; col = min(col, o.outer_left - 8); }
+            else { g = (const char*)(o.p + (int64_t)(wave * K::RPI) * o.ld); voff[0] = (uint32_t)(lrow * ld2 + col * 2); }
+        } else {        // lane l of a request covers row l / 8 of the wave's 8-row band and the chunk that belongs at slot l % 8
+            col = ((lane & 7) ^ ((((wave & 1) << 2) + (lane >> 4)) & 7)) * 8;
+            lds_wave = wave * 8 * 128;
+            row0 = wave * 8 + (lane >> 3);
+            if (CLAMP) {
+                g = (const char*)o.p;
+#pragma unroll
+                for (int r = 0; r < NV; ++r) voff[r] = (uint32_t)(min(row0 + r * ROUND, o.outer_left - 1) * ld2 + col * 2);
+            } else {
+                g = (const char*)(o.p + (int64_t)(wave * 8) * o.ld);
+                voff[0] = (uint32_t)((lane >> 3) * ld2 + col * 2);
+            }
+        }
+    }
+    // CLAMP: offsets for K step `kt` (only the last one may be short; every step is treated alike: no branch in the loop)
+    __device__ __forceinline__ void at_step(int kt) {
+        if (!CLAMP) return;
+        const int64_t left = k_left - (int64_t)kt * 64;
+        const int here = left < 64 ? (int)left : 64;
+        if (KM) {
+#pragma unroll
+            for (int r = 0; r < NV; ++r) voff[r] = (uint32_t)min(row0 + r * ROUND, here - 1) * (uint32_t)ld2 + (uint32_t)(col * 2);
+        } else {
+            const int c = min(col, here - 8);   // the rows' share of voff stays, the chunk's is replaced
+            const uint32_t move = (uint32_t)((c - last_col) * 2);
+#pragma unroll
+            for (int r = 0; r < NV; ++r) voff[r] += move;
+            last_col = c;
+        }
+    }
+    int last_col = 0;
+    __device__ __forceinline__ void start() { last_col = col; at_step(0); }
+    __device__ __forceinline__ void request(int r, char* stage) const {
+        if (CLAMP) load_to_lds_16(g + voff[r], stage + lds_wave + r * LDS_ROUND);
+        else load_to_lds_16(g + (int64_t)(r * ROUND) * ld2 + voff[0], stage + lds_wave + r * LDS_ROUND);
+    }
+};
+
+// Where a lane reads its MFMA fragments of an operand: blocks of 32 outer indices from block `first` on.
+template <class S, int EXT, int NB, bool KM>
+struct Reader {
+    using K = KMajor<EXT, S::NW>;
+    static constexpr int READS = KM ? 2 * NB : NB;    // LDS reads per sub-step
+    int x[KM ? NB : 4][2];    // k-major: byte offsets of a block's two half fragments; else x[sub-step][0]
+    __device__ __forceinline__ Reader(int lane, int first, int base) {
+        if constexpr (KM) {
+            // lane l of a transpose read addresses row 8 (l / 32) + (l % 16) / 4 (+ 4 for the second half of the fragment,
+            // + 16 per sub-step), 8 bytes at column 32 b + 16 ((l / 16) % 2) + 4 (l % 4)
+            const int q = (lane & 15) >> 2;
+            const int sub_bytes = (2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + 8 * (lane & 1);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int row = 8 * (lane >> 5) + q + 4 * h;
+                const int at = base + row * K::ROW_BYTES + ((first ^ ((4 * h + q) & (K::SEGS - 1))) * 64) + sub_bytes;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) x[n][h] = at ^ (n * 64);
+            }
+        } else {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                x[ks][0] = base + (first * 32 + (lane & 31)) * 128 + (((ks * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 16);
+        }
+    }
+    template <int KS, int... N>
+    __device__ __forceinline__ void load_seq(bf16x8 (&f)[NB], uint32_t stage, std::integer_sequence<int, N...>) const {
+        if constexpr (KM) ((f[N] = read_tr_frag<KS * 16 * K::ROW_BYTES>(stage + x[N][0], stage + x[N][1])), ...);
+        else ((f[N] = ds_read128<N * (32 * 128)>(stage + x[KS][0])), ...);
+    }
+    template <int KS>
+    __device__ __forceinline__ void load(bf16x8 (&f)[NB], uint32_t stage) const {
+        load_seq<KS>(f, stage, std::make_integer_sequence<int, NB>{});
+    }
+};
+
+// acc = sum over `ktiles` steps of 64 of A(i, k) B(j, k) for the tile the two operands point at.
+// AK / BK: the operand is k-major; CLAMP: A is read in place (see Loader).
+template <class S, bool AK, bool BK, bool CLAMP, class Pace = NoPace>
+__device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ],
+                                         Pace pace = Pace()) {
+    constexpr int WI = S::WI, WJ = S::WJ, B_STAGE = S::BI * 128;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_i = wave % S::NWI, wave_j = wave / S::NWI;
-
-
-    // global side: lane l of a wave instruction covers chunk slot l % CPR of row l / CPR of its band
-    auto lane_voff = [&](int cpr, int segs, int rpi, int64_t ld) -> uint32_t {
-        const int lrow = lane / cpr, p = lane % cpr;
-        const int row_low = (wave * rpi + lrow) & (segs - 1);
-        const int gseg = (p >> 2) ^ row_low;
-        return (uint32_t)(((int64_t)lrow * ld + (gseg * 4 + (p & 3)) * 8) * 2);
-    };
-    const uint32_t voff_a = lane_voff(KA::CPR, KA::SEGS, KA::RPI, lda);
-    const uint32_t voff_b = lane_voff(KB::CPR, KB::SEGS, KB::RPI, ldb);
-    const char* ga = (const char*)(A + (int64_t)(wave * KA::RPI) * lda);
-    const char* gb = (const char*)(B + (int64_t)(wave * KB::RPI) * ldb);
-    const int64_t round_a = (int64_t)KA::ROUND_ROWS * lda * 2, round_b = (int64_t)KB::ROUND_ROWS * ldb * 2;
-    const int64_t step_a = 64 * lda * 2, step_b = 64 * ldb * 2;
-    const int lds_wave_a = wave * KA::RPI * KA::ROW_BYTES;
-    const int lds_wave_b = KA::TILE_BYTES + wave * KB::RPI * KB::ROW_BYTES;
-
-    // LDS side: lane l of a transpose read addresses row 8 (l / 32) + (l % 16) / 4 (+ 4 for the second
-    // half of the fragment, + 16 per sub-step), 8 bytes at column 32 b + 16 ((l / 16) % 2) + 4 (l % 4)
-    const int q = (lane & 15) >> 2;
-    const int sub_bytes = (2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + 8 * (lane & 1);
-    const int rowpart = 8 * (lane >> 5) + q;
-    int base_a[2], base_b[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int sw = 4 * r + q;   // low bits of the row this lane addresses in half r
-        base_a[r] = (rowpart + 4 * r) * KA::ROW_BYTES + ((((wave_i * WI) ^ (sw & (KA::SEGS - 1))) * 64)) + sub_bytes;
-        base_b[r] = KA::TILE_BYTES + (rowpart + 4 * r) * KB::ROW_BYTES +
-                    ((((wave_j * WJ) ^ (sw & (KB::SEGS - 1))) * 64)) + sub_bytes;
-    }
-
-    int xa[WI][2], xb[WJ][2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-#pragma unroll
-        for (int ib = 0; ib < WI; ++ib) xa[ib][r] = base_a[r] ^ (ib * 64);
-#pragma unroll
-        for (int jb = 0; jb < WJ; ++jb) xb[jb][r] = base_b[r] ^ (jb * 64);
-    }
-    constexpr int NR = 2 * (WI + WJ);   // LDS reads per sub-step
+    Loader<S, S::BI, AK, CLAMP> la(A, wave, lane);
+    Loader<S, S::BJ, BK, false> lb(B, wave, lane);
+    const Reader<S, S::BI, WI, AK> ra(lane, wave_i * WI, 0);
+    const Reader<S, S::BJ, WJ, BK> rb(lane, wave_j * WJ, B_STAGE);
 
 #pragma unroll
     for (int ib = 0; ib < WI; ++ib)
@@ -445,29 +362,48 @@ __device__ __forceinline__ void mainloop_kmajor(const bf16_t* __restrict__ A, in
 
     if (ktiles <= 0) return;
 
-    lds_barrier();   // see mainloop
-    issue_kmajor_load<S::BI, S::NW>(ga, voff_a, round_a, lds + lds_wave_a);
-    issue_kmajor_load<S::BJ, S::NW>(gb, voff_b, round_b, lds + lds_wave_b);
+    constexpr int NRA = Loader<S, S::BI, AK, CLAMP>::ROUNDS, NRB = Loader<S, S::BJ, BK, false>::ROUNDS, T = NRA + NRB;
+    char* dst = lds;        // stage the requests go to
+    auto request = [&](int r) {
+        if (r < NRA) la.request(r, dst); else lb.request(r - NRA, dst + B_STAGE);
+    };
+    // A workgroup runs tile after tile: everybody must be done with the LDS stages of the tile before
+    // (its last reads, its trailing requests, a staged epilogue) before they are filled again.
+    la.start();
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < T; ++r) request(r);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
 
-    // same step structure as mainloop
+    // One K step on stage `cur` = kt % 2 (its first fragments f0 were read at the end of the step before,
+    // and the first half of tile kt+1 was requested there too):
+    //   read f1 (sub-step 1) | MFMA f0 + second half of the requests for tile kt+1
+    //   read f0 (sub-step 2) | MFMA f1
+    //   read f1 (sub-step 3) | MFMA f0
+    //   wait: own requests landed, own reads of `cur` done; barrier
+    //   read f0 of tile kt+1 | MFMA f1 + first half of the requests for tile kt+2 (into `cur`)
+    // After the barrier tile kt+1 is complete and nobody reads `cur` any more.  Steps past the last
+    // tile re-request the last tile into the idle stage, which keeps the loop free of branches and
+    // every address in bounds.  (Skipping those requests with a uniform branch each was tried: the logits
+    // kernels, where they are 6 % of the memory -> LDS traffic, got 2 % slower and dHidden 5 %.)
     Frags<WI, WJ> f0, f1;
-    char* dst = lds + S::STAGE_BYTES;
-    auto request = [&](int r) {
-        if (r < KA::ROUNDS)
-            load_to_lds_16(ga + r * round_a + voff_a, dst + lds_wave_a + r * (KA::ROUND_ROWS * KA::ROW_BYTES));
-        else
-            load_to_lds_16(gb + (r - KA::ROUNDS) * round_b + voff_b,
-                           dst + lds_wave_b + (r - KA::ROUNDS) * (KB::ROUND_ROWS * KB::ROW_BYTES));
+    constexpr int NR = Reader<S, S::BI, WI, AK>::READS + Reader<S, S::BJ, WJ, BK>::READS;   // LDS reads per sub-step
+    auto advance = [&](bool more, int kt) {
+        la.g += more ? A.step : 0;
+        lb.g += more ? B.step : 0;
+        la.at_step(kt);
     };
-    constexpr int T = KA::ROUNDS + KB::ROUNDS;
+    dst = lds + S::STAGE_BYTES;
     {
-        load_frags_kmajor<0, S>(f0, lds_addr(lds), xa, xb);
-        const bool more = ktiles > 1;
-        ga += more ? step_a : 0;
-        gb += more ? step_b : 0;
+        const uint32_t l0 = lds_addr(lds);
+        ra.template load<0>(f0.a, l0);
+        rb.template load<0>(f0.b, l0);
+        advance(ktiles > 1, ktiles > 1 ? 1 : 0);
         request_first_half<S, T>(request);   // of tile 1
+        // A register that an LDS read (issued from inline assembly) is still writing must not meet
+        // a compiler-made copy, and copies appear where control flow splits or joins: every read is
+        // therefore waited for in the block that issued it.
         wait_frags<0>(f0);
     }
     for (int kt = 0; kt < ktiles; ++kt) {
@@ -475,17 +411,20 @@ __device__ __forceinline__ void mainloop_kmajor(const bf16_t* __restrict__ A, in
         char* nxt = lds + ((kt + 1) & 1) * S::STAGE_BYTES;
         const uint32_t lc = lds_addr(cur), ln = lds_addr(nxt);
         fence();
-        load_frags_kmajor<1, S>(f1, lc, xa, xb);
+        ra.template load<1>(f1.a, lc);
+        rb.template load<1>(f1.b, lc);
         fence();
         dst = nxt;
         mma_block_requesting<S, 1, T>(f0, acc, request);
         fence();
-        load_frags_kmajor<2, S>(f0, lc, xa, xb);
+        ra.template load<2>(f0.a, lc);
+        rb.template load<2>(f0.b, lc);
         wait_frags<NR>(f1);
         fence();
         mma_block<WI, WJ>(f1, acc);
         fence();
-        load_frags_kmajor<3, S>(f1, lc, xa, xb);
+        ra.template load<3>(f1.a, lc);
+        rb.template load<3>(f1.b, lc);
         wait_frags<NR>(f0);
         fence();
         mma_block<WI, WJ>(f0, acc);
@@ -493,11 +432,12 @@ __device__ __forceinline__ void mainloop_kmajor(const bf16_t* __restrict__ A, in
         wait_frags<0>(f1);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lds_barrier();
-        load_frags_kmajor<0, S>(f0, ln, xa, xb);
+        pace(kt);   // no LDS read or tile request is in flight here
+        ra.template load<0>(f0.a, ln);
+        rb.template load<0>(f0.b, ln);
         fence();
         const bool more = kt + 2 < ktiles;
-        ga += more ? step_a : 0;
-        gb += more ? step_b : 0;
+        advance(more, more ? kt + 2 : ktiles - 1);
         dst = cur;
         mma_block_requesting<S, 0, T>(f1, acc, request);
         fence();
@@ -646,6 +586,23 @@ inline unsigned grid_for(int tilesI, int tilesJ) {
     return (unsigned)(ids < cus ? ids : cus);
 }
 
+// The head as the first operand of the logits kernels (tile ti of 256 vocabulary entries, contraction over d) and of
+// dHidden (tile ti of the hidden dimension, contraction over the vocabulary from K step k0 on): from the packed copy, or
+// in place, where one of the two layouts has its contraction index last and the other is read k-major.
+template <class S, int WM>
+__device__ __forceinline__ Operand logits_w(const WInPlace& w, const bf16_t* packed, int64_t ldk, int ti) {
+    if (WM == W_PACKED) return Operand{packed + (int64_t)ti * S::BI * ldk, ldk, 128};
+    const int64_t v0 = (int64_t)ti * S::BI;
+    if (WM == W_VD) return Operand{w.W + v0 * w.d, w.d, 128, (int)(w.V - v0), w.d};
+    return Operand{w.W + v0, w.V, w.V * (K_TILE * 2), (int)(w.V - v0), w.d};
+}
+template <class S, int WM>
+__device__ __forceinline__ Operand dh_w(const WInPlace& w, int ti, int k0) {
+    const int64_t d0 = (int64_t)ti * S::BI, v0 = (int64_t)k0 * K_TILE;
+    if (WM == W_VD) return Operand{w.W + v0 * w.d + d0, w.d, w.d * (K_TILE * 2), (int)(w.d - d0), w.V - v0};
+    return Operand{w.W + d0 * w.V + v0, w.V, 128, (int)(w.d - d0), w.V - v0};
+}
+
 template <class S>
 struct Lane {
     int lane, wave, wave_i, wave_j, hi, lj;
@@ -703,6 +660,21 @@ __device__ __forceinline__ void store_tile_through_lds(char* lds, const Lane<S>&
     }
 }
 
+// ragged last vocabulary tile: the columns that do not exist become -infinity
+template <class S>
+__device__ __forceinline__ void mask_padding(f32x16 (&acc)[S::WI][S::WJ], int n_valid, int hi) {
+    if (n_valid >= S::WI * 32) return;
+#pragma unroll
+    for (int ib = 0; ib < S::WI; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < S::WJ; ++jb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int rel = ib * 32 + (v >> 2) * 8 + hi * 4 + (v & 3);
+                acc[ib][jb][v] = rel < n_valid ? acc[ib][jb][v] : -INFINITY;
+            }
+}
+
 // ------------------------------------------------------------------------------------- fwd_lse
 // STORE: also keep, for a backward that reloads them instead of recomputing the logits, the tile's
 // scaled probabilities u[j][v] = exp(z[j][v] - r[j]) in bf16 in a.zc.  The reference r[j] (a.refz) is
@@ -725,17 +697,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
     const int n_valid = (int)a.V - i_base;          // columns of this wave that exist (>= 128: all)
     const int64_t slot = (int64_t)t.ti * S::NWI + L.wave_i;
     const float zs = a.inv_temp * LOG2E;            // inv_temp > 0: max commutes with the scaling
-    if (n_valid < WI * 32) {                        // ragged last vocabulary tile: mask the padding
-#pragma unroll
-        for (int ib = 0; ib < WI; ++ib)
-#pragma unroll
-            for (int jb = 0; jb < WJ; ++jb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int rel = ib * 32 + (v >> 2) * 8 + L.hi * 4 + (v & 3);
-                    acc[ib][jb][v] = rel < n_valid ? acc[ib][jb][v] : -INFINITY;
-                }
-    }
+    mask_padding<S>(acc, n_valid, L.hi);
     float m[WJ], nm[WJ], l[WJ];
 #pragma unroll
     for (int jb = 0; jb < WJ; ++jb) {
@@ -789,7 +751,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
 }
 
 // one workgroup per CU on 256 x 256 tiles: the logits tile on MFMA, then the epilogue above
-template <class S, bool STORE>
+template <class S, bool STORE, int WM>
 __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
@@ -802,8 +764,8 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
     if (!t.valid) continue;
     f32x16 acc[WI][WJ];
-    mainloop<S>(a.Wvd + (int64_t)t.ti * S::BI * a.ldk, a.ldk, a.Hc + j_tile * a.ldk, a.ldk, (int)(a.dpad / K_TILE), lds,
-                acc);
+    mainloop<S, WM == W_DV, false, WM != W_PACKED>(logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti), Operand{a.Hc + j_tile * a.ldk, a.ldk, 128},
+                                                   (int)(a.dpad / K_TILE), lds, acc);
     fwd_epilogue<S, STORE>(a, t, j_tile, M, lds, acc);
     }
 }
@@ -964,7 +926,7 @@ __global__ void block_w32_kernel(const bf16_t* __restrict__ Wvd, int64_t ldk, bf
 }
 
 // ------------------------------------------------------------------------------------------ dz
-template <class S>
+template <class S, int WM>
 __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
@@ -975,17 +937,18 @@ __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
     const TileId t = map_tile(pid, a.tilesV, tilesM, a.gi);
     if (!t.valid) continue;
     f32x16 acc[WI][WJ];
-    mainloop<S>(a.Wvd + (int64_t)t.ti * S::BI * a.ldk, a.ldk,
-                     a.Hc + (int64_t)t.tj * S::BJ * a.ldk, a.ldk, (int)(a.dpad / K_TILE), lds, acc);
+    mainloop<S, WM == W_DV, false, WM != W_PACKED>(logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti),
+                                                   Operand{a.Hc + (int64_t)t.tj * S::BJ * a.ldk, a.ldk, 128}, (int)(a.dpad / K_TILE), lds, acc);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the spare tile request of the last step
     __syncthreads();                                    // every wave is done with both stages
     // dz = -g p here; the +g of the sampled token's column is added by a separate small kernel, so
     // the per-element work is one fma, one exp, one multiply and half a convert.  Rows past the last
-    // token get g = 0; columns past V hold finite values that only ever meet zero weights.
+    // token get g = 0; columns past V are zero (dHidden may meet repeated weights there).
     const Lane<S> L;
     const int64_t i_base = (int64_t)t.ti * S::BI + L.wave_i * (WI * 32);
     const int64_t jl_base = (int64_t)t.tj * S::BJ + L.wave_j * (WJ * 32);   // row in chunk
     const float zs = a.inv_temp * LOG2E;
+    mask_padding<S>(acc, (int)(a.V - i_base), L.hi);
     float ngj[WJ], nlse[WJ];
 #pragma unroll
     for (int jb = 0; jb < WJ; ++jb) {
@@ -1064,6 +1027,9 @@ __device__ __forceinline__ void sum_units(const float* part, const TileShare& sh
 }
 
 // ------------------------------------------------------------------------------------------ dh
+// K steps: the vocabulary rounded up to whole steps (in the packed copy and in dz zeros follow)
+__device__ __forceinline__ int dh_ksteps(const DhArgs& a) { return (int)((a.w.V + K_TILE - 1) / K_TILE); }
+
 // stores a tile of dHidden: accumulators times the row factor (if any), bf16, to the rows' positions
 template <class S>
 __device__ __forceinline__ void dh_store(const DhArgs& a, const TileId& t, int M, const f32x16 (&acc)[S::WI][S::WJ]) {
@@ -1089,19 +1055,20 @@ __device__ __forceinline__ void dh_store(const DhArgs& a, const TileId& t, int M
 }
 
 // acc = the tile's contraction over the K steps [k0, k1)
-template <class S, class Pace>
+template <class S, int WM, class Pace>
 __device__ __forceinline__ void dh_contract(const DhArgs& a, const TileId& t, int k0, int k1, char* lds,
                                             f32x16 (&acc)[S::WI][S::WJ], Pace pace) {
-    if (a.WdvB)   // A from the tile-blocked copy: one contiguous 128-byte-row block per K step
-        mainloop<S, Pace>(a.WdvB + ((int64_t)t.ti * (a.Vpad / K_TILE) + k0) * (S::BI * 64), 64,
-                          a.dz + (int64_t)t.tj * S::BJ * a.ldv + (int64_t)k0 * K_TILE, a.ldv, k1 - k0, lds, acc,
-                          S::BI * 128, 128, pace);
-    else
-        mainloop<S, Pace>(a.Wdv + (int64_t)t.ti * S::BI * a.ldv + (int64_t)k0 * K_TILE, a.ldv,
-                          a.dz + (int64_t)t.tj * S::BJ * a.ldv + (int64_t)k0 * K_TILE, a.ldv, k1 - k0, lds, acc, 128, 128, pace);
+    const Operand z{a.dz + (int64_t)t.tj * S::BJ * a.ldv + (int64_t)k0 * K_TILE, a.ldv, 128};
+    if constexpr (WM != W_PACKED) {
+        mainloop<S, WM == W_VD, false, true, Pace>(dh_w<S, WM>(a.w, t.ti, k0), z, k1 - k0, lds, acc, pace);
+        return;
+    }
+    const Operand w = a.WdvB ? Operand{a.WdvB + ((int64_t)t.ti * (a.Vpad / K_TILE) + k0) * (S::BI * 64), 64, S::BI * 128}   // tile-blocked copy
+                             : Operand{a.Wdv + (int64_t)t.ti * S::BI * a.ldv + (int64_t)k0 * K_TILE, a.ldv, 128};
+    mainloop<S, false, false, false, Pace>(w, z, k1 - k0, lds, acc, pace);
 }
 
-template <class S>
+template <class S, int WM>
 __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
@@ -1112,7 +1079,7 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
     // short last chunk would otherwise leave whole XCDs with nothing but empty tiles
     const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
     const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
-    const int ktiles = (int)(a.Vpad / K_TILE);
+    const int ktiles = dh_ksteps(a);
     const TileShare sh(tilesD * tilesM, grid, ktiles, a.part != nullptr);
     const int gi = a.gi > 0 ? a.gi : tilesD;
     GridPace pace{a.pace, 0u, (unsigned)grid, a.pace ? a.pace_every : 0};   // see GridPace
@@ -1121,7 +1088,7 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
         const TileId t = tile_of_vid((x * sh.full_rounds + round) * sh.wgs + w, tilesD, tilesM, gi);
         f32x16 acc[WI][WJ];
         pace.base = meetings * (unsigned)(grid * round);
-        dh_contract<S, GridPace>(a, t, 0, ktiles, lds, acc, pace);
+        dh_contract<S, WM, GridPace>(a, t, 0, ktiles, lds, acc, pace);
         dh_store<S>(a, t, M, acc);
     }
     // the last round: unit u = (segment u / rem, tile u % rem); the accumulators of a cut tile go to part[u]
@@ -1135,11 +1102,11 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
         const TileId t = tile_of_vid(sh.full_rounds * grid + tpos, tilesD, tilesM, gi);
         f32x16 acc[WI][WJ];
         if (!sh.cut) {
-            dh_contract<S, GridPace>(a, t, k0, k1, lds, acc, pace);
+            dh_contract<S, WM, GridPace>(a, t, k0, k1, lds, acc, pace);
             dh_store<S>(a, t, M, acc);
             continue;
         }
-        dh_contract<S, NoPace>(a, t, k0, k1, lds, acc, NoPace());
+        dh_contract<S, WM, NoPace>(a, t, k0, k1, lds, acc, NoPace());
         store_unit<S>(a.part, u, acc);
     }
 }
@@ -1153,7 +1120,7 @@ __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.m0 >= Mr) return;
     const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
-    const TileShare sh(tilesD * tilesM, grid_of_dh, (int)(a.Vpad / K_TILE), true);
+    const TileShare sh(tilesD * tilesM, grid_of_dh, dh_ksteps(a), true);
     const int tpos = blockIdx.x, ib = blockIdx.y / WJ, jb = blockIdx.y % WJ;
     if (!sh.cut || tpos >= sh.rem) return;
     const TileId t = tile_of_vid(sh.full_rounds * grid_of_dh + tpos, tilesD, tilesM, a.gi > 0 ? a.gi : tilesD);
@@ -1301,9 +1268,10 @@ __global__ __launch_bounds__(S::NT) void dw_kernel(DwArgs a) {
     auto contract = [&](const TileId& t, int k0, int k1, f32x16 (&acc)[WI][WJ]) {
         const bf16_t* z = a.dz + (int64_t)t.ti * (VD ? S::BJ : S::BI) + (int64_t)k0 * K_TILE * a.ldz;
         const bf16_t* h = a.Hc + (int64_t)t.tj * (VD ? S::BI : S::BJ) + (int64_t)k0 * K_TILE * a.ldH;
-        if constexpr (VD) mainloop_kmajor<S>(h, a.ldH, z, a.ldz, k1 - k0, lds, acc);
+        const Operand oz{z, a.ldz, a.ldz * (K_TILE * 2)}, oh{h, a.ldH, a.ldH * (K_TILE * 2)};
+        if constexpr (VD) mainloop<S, true, true, false>(oh, oz, k1 - k0, lds, acc);
         else if constexpr (DEEP) mainloop_kmajor32<S, 4>(z, a.ldz, h, a.ldH, (k1 - k0) * 2, lds, acc);
-        else mainloop_kmajor<S>(z, a.ldz, h, a.ldH, k1 - k0, lds, acc);
+        else mainloop<S, true, true, false>(oz, oh, k1 - k0, lds, acc);
     };
     auto finish = [&](const TileId& t, const f32x16 (&acc)[WI][WJ]) {
         lds_barrier();   // every wave is done with both stages
@@ -1353,12 +1321,14 @@ __global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_
         out.put(off + q * 8, left - q * 8, cur[q], f32x4u{sum[q * 4], sum[q * 4 + 1], sum[q * 4 + 2], sum[q * 4 + 3]});
 }
 
-// Logit of the sampled token: zy[j] = inv_temp * <Hc[j, :], Wvd[tok_j, :]>, one wave per token row
-// (16-byte loads, fp32 accumulation, fixed reduction tree).
+// Logit of the sampled token: zy[j] = inv_temp * <Hc[j, :], W[tok_j, :]>, one wave per token row
+// (16-byte loads, fp32 accumulation, fixed reduction tree).  W has a token's weights in a row, or (GATHER) in a
+// column: 64 bytes are then read for each, which a small batch can afford; the sum is formed in the same order.
 // If refz is given it receives the reference of the storing forward: zy[j] - ref_logp[row_index[j]]
 // (zy[j] alone without ref_logp or where that value is not finite).
-__global__ __launch_bounds__(256) void token_logit_kernel(const bf16_t* __restrict__ Hc, const bf16_t* __restrict__ Wvd,
-                                                          int64_t ldk, int64_t dpad, const int32_t* __restrict__ tokc,
+template <bool GATHER>
+__global__ __launch_bounds__(256) void token_logit_kernel(const bf16_t* __restrict__ Hc, int64_t ldk, const bf16_t* __restrict__ W,
+                                                          int64_t ldw, int64_t d, const int32_t* __restrict__ tokc,
                                                           const int32_t* __restrict__ counts, float inv_temp,
                                                           float* __restrict__ zy, const float* __restrict__ ref_logp,
                                                           const int32_t* __restrict__ row_index,
@@ -1367,10 +1337,17 @@ __global__ __launch_bounds__(256) void token_logit_kernel(const bf16_t* __restri
     if (j >= counts[CNT_M]) return;
     const int lane = threadIdx.x & 63;
     const bf16x8* h = (const bf16x8*)(Hc + j * ldk);
-    const bf16x8* w = (const bf16x8*)(Wvd + (int64_t)tokc[j] * ldk);
+    const bf16_t* w = W + (GATHER ? (int64_t)tokc[j] : (int64_t)tokc[j] * ldw);
     float acc = 0.f;
-    for (int64_t c = lane; c < dpad / 8; c += 64) {
-        const bf16x8 hv = h[c], wv = w[c];
+    for (int64_t c = lane; c < d / 8; c += 64) {
+        const bf16x8 hv = h[c];
+        bf16x8 wv;
+        if (GATHER) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wv[e] = __builtin_bit_cast(__bf16, w[(c * 8 + e) * ldw]);
+        } else {
+            wv = ((const bf16x8*)w)[c];
+        }
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc = fmaf((float)hv[e], (float)wv[e], acc);
     }
@@ -1481,30 +1458,30 @@ using G16 = Geo<2, 8, 4, 1>;       // 256 x 256, 16 waves of 128 x 32
 using G16_I128 = Geo<2, 8, 2, 1>;  // 128 x 256
 using G16_J128 = Geo<4, 4, 2, 1>;  // 256 x 128
 
-template <class S>
+template <class S, int WM>
 void launch_fwd_lse_t(const FwdArgs& a, hipStream_t st) {
     if (a.zc) {
-        allow_lds<&fwd_lse_kernel<S, true>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, true><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+        allow_lds<&fwd_lse_kernel<S, true, WM>>(S::LDS_BYTES);
+        fwd_lse_kernel<S, true, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
     } else {
-        allow_lds<&fwd_lse_kernel<S, false>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, false><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+        allow_lds<&fwd_lse_kernel<S, false, WM>>(S::LDS_BYTES);
+        fwd_lse_kernel<S, false, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
     }
 }
-template <class S>
+template <class S, int WM>
 void launch_dz_t(const DzArgs& a, hipStream_t st) {
-    allow_lds<&dz_kernel<S>>(S::LDS_BYTES);
-    dz_kernel<S><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+    allow_lds<&dz_kernel<S, WM>>(S::LDS_BYTES);
+    dz_kernel<S, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
 }
-template <class S>
+template <class S, int WM>
 void launch_dh_t(const DhArgs& a, hipStream_t st) {
-    allow_lds<&dh_kernel<S>>(S::LDS_BYTES);
+    allow_lds<&dh_kernel<S, WM>>(S::LDS_BYTES);
     const int tilesD = (int)(a.dpadR / S::BI);
     DhArgs b = a;
     if ((size_t)MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
     // with scratch for cut tiles a launch of few tiles takes the whole chip as well
     const unsigned grid = b.part ? (unsigned)(g_num_cu.load() / 8 * 8) : grid_for(tilesD, a.tilesM);
-    dh_kernel<S><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
+    dh_kernel<S, WM><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
     const int64_t tiles = (int64_t)tilesD * a.tilesM;
     if (b.part) dh_reduce_kernel<S><<<dim3((unsigned)(tiles < grid ? tiles : grid), S::WI * S::WJ), S::NT, 0, st>>>(b, (int)grid);
 }
@@ -1523,6 +1500,7 @@ void launch_dw_t(const DwArgs& a, hipStream_t st) {
 }  // namespace
 
 size_t dh_part_bytes() { return (size_t)MAX_UNITS * 256 * 256 * 4; }
+bool default_waves() { return g_waves.load() == 0; }
 void set_waves_per_workgroup(int n) { g_waves = (n == 4 || n == 8 || n == 16) ? n : 0; }
 void set_cu_count(int n) { g_num_cu = n >= 8 ? n : 8; }
 
@@ -1566,20 +1544,34 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
         }
         return;
     }
+    if (a.w.mode == W_VD) { launch_fwd_lse_t<G8, W_VD>(a, st); return; }
+    if (a.w.mode == W_DV) { launch_fwd_lse_t<G8, W_DV>(a, st); return; }
     const int w = waves_for(8);
-    if (w == 16) launch_fwd_lse_t<G16>(a, st); else if (w == 8) launch_fwd_lse_t<G8>(a, st); else launch_fwd_lse_t<G4>(a, st);
+    if (w == 16) launch_fwd_lse_t<G16, W_PACKED>(a, st);
+    else if (w == 8) launch_fwd_lse_t<G8, W_PACKED>(a, st);
+    else launch_fwd_lse_t<G4, W_PACKED>(a, st);
 }
 void launch_token_logit(const FwdArgs& a, int64_t row0, int64_t rows_max, hipStream_t st) {
     if (rows_max <= 0) return;
-    token_logit_kernel<<<(unsigned)((rows_max + 3) / 4), 256, 0, st>>>(a.Hc, a.Wvd, a.ldk, a.dpad, a.tokc, a.counts,
-                                                                     a.inv_temp, a.zy, a.ref_logp, a.row_index,
-                                                                     a.zc ? a.refz : nullptr, row0);
+    const unsigned blocks = (unsigned)((rows_max + 3) / 4);
+    float* refz = a.zc ? a.refz : nullptr;
+    if (a.w.mode == W_DV)
+        token_logit_kernel<true><<<blocks, 256, 0, st>>>(a.Hc, a.ldk, a.w.W, a.w.V, a.w.d, a.tokc, a.counts, a.inv_temp, a.zy,
+                                                         a.ref_logp, a.row_index, refz, row0);
+    else
+        token_logit_kernel<false><<<blocks, 256, 0, st>>>(a.Hc, a.ldk, a.w.mode == W_VD ? a.w.W : a.Wvd, a.w.mode == W_VD ? a.w.d : a.ldk,
+                                                          a.w.d, a.tokc, a.counts, a.inv_temp, a.zy, a.ref_logp, a.row_index,
+                                                          refz, row0);
 }
 int fwd_slots_per_tile() { return 2; }
 
 void launch_dz(const DzArgs& a, hipStream_t st) {
     const int w = waves_for(8);
-    if (w == 16) launch_dz_t<G16>(a, st); else if (w == 8) launch_dz_t<G8>(a, st); else launch_dz_t<G4>(a, st);
+    if (a.w.mode == W_VD) launch_dz_t<G8, W_VD>(a, st);
+    else if (a.w.mode == W_DV) launch_dz_t<G8, W_DV>(a, st);
+    else if (w == 16) launch_dz_t<G16, W_PACKED>(a, st);
+    else if (w == 8) launch_dz_t<G8, W_PACKED>(a, st);
+    else launch_dz_t<G4, W_PACKED>(a, st);
     const int64_t rows = (int64_t)a.tilesM * 256;
     token_onehot_kernel<<<(unsigned)((rows + 255) / 256), 256, 0, st>>>(a.dz, a.ldz, a.m0, rows, a.tokc, a.rowg,
                                                                       a.inv_temp, a.counts);
@@ -1595,11 +1587,12 @@ void launch_cache_finish(bf16_t* u, int64_t ldz, bf16_t* Hc, int64_t ldk, const 
 }
 void launch_dh(const DhArgs& a, hipStream_t st) {
     const int w = waves_for(4);
-    if (a.dpadR % 256 == 0) {
-        if (w == 16) launch_dh_t<G16>(a, st); else if (w == 8) launch_dh_t<G8>(a, st); else launch_dh_t<G4>(a, st);
-    } else {   // d padded to a multiple of 128 only
-        if (w == 16) launch_dh_t<G16_I128>(a, st); else if (w == 8) launch_dh_t<G8_I128>(a, st); else launch_dh_t<G4_I128>(a, st);
-    }
+    const bool d256 = a.dpadR % 256 == 0;   // else d is padded to a multiple of 128 only
+    if (a.w.mode == W_VD) d256 ? launch_dh_t<G4, W_VD>(a, st) : launch_dh_t<G4_I128, W_VD>(a, st);
+    else if (a.w.mode == W_DV) d256 ? launch_dh_t<G4, W_DV>(a, st) : launch_dh_t<G4_I128, W_DV>(a, st);
+    else if (w == 16) d256 ? launch_dh_t<G16, W_PACKED>(a, st) : launch_dh_t<G16_I128, W_PACKED>(a, st);
+    else if (w == 8) d256 ? launch_dh_t<G8, W_PACKED>(a, st) : launch_dh_t<G8_I128, W_PACKED>(a, st);
+    else d256 ? launch_dh_t<G4, W_PACKED>(a, st) : launch_dh_t<G4_I128, W_PACKED>(a, st);
 }
 
 std::atomic<int> g_dw_deep{0};

@@ -46,18 +46,22 @@ __global__ void copy_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_
     }
 }
 
-// 64x64 tile through LDS: dst[c][r] = src[r][c].  16-byte global accesses on both sides when the
+// 64x64 tile through LDS: dst[c][r] = src[r][c], row-major or (RB > 0) in tile blocks as block_rows_bf16_kernel
+// lays them out (a 64 x 64 tile is then 8 KiB of consecutive memory).  16-byte global accesses on both sides when the
 // shapes allow (vec: ld_src, ld_dst multiples of 8, 16-byte aligned bases), elements otherwise.
 // LDS rows are 66 elements (33 banks) apart: the transposed read of 8 rows x 8 columns per 64 lanes
 // is conflict free.
 __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_src,
                                                                  bf16_t* __restrict__ dst, int64_t ld_dst, int64_t R,
                                                                  int64_t C, int64_t Rpad, int64_t Cpad,
-                                                                 const int32_t* __restrict__ counts, int64_t r0, int vec) {
+                                                                 const int32_t* __restrict__ counts, int64_t r0, int vec, int RB) {
     __shared__ bf16_t tile[64][66];
     const RowLimits lim = row_limits(counts, r0, R, Rpad);
     const int64_t rb = (int64_t)blockIdx.x * 64, cb = (int64_t)blockIdx.y * 64;
     if (rb >= lim.Rpad) return;
+    auto at = [&](int64_t c, int64_t r) {
+        return RB ? dst + (c / RB * (Rpad / 64) + r / 64) * (RB * 64) + c % RB * 64 + r % 64 : dst + c * ld_dst + r;
+    };
     if (vec) {
         for (int t = threadIdx.x; t < 512; t += 256) {          // 64 rows x 8 chunks of 8 columns
             const int rr = t >> 3, q = t & 7;
@@ -82,9 +86,9 @@ __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* _
 #pragma unroll
             for (int i = 0; i < 8; ++i) e[i] = tile[q * 8 + i][cc];
             if (r + 8 <= lim.Rpad) {
-                *(uint4*)(dst + c * ld_dst + r) = *(const uint4*)e;
+                *(uint4*)at(c, r) = *(const uint4*)e;
             } else {
-                for (int i = 0; i < 8 && r + i < lim.Rpad; ++i) dst[c * ld_dst + r + i] = e[i];
+                for (int i = 0; i < 8 && r + i < lim.Rpad; ++i) *at(c, r + i) = e[i];
             }
         }
         return;
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* _
     __syncthreads();
     for (int cc = ty; cc < 64; cc += 4) {
         const int64_t c = cb + cc, r = rb + tx;
-        if (c < Cpad && r < lim.Rpad) dst[c * ld_dst + r] = tile[tx][cc];
+        if (c < Cpad && r < lim.Rpad) *at(c, r) = tile[tx][cc];
     }
 }
 
@@ -114,21 +118,41 @@ void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, const int32_t* row_
                                                          counts, r0, vec_ok);
 }
 
-// Row-major [R, ld] (R multiple of RB, C multiple of 64) -> tile-blocked: block (rt, kt) holds rows
+// [R, C] (row stride ld) -> tile-blocked [Rpad, Cpad] (multiples of RB and 64, zero padded): block (rt, kt) holds rows
 // rt*RB .. +RB, columns kt*64 .. +64 as RB contiguous 128-byte rows; blocks ordered (rt, kt).
-__global__ void block_rows_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld, bf16_t* __restrict__ dst, int RB,
-                                       int64_t KT) {
+__global__ __launch_bounds__(256) void block_rows_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld, bf16_t* __restrict__ dst,
+                                                              int64_t R, int64_t C, int RB, int64_t KT, int vec) {
     const int64_t rt = blockIdx.y, kt = blockIdx.x;
-    const bf16_t* s = src + rt * RB * ld + kt * 64;
     bf16_t* d = dst + (rt * KT + kt) * RB * 64;
-    for (int c = threadIdx.x; c < RB * 8; c += blockDim.x) {
-        const int r = c >> 3, q = c & 7;
-        *(uint4*)(d + r * 64 + q * 8) = *(const uint4*)(s + (int64_t)r * ld + q * 8);
+#pragma unroll 8
+    for (int t = threadIdx.x; t < RB * 8; t += 256) {
+        const int64_t r = rt * RB + (t >> 3), c = kt * 64 + (t & 7) * 8;
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (r < R && c < C) {
+            const bf16_t* s = src + r * ld + c;
+            if (vec && c + 8 <= C) {
+                v = *(const uint4*)s;
+            } else {
+                bf16_t e[8];
+                for (int i = 0; i < 8; ++i) e[i] = c + i < C ? s[i] : (bf16_t)0;
+                v = *(const uint4*)e;
+            }
+        }
+        *(uint4*)(d + (int64_t)t * 8) = v;
     }
 }
-void launch_block_rows_bf16(const bf16_t* src, int64_t ld, bf16_t* dst, int64_t R, int64_t C, int RB, hipStream_t st) {
-    dim3 grid((unsigned)(C / 64), (unsigned)(R / RB));
-    block_rows_bf16_kernel<<<grid, 256, 0, st>>>(src, ld, dst, RB, C / 64);
+void launch_block_rows_bf16(const bf16_t* src, int64_t ld, bf16_t* dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad, int RB,
+                            hipStream_t st) {
+    dim3 grid((unsigned)(Cpad / 64), (unsigned)(Rpad / RB));
+    const int vec = (ld % 8 == 0) && (((uintptr_t)src) % 16 == 0);
+    block_rows_bf16_kernel<<<grid, 256, 0, st>>>(src, ld, dst, R, C, RB, Cpad / 64, vec);
+}
+
+void launch_transpose_blocks_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad,
+                                  int RB, hipStream_t st) {
+    dim3 grid((unsigned)((Rpad + 63) / 64), (unsigned)((Cpad + 63) / 64));
+    const int vec = (ld_src % 8 == 0) && (((uintptr_t)src) % 16 == 0);
+    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, 0, R, C, Rpad, Cpad, nullptr, 0, vec, RB);
 }
 
 void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R,
@@ -137,7 +161,7 @@ void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, i
     if (Rpad <= 0 || Cpad <= 0) return;
     dim3 grid((unsigned)((Rpad + 63) / 64), (unsigned)((Cpad + 63) / 64));
     const int vec = (ld_src % 8 == 0) && (ld_dst % 8 == 0) && (((uintptr_t)src) % 16 == 0) && (((uintptr_t)dst) % 16 == 0);
-    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, ld_dst, R, C, Rpad, Cpad, counts, r0, vec);
+    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, ld_dst, R, C, Rpad, Cpad, counts, r0, vec, 0);
 }
 
 }  // namespace rapid

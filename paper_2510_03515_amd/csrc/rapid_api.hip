@@ -341,14 +341,48 @@ struct FwdIo {
     const int32_t* group_ids = nullptr;
 };
 
+// Whether a kernel reads W in place (see WInPlace) instead of from a packed copy.  The copies cost one pass over W each
+// (0.2 ms at d = 1536, V = 151936), in-place reads a share of the contraction's time, so it is a matter of rows: measured
+// with 13 000 to 300 000 tokens, the logits kernels lose 0.5 % on a [V, d] head (its rows are the operand's) and 3 % on
+// a [d, V] head (read k-major; and the sampled tokens' logits gather columns), dHidden 2 % on [d, V] (rows far apart instead
+// of the copy's blocks) and 7 % on [V, d] (k-major).  The bounds are about where the two sides meet if half of the
+// N * T positions hold tokens.  (About 2100 rows: step 4.75 -> 4.45 ms at d = 1536; 290 rows, forward only: 432 -> 280 us.)
+enum WReader { W_FOR_LOGITS, W_FOR_DHIDDEN };
+WInPlace w_in_place(const Plan& p, const void* W, int w_layout, WReader reader) {
+    WInPlace w{(const bf16_t*)W, p.d, p.V, W_PACKED};
+    const bool vd = w_layout == RAPID_W_VD;
+    // whole 16-byte chunks of a row have to exist (d % 8 == 0 holds for every bf16 call)
+    if (p.two_wg || !default_waves() || (!vd && p.V % 8 != 0)) return w;
+    const int64_t most = reader == W_FOR_LOGITS ? (vd ? 131072 : 16384) : (vd ? 12288 : 16384);
+    if (p.Mmax <= most) w.mode = vd ? W_VD : W_DV;
+    return w;
+}
+
 // packs W as [Vpad, ldk] (the operand of the logits kernels)
 void pack_w_for_logits(const Plan& p, void* ws, const void* W, int w_layout, hipStream_t st) {
+    if (w_in_place(p, W, w_layout, W_FOR_LOGITS).mode != W_PACKED) return;
     bf16_t* Wvd = at<bf16_t>(ws, p.Wvd);
     if (w_layout == RAPID_W_VD)
         launch_copy_pad_bf16((const bf16_t*)W, p.d, nullptr, Wvd, p.ldk, p.V, p.d, p.Vpad, p.dpad, nullptr, 0, st);
     else
         launch_transpose_pad_bf16((const bf16_t*)W, p.V, Wvd, p.ldk, p.d, p.V, p.dpad, p.Vpad, nullptr, 0, st);
     if (p.two_wg) launch_block_w32(Wvd, p.ldk, at<bf16_t>(ws, p.Wvd32), p.Vpad, p.dpad, st);
+}
+
+// packs W as [dpadR, Vpad], in tile blocks or row-major (tuning key 14) (the operand of dHidden)
+void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, hipStream_t st) {
+    if (w_in_place(p, W, w_layout, W_FOR_DHIDDEN).mode != W_PACKED) return;
+    bf16_t* Wdv = at<bf16_t>(ws, p.Wdv);
+    bf16_t* WdvB = at<bf16_t>(ws, p.WdvB);
+    const int RB = p.dpadR % 256 == 0 ? 256 : 128;
+    const bool blocked = g_blocked_wdv.load() != 0;
+    if (w_layout == RAPID_W_DV) {
+        if (blocked) launch_block_rows_bf16((const bf16_t*)W, p.V, WdvB, p.d, p.V, p.dpadR, p.Vpad, RB, st);
+        else launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, p.dpadR, p.Vpad, nullptr, 0, st);
+    } else {
+        if (blocked) launch_transpose_blocks_bf16((const bf16_t*)W, p.d, WdvB, p.V, p.d, p.Vpad, p.dpadR, RB, st);
+        else launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, p.dpadR, nullptr, 0, st);
+    }
 }
 
 // bf16 forward over the compact rows [base, base + rows) (rows a multiple of 256; `counts` holds the end of the
@@ -359,6 +393,7 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
     int32_t* row_index = at<int32_t>(ws, p.row_index);
     int32_t* tokc = at<int32_t>(ws, p.tokc);
     bf16_t* Hc = at<bf16_t>(ws, p.Hc);
+    const WInPlace w = w_in_place(p, io.W, io.w_layout, W_FOR_LOGITS);
     const float inv_temp = 1.0f / io.temperature;
     {
         Span sp(ST_COMPACT, st);
@@ -375,6 +410,7 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
                                  p.dpadR, counts, base, st);
     }
     FwdArgs a;
+    a.w = w;
     a.Wvd = at<bf16_t>(ws, p.Wvd); a.Hc = Hc; a.dpad = p.dpad; a.ldk = p.ldk;
     a.tilesV = (int)(p.Vpad / 256); a.tilesM = (int)(rows / 256);
     a.V = p.V; a.inv_temp = inv_temp; a.tokc = tokc; a.counts = counts;
@@ -1007,13 +1043,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         {
             Span sp(ST_PACK, st);
             pack_w_for_logits(p, ws, W, o.w_layout, st);
-            bf16_t* Wdv = at<bf16_t>(ws, p.Wdv);
-            if (o.w_layout == RAPID_W_DV)
-                launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, p.dpadR, p.Vpad, nullptr, 0, st);
-            else
-                launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, p.dpadR, nullptr, 0, st);
-            if (blocked_wdv)
-                launch_block_rows_bf16(Wdv, p.ldv, at<bf16_t>(ws, p.WdvB), p.dpadR, p.Vpad, p.dpadR % 256 == 0 ? 256 : 128, st);
+            pack_w_for_dhidden(p, ws, W, o.w_layout, st);
         }
         {
             Span sp(ST_ZERO, st);
@@ -1062,6 +1092,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             for (int64_t r0 = 0; r0 < p.Rcap; r0 += cstep) {
                 const int64_t rows = (p.Rcap - r0) < cstep ? (p.Rcap - r0) : cstep;
                 DhArgs ha;
+                ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
                 ha.Wdv = at<bf16_t>(ws, p.Wdv); ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = cache + r0 * p.ldv;
                 ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dpadR;
                 ha.tilesM = (int)(rows / 256); ha.m0 = base + r0; ha.row_index = row_index; ha.counts = cnt + CH_LIVE;
@@ -1170,14 +1201,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         const bool blocked_wdv = g_blocked_wdv.load() != 0;
         {
             Span sp(ST_PACK, st);
-            if (o.w_layout == RAPID_W_DV)
-                launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, p.dpadR, p.Vpad,
-                                     nullptr, 0, st);
-            else
-                launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, p.dpadR, nullptr,
-                                          0, st);
-            if (blocked_wdv)
-                launch_block_rows_bf16(Wdv, p.ldv, at<bf16_t>(ws, p.WdvB), p.dpadR, p.Vpad, p.dpadR % 256 == 0 ? 256 : 128, st);
+            pack_w_for_dhidden(p, ws, W, o.w_layout, st);
         }
         const int64_t step = p.Mc;
         int chunk = 0;
@@ -1185,6 +1209,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             const int64_t rows = (p.Mmax_pad - m0) < step ? (p.Mmax_pad - m0) : step;   // multiple of 256
             bf16_t* dz = at<bf16_t>(ws, p.chunk0);
             DzArgs za;
+            za.w = w_in_place(p, W, o.w_layout, W_FOR_LOGITS);
             za.Wvd = Wvd; za.Hc = Hc + m0 * p.ldk; za.dpad = p.dpad; za.ldk = p.ldk; za.ldz = p.ldv;
             za.tilesV = (int)(p.Vpad / 256); za.tilesM = (int)(rows / 256);
             za.V = p.V; za.Vpad = p.Vpad; za.inv_temp = inv_temp; za.m0 = m0;
@@ -1202,6 +1227,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 }
             }
             DhArgs ha;
+            ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
             ha.Wdv = Wdv; ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = dz; ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dpadR;
             ha.tilesM = (int)(rows / 256); ha.m0 = m0; ha.row_index = row_index; ha.counts = bwd_counts;
             ha.rowc = nullptr;

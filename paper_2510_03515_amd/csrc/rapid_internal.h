@@ -152,8 +152,13 @@ void launch_f32_to_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t st
 void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, const int32_t* row_index, bf16_t* dst,
                           int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad,
                           const int32_t* counts, int64_t r0, hipStream_t st);
+// dst = src [R, C] in zero-padded tile blocks of RB rows x 64 columns (see block_rows_bf16_kernel); the second one takes
+// the transpose of src [R, C], so that the blocks run over src's columns.
+void launch_block_rows_bf16(const bf16_t* src, int64_t ld, bf16_t* dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad, int RB,
+                            hipStream_t st);
+void launch_transpose_blocks_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad,
+                                  int RB, hipStream_t st);
 // dst[c][r] (ld_dst) = src[r][c] for r < R, c < C else 0, over r < Rpad, c < Cpad.
-void launch_block_rows_bf16(const bf16_t* src, int64_t ld, bf16_t* dst, int64_t R, int64_t C, int RB, hipStream_t st);
 void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R,
                                int64_t C, int64_t Rpad, int64_t Cpad, const int32_t* counts, int64_t r0,
                                hipStream_t st);
@@ -176,8 +181,18 @@ void launch_rmsnorm_backward(const bf16_t* x, bf16_t* dh, int64_t d, const bf16_
 void launch_rmsnorm_dweight_reduce(const float* part, int64_t d, int64_t nblk, float* dweight, hipStream_t st);
 
 // ---- gemm_bf16.hip ----------------------------------------------------------------------------
+// The head as the caller has it.  mode says how a kernel reads it: from a packed copy (the argument structs hold those),
+// or in place, stored [V, d] or [d, V].
+enum { W_PACKED = 0, W_VD = 1, W_DV = 2 };
+struct WInPlace {
+    const bf16_t* W = nullptr;
+    int64_t d = 0, V = 0;
+    int mode = W_PACKED;
+};
+
 struct FwdArgs {          // logits tile -> per-slot (max, sumexp) and gathered logit
-    const bf16_t* Wvd;    // [Vpad, dpad]
+    WInPlace w;
+    const bf16_t* Wvd;    // [Vpad, dpad] (packed)
     const bf16_t* Hc;     // [Mmax_pad, dpad]
     int64_t dpad;         // contraction extent (multiple of 64)
     int64_t ldk;          // leading dimension of Wvd and Hc (elements)
@@ -213,6 +228,7 @@ void launch_token_logit(const FwdArgs& a, int64_t row0, int64_t rows_max, hipStr
 int fwd_slots_per_tile();
 
 struct DzArgs {           // logits tile -> dz = g (onehot - p) / temperature, bf16 [Mc, Vpad]
+    WInPlace w;
     const bf16_t* Wvd;
     const bf16_t* Hc;     // already offset to the chunk's first row
     int64_t dpad, ldk;
@@ -238,7 +254,8 @@ void launch_cache_finish(bf16_t* u, int64_t ldz, bf16_t* Hc, int64_t ldk, const 
                          hipStream_t st);
 
 struct DhArgs {           // dH[row, :] = dz[row, :] . Wdv^T
-    const bf16_t* Wdv;    // [dpadR, Vpad]
+    WInPlace w;
+    const bf16_t* Wdv;    // [dpadR, Vpad] (packed)
     const bf16_t* WdvB;   // the same, tile-blocked (blocks of tile-rows x 64 columns), or NULL
     const bf16_t* dz;     // [Mc, Vpad]
     int64_t Vpad;         // contraction extent
@@ -278,6 +295,7 @@ struct DwArgs {           // dW (+)= Hc^T . dz over the chunk's rows
 };
 void launch_dw(const DwArgs& a, hipStream_t st);
 void set_waves_per_workgroup(int n);   // 4, 8 or 16 waves per contraction workgroup
+bool default_waves();                  // each kernel runs its own choice
 void set_dw_deep(int on);              // dW with K steps of 32 rows and requests three steps ahead
 void set_cu_count(int n);              // compute units of the device: the contraction kernels launch one workgroup each
 

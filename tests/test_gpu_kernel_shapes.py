@@ -76,3 +76,24 @@ def test_dw_leaves_in_every_form(rb, d, V, layout, cache):
     buf.dW.copy_(old)
     added = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=buf, w_layout=lay, logits_cache=cache, accumulate_dw=True).dW
     assert torch.equal(added, old + base)
+
+
+@pytest.mark.parametrize("d,V", [(64, 512), (72, 264), (200, 1000), (328, 776), (8, 8), (136, 1003)])
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("cache", [False, True])
+def test_w_read_in_place(rb, d, V, layout, cache):
+    """The head read in place, as small batches do, at whole tiles and steps and past their ends: log-probs bit for bit those
+    from the packed copies (tuning key 2 = 8: the same geometry for the logits), gradients within the oracle's bounds
+    ([d, V] with V = 1003 is never read in place)."""
+    print(f"W in place d {d} V {V} {layout} cache {cache}", flush=True)
+    spec = wl.small_spec("in_place", "bf16", d=d, V=V, prompts=5, G=3, len_lo=5, len_hi=70, reward="uniform")
+    got = []
+    try:
+        for waves in (0, 8):
+            rb.rapid_set_tuning(2, waves)
+            w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
+            _check_pair(rb, spec, out, ref, layout)
+            got.append(out.logp_cur.clone())
+    finally:
+        rb.rapid_set_tuning(2, 0)
+    assert torch.equal(got[0], got[1])
