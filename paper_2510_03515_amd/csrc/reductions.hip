@@ -304,28 +304,40 @@ __global__ void gather_tokens_kernel(const int32_t* __restrict__ tokens, const i
 }
 
 // lse[j] = log sum_p part_sum[p][j] exp(part_max[p][j]) ; logp = zy - lse, scattered to [N,T].
-// Four lanes share a column: lane group q (lanes 16 q .. 16 q + 15 of a wave) folds the slots
-// [q P/4, (q+1) P/4) of 16 neighbouring columns, then the four (max, sum) pairs of a column are merged in
-// the order ((0, 1), (2, 3)).  A thread's loads are a dependent chain of P / 32 batches; one thread per column
-// left a 90 000-row chunk with too few threads to cover the memory latency.
-__global__ __launch_bounds__(256) void merge_lse_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
+// A block of 1024 threads takes 32 columns (a line of each slot): half a wave, one column per lane, is one of 32 groups
+// that fold P / 32 slots each, then the 32 (max, sum) pairs of a column are merged in a fixed tree: the two of a
+// wave in registers, the 16 waves through LDS.  A group's loads are a chain of batches, each a trip to memory: with 4
+// groups per column a few hundred rows took 50 us at P = 1188 (37 batches), now 13; 74 000 rows 166, now 138.
+// How P is shared out does not depend on the number of rows: every call forms a row's sum in the same order.
+struct MaxSum { float mx; double acc; };
+// the lower-numbered operand first
+__device__ inline MaxSum merge_pair(const MaxSum& a, const MaxSum& b) {
+    MaxSum r;
+    r.mx = fmaxf(a.mx, b.mx);
+    r.acc = 0.0;
+    if (a.acc > 0.0) r.acc += a.acc * (double)__expf(a.mx - r.mx);
+    if (b.acc > 0.0) r.acc += b.acc * (double)__expf(b.mx - r.mx);
+    return r;
+}
+__global__ __launch_bounds__(1024) void merge_lse_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
                                  int64_t ld_part, const float* __restrict__ zy,
                                  const int32_t* __restrict__ row_index, const int32_t* __restrict__ counts,
                                  int64_t row0, float* __restrict__ lse_c, float* __restrict__ logp_out,
                                  float* __restrict__ lse_out) {
-    const int lane = threadIdx.x & 63, q = lane >> 4;
-    // 64 columns per block of 256 threads: wave w covers columns 16 w .. 16 w + 15 of the block
-    const int64_t jl = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 6) * 16 + (lane & 15);
+    __shared__ float s_mx[16][32];
+    __shared__ double s_acc[16][32];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = wave * 2 + (lane >> 5), col = lane & 31;
+    const int64_t jl = (int64_t)blockIdx.x * 32 + col;
     const int64_t j = row0 + jl;
     const int M = counts[CNT_M];
+    if (row0 + (int64_t)blockIdx.x * 32 >= M) return;
     const bool live = j < M;
     // one pass with a running maximum; slots are merged in a fixed order, so the result is reproducible.
     // The weights exp(pm - mx) are fp32 (relative error 1e-7, far below the fp32 rounding of the
     // partial sums themselves), the accumulation fp64.
-    float mx = -INFINITY;
-    double acc = 0.0;
-    constexpr int UN = 8;   // slots loaded ahead of the fold: the loads of a batch are in flight together
-    const int p_begin = (int)((int64_t)P * q / 4), p_end = (int)((int64_t)P * (q + 1) / 4);
+    MaxSum m{-INFINITY, 0.0};
+    constexpr int UN = 10;   // slots loaded ahead of the fold: the loads of a batch are in flight together
+    const int p_begin = (int)((int64_t)P * q / 32), p_end = (int)((int64_t)P * (q + 1) / 32);
     if (live) {
         for (int p0 = p_begin; p0 < p_end; p0 += UN) {
             float pmv[UN], psv[UN];
@@ -339,33 +351,33 @@ __global__ __launch_bounds__(256) void merge_lse_kernel(const float* __restrict_
             for (int u = 0; u < UN; ++u) {
                 const float pm = pmv[u], ps = psv[u];
                 if (!(ps > 0.f)) continue;
-                if (pm > mx) {
-                    acc = acc * (double)__expf(mx - pm) + (double)ps;   // exp(-inf) = 0 on the first slot
-                    mx = pm;
+                if (pm > m.mx) {
+                    m.acc = m.acc * (double)__expf(m.mx - pm) + (double)ps;   // exp(-inf) = 0 on the first slot
+                    m.mx = pm;
                 } else {
-                    acc += (double)ps * (double)__expf(pm - mx);
+                    m.acc += (double)ps * (double)__expf(pm - m.mx);
                 }
             }
         }
     }
-    // merge the four lane groups of the column: (0, 1) and (2, 3), then the two results
-#pragma unroll
-    for (int step = 16; step <= 32; step <<= 1) {
-        const float omx = __shfl_xor(mx, step, 64);
-        const double oacc = __shfl_xor(acc, step, 64);
-        // both partners compute the same merged pair: the lower lane's operand first
-        const bool low = (lane & step) == 0;
-        const float m0 = low ? mx : omx, m1 = low ? omx : mx;
-        const double a0 = low ? acc : oacc, a1 = low ? oacc : acc;
-        const float mm = fmaxf(m0, m1);
-        double r = 0.0;
-        if (a0 > 0.0) r += a0 * (double)__expf(m0 - mm);
-        if (a1 > 0.0) r += a1 * (double)__expf(m1 - mm);
-        mx = mm;
-        acc = r;
+    auto merge_halves = [&]() {   // both partners compute the same pair
+        const MaxSum o{__shfl_xor(m.mx, 32, 64), __shfl_xor(m.acc, 32, 64)};
+        m = lane < 32 ? merge_pair(m, o) : merge_pair(o, m);
+    };
+    merge_halves();
+    if (lane < 32) {
+        s_mx[wave][col] = m.mx;
+        s_acc[wave][col] = m.acc;
     }
-    if (!live || q != 0) return;
-    const double lse = (double)mx + log(acc);
+    __syncthreads();
+    if (wave != 0) return;
+    const int g = lane >> 5;   // wave 0: its halves fold the results of waves 0 .. 7 and 8 .. 15
+    m = MaxSum{s_mx[g * 8][col], s_acc[g * 8][col]};
+#pragma unroll
+    for (int w = 1; w < 8; ++w) m = merge_pair(m, MaxSum{s_mx[g * 8 + w][col], s_acc[g * 8 + w][col]});
+    merge_halves();
+    if (!live || g != 0) return;
+    const double lse = (double)m.mx + log(m.acc);
     const float lse_f = (float)lse;
     lse_c[j] = lse_f;
     const int32_t pos = row_index[j];
@@ -748,7 +760,7 @@ void launch_merge_lse(const float* part_max, const float* part_sum, int P, int64
                       const int32_t* row_index, const int32_t* counts, int64_t row0, int64_t rows_max, float* lse_c,
                       float* logp_out, float* lse_out, hipStream_t st) {
     if (rows_max > 0)
-        merge_lse_kernel<<<blocks_for(rows_max, 64), 256, 0, st>>>(part_max, part_sum, P, ld_part, zy, row_index,
+        merge_lse_kernel<<<blocks_for(rows_max, 32), 1024, 0, st>>>(part_max, part_sum, P, ld_part, zy, row_index,
                                                                     counts, row0, lse_c, logp_out, lse_out);
 }
 
