@@ -339,7 +339,16 @@ struct FwdIo {
     // the chunk table's one entry says where those end
     IdleArgs idle;
     const int32_t* group_ids = nullptr;
+    int32_t* runs = nullptr;   // if set (with group_ids): where each group lies in the batch
 };
+
+PlanArgs plan_args(const Plan& p, void* ws, const int32_t* group_ids, int32_t* dev_status) {
+    PlanArgs a;
+    a.N = p.N; a.K = p.K; a.gid = group_ids; a.dev_status = dev_status;
+    a.seq_len = at<int32_t>(ws, p.seq_len); a.cu = at<int32_t>(ws, p.cu); a.counts = at<int32_t>(ws, p.counts);
+    a.gen_row0 = at<int32_t>(ws, p.gen_row0); a.gen_chunk = at<int32_t>(ws, p.gen_chunk); a.gseen = at<int32_t>(ws, p.gseen);
+    return a;
+}
 
 // Whether a kernel reads W in place (see WInPlace) instead of from a packed copy.  The copies cost one pass over W each
 // (0.2 ms at d = 1536, V = 151936), in-place reads a share of the contraction's time, so it is a matter of rows: measured
@@ -386,8 +395,8 @@ void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, hi
 }
 
 // bf16 forward over the compact rows [base, base + rows) (rows a multiple of 256; `counts` holds the end of the
-// valid rows among them): token ids, packed hidden rows, sampled-token logits, streaming log-softmax, log-probs.
-// Leaves tokc, seqc, zy, lse_c (and Hc) of those rows in the workspace for the backward.  Wvd is packed already.
+// valid rows among them): packed hidden rows, sampled-token logits, streaming log-softmax, log-probs.
+// Leaves zy, lse_c (and Hc) of those rows in the workspace for the backward.  Wvd is packed already.
 void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* counts, int64_t base, int64_t rows,
                        hipStream_t st) {
     int32_t* row_index = at<int32_t>(ws, p.row_index);
@@ -395,11 +404,6 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
     bf16_t* Hc = at<bf16_t>(ws, p.Hc);
     const WInPlace w = w_in_place(p, io.W, io.w_layout, W_FOR_LOGITS);
     const float inv_temp = 1.0f / io.temperature;
-    {
-        Span sp(ST_COMPACT, st);
-        launch_gather_tokens(io.tokens, row_index, counts, base, rows, p.T, p.V, tokc, at<int32_t>(ws, p.seqc),
-                             io.dev_status, st);
-    }
     {
         Span sp(ST_PACK, st);
         if (io.rms_weight)
@@ -454,16 +458,17 @@ void run_forward(const Plan& p, void* ws, const FwdIo& io, hipStream_t st) {
     const float inv_temp = 1.0f / io.temperature;
     {
         Span sp(ST_COMPACT, st);
-        if (io.idle.idle)
-            launch_compaction_chunked(io.mask, io.group_ids, p.N, p.T, p.K, io.row_cap < p.Mmax_pad ? io.row_cap : p.Mmax_pad, 1,
-                                      at<int32_t>(ws, p.seq_len), at<int32_t>(ws, p.cu), at<int32_t>(ws, p.tab),
-                                      at<int32_t>(ws, p.gen_row0), at<int32_t>(ws, p.gen_chunk), at<int32_t>(ws, p.gseen),
-                                      row_index, counts, io.dev_status, io.idle, st);
-        else
-            launch_compaction(io.mask, p.N, p.T, at<int32_t>(ws, p.seq_len), at<int32_t>(ws, p.cu), row_index, counts,
-                              io.row_cap, io.dev_status, st);
-        launch_fill_f32(io.logp_out, p.Mmax, 0.f, st);
-        if (io.lse_out) launch_fill_f32(io.lse_out, p.Mmax, 0.f, st);
+        PlanArgs plan = plan_args(p, ws, io.group_ids, io.dev_status);
+        plan.idle = io.idle;
+        plan.runs = io.runs;
+        if (io.idle.idle) {
+            plan.Rcap = io.row_cap < p.Mmax_pad ? io.row_cap : p.Mmax_pad;
+            plan.tab = at<int32_t>(ws, p.tab);
+            plan.Cmax = 1;
+        } else {
+            plan.Rcap = io.row_cap;
+        }
+        launch_compaction(io.mask, p.N, p.T, plan, io.logp_out, io.lse_out, row_index, RowTokens{io.tokens, p.V, tokc, seqc}, st);
     }
     if (p.dtype == RAPID_DTYPE_BF16) {
         {
@@ -472,10 +477,6 @@ void run_forward(const Plan& p, void* ws, const FwdIo& io, hipStream_t st) {
         }
         forward_rows_bf16(p, ws, io, counts, 0, p.Mmax_pad, st);
     } else {
-        {
-            Span sp(ST_COMPACT, st);
-            launch_gather_tokens(io.tokens, row_index, counts, 0, p.Mmax_pad, p.T, p.V, tokc, seqc, io.dev_status, st);
-        }
         float* z = at<float>(ws, p.chunk0);
         Span sp(ST_F32, st);
         for (int64_t m0 = 0; m0 < p.Mmax; m0 += p.Mc) {
@@ -810,8 +811,9 @@ int rapid_compaction(const uint8_t* mask, int64_t N, int64_t T, int32_t* seq_len
     }
     int rc = check_arch();
     if (rc) return rc;
-    launch_compaction(mask, N, T, seq_len_out, cu_seqlen_out, row_index_out, nullptr, INT64_MAX, nullptr,
-                      (hipStream_t)stream);
+    PlanArgs plan;
+    plan.N = N; plan.seq_len = seq_len_out; plan.cu = cu_seqlen_out;
+    launch_compaction(mask, N, T, plan, nullptr, nullptr, row_index_out, RowTokens(), (hipStream_t)stream);
     return check_launch("rapid_compaction");
 }
 
@@ -999,7 +1001,6 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
 
     // where each group lies in the batch: groups that are one run are reduced over that run alone
     int32_t* gruns = at<int32_t>(ws, p.gruns);
-    launch_group_runs(group_ids, N, K, gruns, st);
 
     FwdIo io{hidden, W, tokens, mask, o.w_layout, o.temperature, logp_cur, nullptr, dev_status};
     io.rms_weight = o.rms_weight;
@@ -1033,11 +1034,10 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         }
         {
             Span sp(ST_COMPACT, st);
-            launch_compaction_chunked(mask, group_ids, N, T, K, p.Rcap, p.Cmax, at<int32_t>(ws, p.seq_len),
-                                      at<int32_t>(ws, p.cu), tab, at<int32_t>(ws, p.gen_row0), gen_chunk,
-                                      at<int32_t>(ws, p.gseen), row_index, counts, dev_status, idle_args, st);
-            launch_fill_f32(logp_cur, p.Mmax, 0.f, st);
-            launch_fill_f64(lam_state, 1, -INFINITY, st);
+            PlanArgs plan = plan_args(p, ws, group_ids, dev_status);
+            plan.Rcap = p.Rcap; plan.Cmax = p.Cmax; plan.tab = tab; plan.runs = gruns; plan.idle = idle_args;
+            plan.lam_state = lam_state;
+            launch_compaction(mask, N, T, plan, logp_cur, nullptr, row_index, RowTokens{tokens, V, tokc, seqc}, st);
         }
         const bool blocked_wdv = g_blocked_wdv.load() != 0;
         {
@@ -1158,11 +1158,12 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     // bf16: the generations without gradient (see the cached backward above) come last, and dz, dHidden and dW
     // stop in front of them
     const int32_t* bwd_counts = counts;
+    io.group_ids = group_ids;
+    io.runs = gruns;
     if (dtype == RAPID_DTYPE_BF16 && g_skip_idle.load() && !(clip && clip->o.kl_beta != 0.f)) {
         io.idle.rewards = rewards; io.idle.coef_override = clip ? nullptr : o.coef_override;
         io.idle.idle = at<int32_t>(ws, p.idle); io.idle.len_live = at<int32_t>(ws, p.len_live);
         io.idle.cu_live = at<int32_t>(ws, p.cu_live); io.idle.live_group = at<int32_t>(ws, p.live_group);
-        io.group_ids = group_ids;
         bwd_counts = at<int32_t>(ws, p.tab) + CH_LIVE;
     }
     run_forward(p, ws, io, st);

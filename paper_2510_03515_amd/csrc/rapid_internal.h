@@ -37,19 +37,6 @@ constexpr int ROW_TILE = 256;  // compact rows are padded to this
 constexpr int K_TILE = 64;     // contraction tile of the MFMA kernels (bf16 elements)
 
 // ---- reductions.hip ---------------------------------------------------------------------------
-// counts (optional): M and M rounded up to a row tile, both clipped to row_cap (sets RAPID_STATUS_TOKEN_BOUND)
-void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, int32_t* seq_len, int32_t* cu_seqlen,
-                       int32_t* row_index, int32_t* counts, int64_t row_cap, int32_t* dev_status, hipStream_t st);
-// Compaction for the cached backward: sequence lengths and their prefix sum as above, then the
-// generations are dealt to at most Cmax chunks of at most Rcap compact rows each, whole groups
-// (maximal runs of equal group id) at a time, in order, each chunk as full as it gets; chunk c's
-// rows start at compact row c * Rcap.  Writes the chunk table `tab` [Cmax][CH_WORDS], gen_row0 [N]
-// (compact row of each generation's first token, -1 for a generation that was left out),
-// gen_chunk [N], row_index [Cmax * Rcap] and counts[CNT_M] = the tokens that were placed.
-// Cmax == 1: one chunk takes every generation, groups may lie anywhere; tokens past Rcap are left
-// out (RAPID_STATUS_TOKEN_BOUND).  Cmax > 1: a group whose members are not adjacent, or whose tokens
-// exceed Rcap, sets RAPID_STATUS_GROUP_LAYOUT; more chunks than Cmax sets RAPID_STATUS_TOKEN_BOUND.
-// gseen [K] is scratch.
 // IdleArgs (idle == NULL: off): generations whose coefficient is zero whatever their log-probs are (all rewards
 // of the group exactly 0, or a coefficient override of 0) are marked in idle [N] and placed behind the others
 // inside their chunk; the chunk's CH_LIVE / CH_LIVER say where the rows that carry gradient end.
@@ -61,15 +48,42 @@ struct IdleArgs {
     int32_t* cu_live = nullptr;            // scratch [N + 1]
     int32_t* live_group = nullptr;         // scratch [K]
 };
-void launch_compaction_chunked(const uint8_t* mask, const int32_t* group_ids, int64_t N, int64_t T, int64_t K,
-                               int64_t Rcap, int Cmax, int32_t* seq_len, int32_t* cu_seqlen, int32_t* tab,
-                               int32_t* gen_row0, int32_t* gen_chunk, int32_t* gseen, int32_t* row_index,
-                               int32_t* counts, int32_t* dev_status, const IdleArgs& z, hipStream_t st);
+// What the plan of a batch is made from and what it fills in (see plan_kernel).  cu [N + 1]: prefix sum of seq_len [N].
+// tab NULL: one region; counts (optional) = M and M rounded up to a row tile, both clipped to Rcap (sets
+// RAPID_STATUS_TOKEN_BOUND).  With tab the generations are dealt to at most Cmax chunks of at most Rcap compact rows
+// each, whole groups (maximal runs of equal group id) at a time, in order, each chunk as full as it gets; chunk c's
+// rows start at compact row c * Rcap.  Writes the chunk table `tab` [Cmax][CH_WORDS], gen_row0 [N]
+// (compact row of each generation's first token, -1 for a generation that was left out),
+// gen_chunk [N], and counts[CNT_M] = the tokens that were placed.
+// Cmax == 1: one chunk takes every generation, groups may lie anywhere; tokens past Rcap are left
+// out (RAPID_STATUS_TOKEN_BOUND).  Cmax > 1: a group whose members are not adjacent, or whose tokens
+// exceed Rcap, sets RAPID_STATUS_GROUP_LAYOUT; more chunks than Cmax sets RAPID_STATUS_TOKEN_BOUND.
+// gseen [K] is scratch.  runs [3K + 1] (optional): where each group lies in the batch; given to launch_group_advantage
+// it lets a group that is one run of the batch look at that run alone.  lam_state (optional): set to -infinity.
+struct PlanArgs {
+    int64_t N = 0, K = 0;
+    const int32_t* gid = nullptr;
+    int32_t *seq_len = nullptr, *cu = nullptr, *counts = nullptr;
+    int64_t Rcap = INT64_MAX;
+    int32_t* tab = nullptr;
+    int Cmax = 0;
+    int32_t *gen_row0 = nullptr, *gen_chunk = nullptr, *gseen = nullptr, *runs = nullptr;
+    double* lam_state = nullptr;
+    IdleArgs idle;
+    int32_t* dev_status = nullptr;
+};
+struct ZeroWords { int32_t* p[3] = {nullptr, nullptr, nullptr}; int64_t n[3] = {0, 0, 0}; };
+// token ids of the compact rows, if wanted
+struct RowTokens {
+    const int32_t* tokens = nullptr;
+    int64_t V = 0;
+    int32_t *tokc = nullptr, *seqc = nullptr;   // token id and generation per compact row
+};
+// Lengths, plan, and (row_index not NULL) the flat position, token and generation of every compact row, three launches.
+// zero_a, zero_b (optional): [N * T] outputs set to 0.
+void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, float* zero_a, float* zero_b,
+                       int32_t* row_index, const RowTokens& tok, hipStream_t st);
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t st);
-// compact rows [row0, row0 + rows_max) (those below counts[CNT_MR])
-void launch_gather_tokens(const int32_t* tokens, const int32_t* row_index, const int32_t* counts, int64_t row0,
-                          int64_t rows_max, int64_t T, int64_t V, int32_t* tokc, int32_t* seqc,
-                          int32_t* dev_status, hipStream_t st);
 // lse/logp from per-slot partial (max, sumexp) and the gathered logit, compact rows [row0, row0 + rows_max);
 // the partials of row j sit at column j - row0
 void launch_merge_lse(const float* part_max, const float* part_sum, int P, int64_t ld_part,
@@ -90,10 +104,6 @@ void launch_group_advantage(const float* rewards, const int32_t* group_ids, cons
                             float* weight, float* gmean, float* gstd, int32_t* gsize, const int32_t* gen_range,
                             int32_t* dev_status, hipStream_t st, float adv_eps = 0.f, int std_ddof = 0,
                             const int32_t* runs = nullptr);
-// runs [3K + 1] (see group_runs_kernel): where each group lies in the batch; given to launch_group_advantage it
-// lets a group that is one run of the batch look at that run alone
-void launch_group_runs(const int32_t* group_ids, int64_t N, int64_t K, int32_t* runs, hipStream_t st);
-
 // Token-level clipped surrogate with KL penalty (the loss step of the GRPO / DAPO baselines).
 struct ClipArgs {
     const float* logp_cur; const float* logp_old; const float* logp_ref;   // [N,T]; old NULL: ratios 1; ref NULL: no KL term
@@ -135,8 +145,6 @@ void launch_row_coefficients(const float* g, const double* g64, const int32_t* s
 // exp(lam_chunk[gen_chunk[n]] - lam_state[0]) (the scale its chunk used against the final one)
 void launch_rescale_rows(void* dhidden, const uint8_t* mask, int64_t N, int64_t T, int64_t d, const int32_t* gen_chunk,
                          const double* lam_chunk, const double* lam_state, hipStream_t st);
-void launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
-void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 // dst[i] += src[i]
 void launch_f32_add(const float* src, float* dst, int64_t n, hipStream_t st);
 // rows of masked positions, and (idle != NULL) of every position of an idle generation, set to zero

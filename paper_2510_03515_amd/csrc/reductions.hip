@@ -50,139 +50,155 @@ __device__ inline double block_max(double v, double* sm) {
 }
 
 // ------------------------------------------------------------------ compaction of the padding mask
-// one wave per generation: number of valid tokens
-__global__ void seq_len_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
-                               int32_t* __restrict__ seq_len) {
+// Three launches whatever is asked for: a small batch's call is a matter of launches (about 5 us each), and these
+// kernels have next to nothing to do.  Before (one kernel per array): 8 launches for a forward, 13 for a cached step.
+
+// One wave per generation: number of valid tokens, and zeros in its rows of the per-token outputs; the waves together
+// clear the plan's counters.
+__global__ __launch_bounds__(64) void seq_len_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
+                                                     int32_t* __restrict__ seq_len, float* __restrict__ zero_a,
+                                                     float* __restrict__ zero_b, ZeroWords z) {
     const int64_t n = blockIdx.x;
-    if (n >= N) return;
+    const int lane = threadIdx.x;
     int cnt = 0;
-    for (int64_t t = threadIdx.x; t < T; t += WAVE) cnt += mask[n * T + t] != 0;
+    const uint8_t* row = mask + n * T;
+    if ((T & 3) == 0 && ((uintptr_t)mask & 3) == 0) {
+        for (int64_t t = lane; t < T / 4; t += WAVE) {
+            const uint32_t w = ((const uint32_t*)row)[t];
+            cnt += __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);   // top bit of every byte that is not 0
+        }
+    } else {
+        for (int64_t t = lane; t < T; t += WAVE) cnt += row[t] != 0;
+    }
+    for (int64_t t = lane; t < T; t += WAVE) {
+        if (zero_a) zero_a[n * T + t] = 0.f;
+        if (zero_b) zero_b[n * T + t] = 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        for (int64_t i = n * WAVE + lane; i < z.n[k]; i += N * WAVE) z.p[k][i] = 0;
     cnt = wave_sum_i(cnt);
-    if (threadIdx.x == 0) seq_len[n] = cnt;
+    if (lane == 0) seq_len[n] = cnt;
 }
 
-// single block: exclusive prefix sum of seq_len, and the counters M / M rounded up to a row tile.
-// The counters never exceed row_cap (the rows the caller's buffers hold): tokens past it are left
-// out of everything downstream and RAPID_STATUS_TOKEN_BOUND is set.
-__global__ void scan_kernel(const int32_t* __restrict__ seq_len, int64_t N, int32_t* __restrict__ cu,
-                            int32_t* __restrict__ counts, int64_t row_cap, int32_t* __restrict__ dev_status) {
+// exclusive prefix sum of v [N] -> cu [N + 1] by a block of 1024 threads; returns the total to every thread
+__device__ int block_scan(const int32_t* v, int64_t N, int32_t* cu) {
     constexpr int PER = 8;   // consecutive entries per thread: 8192 per sweep of the block
-    __shared__ int sm[1024];
-    __shared__ int carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
+    __shared__ int s_wave[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int carry = 0;
     for (int64_t base = 0; base < N; base += 1024 * PER) {
         const int64_t n0 = base + (int64_t)threadIdx.x * PER;
-        int v[PER], mine = 0;
+        int e[PER], mine = 0;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            v[u] = n0 + u < N ? seq_len[n0 + u] : 0;
-            mine += v[u];
+            e[u] = n0 + u < N ? v[n0 + u] : 0;
+            mine += e[u];
         }
-        sm[threadIdx.x] = mine;
+        int incl = mine;     // inclusive scan of the threads' sums: within the wave, then over the waves
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(incl, o, WAVE);
+            if (lane >= o) incl += up;
+        }
         __syncthreads();
-        for (int o = 1; o < 1024; o <<= 1) {   // Hillis-Steele inclusive scan of the threads' sums
-            int add = threadIdx.x >= o ? sm[threadIdx.x - o] : 0;
-            __syncthreads();
-            sm[threadIdx.x] += add;
-            __syncthreads();
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int before = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            before += w < wave ? s_wave[w] : 0;
+            total += s_wave[w];
         }
-        const int incl = sm[threadIdx.x];
-        int run = carry + incl - mine;
+        int run = carry + before + incl - mine;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
             if (n0 + u < N && cu) cu[n0 + u] = run;
-            run += v[u];
+            run += e[u];
         }
-        __syncthreads();
-        if (threadIdx.x == 1023) carry += incl;
-        __syncthreads();
+        carry += total;
     }
-    if (threadIdx.x == 0) {
-        if (cu) cu[N] = carry;
-        if (counts) {
-            int m = carry;
-            if ((int64_t)m > row_cap) {
-                m = (int)row_cap;
-                if (dev_status) atomicOr(dev_status, RAPID_STATUS_TOKEN_BOUND);
-            }
-            counts[CNT_M] = m;
-            counts[CNT_MR] = (m + ROW_TILE - 1) / ROW_TILE * ROW_TILE;
-        }
-    }
-}
-
-// one wave per generation: flat positions of its valid tokens, in order, from compact row first_row[n]
-// on (a negative first row: the generation was left out).  The compact rows come in regions of
-// `region` rows; a generation never writes past the end of the region its first row lies in.
-__global__ void row_index_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
-                                 const int32_t* __restrict__ first_row, int64_t region,
-                                 int32_t* __restrict__ row_index) {
-    const int64_t n = blockIdx.x;
-    if (n >= N) return;
-    int64_t base = first_row[n];
-    if (base < 0) return;
-    const int64_t limit = (base / region + 1) * region;
-    const int lane = threadIdx.x;
-    for (int64_t t0 = 0; t0 < T; t0 += WAVE) {
-        const int64_t t = t0 + lane;
-        const bool v = t < T && mask[n * T + t] != 0;
-        const unsigned long long b = __ballot(v);
-        const int before = __popcll(b & ((1ull << lane) - 1ull));
-        if (v && base + before < limit) row_index[base + before] = (int32_t)(n * T + t);
-        base += __popcll(b);
-    }
+    if (threadIdx.x == 0 && cu) cu[N] = carry;
+    return carry;
 }
 
 // Generations whose coefficient dLoss/dlogp is zero whatever the log-probs turn out to be: every reward of the
 // group is exactly 0 (then the weighted baseline of Eq. (5) is 0 too, A_n = R_n - b = 0, in every baseline mode;
 // likewise the normalised advantage of the clipped surrogate), or the caller's coefficient override is 0.
 // Their rows get no gradient: dHidden rows are zero and they add nothing to dW, so the two gradient
-// contractions can leave them out.  Step 1: live_group[g] = 1 for a group with a reward that is not 0.
-__global__ void live_groups_kernel(const float* __restrict__ rewards, const int32_t* __restrict__ gid, int64_t N,
-                                   int64_t K, int32_t* __restrict__ live_group) {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    const float R = rewards[n];
-    const int32_t g = gid[n];
-    // a reward that is not finite counts as 0 in the estimator as well; equal values from several threads
-    if (g >= 0 && g < K && isfinite(R) && R != 0.f) live_group[g] = 1;
-}
-// Step 2: idle[n], and the generation's length if it is not idle (for the prefix sum the chunk plan uses).
-// A generation with a group id outside [0, K) is never idle.
-__global__ void idle_generations_kernel(const int32_t* __restrict__ gid, const float* __restrict__ coef_override,
-                                        const int32_t* __restrict__ live_group, const int32_t* __restrict__ seq_len,
-                                        int64_t N, int64_t K, int32_t* __restrict__ idle,
-                                        int32_t* __restrict__ len_live) {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    bool z;
-    if (coef_override) {
-        z = coef_override[n] == 0.f;
-    } else {
-        const int32_t g = gid[n];
-        z = g >= 0 && g < K && live_group[g] == 0;
-    }
-    idle[n] = z ? 1 : 0;
-    len_live[n] = z ? 0 : seq_len[n];
-}
-
-// Single block: deals the generations to chunks (see launch_compaction_chunked in rapid_internal.h).
+// contractions can leave them out.  A generation with a group id outside [0, K) is never idle.
+//
+// The plan of a batch, by one block: where each group lies (runs), which generations are idle, the prefix sums of the
+// lengths, and either the counters of one region (tab NULL) or the chunk table.
 // Thread 0 walks the runs of equal group id in order and fills chunk after chunk; then all threads
 // give every generation its chunk and first compact row and count each run's group id once.
-// With `idle` (see idle_generations_kernel; cu_live = prefix sum of the other generations' lengths) a chunk's
+// With idle generations (cu_live = prefix sum of the other generations' lengths) a chunk's
 // rows are ordered: the generations that carry gradient first, in batch order, then the idle ones, so that the
 // two gradient contractions stop at CH_LIVE.
-__global__ __launch_bounds__(1024) void plan_chunks_kernel(const int32_t* __restrict__ cu,
-                                                           const int32_t* __restrict__ cu_live,
-                                                           const int32_t* __restrict__ idle,
-                                                           const int32_t* __restrict__ gid, int64_t N, int64_t K,
-                                                           int64_t Rcap, int Cmax, int32_t* __restrict__ gseen,
-                                                           int32_t* __restrict__ tab, int32_t* __restrict__ gen_row0,
-                                                           int32_t* __restrict__ gen_chunk,
-                                                           int32_t* __restrict__ counts,
-                                                           int32_t* __restrict__ dev_status) {
+// runs[k] = number of maximal runs of group id k, runs[K + k] / runs[2K + k] = begin / end of (the last of) them,
+// runs[3K] = 1 if some group has more than one run.  With one run per group, which is how a sampler that draws G
+// generations per prompt lays a batch out, the per-group pass below visits each generation once instead of once
+// per group.  runs, live_group and gseen are zero on entry (seq_len_kernel).
+__global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     __shared__ int s_status;
+    const int64_t N = a.N, K = a.K;
+    const int32_t* gid = a.gid;
+    if (a.runs || (a.idle.idle && !a.idle.coef_override)) {
+        for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
+            const int32_t g = gid[n];
+            if (g < 0 || g >= K) continue;
+            if (a.runs) {
+                if (n == 0 || gid[n - 1] != g) {
+                    if (atomicAdd(&a.runs[g], 1) > 0) a.runs[3 * K] = 1;
+                    a.runs[K + g] = (int32_t)n;
+                }
+                if (n == N - 1 || gid[n + 1] != g) a.runs[2 * K + g] = (int32_t)(n + 1);
+            }
+            if (a.idle.idle && !a.idle.coef_override) {
+                // a reward that is not finite counts as 0 in the estimator as well; equal values from several threads
+                const float R = a.idle.rewards[n];
+                if (isfinite(R) && R != 0.f) a.idle.live_group[g] = 1;
+            }
+        }
+        __syncthreads();
+    }
+    if (a.idle.idle) {
+        for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
+            bool z;
+            if (a.idle.coef_override) {
+                z = a.idle.coef_override[n] == 0.f;
+            } else {
+                const int32_t g = gid[n];
+                z = g >= 0 && g < K && a.idle.live_group[g] == 0;
+            }
+            a.idle.idle[n] = z ? 1 : 0;
+            a.idle.len_live[n] = z ? 0 : a.seq_len[n];
+        }
+        __syncthreads();
+    }
+    const int32_t* cu_live = a.idle.idle ? a.idle.cu_live : nullptr;
+    const int64_t total = block_scan(a.seq_len, N, a.cu);
+    if (a.idle.idle) block_scan(a.idle.len_live, N, a.idle.cu_live);
+    if (threadIdx.x == 0 && a.lam_state) a.lam_state[0] = -INFINITY;
+    if (!a.tab) {
+        // The counters never exceed row_cap (the rows the caller's buffers hold): tokens past it are left
+        // out of everything downstream and RAPID_STATUS_TOKEN_BOUND is set.
+        if (threadIdx.x == 0 && a.counts) {
+            int m = (int)total;
+            if (total > a.Rcap) {
+                m = (int)a.Rcap;
+                if (a.dev_status) atomicOr(a.dev_status, RAPID_STATUS_TOKEN_BOUND);
+            }
+            a.counts[CNT_M] = m;
+            a.counts[CNT_MR] = (m + ROW_TILE - 1) / ROW_TILE * ROW_TILE;
+        }
+        return;
+    }
+    __syncthreads();
+    const int64_t Rcap = a.Rcap;
+    const int Cmax = a.Cmax;
+    int32_t* tab = a.tab;
+    const int32_t* cu = a.cu;
     if (threadIdx.x == 0) {
         int status = 0, c = 0;
         int64_t placed = 0;
@@ -201,7 +217,6 @@ __global__ __launch_bounds__(1024) void plan_chunks_kernel(const int32_t* __rest
             ++c;
         };
         if (Cmax == 1) {
-            const int64_t total = cu[N];
             if (total > Rcap) status |= RAPID_STATUS_TOKEN_BOUND;
             close(0, N, total);
         } else {
@@ -229,8 +244,8 @@ __global__ __launch_bounds__(1024) void plan_chunks_kernel(const int32_t* __rest
             close(chunk_g0, run0, chunk_rows);      // run0 == N unless the chunks ran out
         }
         while (c < Cmax) close(N, N, 0);            // chunks that stay empty (close() counts c up)
-        counts[CNT_M] = (int32_t)placed;
-        counts[CNT_MR] = (int32_t)((placed + ROW_TILE - 1) / ROW_TILE * ROW_TILE);
+        a.counts[CNT_M] = (int32_t)placed;
+        a.counts[CNT_MR] = (int32_t)((placed + ROW_TILE - 1) / ROW_TILE * ROW_TILE);
         s_status = status;
     }
     __syncthreads();
@@ -239,7 +254,7 @@ __global__ __launch_bounds__(1024) void plan_chunks_kernel(const int32_t* __rest
         int c = -1;
         for (int k = 0; k < Cmax; ++k)
             if (n >= tab[k * CH_WORDS + CH_G0] && n < tab[k * CH_WORDS + CH_G1]) { c = k; break; }
-        gen_chunk[n] = c;
+        a.gen_chunk[n] = c;
         int64_t row0 = -1;
         if (c >= 0) {
             const int64_t g0 = tab[c * CH_WORDS + CH_G0], g1 = tab[c * CH_WORDS + CH_G1];
@@ -247,29 +262,66 @@ __global__ __launch_bounds__(1024) void plan_chunks_kernel(const int32_t* __rest
             if (cu_live) {
                 const int64_t live_before = (int64_t)cu_live[n] - (int64_t)cu_live[g0];
                 const int64_t live_all = (int64_t)cu_live[g1] - (int64_t)cu_live[g0];
-                row0 = (int64_t)c * Rcap + (idle[n] ? live_all + (before - live_before) : live_before);
+                row0 = (int64_t)c * Rcap + (a.idle.idle[n] ? live_all + (before - live_before) : live_before);
             } else {
                 row0 = (int64_t)c * Rcap + before;
             }
         }
-        gen_row0[n] = (int32_t)row0;
+        a.gen_row0[n] = (int32_t)row0;
         if (Cmax > 1 && (n == 0 || gid[n] != gid[n - 1])) {       // first generation of a run
             const int32_t g = gid[n];
-            if (g >= 0 && g < K && atomicAdd(&gseen[g], 1) > 0) status |= RAPID_STATUS_GROUP_LAYOUT;
+            if (g >= 0 && g < K && atomicAdd(&a.gseen[g], 1) > 0) status |= RAPID_STATUS_GROUP_LAYOUT;
         }
     }
     if (threadIdx.x == 0) status |= s_status;
-    if (status && dev_status) atomicOr(dev_status, status);
+    if (status && a.dev_status) atomicOr(a.dev_status, status);
 }
 
-__global__ void fill_i32_kernel(int32_t* p, int64_t n, int32_t v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+// One wave per generation: flat positions of its valid tokens, in order, from compact row first_row[n]
+// on (a negative first row: the generation was left out), and their token ids and generation (out-of-range ids are flagged
+// and replaced by 0).  The compact rows come in regions of `region` rows; a generation never writes past the end of the
+// region its first row lies in.  Rows that fill a region's last row tile up (its counters: limits[e * stride]) get token 0.
+__global__ __launch_bounds__(64) void row_index_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
+                                                       const int32_t* __restrict__ first_row, int64_t region,
+                                                       int32_t* __restrict__ row_index, const int32_t* __restrict__ tokens,
+                                                       int64_t V, int32_t* __restrict__ tokc, int32_t* __restrict__ seqc,
+                                                       const int32_t* __restrict__ limits, int stride, int entries,
+                                                       int32_t* __restrict__ dev_status) {
+    const int64_t n = blockIdx.x;
+    const int lane = threadIdx.x;
+    if (tokc)
+        for (int64_t e = n; e < entries; e += N)
+            for (int j = limits[e * stride + CNT_M] + lane; j < limits[e * stride + CNT_MR]; j += WAVE) {
+                tokc[j] = 0;
+                seqc[j] = 0;
+            }
+    int64_t base = first_row[n];
+    if (base < 0) return;
+    const int64_t limit = (base / region + 1) * region;
+    bool bad = false;
+    for (int64_t t0 = 0; t0 < T; t0 += WAVE) {
+        const int64_t t = t0 + lane;
+        const bool v = t < T && mask[n * T + t] != 0;
+        const unsigned long long b = __ballot(v);
+        const int before = __popcll(b & ((1ull << lane) - 1ull));
+        if (v && base + before < limit) {
+            const int64_t j = base + before;
+            row_index[j] = (int32_t)(n * T + t);
+            if (tokc) {
+                int tok = tokens[n * T + t];
+                if (tok < 0 || tok >= V) {
+                    tok = 0;
+                    bad = true;
+                }
+                tokc[j] = tok;
+                seqc[j] = (int32_t)n;
+            }
+        }
+        base += __popcll(b);
+    }
+    if (bad && dev_status) atomicOr(dev_status, RAPID_STATUS_BAD_TOKEN);
 }
-__global__ void fill_f64_kernel(double* p, int64_t n, double v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
+
 __global__ void f32_add_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t n) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) dst[i] += src[i];
@@ -278,29 +330,6 @@ __global__ void f32_add_kernel(const float* __restrict__ src, float* __restrict_
 __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
-}
-
-// compact token ids and generation ids; out-of-range ids are flagged and replaced by 0
-__global__ void gather_tokens_kernel(const int32_t* __restrict__ tokens, const int32_t* __restrict__ row_index,
-                                     const int32_t* __restrict__ counts, int64_t row0, int64_t rows_max, int64_t T,
-                                     int64_t V, int32_t* __restrict__ tokc, int32_t* __restrict__ seqc,
-                                     int32_t* __restrict__ dev_status) {
-    const int64_t jl = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t j = row0 + jl;
-    const int M = counts[CNT_M], Mr = counts[CNT_MR];
-    if (j >= Mr || jl >= rows_max) return;
-    int tok = 0, seq = 0;
-    if (j < M) {
-        const int32_t pos = row_index[j];
-        tok = tokens[pos];
-        seq = (int32_t)(pos / T);
-        if (tok < 0 || tok >= V) {
-            tok = 0;
-            if (dev_status) atomicOr(dev_status, RAPID_STATUS_BAD_TOKEN);
-        }
-    }
-    tokc[j] = tok;
-    seqc[j] = seq;
 }
 
 // lse[j] = log sum_p part_sum[p][j] exp(part_max[p][j]) ; logp = zy - lse, scattered to [N,T].
@@ -456,22 +485,6 @@ __global__ void group_init_kernel(const float* __restrict__ rewards, const int32
     adv[n] = 0.f;
     if (adv64) adv64[n] = 0.0;
     if (weight) weight[n] = (float)clipped_weight(s32, s64, n, log_eta);
-}
-
-// Where each group lies in the batch: runs[k] = number of maximal runs of group id k, runs[K + k] / runs[2K + k] =
-// begin / end of (the last of) them, runs[3K] = 1 if some group has more than one run.  With one run per group,
-// which is how a sampler that draws G generations per prompt lays a batch out, the per-group pass below visits
-// each generation once instead of once per group.  runs [3K + 1] must be zero on entry.
-__global__ void group_runs_kernel(const int32_t* __restrict__ gid, int64_t N, int64_t K, int32_t* __restrict__ runs) {
-    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
-    const int32_t g = gid[n];
-    if (g < 0 || g >= K) return;
-    if (n == 0 || gid[n - 1] != g) {
-        if (atomicAdd(&runs[g], 1) > 0) runs[3 * K] = 1;
-        runs[K + g] = (int32_t)n;
-    }
-    if (n == N - 1 || gid[n + 1] != g) runs[2 * K + g] = (int32_t)(n + 1);
 }
 
 // one block per group: size, mean/std of R, clipped-weight baseline, advantages of its members.
@@ -707,53 +720,26 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
-void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, int32_t* seq_len, int32_t* cu_seqlen,
-                       int32_t* row_index, int32_t* counts, int64_t row_cap, int32_t* dev_status, hipStream_t st) {
-    seq_len_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, seq_len);
-    scan_kernel<<<1, 1024, 0, st>>>(seq_len, N, cu_seqlen, counts, row_cap, dev_status);
-    if (row_index) row_index_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, cu_seqlen, INT64_MAX / 4, row_index);
-}
-
-void launch_compaction_chunked(const uint8_t* mask, const int32_t* group_ids, int64_t N, int64_t T, int64_t K,
-                               int64_t Rcap, int Cmax, int32_t* seq_len, int32_t* cu_seqlen, int32_t* tab,
-                               int32_t* gen_row0, int32_t* gen_chunk, int32_t* gseen, int32_t* row_index,
-                               int32_t* counts, int32_t* dev_status, const IdleArgs& z, hipStream_t st) {
-    seq_len_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, seq_len);
-    scan_kernel<<<1, 1024, 0, st>>>(seq_len, N, cu_seqlen, nullptr, INT64_MAX, nullptr);
-    if (z.idle) {
-        if (!z.coef_override) {
-            launch_fill_i32(z.live_group, K, 0, st);
-            live_groups_kernel<<<blocks_for(N, 256), 256, 0, st>>>(z.rewards, group_ids, N, K, z.live_group);
-        }
-        idle_generations_kernel<<<blocks_for(N, 256), 256, 0, st>>>(group_ids, z.coef_override, z.live_group, seq_len, N, K,
-                                                                    z.idle, z.len_live);
-        scan_kernel<<<1, 1024, 0, st>>>(z.len_live, N, z.cu_live, nullptr, INT64_MAX, nullptr);
-    }
-    if (Cmax > 1) launch_fill_i32(gseen, K, 0, st);
-    plan_chunks_kernel<<<1, 1024, 0, st>>>(cu_seqlen, z.idle ? z.cu_live : nullptr, z.idle, group_ids, N, K, Rcap, Cmax, gseen,
-                                           tab, gen_row0, gen_chunk, counts, dev_status);
-    row_index_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, gen_row0, Rcap, row_index);
+void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, float* zero_a, float* zero_b,
+                       int32_t* row_index, const RowTokens& tok, hipStream_t st) {
+    ZeroWords z;
+    if (plan.runs) { z.p[0] = plan.runs; z.n[0] = 3 * plan.K + 1; }
+    if (plan.idle.idle && !plan.idle.coef_override) { z.p[1] = plan.idle.live_group; z.n[1] = plan.K; }
+    if (plan.tab && plan.Cmax > 1) { z.p[2] = plan.gseen; z.n[2] = plan.K; }
+    seq_len_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, plan.seq_len, zero_a, zero_b, z);
+    plan_kernel<<<1, 1024, 0, st>>>(plan);
+    if (row_index)
+        row_index_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, plan.tab ? plan.gen_row0 : plan.cu, plan.tab ? plan.Rcap : INT64_MAX / 4,
+                                                       row_index, tok.tokens, tok.V, tok.tokc, tok.seqc,
+                                                       plan.tab ? plan.tab : plan.counts, plan.tab ? (int)CH_WORDS : 0,
+                                                       plan.tab ? plan.Cmax : 1, plan.dev_status);
 }
 
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t st) {
     if (n > 0) fill_f32_kernel<<<blocks_for(n, 256), 256, 0, st>>>(p, n, v);
 }
-void launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {
-    if (n > 0) fill_i32_kernel<<<blocks_for(n, 256), 256, 0, st>>>(p, n, v);
-}
-void launch_fill_f64(double* p, int64_t n, double v, hipStream_t st) {
-    if (n > 0) fill_f64_kernel<<<blocks_for(n, 256), 256, 0, st>>>(p, n, v);
-}
 void launch_f32_add(const float* src, float* dst, int64_t n, hipStream_t st) {
     if (n > 0) f32_add_kernel<<<blocks_for(n, 256), 256, 0, st>>>(src, dst, n);
-}
-
-void launch_gather_tokens(const int32_t* tokens, const int32_t* row_index, const int32_t* counts, int64_t row0,
-                          int64_t rows_max, int64_t T, int64_t V, int32_t* tokc, int32_t* seqc,
-                          int32_t* dev_status, hipStream_t st) {
-    if (rows_max > 0)
-        gather_tokens_kernel<<<blocks_for(rows_max, 256), 256, 0, st>>>(tokens, row_index, counts, row0, rows_max, T, V,
-                                                                        tokc, seqc, dev_status);
 }
 
 void launch_merge_lse(const float* part_max, const float* part_sum, int P, int64_t ld_part, const float* zy,
@@ -782,11 +768,6 @@ void launch_group_advantage(const float* rewards, const int32_t* group_ids, cons
     group_advantage_kernel<<<(unsigned)K, 256, 0, st>>>(rewards, group_ids, s32, s64, N, log_eta, baseline_mode, adv,
                                                         adv64, gmean, gstd, gsize, gen_range, (double)adv_eps, std_ddof,
                                                         runs, K);
-}
-
-void launch_group_runs(const int32_t* group_ids, int64_t N, int64_t K, int32_t* runs, hipStream_t st) {
-    launch_fill_i32(runs, 3 * K + 1, 0, st);
-    group_runs_kernel<<<blocks_for(N, 256), 256, 0, st>>>(group_ids, N, K, runs);
 }
 
 // ---- the token-level clipped surrogate of the GRPO / DAPO loss steps ---------------------------
