@@ -4,7 +4,8 @@ import pytest
 import torch
 
 from paper_2510_03515_amd import workloads as wl
-from test_gpu_parity import _check_pair, _run_pair, rb  # noqa: F401  (rb is the library fixture)
+from oracle import rapid_oracle as orc
+from test_gpu_parity import _check_pair, _dh_ok, _dw_ok, _make, _np, _oracle_inputs, _rel, _run_pair, rb  # noqa: F401  (rb is the library fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +98,48 @@ def test_w_read_in_place(rb, d, V, layout, cache):
     finally:
         rb.rapid_set_tuning(2, 0)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("d,V,prompts,length", [
+    (448, 1321, 5, 70),      # ragged vocabulary; more rows than one chunk of the smallest workspace
+    (456, 512, 1, 40),       # whole workgroups of columns, few rows
+    (512, 130, 6, 64),       # less than one workgroup of columns, whole row tiles
+])
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("scale", [1.0, 100.0])
+def test_probabilities_kept_by_the_forward(rb, d, V, prompts, length, layout, scale):
+    """Backward without a cache from the forward's kept probabilities (d >= 448), all rows or (smallest workspace) the first
+    256 with the others' logits formed again: the oracle's bounds, and no further from it than logits formed again for
+    all rows (tuning key 2 = 8); scale: logits hundreds of nats apart."""
+    print(f"kept probabilities d {d} V {V} {layout} scale {scale}", flush=True)
+    spec = wl.small_spec("kept", "bf16", d=d, V=V, prompts=prompts, G=4, len_lo=length - 9, len_hi=length, reward="uniform")
+    w, g = _make(spec)
+    W = (w["W"].float() * scale).to(torch.bfloat16)
+    Wg = (W if layout == "dv" else W.t().contiguous()).cuda()
+    lay = rb.W_DV if layout == "dv" else rb.W_VD
+    H, _, _, mask = _oracle_inputs(w)
+    # any token but the likeliest: where that one's probability is 1 to fp32, 1 - p has no correct digits to compare
+    other = torch.randint(1, V, tuple(w["tokens"].shape), generator=torch.Generator().manual_seed(3))
+    w["tokens"] = ((torch.from_numpy(H @ _np(W)).argmax(-1) + other) % V).to(torch.int32)
+    g["tokens"], tok = w["tokens"].cuda(), _np(w["tokens"])
+    logp_b, _ = rb.rapid_logprob_fwd(g["hidden"], Wg, g["tokens"], g["mask"], w_layout=lay)
+    ref = orc.iw_pg_loss_fwd_bwd(H, _np(W), tok, mask, _np(logp_b), _np(w["rewards"]), _np(w["group_ids"]), w["K"])
+    far = {}
+    try:
+        for again, min_ws in ((False, False), (False, True), (True, False)):
+            rb.rapid_set_tuning(2, 8 if again else 0)
+            buf = rb.IwPgBuffers(g["hidden"], Wg, w["K"], lay, minimum_workspace=min_ws)
+            out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], Wg, g["tokens"], g["mask"], logp_b, g["rewards"], g["group_ids"],
+                                              w["K"], buffers=buf, w_layout=lay)
+            torch.cuda.synchronize()
+            dW = _np(out.dW) if layout == "dv" else _np(out.dW).T
+            assert out.dev_status.item() == 0
+            _dh_ok(out.dhidden, ref["dH"])
+            _dw_ok(dW, ref["dW"])
+            far[again, min_ws] = _rel(dW, ref["dW"]), _rel(_np(out.dhidden), ref["dH"])
+    finally:
+        rb.rapid_set_tuning(2, 0)
+    print("relative errors (dW, dHidden): " + str(far), flush=True)
+    for kept in ((False, False), (False, True)):
+        # both round dz to bf16 (8 bits); 11 bits before that add 1 / 64 of its variance at most
+        assert all(a <= b * 1.02 for a, b in zip(far[kept], far[True, False]))
