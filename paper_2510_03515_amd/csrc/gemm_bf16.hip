@@ -56,7 +56,10 @@ struct Geo {
     static constexpr int NWI = NWI_, NWJ = NWJ_, WI = WI_, WJ = WJ_;
     static constexpr int NW = NWI * NWJ, NT = 64 * NW;
     static constexpr int BI = NWI * WI * 32, BJ = NWJ * WJ * 32;
-    static constexpr int STAGE_BYTES = (BI + BJ) * 128;
+    // A k-major operand of 192 (or 224) columns is loaded as 256 (a request then covers whole rows; the last columns are
+    // not used), so an LDS stage has room for a power of two.
+    static constexpr int LI = BI > 128 ? 256 : BI, LJ = BJ > 128 ? 256 : BJ;
+    static constexpr int STAGE_BYTES = (LI + LJ) * 128;
     static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
 };
 
@@ -317,9 +320,9 @@ struct Reader {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int row = 8 * (lane >> 5) + q + 4 * h;
-                const int at = base + row * K::ROW_BYTES + ((first ^ ((4 * h + q) & (K::SEGS - 1))) * 64) + sub_bytes;
+                const int at = base + row * K::ROW_BYTES + sub_bytes;
 #pragma unroll
-                for (int n = 0; n < NB; ++n) x[n][h] = at ^ (n * 64);
+                for (int n = 0; n < NB; ++n) x[n][h] = at + (((first + n) ^ ((4 * h + q) & (K::SEGS - 1))) * 64);
             }
         } else {
 #pragma unroll
@@ -343,15 +346,16 @@ struct Reader {
 template <class S, bool AK, bool BK, bool CLAMP, class Pace = NoPace>
 __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ],
                                          Pace pace = Pace()) {
-    constexpr int WI = S::WI, WJ = S::WJ, B_STAGE = S::BI * 128;
+    constexpr int WI = S::WI, WJ = S::WJ, B_STAGE = S::LI * 128;
+    constexpr int EA = AK ? S::LI : S::BI, EB = BK ? S::LJ : S::BJ;     // outer indices that are loaded
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_i = wave % S::NWI, wave_j = wave / S::NWI;
-    Loader<S, S::BI, AK, CLAMP> la(A, wave, lane);
-    Loader<S, S::BJ, BK, false> lb(B, wave, lane);
-    const Reader<S, S::BI, WI, AK> ra(lane, wave_i * WI, 0);
-    const Reader<S, S::BJ, WJ, BK> rb(lane, wave_j * WJ, B_STAGE);
+    Loader<S, EA, AK, CLAMP> la(A, wave, lane);
+    Loader<S, EB, BK, false> lb(B, wave, lane);
+    const Reader<S, EA, WI, AK> ra(lane, wave_i * WI, 0);
+    const Reader<S, EB, WJ, BK> rb(lane, wave_j * WJ, B_STAGE);
 
 #pragma unroll
     for (int ib = 0; ib < WI; ++ib)
@@ -362,7 +366,7 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
 
     if (ktiles <= 0) return;
 
-    constexpr int NRA = Loader<S, S::BI, AK, CLAMP>::ROUNDS, NRB = Loader<S, S::BJ, BK, false>::ROUNDS, T = NRA + NRB;
+    constexpr int NRA = Loader<S, EA, AK, CLAMP>::ROUNDS, NRB = Loader<S, EB, BK, false>::ROUNDS, T = NRA + NRB;
     char* dst = lds;        // stage the requests go to
     auto request = [&](int r) {
         if (r < NRA) la.request(r, dst); else lb.request(r - NRA, dst + B_STAGE);
@@ -388,7 +392,7 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
     // every address in bounds.  (Skipping those requests with a uniform branch each was tried: the logits
     // kernels, where they are 6 % of the memory -> LDS traffic, got 2 % slower and dHidden 5 %.)
     Frags<WI, WJ> f0, f1;
-    constexpr int NR = Reader<S, S::BI, WI, AK>::READS + Reader<S, S::BJ, WJ, BK>::READS;   // LDS reads per sub-step
+    constexpr int NR = Reader<S, EA, WI, AK>::READS + Reader<S, EB, WJ, BK>::READS;   // LDS reads per sub-step
     auto advance = [&](bool more, int kt) {
         la.g += more ? A.step : 0;
         lb.g += more ? B.step : 0;
@@ -1279,7 +1283,8 @@ struct DwOut {
 template <class S>
 __device__ __forceinline__ void dw_store(char* lds, const DwOut& out, int64_t i_tile, int64_t j_tile, const f32x16 (&acc)[S::WI][S::WJ]) {
     constexpr int fit = S::LDS_BYTES / S::NW / (32 * 128);                          // blocks of 32 x 32 floats per wave
-    constexpr int IBW = fit >= S::WI ? S::WI : fit >= S::WI / 2 ? S::WI / 2 : 1;
+    constexpr int pow2 = S::WI & -S::WI;                                            // largest power of two that divides WI
+    constexpr int IBW = fit >= pow2 ? pow2 : fit >= pow2 / 2 ? pow2 / 2 : 1;
     constexpr int C = IBW * 8, R = 64 / C, T = 32 / R;                              // 16-byte chunks per row; rows per access
     static_assert(fit >= 1 && S::WI % IBW == 0 && C <= 64, "region");
     const Lane<S> L;
@@ -1545,6 +1550,10 @@ using G8_J128 = Geo<2, 4, 4, 1>;   // 256 x 128
 using G16 = Geo<2, 8, 4, 1>;       // 256 x 256, 16 waves of 128 x 32
 using G16_I128 = Geo<2, 8, 2, 1>;  // 128 x 256
 using G16_J128 = Geo<4, 4, 2, 1>;  // 256 x 128
+// hidden dimension in tiles of 224 or 192 (see hidden_tile)
+using G4_I224 = Geo<1, 4, 7, 2>;   // 224 x 256, waves of 224 x 64
+using G4_I192 = Geo<2, 2, 3, 4>;   // 192 x 256, waves of 96 x 128
+using G4_J192 = Geo<2, 2, 4, 3>;   // 256 x 192
 
 template <class S, int WM>
 void launch_fwd_lse_t(const FwdArgs& a, hipStream_t st) {
@@ -1681,8 +1690,12 @@ void launch_cache_finish(bf16_t* u, int64_t ldz, bf16_t* Hc, int64_t ldk, const 
 }
 void launch_dh(const DhArgs& a, hipStream_t st) {
     const int w = waves_for(4);
-    const bool d256 = a.dpadR % 256 == 0;   // else d is padded to a multiple of 128 only
-    if (a.w.mode == W_VD) d256 ? launch_dh_t<G4, W_VD>(a, st) : launch_dh_t<G4_I128, W_VD>(a, st);
+    const bool d256 = a.dtile == 256;   // else 128, or 192 or 224 in the default geometry
+    if (a.dtile == 224)
+        a.w.mode == W_VD ? launch_dh_t<G4_I224, W_VD>(a, st) : a.w.mode == W_DV ? launch_dh_t<G4_I224, W_DV>(a, st) : launch_dh_t<G4_I224, W_PACKED>(a, st);
+    else if (a.dtile == 192)
+        a.w.mode == W_VD ? launch_dh_t<G4_I192, W_VD>(a, st) : a.w.mode == W_DV ? launch_dh_t<G4_I192, W_DV>(a, st) : launch_dh_t<G4_I192, W_PACKED>(a, st);
+    else if (a.w.mode == W_VD) d256 ? launch_dh_t<G4, W_VD>(a, st) : launch_dh_t<G4_I128, W_VD>(a, st);
     else if (a.w.mode == W_DV) d256 ? launch_dh_t<G4, W_DV>(a, st) : launch_dh_t<G4_I128, W_DV>(a, st);
     else if (w == 16) d256 ? launch_dh_t<G16, W_PACKED>(a, st) : launch_dh_t<G16_I128, W_PACKED>(a, st);
     else if (w == 8) d256 ? launch_dh_t<G8, W_PACKED>(a, st) : launch_dh_t<G8_I128, W_PACKED>(a, st);
@@ -1693,7 +1706,8 @@ std::atomic<int> g_dw_deep{0};
 void set_dw_deep(int on) { g_dw_deep = on ? 1 : 0; }
 void launch_dw(const DwArgs& a, hipStream_t st) {
     const int w = waves_for(8);
-    const bool d256 = a.dpadR % 256 == 0;   // else d is padded to a multiple of 128 only
+    const bool d256 = a.dtile == 256;   // else 128, or 192 in the default geometry
+    if (a.dtile == 192) { a.w_layout == RAPID_W_VD ? launch_dw_t<G4_I192, true>(a, st) : launch_dw_t<G4_J192, false>(a, st); return; }
     if (a.w_layout == RAPID_W_VD) {
         if (w == 16) d256 ? launch_dw_t<G16, true>(a, st) : launch_dw_t<G16_I128, true>(a, st);
         else if (w == 8) d256 ? launch_dw_t<G8, true>(a, st) : launch_dw_t<G8_I128, true>(a, st);

@@ -101,10 +101,13 @@ struct Span {
     ~Span() { g_prof.end(st); }
 };
 
+struct HiddenTile { int tile; int64_t padded; };   // see hidden_tile
 struct Plan {
     int op, dtype;
     int64_t N, T, d, V, K;
-    int64_t Mmax, Mmax_pad, dpad, dpadR, Vpad;
+    int64_t Mmax, Mmax_pad, dpad, Vpad;
+    HiddenTile dh, dw;  // how dHidden and dW tile the hidden dimension
+    int64_t hpad;       // columns of Hc that are written
     int64_t ldk, ldv;   // leading dimensions of the [*, dpad] and [*, Vpad] operands
     int P;              // log-sum-exp partial slots per row
     int64_t Mc;         // rows per backward chunk (f32: also per forward chunk)
@@ -121,6 +124,27 @@ struct Plan {
     size_t counts, pace, seq_len, cu, row_index, tokc, seqc, zy, refz, lse_c, inv_rms, rms_part, rowc, rowg, logp_tmp, s64, s32, adv, adv64, g, g64, tsum, tmax,
         Hc, Wvd, Wdv, WdvB, dh_part, part_max, part_sum, dw32, chunk0, tab, gen_row0, gen_chunk, gseen, lam_state, lam_chunk, beta_scale, idle, len_live, cu_live, live_group, gruns, Wvd32;
 };
+
+// Tile of the hidden dimension in dHidden and dW, and d rounded up to whole tiles.  Tiles of 256 are the most efficient
+// (they read the fewest LDS bytes per product: a tile of 192 keeps the LDS busy 87 % of the time its products take, one of
+// 224 91 %), but what they pad is computed all the same.  Cost of a tile relative to one of 256, measured over d = 200 ..
+// 1152 with 37 000 tokens, V = 65536 (dHidden and dW together, 256 or 128 only against this rule: d = 384 4.51 -> 3.51 ms,
+// d = 576 7.74 -> 5.58 ms; dHidden at d = 896 3.84 -> 3.64 ms; dW gains nothing from tiles of 224).
+enum { TILES_256_128 = 0, TILES_DH, TILES_DW };
+HiddenTile hidden_tile(int64_t d, int allowed) {
+    const int tile = (round_up(d, 256) - d) * 6 <= d ? 256 : 128;
+    HiddenTile best{tile, round_up(d, tile)};
+    if (allowed == TILES_256_128) return best;
+    float best_cost = (float)(best.padded / tile) * (tile == 256 ? 1.f : 0.73f);
+    const struct { int tile; float cost; } kinds[] = {{256, 1.f}, {224, 0.955f}, {192, 0.88f}};
+    for (const auto& k : kinds) {
+        if (k.tile == 224 && allowed == TILES_DW) continue;
+        const int64_t n = (d + k.tile - 1) / k.tile;
+        const float cost = (float)n * k.cost;
+        if (cost < best_cost) { best = HiddenTile{k.tile, n * k.tile}; best_cost = cost; }
+    }
+    return best;
+}
 
 size_t take(size_t& cur, size_t bytes) {
     const size_t at = cur;
@@ -147,11 +171,13 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
     p.ld_part = Cmax > 0 ? Rcap : p.Mmax_pad;
     if (p.Mmax_pad > (int64_t)2100000000) return false;   // compact row indices are int32
     p.dpad = round_up(d, K_TILE);
-    // dHidden / dW tile d by 256 when that pads by at most a sixth (full-size tiles beat the padding),
-    // else by 128
-    p.dpadR = (round_up(d, 256) - d) * 6 <= d ? round_up(d, 256) : round_up(d, 128);
+    const bool any_width = op == RAPID_OP_IW_PG_FWD_BWD && default_waves();
+    p.dh = hidden_tile(d, any_width ? TILES_DH : TILES_256_128);
+    p.dw = hidden_tile(d, any_width ? TILES_DW : TILES_256_128);
+    p.hpad = p.dw.padded > p.dpad ? p.dw.padded : p.dpad;
     p.Vpad = round_up(V, 256);
-    p.ldk = padded_ld(p.dpadR);   // >= dpad; the dW kernel reads whole 128-column tiles of Hc
+    // the dW kernel reads whole tiles of Hc, and 256 columns where a tile has 192
+    p.ldk = padded_ld(round_up(p.dw.tile == 192 && p.dw.padded + 64 > p.hpad ? p.dw.padded + 64 : p.hpad, 64));
     p.ldv = padded_ld(p.Vpad);
     p.P = (int)(p.Vpad / 256) * fwd_slots_per_tile();
     const bool bwd = op == RAPID_OP_IW_PG_FWD_BWD;
@@ -207,8 +233,8 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
         p.part_max = take(cur, (size_t)p.P * p.ld_part * 4);
         p.part_sum = take(cur, (size_t)p.P * p.ld_part * 4);
         if (bwd) {
-            p.Wdv = take(cur, (size_t)p.dpadR * p.ldv * 2);
-            p.WdvB = take(cur, (size_t)p.dpadR * p.Vpad * 2);
+            p.Wdv = take(cur, (size_t)p.dh.padded * p.ldv * 2);
+            p.WdvB = take(cur, (size_t)p.dh.padded * p.Vpad * 2);
             p.dh_part = take(cur, dh_part_bytes());
             p.per_row = (size_t)p.ldv * 2;   // the dz chunk
         }
@@ -389,19 +415,20 @@ void pack_w_for_logits(const Plan& p, void* ws, const void* W, int w_layout, hip
     if (p.two_wg) launch_block_w32(Wvd, p.ldk, at<bf16_t>(ws, p.Wvd32), p.Vpad, p.dpad, st);
 }
 
-// packs W as [dpadR, Vpad], in tile blocks or row-major (tuning key 14) (the operand of dHidden)
+// packs W as [dh.padded, Vpad], in tile blocks or row-major (tuning key 14) (the operand of dHidden)
 void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, hipStream_t st) {
     if (w_in_place(p, W, w_layout, W_FOR_DHIDDEN).mode != W_PACKED) return;
     bf16_t* Wdv = at<bf16_t>(ws, p.Wdv);
     bf16_t* WdvB = at<bf16_t>(ws, p.WdvB);
-    const int RB = p.dpadR % 256 == 0 ? 256 : 128;
+    const int RB = p.dh.tile;
+    const int64_t dpadR = p.dh.padded;
     const bool blocked = g_blocked_wdv.load() != 0;
     if (w_layout == RAPID_W_DV) {
-        if (blocked) launch_block_rows_bf16((const bf16_t*)W, p.V, WdvB, p.d, p.V, p.dpadR, p.Vpad, RB, st);
-        else launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, p.dpadR, p.Vpad, nullptr, 0, st);
+        if (blocked) launch_block_rows_bf16((const bf16_t*)W, p.V, WdvB, p.d, p.V, dpadR, p.Vpad, RB, st);
+        else launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, dpadR, p.Vpad, nullptr, 0, st);
     } else {
-        if (blocked) launch_transpose_blocks_bf16((const bf16_t*)W, p.d, WdvB, p.V, p.d, p.Vpad, p.dpadR, RB, st);
-        else launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, p.dpadR, nullptr, 0, st);
+        if (blocked) launch_transpose_blocks_bf16((const bf16_t*)W, p.d, WdvB, p.V, p.d, p.Vpad, dpadR, RB, st);
+        else launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, dpadR, nullptr, 0, st);
     }
 }
 
@@ -419,10 +446,10 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
         Span sp(ST_PACK, st);
         if (io.rms_weight)
             launch_rmsnorm_pad_bf16((const bf16_t*)io.hidden, p.d, row_index, (const bf16_t*)io.rms_weight, io.rms_eps,
-                                    Hc, p.ldk, base, rows, p.dpadR, counts, at<float>(ws, p.inv_rms), st);
+                                    Hc, p.ldk, base, rows, p.hpad, counts, at<float>(ws, p.inv_rms), st);
         else
             launch_copy_pad_bf16((const bf16_t*)io.hidden, p.d, row_index, Hc + base * p.ldk, p.ldk, rows, p.d, rows,
-                                 p.dpadR, counts, base, st);
+                                 p.hpad, counts, base, st);
     }
     FwdArgs a;
     a.w = w;
@@ -1109,7 +1136,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 DhArgs ha;
                 ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
                 ha.Wdv = at<bf16_t>(ws, p.Wdv); ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = cache + r0 * p.ldv;
-                ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dpadR;
+                ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dh.padded; ha.dtile = p.dh.tile;
                 ha.tilesM = (int)(rows / 256); ha.m0 = base + r0; ha.row_index = row_index; ha.counts = cnt + CH_LIVE;
                 ha.rowc = at<float>(ws, p.rowc);
                 ha.pace = pace_every > 0 ? at<unsigned>(ws, p.pace) : nullptr; ha.pace_every = pace_every;
@@ -1124,7 +1151,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 const int64_t rows = (p.Rcap - r0) < wstep ? (p.Rcap - r0) : wstep;
                 DwArgs wa;
                 wa.dz = cache + r0 * p.ldv; wa.Hc = Hc + (base + r0) * p.ldk; wa.Mc = rows; wa.ldz = p.ldv; wa.ldH = p.ldk;
-                wa.d = p.d; wa.dpadR = p.dpadR; wa.V = p.V; wa.Vpad = p.Vpad; wa.m0 = base + r0; wa.counts = cnt + CH_LIVE;
+                wa.d = p.d; wa.dpadR = p.dw.padded; wa.dtile = p.dw.tile; wa.V = p.V; wa.Vpad = p.Vpad; wa.m0 = base + r0; wa.counts = cnt + CH_LIVE;
                 wa.dW = dW32; wa.w_layout = o.w_layout; wa.gi = g_gi_dw;
                 wa.beta = (c > 0 || piece > 0 || dw_adds_to_caller) ? 1 : 0;
                 // the sum over the earlier chunks is brought to this chunk's scale, once, by its first piece
@@ -1253,7 +1280,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             }
             DhArgs ha;
             ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
-            ha.Wdv = Wdv; ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = dz; ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dpadR;
+            ha.Wdv = Wdv; ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = dz; ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dh.padded; ha.dtile = p.dh.tile;
             ha.tilesM = (int)(rows / 256); ha.m0 = m0; ha.row_index = row_index; ha.counts = bwd_counts;
             ha.rowc = nullptr;
             const int pace_every = g_pace_every.load();
@@ -1267,7 +1294,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             }
             DwArgs wa;
             wa.dz = dz; wa.Hc = Hc + m0 * p.ldk; wa.Mc = step; wa.ldz = p.ldv; wa.ldH = p.ldk;
-            wa.d = p.d; wa.dpadR = p.dpadR; wa.V = p.V; wa.Vpad = p.Vpad; wa.m0 = m0; wa.counts = bwd_counts;
+            wa.d = p.d; wa.dpadR = p.dw.padded; wa.dtile = p.dw.tile; wa.V = p.V; wa.Vpad = p.Vpad; wa.m0 = m0; wa.counts = bwd_counts;
             wa.dW = dW32; wa.w_layout = o.w_layout; wa.beta = (chunk > 0 || o.accumulate_dw) ? 1 : 0; wa.gi = g_gi_dw;
             if (dw_staged && m0 + step >= p.Mmax_pad) wa.dW16 = (bf16_t*)dW_out;   // the last launch rounds it on its way out
             wa.part = ha.part; wa.part_bytes = ha.part_bytes;

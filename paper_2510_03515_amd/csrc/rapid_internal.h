@@ -275,7 +275,8 @@ struct DhArgs {           // dH[row, :] = dz[row, :] . Wdv^T
     const bf16_t* dz;     // [Mc, Vpad]
     int64_t Vpad;         // contraction extent
     int64_t ldv;          // leading dimension of Wdv and dz
-    int64_t d, dpadR;
+    int64_t d, dpadR;     // dpadR: d rounded up to tiles of dtile (256, 224, 192 or 128)
+    int dtile;
     int tilesM;
     int64_t m0;
     const int32_t* row_index;
@@ -293,10 +294,11 @@ size_t dh_part_bytes();   // scratch that lets a dHidden or dW launch cut its la
 
 struct DwArgs {           // dW (+)= Hc^T . dz over the chunk's rows
     const bf16_t* dz;     // [Mc, Vpad] chunk (rows = tokens)
-    const bf16_t* Hc;     // [Mmax_pad, >= dpadR], already offset to the chunk's first row
+    const bf16_t* Hc;     // [Mmax_pad, >= dpadR; + 64 with tiles of 192], already offset to the chunk's first row
     int64_t Mc;           // rows of the chunk buffer (contraction extent is min(Mc, rows left))
     int64_t ldz, ldH;     // leading dimensions of dz and Hc
     int64_t d, dpadR, V, Vpad;
+    int dtile;            // 256, 192 or 128
     int64_t m0;
     const int32_t* counts;
     float* dW;            // fp32, layout per w_layout

@@ -143,3 +143,16 @@ def test_probabilities_kept_by_the_forward(rb, d, V, prompts, length, layout, sc
     for kept in ((False, False), (False, True)):
         # both round dz to bf16 (8 bits); 11 bits before that add 1 / 64 of its variance at most
         assert all(a <= b * 1.02 for a, b in zip(far[kept], far[True, False]))
+
+
+@pytest.mark.parametrize("d", [136, 192, 200, 384, 448, 568])     # tiles of 192 (one, whole, two, three) and, dHidden, of 224
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("packed", [False, True])
+def test_hidden_tiles_of_192_and_224(rb, d, layout, packed):
+    """dHidden and dW in tiles of the hidden dimension that are no power of two, with few tiles (cut) and with the head read
+    in place or, in a batch padded to more positions than that is done for, packed."""
+    print(f"hidden tiles d {d} {layout} packed {packed}", flush=True)
+    spec = wl.small_spec("tiles", "bf16", d=d, V=520, prompts=8, G=5, len_lo=10, len_hi=420 if packed else 40, reward="uniform")
+    for cache in (False, True):
+        w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
+        _check_pair(rb, spec, out, ref, layout)
