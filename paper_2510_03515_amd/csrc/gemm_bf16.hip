@@ -342,10 +342,11 @@ struct Reader {
 };
 
 // acc = sum over `ktiles` steps of 64 of A(i, k) B(j, k) for the tile the two operands point at.
-// AK / BK: the operand is k-major; CLAMP: A is read in place (see Loader).
-template <class S, bool AK, bool BK, bool CLAMP, class Pace = NoPace>
+// AK / BK: the operand is k-major; CLAMP: A is read in place (see Loader).  TAIL: of B's outer indices only the first live_j
+// matter; waves without any of them leave acc 0.
+template <class S, bool AK, bool BK, bool CLAMP, bool TAIL = false, class Pace = NoPace>
 __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ],
-                                         Pace pace = Pace()) {
+                                         Pace pace = Pace(), int live_j = 0) {
     constexpr int WI = S::WI, WJ = S::WJ, B_STAGE = S::LI * 128;
     constexpr int EA = AK ? S::LI : S::BI, EB = BK ? S::LJ : S::BJ;     // outer indices that are loaded
     const int tid = threadIdx.x;
@@ -399,6 +400,25 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
         la.at_step(kt);
     };
     dst = lds + S::STAGE_BYTES;
+    if constexpr (TAIL) {
+        if (wave_j * (WJ * 32) >= live_j) {     // the wave only makes its share of the requests (those that others read)
+            auto requests = [&](int kt) {
+                advance(kt < ktiles, kt < ktiles ? kt : ktiles - 1);
+#pragma unroll
+                for (int r = 0; r < T; ++r)
+                    if (r < NRA || (r - NRA) * (8 * S::NW) < live_j) request(r);
+            };
+            requests(1);
+            for (int kt = 0; kt < ktiles; ++kt) {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                lds_barrier();
+                dst = lds + (kt & 1) * S::STAGE_BYTES;
+                requests(kt + 2);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            return;
+        }
+    }
     {
         const uint32_t l0 = lds_addr(lds);
         ra.template load<0>(f0.a, l0);
@@ -794,13 +814,21 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     if (a.row0 >= Mr) return;
     // the order (and with it the split over the XCDs) covers the row tiles that hold tokens only
     const int tilesM = min(a.tilesM, (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
-    for (int pid = blockIdx.x, ids = ids_for(a.tilesV, tilesM); pid < ids; pid += gridDim.x) {
-    const TileId t = map_tile(pid, a.tilesV, tilesM, a.gi);
+    const int per = ids_for(a.tilesV, tilesM) / 8, wgs = gridDim.x / 8, x = blockIdx.x & 7, w = blockIdx.x >> 3;
+    // The last row tile is the cheaper the fewer tokens it holds (waves without any do no products: 260 to 300 tokens at
+    // d = 1536, V = 151936 241 -> 212 us a call, 16 to 100 tokens 174 -> 153 us).  Where a round of workgroups covers whole groups of the
+    // order, a workgroup would meet the same row tile in every round: it moves on by one row tile per round then.
+    const int turn = wgs % (a.gi * tilesM) == 0 ? a.gi : 0;
+    for (int r = 0; r * wgs < per; ++r) {
+    const int pos = r * wgs + (w + r * turn) % wgs;
+    const TileId t = tile_of_vid(x * per + pos, a.tilesV, tilesM, a.gi);
     const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
-    if (!t.valid) continue;
+    if (pos >= per || !t.valid) continue;
     f32x16 acc[WI][WJ];
-    mainloop<S, WM == W_DV, false, WM != W_PACKED>(logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti), Operand{a.Hc + j_tile * a.ldk, a.ldk, 128},
-                                                   (int)(a.dpad / K_TILE), lds, acc);
+    const int live = (int)min((int64_t)S::BJ, M - j_tile);
+    mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti), Operand{a.Hc + j_tile * a.ldk, a.ldk, 128},
+                                                         (int)(a.dpad / K_TILE), lds, acc, NoPace(), live);
+    if (STORE == STORE_NOT && (int)(threadIdx.x >> 6) / S::NWI * (WJ * 32) >= live) continue;   // no token of this wave's
     fwd_epilogue<S, STORE>(a, t, j_tile, M, lds, acc);
     }
 }
@@ -1152,12 +1180,12 @@ __device__ __forceinline__ void dh_contract(const DhArgs& a, const TileId& t, in
                                             f32x16 (&acc)[S::WI][S::WJ], Pace pace) {
     const Operand z{a.dz + (int64_t)t.tj * S::BJ * a.ldv + (int64_t)k0 * K_TILE, a.ldv, 128};
     if constexpr (WM != W_PACKED) {
-        mainloop<S, WM == W_VD, false, true, Pace>(dh_w<S, WM>(a.w, t.ti, k0), z, k1 - k0, lds, acc, pace);
+        mainloop<S, WM == W_VD, false, true, false, Pace>(dh_w<S, WM>(a.w, t.ti, k0), z, k1 - k0, lds, acc, pace);
         return;
     }
     const Operand w = a.WdvB ? Operand{a.WdvB + ((int64_t)t.ti * (a.Vpad / K_TILE) + k0) * (S::BI * 64), 64, S::BI * 128}   // tile-blocked copy
                              : Operand{a.Wdv + (int64_t)t.ti * S::BI * a.ldv + (int64_t)k0 * K_TILE, a.ldv, 128};
-    mainloop<S, false, false, false, Pace>(w, z, k1 - k0, lds, acc, pace);
+    mainloop<S, false, false, false, false, Pace>(w, z, k1 - k0, lds, acc, pace);
 }
 
 template <class S, int WM>

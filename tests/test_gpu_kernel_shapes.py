@@ -156,3 +156,23 @@ def test_hidden_tiles_of_192_and_224(rb, d, layout, packed):
     for cache in (False, True):
         w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
         _check_pair(rb, spec, out, ref, layout)
+
+
+@pytest.mark.parametrize("rows", [1, 64, 65, 192, 193, 257, 300, 1030])    # tokens of the last row tile: one to all waves' shares
+@pytest.mark.parametrize("V", [700, 33330, 67000])                        # less than one round of workgroups, and up to nine
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+def test_forward_with_a_short_last_row_tile(rb, rows, V, layout):
+    print(f"short last row tile rows {rows} V {V} {layout}", flush=True)
+    gen = torch.Generator().manual_seed(rows)
+    hidden = torch.randn((1, rows, 72), generator=gen).to(torch.bfloat16)
+    W = (torch.randn((72, V), generator=gen) * 0.3).to(torch.bfloat16)
+    tokens = torch.randint(0, V, (1, rows), generator=gen, dtype=torch.int32)
+    z = hidden[0].double() @ W.double()
+    lse = torch.logsumexp(z, -1)
+    want = z.gather(1, tokens[0].long()[:, None])[:, 0] - lse
+    logp, got = rb.rapid_logprob_fwd(hidden.cuda(), (W if layout == "dv" else W.t().contiguous()).cuda(), tokens.cuda(),
+                                     torch.ones((1, rows), dtype=torch.uint8).cuda(), want_lse=True,
+                                     w_layout=rb.W_DV if layout == "dv" else rb.W_VD)
+    torch.cuda.synchronize()
+    # fp32 sums of 72 products of magnitude up to about 4, and of the exponentials
+    assert (logp.cpu().double()[0] - want).abs().max() <= 2e-5 and (got.cpu().double()[0] - lse).abs().max() <= 2e-5
