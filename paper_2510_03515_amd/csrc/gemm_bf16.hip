@@ -95,6 +95,9 @@ __device__ __forceinline__ s16x4 ds_read_tr64(uint32_t addr) {
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFF) : "memory");
     return v;
 }
+__device__ __forceinline__ void ds_write64(uint32_t addr, uint2 v) {
+    asm volatile("ds_write_b64 %0, %1" ::"v"(addr), "v"(__builtin_bit_cast(unsigned long, v)) : "memory");
+}
 // waits until at most N LDS reads are outstanding, and makes the fragments depend on the wait
 template <int N, int WI, int WJ>
 __device__ __forceinline__ void wait_frags(Frags<WI, WJ>& f) {
@@ -344,9 +347,10 @@ struct Reader {
 // acc = sum over `ktiles` steps of 64 of A(i, k) B(j, k) for the tile the two operands point at.
 // AK / BK: the operand is k-major; CLAMP: A is read in place (see Loader).  TAIL: of B's outer indices only the first live_j
 // matter; waves without any of them leave acc 0.
+// first_requested: prefetch_tile has requested step 0.
 template <class S, bool AK, bool BK, bool CLAMP, bool TAIL = false, class Pace = NoPace>
 __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ],
-                                         Pace pace = Pace(), int live_j = 0) {
+                                         Pace pace = Pace(), int live_j = 0, bool first_requested = false) {
     constexpr int WI = S::WI, WJ = S::WJ, B_STAGE = S::LI * 128;
     constexpr int EA = AK ? S::LI : S::BI, EB = BK ? S::LJ : S::BJ;     // outer indices that are loaded
     const int tid = threadIdx.x;
@@ -375,9 +379,11 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
     // A workgroup runs tile after tile: everybody must be done with the LDS stages of the tile before
     // (its last reads, its trailing requests, a staged epilogue) before they are filled again.
     la.start();
-    lds_barrier();
+    if (!first_requested) {
+        lds_barrier();
 #pragma unroll
-    for (int r = 0; r < T; ++r) request(r);
+        for (int r = 0; r < T; ++r) request(r);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
 
@@ -468,6 +474,22 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
         wait_frags<0>(f0);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests for steps that do not exist
+}
+
+// Requests step 0 of a tile into LDS stage 0, for a mainloop call that is told so: right after the mainloop of the tile
+// before, whose epilogue then covers the trip to memory (and must keep to stage 1).  No barrier is needed: nobody reads
+// the stages any more for values that count, and a wave fills the same bytes of a stage in every step.
+template <class S, bool AK, bool BK, bool CLAMP>
+__device__ __forceinline__ void prefetch_tile(const Operand& A, const Operand& B, char* lds) {
+    constexpr int EA = AK ? S::LI : S::BI, EB = BK ? S::LJ : S::BJ;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Loader<S, EA, AK, CLAMP> la(A, wave, lane);
+    const Loader<S, EB, BK, false> lb(B, wave, lane);
+    la.start();
+#pragma unroll
+    for (int r = 0; r < Loader<S, EA, AK, CLAMP>::ROUNDS; ++r) la.request(r, lds);
+#pragma unroll
+    for (int r = 0; r < Loader<S, EB, BK, false>::ROUNDS; ++r) lb.request(r, lds + S::LI * 128);
 }
 
 // The same contraction with K steps of 32 rows through NST LDS stages (NST x 32 rows = the same LDS as two
@@ -647,8 +669,8 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
 }
 
 // A 256 x 256 tile of bf16 values leaves through LDS so that it reaches memory as whole 256-byte row
-// segments.  Each wave owns a private region (its WJ * 32 token rows x 128 columns, 256 bytes per
-// row; the regions are exactly the two idle LDS stages).  A lane writes its runs of 4 consecutive
+// segments, 32 token rows per wave at a time.  Each wave owns a private region for them (128 columns, 256 bytes per
+// row).  A lane writes its runs of 4 consecutive
 // columns (8 bytes) at 16-byte chunk c ^ (row % 16) of the row, then the wave reads the region back
 // row-wise, 16 lanes x 16 bytes per row, and stores 4 full rows per instruction.  The stores are
 // streamed (non-temporal): the destination is far larger than the L2s and must not push the
@@ -662,27 +684,30 @@ template <class S, class Pack = PackBf16, class F>
 __device__ __forceinline__ void store_tile_through_lds(char* lds, const Lane<S>& L, bf16_t* out, int64_t ld, F&& value) {
     constexpr int WI = S::WI, WJ = S::WJ;
     static_assert(WI == 4, "laid out for 128 columns (256 bytes) per wave row");
-    char* region = lds + L.wave * (WJ * 32 * 256);
+    const uint32_t region = lds_addr(lds) + L.wave * (32 * 256), lrow = region + L.lj * 256 + L.hi * 8;
+    const int rx = L.lj & 15;
+    // read back row-wise: lane l covers chunk l % 16 of row 4 t + l / 16
+    const int c = L.lane & 15, r4 = L.lane >> 4;
+    bf16_t* o = out + (int64_t)r4 * ld + c * 8;
 #pragma unroll
     for (int jb = 0; jb < WJ; ++jb) {
-        const int row = jb * 32 + L.lj;
-        char* lrow = region + row * 256 + L.hi * 8;
-        const int rx = row & 15;
 #pragma unroll
         for (int ib = 0; ib < WI; ++ib)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                *(uint2*)(lrow + (((ib * 4 + q) ^ rx) * 16)) =
-                    Pack()(value(ib, jb, q * 4), value(ib, jb, q * 4 + 1), value(ib, jb, q * 4 + 2), value(ib, jb, q * 4 + 3));
-    }
-    // read back row-wise and store: lane l covers chunk l % 16 of row 4 t + l / 16
-    const int c = L.lane & 15, r4 = L.lane >> 4;
-    bf16_t* o = out + (int64_t)r4 * ld + c * 8;
-#pragma unroll 8
-    for (int tt = 0; tt < WJ * 8; ++tt) {
-        const int row = tt * 4 + r4;
-        const uint4 v = *(const uint4*)(region + row * 256 + ((c ^ (row & 15)) * 16));
-        __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4*)(o + (int64_t)tt * 4 * ld));
+                ds_write64(lrow + (((ib * 4 + q) ^ rx) * 16),
+                           Pack()(value(ib, jb, q * 4), value(ib, jb, q * 4 + 1), value(ib, jb, q * 4 + 2), value(ib, jb, q * 4 + 3)));
+        // LDS accesses of a wave complete in order.  All by hand: the compiler would wait for a prefetch into the other
+        // stage before it touches the LDS.
+        bf16x8 v[8];
+#pragma unroll
+        for (int tt = 0; tt < 8; ++tt) v[tt] = ds_read128<0>(region + (tt * 4 + r4) * 256 + ((c ^ ((tt * 4 + r4) & 15)) * 16));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int tt = 0; tt < 8; ++tt) asm volatile("" : "+v"(v[tt]));
+#pragma unroll
+        for (int tt = 0; tt < 8; ++tt)
+            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v[tt]), (u32x4*)(o + (int64_t)(jb * 8 + tt) * 4 * ld));
     }
 }
 
@@ -734,9 +759,19 @@ __device__ __forceinline__ void mask_padding(f32x16 (&acc)[S::WI][S::WJ], int n_
 // STORE 2, for the backward that is not given a cache: keeps exp(z - m) in a.zc, m the largest of the row's 128 logits
 // of this wave, which the log-sum-exp partials hold anyway; kept_dz_kernel turns it into dz.
 enum { STORE_NOT = 0, STORE_CACHE = 1, STORE_KEEP = 2 };
+template <class S>
+__device__ __forceinline__ void load_references(const FwdArgs& a, int64_t j_tile, int M, float (&ref)[S::WJ]) {
+    const Lane<S> L;
+#pragma unroll
+    for (int jb = 0; jb < S::WJ; ++jb) {
+        const int64_t j = j_tile + (L.wave_j * S::WJ + jb) * 32 + L.lj;
+        ref[jb] = a.refz[j < M ? j : M - 1];
+        if (j >= M) ref[jb] = 0.f;      // rows past the last token: zero logits
+    }
+}
 template <class S, int STORE>
 __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, int64_t j_tile, int M, char* lds,
-                                             f32x16 (&acc)[S::WI][S::WJ]) {
+                                             f32x16 (&acc)[S::WI][S::WJ], const float (&ref)[S::WJ]) {
     constexpr int WI = S::WI, WJ = S::WJ;
     const Lane<S> L;
     const int i_base = t.ti * S::BI + L.wave_i * (WI * 32);
@@ -758,7 +793,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
         l[jb] = 0.f;
     }
     if constexpr (STORE == STORE_KEEP) {
-        __syncthreads();   // every wave is done with both stages
+        lds_barrier();     // every wave is done with the stage that is used below; a prefetch into the other one goes on
         store_tile_through_lds<S, PackKept>(lds, L,
                                             a.zc + (j_tile - a.zc_row0 + L.wave_j * (WJ * 32)) * a.ldz + (int64_t)t.ti * S::BI + L.wave_i * (WI * 32),
                                             a.ldz, [&](int ib, int jb, int v) {
@@ -771,14 +806,13 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
         bool clamped = false;
 #pragma unroll
         for (int jb = 0; jb < WJ; ++jb) {
-            const int64_t j = j_tile + L.wave_j * (WJ * 32) + jb * 32 + L.lj;
-            const float r2 = j < M ? a.refz[j] * LOG2E : 0.f;   // rows past the last token: zero logits
+            const float r2 = ref[jb] * LOG2E;
             float e2 = m[jb] * zs - r2;                        // -inf for a wave of padding columns only
             if (e2 > 115.f) { e2 = 115.f; clamped = true; }
             f[jb] = __builtin_amdgcn_exp2f(e2);
         }
         if (clamped && a.dev_status) atomicOr(a.dev_status, RAPID_STATUS_LOGIT_RANGE);
-        __syncthreads();   // every wave is done with both stages
+        lds_barrier();     // as above
         store_tile_through_lds<S>(lds, L,
                                   a.zc + (j_tile - a.zc_row0 + L.wave_j * (WJ * 32)) * a.ldz + (int64_t)t.ti * S::BI + L.wave_i * (WI * 32),
                                   a.ldz, [&](int ib, int jb, int v) {
@@ -819,17 +853,36 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     // d = 1536, V = 151936 241 -> 212 us a call, 16 to 100 tokens 174 -> 153 us).  Where a round of workgroups covers whole groups of the
     // order, a workgroup would meet the same row tile in every round: it moves on by one row tile per round then.
     const int turn = wgs % (a.gi * tilesM) == 0 ? a.gi : 0;
-    for (int r = 0; r * wgs < per; ++r) {
-    const int pos = r * wgs + (w + r * turn) % wgs;
-    const TileId t = tile_of_vid(x * per + pos, a.tilesV, tilesM, a.gi);
-    const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
-    if (pos >= per || !t.valid) continue;
-    f32x16 acc[WI][WJ];
-    const int live = (int)min((int64_t)S::BJ, M - j_tile);
-    mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti), Operand{a.Hc + j_tile * a.ldk, a.ldk, 128},
-                                                         (int)(a.dpad / K_TILE), lds, acc, NoPace(), live);
-    if (STORE == STORE_NOT && (int)(threadIdx.x >> 6) / S::NWI * (WJ * 32) >= live) continue;   // no token of this wave's
-    fwd_epilogue<S, STORE>(a, t, j_tile, M, lds, acc);
+    auto tile = [&](int r) {        // of round r; once there is none, later rounds have none either
+        const int pos = r * wgs + (w + r * turn) % wgs;
+        TileId t = tile_of_vid(x * per + pos, a.tilesV, tilesM, a.gi);
+        t.valid = t.valid && r * wgs < per && pos < per;
+        return t;
+    };
+    auto opW = [&](const TileId& t) { return logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti); };
+    auto opH = [&](const TileId& t) { return Operand{a.Hc + (a.row0 + (int64_t)t.tj * S::BJ) * a.ldk, a.ldk, 128}; };
+    // The next tile's first step is on its way while this tile's epilogue runs (in stage 1, if its waves' regions fit): a
+    // trip to memory per tile of a few dozen steps.  Worth 1 % of a step at d = 896 (53.4 -> 52.8 ms) and 1 to 2 % at
+    // d = 1536 (333 -> 327 ms); the chip is near its power limit there.
+    constexpr bool AHEAD = STORE == STORE_NOT || S::NW * (32 * 256) <= S::STAGE_BYTES;
+    TileId t = tile(0);
+    for (int r = 0; t.valid; ++r) {
+        const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
+        const int live = (int)min((int64_t)S::BJ, M - j_tile);
+        f32x16 acc[WI][WJ];
+        float ref[WJ];
+        if (STORE == STORE_CACHE) load_references<S>(a, j_tile, M, ref);
+        mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(opW(t), opH(t), (int)(a.dpad / K_TILE), lds, acc, NoPace(), live,
+                                                             AHEAD && r > 0);
+        const TileId next = tile(r + 1);
+        if (STORE == STORE_CACHE) {     // they are here: the compiler shall see that before the requests below
+#pragma unroll
+            for (int jb = 0; jb < WJ; ++jb) asm volatile("" : "+v"(ref[jb]));
+        }
+        if (AHEAD && next.valid) prefetch_tile<S, WM == W_DV, false, WM != W_PACKED>(opW(next), opH(next), lds);
+        if (STORE != STORE_NOT || (int)(threadIdx.x >> 6) / S::NWI * (WJ * 32) < live)      // else: no token of this wave's
+            fwd_epilogue<S, STORE>(a, t, j_tile, M, lds + (AHEAD ? S::STAGE_BYTES : 0), acc, ref);
+        t = next;
     }
 }
 
@@ -969,7 +1022,9 @@ __global__ __launch_bounds__(64 * F2::NW, (F2::NW == 4 && F2::S::WJ == 2) ? 2 : 
         const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;
         f32x16 acc[4][S::WJ];
         mainloop32<F2>((const char*)a.WvdB + (int64_t)t.ti * ksteps * F2::A_BYTES, a.Hc + j_tile * a.ldk, a.ldk, ksteps, lds, acc);
-        fwd_epilogue<S, STORE>(a, t, j_tile, M, lds, acc);
+        float ref[S::WJ];
+        if (STORE == STORE_CACHE) load_references<S>(a, j_tile, M, ref);
+        fwd_epilogue<S, STORE>(a, t, j_tile, M, lds, acc, ref);
     }
 }
 
