@@ -1115,7 +1115,9 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 launch_group_advantage(rewards, group_ids, nullptr, logp_behav ? s64 : nullptr, N, K, o.eta, o.baseline_mode,
                                        adv, adv64, nullptr, nullptr, nullptr, nullptr, gen_range, dev_status, st, 0.f, 0, gruns);
                 CoefArgs cc = ca;
-                cc.gen_range = gen_range; cc.lam_state = lam_state; cc.lam_chunk = lam_chunk + c; cc.beta_out = beta_scale;
+                if (p.Cmax > 1) {   // one chunk is the whole batch: coefficients and loss in one pass
+                    cc.gen_range = gen_range; cc.lam_state = lam_state; cc.lam_chunk = lam_chunk + c; cc.beta_out = beta_scale;
+                }
                 launch_coefficients(cc, st);
                 launch_row_coefficients(g, ca.g64, seqc, row_index, cnt, logp_cur, logp_behav, per_token, o.eta,
                                         o.coef_mode == 1, base, p.Rcap, rowg, st);
@@ -1168,7 +1170,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             if (clip) {
                 launch_clip_finish(at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), N, counts, loss_out,
                                    clip->diag, st);
-            } else {
+            } else if (p.Cmax > 1) {
                 CoefArgs cf = ca;
                 cf.write_g = 0;
                 launch_coefficients(cf, st);
