@@ -864,18 +864,20 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     // The next tile's first step is on its way while this tile's epilogue runs (in stage 1, if its waves' regions fit): a
     // trip to memory per tile of a few dozen steps.  Worth 1 % of a step at d = 896 (53.4 -> 52.8 ms) and 1 to 2 % at
     // d = 1536 (333 -> 327 ms); the chip is near its power limit there.
-    constexpr bool AHEAD = STORE == STORE_NOT || S::NW * (32 * 256) <= S::STAGE_BYTES;
+    // In-place reads with a store have no registers left for it (11 spilled; small head's forward 15.5 -> 17.6 us).
+    constexpr bool AHEAD = STORE == STORE_NOT || (WM == W_PACKED && S::NW * (32 * 256) <= S::STAGE_BYTES);
     TileId t = tile(0);
     for (int r = 0; t.valid; ++r) {
         const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
         const int live = (int)min((int64_t)S::BJ, M - j_tile);
         f32x16 acc[WI][WJ];
         float ref[WJ];
-        if (STORE == STORE_CACHE) load_references<S>(a, j_tile, M, ref);
+        if (STORE == STORE_CACHE && AHEAD) load_references<S>(a, j_tile, M, ref);
         mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(opW(t), opH(t), (int)(a.dpad / K_TILE), lds, acc, NoPace(), live,
                                                              AHEAD && r > 0);
         const TileId next = tile(r + 1);
-        if (STORE == STORE_CACHE) {     // they are here: the compiler shall see that before the requests below
+        if (STORE == STORE_CACHE && !AHEAD) load_references<S>(a, j_tile, M, ref);
+        if (STORE == STORE_CACHE && AHEAD) {     // they are here: the compiler shall see that before the requests below
 #pragma unroll
             for (int jb = 0; jb < WJ; ++jb) asm volatile("" : "+v"(ref[jb]));
         }
