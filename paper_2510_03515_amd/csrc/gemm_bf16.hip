@@ -1207,6 +1207,12 @@ __device__ __forceinline__ void sum_units(const float* part, const TileShare& sh
 // K steps: the vocabulary rounded up to whole steps (in the packed copy and in dz zeros follow)
 __device__ __forceinline__ int dh_ksteps(const DhArgs& a) { return (int)((a.w.V + K_TILE - 1) / K_TILE); }
 
+// row tiles that hold tokens (tilesM counts 256 rows each)
+template <class S>
+__device__ __forceinline__ int dh_row_tiles(const DhArgs& a, int M) {
+    return (int)min((int64_t)a.tilesM * (256 / S::BJ), (M - a.m0 + S::BJ - 1) / S::BJ);
+}
+
 // stores a tile of dHidden: accumulators times the row factor (if any), bf16, to the rows' positions
 template <class S>
 __device__ __forceinline__ void dh_store(const DhArgs& a, const TileId& t, int M, const f32x16 (&acc)[S::WI][S::WJ]) {
@@ -1250,11 +1256,11 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
     const int tilesD = (int)(a.dpadR / S::BI);
-    const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
-    if (a.m0 >= Mr) return;
+    const int M = a.counts[CNT_M];
+    if (a.m0 >= M) return;
     // the order (and with it the split over the XCDs) covers the row tiles that hold tokens only: a
     // short last chunk would otherwise leave whole XCDs with nothing but empty tiles
-    const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
+    const int tilesM = dh_row_tiles<S>(a, M);
     const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
     const int ktiles = dh_ksteps(a);
     const TileShare sh(tilesD * tilesM, grid, ktiles, a.part != nullptr);
@@ -1294,9 +1300,9 @@ template <class S>
 __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_dh) {
     constexpr int WI = S::WI, WJ = S::WJ;
     const int tilesD = (int)(a.dpadR / S::BI);
-    const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
-    if (a.m0 >= Mr) return;
-    const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));
+    const int M = a.counts[CNT_M];
+    if (a.m0 >= M) return;
+    const int tilesM = dh_row_tiles<S>(a, M);
     const TileShare sh(tilesD * tilesM, grid_of_dh, dh_ksteps(a), true);
     const int tpos = blockIdx.x, ib = blockIdx.y / WJ, jb = blockIdx.y % WJ;
     if (!sh.cut || tpos >= sh.rem) return;
@@ -1637,6 +1643,7 @@ using G16_I128 = Geo<2, 8, 2, 1>;  // 128 x 256
 using G16_J128 = Geo<4, 4, 2, 1>;  // 256 x 128
 // hidden dimension in tiles of 224 or 192 (see hidden_tile)
 using G4_I224 = Geo<1, 4, 7, 2>;   // 224 x 256, waves of 224 x 64
+using G4_128 = Geo<2, 2, 2, 2>;    // 128 x 128, for a launch with little to contract
 using G4_I192 = Geo<2, 2, 3, 4>;   // 192 x 256, waves of 96 x 128
 using G4_J192 = Geo<2, 2, 4, 3>;   // 256 x 192
 
@@ -1658,6 +1665,11 @@ void launch_dz_t(const DzArgs& a, hipStream_t st) {
     allow_lds<&dz_kernel<S, WM>>(S::LDS_BYTES);
     dz_kernel<S, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
 }
+// workgroups of a launch that may cut tiles: as many as the chip holds
+template <class S>
+unsigned grid_of_cut() {
+    return (unsigned)(g_num_cu.load() / 8 * 8 * (2 * S::LDS_BYTES <= 160 * 1024 ? 2 : 1));
+}
 template <class S, int WM>
 void launch_dh_t(const DhArgs& a, hipStream_t st) {
     allow_lds<&dh_kernel<S, WM>>(S::LDS_BYTES);
@@ -1665,9 +1677,9 @@ void launch_dh_t(const DhArgs& a, hipStream_t st) {
     DhArgs b = a;
     if ((size_t)MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
     // with scratch for cut tiles a launch of few tiles takes the whole chip as well
-    const unsigned grid = b.part ? (unsigned)(g_num_cu.load() / 8 * 8) : grid_for(tilesD, a.tilesM);
+    const unsigned grid = b.part ? grid_of_cut<S>() : grid_for(tilesD, a.tilesM * (256 / S::BJ));
     dh_kernel<S, WM><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
-    const int64_t tiles = (int64_t)tilesD * a.tilesM;
+    const int64_t tiles = (int64_t)tilesD * a.tilesM * (256 / S::BJ);
     if (b.part) dh_reduce_kernel<S><<<dim3((unsigned)(tiles < grid ? tiles : grid), S::WI * S::WJ), S::NT, 0, st>>>(b, (int)grid);
 }
 template <class S, bool VD, bool DEEP = false>
@@ -1676,7 +1688,7 @@ void launch_dw_t(const DwArgs& a, hipStream_t st) {
     const int64_t tilesV = a.Vpad / (VD ? S::BJ : S::BI), tilesD = a.dpadR / (VD ? S::BI : S::BJ), tiles = tilesV * tilesD;
     DwArgs b = a;
     if ((size_t)MAX_UNITS * S::BI * S::BJ * 4 > a.part_bytes) b.part = nullptr;
-    const unsigned grid = b.part ? (unsigned)(g_num_cu.load() / 8 * 8) : grid_for((int)tilesV, (int)tilesD);
+    const unsigned grid = b.part ? grid_of_cut<S>() : grid_for((int)tilesV, (int)tilesD);
     dw_kernel<S, VD, DEEP><<<grid, S::NT, S::LDS_BYTES, st>>>(b);
     if (b.part && tiles % grid != 0)
         dw_reduce_kernel<S, VD><<<dim3((unsigned)(tiles % grid), S::WI * S::WJ), S::NT, 0, st>>>(b, (int)grid);
@@ -1773,9 +1785,22 @@ void launch_cache_finish(bf16_t* u, int64_t ldz, bf16_t* Hc, int64_t ldk, const 
     cache_finish_kernel<<<(unsigned)((rows_max + 3) / 4), 256, 0, st>>>(u, ldz, Hc, ldk, tokc, zy, refz, lse_c, rowg,
                                                                         inv_temp, counts, row0, rowc, dev_status);
 }
+// A launch whose contraction is short when it is spread over the whole chip leaves 256 KiB of pieces per workgroup behind,
+// and passing them through memory twice takes longer than the products do: tiles of 128 x 128 then, which are cut into
+// fewer segments (two workgroups share a compute unit).  Measured, dHidden and dW with both tiles, `most` = K steps per
+// compute unit with tiles of 256 (upper bounds of the batch): d = 256, V = 4096 (3 steps) 35 -> 26 us and 31 -> 25 us;
+// d = 1024, V = 2000 (8) 40 / 40 and 40 -> 32; d = 128, V = 30000 (13) 56 -> 54 and 39 -> 31; d = 768, V = 20000 (15) 56 -> 51, but
+// dW, whose 237 tiles fill the chip as they are, 43 -> 47; d = 512, V = 16000 (29) 71 -> 73 and 72 -> 63.
+static bool few_steps(int64_t tiles, int64_t ksteps, int most) { return tiles * ksteps <= (int64_t)most * g_num_cu.load(); }
 void launch_dh(const DhArgs& a, hipStream_t st) {
     const int w = waves_for(4);
     const bool d256 = a.dtile == 256;   // else 128, or 192 or 224 in the default geometry
+    if (a.w.mode != W_PACKED && a.part && few_steps((a.d + 255) / 256 * a.tilesM, (a.w.V + K_TILE - 1) / K_TILE, 16)) {
+        DhArgs b = a;
+        b.dpadR = round_up(a.d, 128);
+        a.w.mode == W_VD ? launch_dh_t<G4_128, W_VD>(b, st) : launch_dh_t<G4_128, W_DV>(b, st);
+        return;
+    }
     if (a.dtile == 224)
         a.w.mode == W_VD ? launch_dh_t<G4_I224, W_VD>(a, st) : a.w.mode == W_DV ? launch_dh_t<G4_I224, W_DV>(a, st) : launch_dh_t<G4_I224, W_PACKED>(a, st);
     else if (a.dtile == 192)
@@ -1792,6 +1817,13 @@ void set_dw_deep(int on) { g_dw_deep = on ? 1 : 0; }
 void launch_dw(const DwArgs& a, hipStream_t st) {
     const int w = waves_for(8);
     const bool d256 = a.dtile == 256;   // else 128, or 192 in the default geometry
+    const int64_t tiles = (a.d + 255) / 256 * (a.Vpad / 256);
+    if (default_waves() && a.part && tiles <= g_num_cu.load() / 2 && few_steps(tiles, a.Mc / K_TILE, 32)) {
+        DwArgs b = a;
+        b.dpadR = round_up(a.d, 128);
+        a.w_layout == RAPID_W_VD ? launch_dw_t<G4_128, true>(b, st) : launch_dw_t<G4_128, false>(b, st);
+        return;
+    }
     if (a.dtile == 192) { a.w_layout == RAPID_W_VD ? launch_dw_t<G4_I192, true>(a, st) : launch_dw_t<G4_J192, false>(a, st); return; }
     if (a.w_layout == RAPID_W_VD) {
         if (w == 16) d256 ? launch_dw_t<G16, true>(a, st) : launch_dw_t<G16_I128, true>(a, st);

@@ -176,3 +176,19 @@ def test_forward_with_a_short_last_row_tile(rb, rows, V, layout):
     torch.cuda.synchronize()
     # fp32 sums of 72 products of magnitude up to about 4, and of the exponentials
     assert (logp.cpu().double()[0] - want).abs().max() <= 2e-5 and (got.cpu().double()[0] - lse).abs().max() <= 2e-5
+
+
+@pytest.mark.parametrize("d,V,prompts,length", [
+    (8, 9, 1, 2),            # one tile of 128, one step
+    (128, 1024, 2, 64),      # whole tiles of 128
+    (136, 1032, 3, 90),      # two of the hidden dimension, remainders in every direction
+    (584, 264, 4, 50),       # Hc padded to tiles of 192, read in tiles of 128
+    (256, 4096, 8, 100),     # more K steps than segments
+])
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("cache", [False, True])
+def test_short_contractions_in_tiles_of_128(rb, d, V, prompts, length, layout, cache):
+    print(f"tiles of 128 d {d} V {V} rows {prompts * 4 * length} {layout} cache {cache}", flush=True)
+    spec = wl.small_spec("short", "bf16", d=d, V=V, prompts=prompts, G=4, len_lo=max(1, length - 9), len_hi=length, reward="uniform")
+    w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
+    _check_pair(rb, spec, out, ref, layout)
