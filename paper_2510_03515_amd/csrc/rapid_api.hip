@@ -1336,7 +1336,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             if (o.w_layout == RAPID_W_DV) { gz.sb_k = V; gz.sb_j = 1; } else { gz.sb_k = 1; gz.sb_j = d; }
             gz.C = z; gz.sc_i = V; gz.sc_j = 1;
             gz.I = rows; gz.J = V; gz.Kd = d; gz.beta = 0; gz.counts = counts; gz.i0 = m0; gz.alpha = inv_temp; gz.skip_last = 1;
-            launch_f32_gemm(gz, st);
+            if (p.Mc < p.Mmax) launch_f32_gemm(gz, st);     // one chunk: they are always there
             launch_f32_dz(z, V, rows, m0, tokc, lse_c, rowg, inv_temp, counts, st);
             // dH[row] = dz[row, :] . W^T
             F32Gemm gh;
