@@ -12,8 +12,8 @@ dHidden and dW contract them, so 6 d V flop per token are executed and nothing o
 outlives a chunk.  Generations of a group whose rewards are all 0 have advantage 0 by Eq. (5) and so
 no gradient; the backward leaves them out of its contractions (exactly), and the flop counts
 here leave them out as well (`response_tokens_with_gradient`).  Beside it, never as `value`: the same call with a cache that holds the whole batch
-at once ("whole", 91 GiB), with the backward that is given no cache ("recompute": the logits of all rows but the
-first 65536, whose probabilities the forward leaves in the dz chunk, are formed again, 2 d V flop more per token), and on the workload's calibrated companion (dense gradients: every generation carries
+at once ("whole", 91 GiB), with the backward that regenerates the logits ("recompute", 8 d V flop
+per token), and on the workload's calibrated companion (dense gradients: every generation carries
 weight).
 
 Prints ONE JSON line: response tokens/s, the roofline of the dominant kernel (HIP-event timing of
@@ -148,7 +148,7 @@ def main():
     ap.add_argument("--mode", choices=["chunks", "whole", "recompute"], default="chunks",
                     help="backward of the timed call: 'chunks' = opts.logits_cache 1 with the recommended workspace (a cache "
                          "of 90112 rows, chunks of whole groups, 6 d V flop per token executed); 'whole' = the same with a "
-                         "cache for every token of the batch; 'recompute' = logits_cache 0 (logits past the first chunk regenerated)")
+                         "cache for every token of the batch; 'recompute' = logits_cache 0 (logits regenerated, 8 d V)")
     ap.add_argument("--one-mode", action="store_true", help="skip the extra measurements (other modes, calibrated companion)")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -248,9 +248,7 @@ def main():
     flops_needed = 2.0 * d * V * M + 4.0 * d * V * M_grad
     # the scope table's count: 6 d V per response token (2 d V for the forward-only workload), whatever its reward
     flops_per_call = (2.0 if fwd_only else 6.0) * d * V * M
-    # without a cache the rows past the first dz chunk (all rows if d < 448) have their logits formed again
-    again = max(0.0, 1.0 - BWD_BLOCK_ROWS / M) if d >= 448 else 1.0
-    per_token = {"forward only": 2.0, "chunks": 6.0, "whole": 6.0, "recompute": 6.0 + 2.0 * again}
+    per_token = {"forward only": 2.0, "chunks": 6.0, "whole": 6.0, "recompute": 8.0}
     executed = per_token[mode] * d * V
 
     # the MFMA pipe on its own (no memory traffic), outside the timed region: what the published
@@ -281,7 +279,7 @@ def main():
         per_stage = {}
         for st_name in gemm_stages:
             ms = stages[st_name]["ms_per_step"]
-            rate = 2.0 * d * V * (M if st_name == "fwd_lse" else M_grad * again if st_name == "dz" else M_grad) / (ms * 1e-3) / 1e12
+            rate = 2.0 * d * V * (M if st_name == "fwd_lse" else M_grad) / (ms * 1e-3) / 1e12
             per_stage[st_name] = {"achieved": rate, "frac": rate * 1e12 / PEAK_BF16_MFMA, "frac_of_probe": rate / tf_rnd,
                                   "ms_per_step": ms, "live_launches_per_step": live.get(st_name),
                                   "avg_live_launch_ms": ms / live[st_name] if live.get(st_name) else None}

@@ -94,9 +94,8 @@ typedef struct rapid_iw_pg_opts {
     int normalized_grads;  /* 1: loss, dhidden and dW are returned multiplied by exp(-lambda), with
                               lambda = log max_n |g_n| reported in diag->grad_log_scale, so that
                               ratios that underflow fp32 still give usable gradients */
-    int logits_cache;      /* 0 (default): the backward works in row chunks; it regenerates their logits tile by tile
-                              from hidden and W, or (first chunk, d >= 448) takes the probabilities that the
-                              forward left, to 11 bits, in the chunk's buffer.  1 (bf16 inputs only): the
+    int logits_cache;      /* 0 (default): the backward regenerates the logits tile by tile from hidden and W;
+                              nothing of size rows x V outlives a row chunk.  1 (bf16 inputs only): the
                               forward also stores, in the workspace, exp(z_v - r) (bf16) for every vocabulary
                               entry, r = the sampled token's logit minus its behaviour log-prob (an estimate
                               of the row's log-sum-exp that is known before the sweep, so the stored value

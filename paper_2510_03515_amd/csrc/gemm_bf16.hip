@@ -677,10 +677,7 @@ __device__ __forceinline__ uint2 pack_bf16x4(float a, float b, float c, float d)
 // operand panels out.  `value(ib, jb, v)` is the element the lane holds in accumulator register v of
 // block (ib, jb); `out` points at (first row of the wave, first column of the wave) of the tile.
 // All waves must be done with both LDS stages (barrier) before the call.
-struct PackBf16 {
-    __device__ __forceinline__ uint2 operator()(float a, float b, float c, float d) const { return pack_bf16x4(a, b, c, d); }
-};
-template <class S, class Pack = PackBf16, class F>
+template <class S, class F>
 __device__ __forceinline__ void store_tile_through_lds(char* lds, const Lane<S>& L, bf16_t* out, int64_t ld, F&& value) {
     constexpr int WI = S::WI, WJ = S::WJ;
     static_assert(WI == 4, "laid out for 128 columns (256 bytes) per wave row");
@@ -696,7 +693,7 @@ __device__ __forceinline__ void store_tile_through_lds(char* lds, const Lane<S>&
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 ds_write64(lrow + (((ib * 4 + q) ^ rx) * 16),
-                           Pack()(value(ib, jb, q * 4), value(ib, jb, q * 4 + 1), value(ib, jb, q * 4 + 2), value(ib, jb, q * 4 + 3)));
+                           pack_bf16x4(value(ib, jb, q * 4), value(ib, jb, q * 4 + 1), value(ib, jb, q * 4 + 2), value(ib, jb, q * 4 + 3)));
         // LDS accesses of a wave complete in order.  All by hand: the compiler would wait for a prefetch into the other
         // stage before it touches the LDS.
         bf16x8 v[8];
@@ -709,22 +706,6 @@ __device__ __forceinline__ void store_tile_through_lds(char* lds, const Lane<S>&
         for (int tt = 0; tt < 8; ++tt)
             __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v[tt]), (u32x4*)(o + (int64_t)(jb * 8 + tt) * 4 * ld));
     }
-}
-
-// A number e in [0, 1] in 16 bits without a sign: 11 significant bits (a bf16 has 8) from 2^-54 up, below that the bits
-// of a bf16.  Float bits b below KEPT_FINE shift right by 16, what lies above that by 13.
-constexpr uint32_t KEPT_FINE = 73u << 23;
-struct PackKept {
-    static __device__ __forceinline__ uint32_t high(float e) {      // code in the upper half; fine codes are rounded to nearest
-        const uint32_t b = __builtin_bit_cast(uint32_t, e);
-        return (__builtin_elementwise_sub_sat(b, KEPT_FINE) << 3) + min(b, KEPT_FINE + 0x8000u);
-    }
-    __device__ __forceinline__ uint2 operator()(float a, float b, float c, float d) const {
-        return make_uint2(__builtin_amdgcn_perm(high(b), high(a), 0x07060302u), __builtin_amdgcn_perm(high(d), high(c), 0x07060302u));
-    }
-};
-__device__ __forceinline__ float kept_value(uint32_t code) {
-    return __builtin_bit_cast(float, (min(code, KEPT_FINE >> 16) << 16) + (__builtin_elementwise_sub_sat(code, KEPT_FINE >> 16) << 13));
 }
 
 // ragged last vocabulary tile: the columns that do not exist become -infinity
@@ -755,10 +736,6 @@ __device__ __forceinline__ void mask_padding(f32x16 (&acc)[S::WI][S::WJ], int n_
 // Epilogue of a logits tile: per token row j (one lane pair) the max and the sum of exponentials over this
 // wave's 128 vocabulary columns.  The logit of the sampled token is gathered by a separate small kernel,
 // so the per-element work is one max, one fma, one exp and one add (STORE: and one multiply).
-//
-// STORE 2, for the backward that is not given a cache: keeps exp(z - m) in a.zc, m the largest of the row's 128 logits
-// of this wave, which the log-sum-exp partials hold anyway; kept_dz_kernel turns it into dz.
-enum { STORE_NOT = 0, STORE_CACHE = 1, STORE_KEEP = 2 };
 template <class S>
 __device__ __forceinline__ void load_references(const FwdArgs& a, int64_t j_tile, int M, float (&ref)[S::WJ]) {
     const Lane<S> L;
@@ -769,7 +746,7 @@ __device__ __forceinline__ void load_references(const FwdArgs& a, int64_t j_tile
         if (j >= M) ref[jb] = 0.f;      // rows past the last token: zero logits
     }
 }
-template <class S, int STORE>
+template <class S, bool STORE>
 __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, int64_t j_tile, int M, char* lds,
                                              f32x16 (&acc)[S::WI][S::WJ], const float (&ref)[S::WJ]) {
     constexpr int WI = S::WI, WJ = S::WJ;
@@ -792,16 +769,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
         nm[jb] = (mx == -INFINITY) ? 0.f : -mx * zs;
         l[jb] = 0.f;
     }
-    if constexpr (STORE == STORE_KEEP) {
-        lds_barrier();     // every wave is done with the stage that is used below; a prefetch into the other one goes on
-        store_tile_through_lds<S, PackKept>(lds, L,
-                                            a.zc + (j_tile - a.zc_row0 + L.wave_j * (WJ * 32)) * a.ldz + (int64_t)t.ti * S::BI + L.wave_i * (WI * 32),
-                                            a.ldz, [&](int ib, int jb, int v) {
-                                                const float e = __builtin_amdgcn_exp2f(fmaf(acc[ib][jb][v], zs, nm[jb]));
-                                                l[jb] += e;
-                                                return e;
-                                            });
-    } else if constexpr (STORE == STORE_CACHE) {
+    if (STORE) {
         float f[WJ];   // exp(wave maximum - reference): turns exp(z - maximum) into exp(z - reference)
         bool clamped = false;
 #pragma unroll
@@ -812,7 +780,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
             f[jb] = __builtin_amdgcn_exp2f(e2);
         }
         if (clamped && a.dev_status) atomicOr(a.dev_status, RAPID_STATUS_LOGIT_RANGE);
-        lds_barrier();     // as above
+        lds_barrier();     // every wave is done with the stage that is used below; a prefetch into the other one goes on
         store_tile_through_lds<S>(lds, L,
                                   a.zc + (j_tile - a.zc_row0 + L.wave_j * (WJ * 32)) * a.ldz + (int64_t)t.ti * S::BI + L.wave_i * (WI * 32),
                                   a.ldz, [&](int ib, int jb, int v) {
@@ -840,7 +808,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
 }
 
 // one workgroup per CU on 256 x 256 tiles: the logits tile on MFMA, then the epilogue above
-template <class S, int STORE, int WM>
+template <class S, bool STORE, int WM>
 __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
@@ -865,24 +833,24 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     // trip to memory per tile of a few dozen steps.  Worth 1 % of a step at d = 896 (53.4 -> 52.8 ms) and 1 to 2 % at
     // d = 1536 (333 -> 327 ms); the chip is near its power limit there.
     // In-place reads with a store have no registers left for it (11 spilled; small head's forward 15.5 -> 17.6 us).
-    constexpr bool AHEAD = STORE == STORE_NOT || (WM == W_PACKED && S::NW * (32 * 256) <= S::STAGE_BYTES);
+    constexpr bool AHEAD = !STORE || (WM == W_PACKED && S::NW * (32 * 256) <= S::STAGE_BYTES);
     TileId t = tile(0);
     for (int r = 0; t.valid; ++r) {
         const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
         const int live = (int)min((int64_t)S::BJ, M - j_tile);
         f32x16 acc[WI][WJ];
         float ref[WJ];
-        if (STORE == STORE_CACHE && AHEAD) load_references<S>(a, j_tile, M, ref);
+        if (STORE && AHEAD) load_references<S>(a, j_tile, M, ref);
         mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(opW(t), opH(t), (int)(a.dpad / K_TILE), lds, acc, NoPace(), live,
                                                              AHEAD && r > 0);
         const TileId next = tile(r + 1);
-        if (STORE == STORE_CACHE && !AHEAD) load_references<S>(a, j_tile, M, ref);
-        if (STORE == STORE_CACHE && AHEAD) {     // they are here: the compiler shall see that before the requests below
+        if (STORE && !AHEAD) load_references<S>(a, j_tile, M, ref);
+        if (STORE && AHEAD) {     // they are here: the compiler shall see that before the requests below
 #pragma unroll
             for (int jb = 0; jb < WJ; ++jb) asm volatile("" : "+v"(ref[jb]));
         }
         if (AHEAD && next.valid) prefetch_tile<S, WM == W_DV, false, WM != W_PACKED>(opW(next), opH(next), lds);
-        if (STORE != STORE_NOT || (int)(threadIdx.x >> 6) / S::NWI * (WJ * 32) < live)      // else: no token of this wave's
+        if (STORE || (int)(threadIdx.x >> 6) / S::NWI * (WJ * 32) < live)      // else: no token of this wave's
             fwd_epilogue<S, STORE>(a, t, j_tile, M, lds + (AHEAD ? S::STAGE_BYTES : 0), acc, ref);
         t = next;
     }
@@ -1009,7 +977,7 @@ __device__ __forceinline__ void mainloop32(const char* __restrict__ wblk, const 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the requests for steps that do not exist
 }
 
-template <class F2, int STORE>
+template <class F2, bool STORE>
 __global__ __launch_bounds__(64 * F2::NW, (F2::NW == 4 && F2::S::WJ == 2) ? 2 : 1) void fwd_lse2_kernel(FwdArgs a) {
     using S = typename F2::S;
     extern __shared__ __attribute__((aligned(128))) char lds[];
@@ -1025,7 +993,7 @@ __global__ __launch_bounds__(64 * F2::NW, (F2::NW == 4 && F2::S::WJ == 2) ? 2 : 
         f32x16 acc[4][S::WJ];
         mainloop32<F2>((const char*)a.WvdB + (int64_t)t.ti * ksteps * F2::A_BYTES, a.Hc + j_tile * a.ldk, a.ldk, ksteps, lds, acc);
         float ref[S::WJ];
-        if (STORE == STORE_CACHE) load_references<S>(a, j_tile, M, ref);
+        if (STORE) load_references<S>(a, j_tile, M, ref);
         fwd_epilogue<S, STORE>(a, t, j_tile, M, lds, acc, ref);
     }
 }
@@ -1080,63 +1048,6 @@ __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
     store_tile_through_lds<S>(lds, L, a.dz + jl_base * a.ldz + i_base, a.ldz, [&](int ib, int jb, int v) {
         return ngj[jb] * __builtin_amdgcn_exp2f(fmaf(acc[ib][jb][v], zs, nlse[jb]));
     });
-    }
-}
-
-// dz from what a forward with STORE_KEEP left in its place: dz = g (onehot - p) / temperature with
-// p = kept exp(m - lse), m the slot's maximum.  Bound by memory (2 bytes in, 2 out per element), where forming the
-// logits again is a contraction over d: at d = 1536, V = 151936 a step of 2200 tokens 3.10 -> 2.60 ms, of 13 300 tokens
-// 24.0 -> 20.4 ms.  A workgroup does 64 rows x 512 columns, a wave a row at a time with eight rows in flight.
-__global__ __launch_bounds__(256) void kept_dz_kernel(DzArgs a) {
-    constexpr int ROWS = 64, SLOTS = 4, RPW = ROWS / 4;      // slots: of 128 columns
-    __shared__ float fac[ROWS][SLOTS];
-    const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
-    const int across = (int)((a.Vpad + SLOTS * 128 - 1) / (SLOTS * 128)), bx = blockIdx.x % across;
-    const int64_t j0 = a.m0 + (int64_t)(blockIdx.x / across) * ROWS;
-    if (j0 >= Mr) return;
-    {
-        const int r = threadIdx.x & (ROWS - 1), s = threadIdx.x / ROWS, slot = bx * SLOTS + s;
-        const int64_t j = j0 + r;
-        float f = 0.f;
-        if (j < M && slot * 128 < a.Vpad)
-            f = -a.rowg[j] * a.inv_temp * __expf(a.part_max[(int64_t)slot * a.ld_part + j] - a.lse_c[j]);
-        fac[r][s] = f;
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, r0 = (threadIdx.x >> 6) * RPW;
-    const int64_t col = (int64_t)bx * (SLOTS * 128) + lane * 8;
-    bf16_t* row = a.dz + (j0 - a.m0 + r0) * a.ldz + col;
-    if (col < a.Vpad) {
-#pragma unroll
-        for (int b = 0; b < RPW; b += 8) {
-            uint4 in[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) in[t] = *(const uint4*)(row + (b + t) * a.ldz);
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const bool live = j0 + r0 + b + t < M;
-                const float f = fac[r0 + b + t][lane >> 4];
-                const uint32_t w[4] = {in[t].x, in[t].y, in[t].z, in[t].w};
-                float o[8];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    o[2 * e] = live ? f * kept_value(w[e] & 0xffffu) : 0.f;
-                    o[2 * e + 1] = live ? f * kept_value(w[e] >> 16) : 0.f;
-                }
-                const uint2 lo = pack_bf16x4(o[0], o[1], o[2], o[3]), hi = pack_bf16x4(o[4], o[5], o[6], o[7]);
-                *(uint4*)(row + (b + t) * a.ldz) = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            }
-        }
-    }
-    // the sampled tokens' elements, by the wave that wrote their rows, when those stores are done
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int64_t j = j0 + r0 + lane;
-    if (lane < RPW && j < M) {
-        const int64_t y = a.tokc[j];
-        if (y / (SLOTS * 128) == bx) {
-            const __bf16 v = (__bf16)(-a.rowg[j] * a.inv_temp * expm1f(a.zy[j] - a.lse_c[j]));   // g (1 - p_y) / temperature
-            a.dz[(j - a.m0) * a.ldz + y] = __builtin_bit_cast(bf16_t, v);
-        }
     }
 }
 
@@ -1649,15 +1560,12 @@ using G4_J192 = Geo<2, 2, 4, 3>;   // 256 x 192
 
 template <class S, int WM>
 void launch_fwd_lse_t(const FwdArgs& a, hipStream_t st) {
-    if (a.zc && a.zc_keep) {
-        allow_lds<&fwd_lse_kernel<S, STORE_KEEP, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, STORE_KEEP, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
-    } else if (a.zc) {
-        allow_lds<&fwd_lse_kernel<S, STORE_CACHE, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, STORE_CACHE, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+    if (a.zc) {
+        allow_lds<&fwd_lse_kernel<S, true, WM>>(S::LDS_BYTES);
+        fwd_lse_kernel<S, true, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
     } else {
-        allow_lds<&fwd_lse_kernel<S, STORE_NOT, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, STORE_NOT, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+        allow_lds<&fwd_lse_kernel<S, false, WM>>(S::LDS_BYTES);
+        fwd_lse_kernel<S, false, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
     }
 }
 template <class S, int WM>
@@ -1710,22 +1618,22 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
     if (a.WvdB && a.k32_mode == 3) {   // one workgroup of 4 waves per CU, K steps of 32 requested three steps ahead
         const unsigned grid = grid_for(a.tilesV, a.tilesM);
         if (a.zc) {
-            allow_lds<&fwd_lse2_kernel<Fwd4, STORE_CACHE>>(Fwd4::LDS_BYTES);
-            fwd_lse2_kernel<Fwd4, STORE_CACHE><<<grid, 256, Fwd4::LDS_BYTES, st>>>(a);
+            allow_lds<&fwd_lse2_kernel<Fwd4, true>>(Fwd4::LDS_BYTES);
+            fwd_lse2_kernel<Fwd4, true><<<grid, 256, Fwd4::LDS_BYTES, st>>>(a);
         } else {
-            allow_lds<&fwd_lse2_kernel<Fwd4, STORE_NOT>>(Fwd4::LDS_BYTES);
-            fwd_lse2_kernel<Fwd4, STORE_NOT><<<grid, 256, Fwd4::LDS_BYTES, st>>>(a);
+            allow_lds<&fwd_lse2_kernel<Fwd4, false>>(Fwd4::LDS_BYTES);
+            fwd_lse2_kernel<Fwd4, false><<<grid, 256, Fwd4::LDS_BYTES, st>>>(a);
         }
         return;
     }
     if (a.WvdB && a.k32_mode == 2) {   // one workgroup of 8 waves per CU, K steps of 32 requested three steps ahead
         const unsigned grid = grid_for(a.tilesV, a.tilesM);
         if (a.zc) {
-            allow_lds<&fwd_lse2_kernel<Fwd3, STORE_CACHE>>(Fwd3::LDS_BYTES);
-            fwd_lse2_kernel<Fwd3, STORE_CACHE><<<grid, 512, Fwd3::LDS_BYTES, st>>>(a);
+            allow_lds<&fwd_lse2_kernel<Fwd3, true>>(Fwd3::LDS_BYTES);
+            fwd_lse2_kernel<Fwd3, true><<<grid, 512, Fwd3::LDS_BYTES, st>>>(a);
         } else {
-            allow_lds<&fwd_lse2_kernel<Fwd3, STORE_NOT>>(Fwd3::LDS_BYTES);
-            fwd_lse2_kernel<Fwd3, STORE_NOT><<<grid, 512, Fwd3::LDS_BYTES, st>>>(a);
+            allow_lds<&fwd_lse2_kernel<Fwd3, false>>(Fwd3::LDS_BYTES);
+            fwd_lse2_kernel<Fwd3, false><<<grid, 512, Fwd3::LDS_BYTES, st>>>(a);
         }
         return;
     }
@@ -1733,11 +1641,11 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
         const int ids = ids_for(a.tilesV, a.tilesM * 2), slots = g_num_cu.load() / 8 * 8 * 2;
         const unsigned grid = (unsigned)(ids < slots ? ids : slots);
         if (a.zc) {
-            allow_lds<&fwd_lse2_kernel<Fwd2, STORE_CACHE>>(Fwd2::LDS_BYTES);
-            fwd_lse2_kernel<Fwd2, STORE_CACHE><<<grid, 256, Fwd2::LDS_BYTES, st>>>(a);
+            allow_lds<&fwd_lse2_kernel<Fwd2, true>>(Fwd2::LDS_BYTES);
+            fwd_lse2_kernel<Fwd2, true><<<grid, 256, Fwd2::LDS_BYTES, st>>>(a);
         } else {
-            allow_lds<&fwd_lse2_kernel<Fwd2, STORE_NOT>>(Fwd2::LDS_BYTES);
-            fwd_lse2_kernel<Fwd2, STORE_NOT><<<grid, 256, Fwd2::LDS_BYTES, st>>>(a);
+            allow_lds<&fwd_lse2_kernel<Fwd2, false>>(Fwd2::LDS_BYTES);
+            fwd_lse2_kernel<Fwd2, false><<<grid, 256, Fwd2::LDS_BYTES, st>>>(a);
         }
         return;
     }
@@ -1751,7 +1659,7 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
 void launch_token_logit(const FwdArgs& a, int64_t row0, int64_t rows_max, hipStream_t st) {
     if (rows_max <= 0) return;
     const unsigned blocks = (unsigned)((rows_max + 3) / 4);
-    float* refz = a.zc && !a.zc_keep ? a.refz : nullptr;
+    float* refz = a.zc ? a.refz : nullptr;
     if (a.w.mode == W_DV)
         token_logit_kernel<true><<<blocks, 256, 0, st>>>(a.Hc, a.ldk, a.w.W, a.w.V, a.w.d, a.tokc, a.counts, a.inv_temp, a.zy,
                                                          a.ref_logp, a.row_index, refz, row0);
@@ -1762,9 +1670,6 @@ void launch_token_logit(const FwdArgs& a, int64_t row0, int64_t rows_max, hipStr
 }
 int fwd_slots_per_tile() { return 2; }
 
-void launch_kept_dz(const DzArgs& a, hipStream_t st) {
-    kept_dz_kernel<<<(unsigned)((a.Vpad + 511) / 512 * a.tilesM * 4), 256, 0, st>>>(a);
-}
 void launch_dz(const DzArgs& a, hipStream_t st) {
     const int w = waves_for(8);
     if (a.w.mode == W_VD) launch_dz_t<G8, W_VD>(a, st);

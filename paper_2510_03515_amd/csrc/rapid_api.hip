@@ -365,8 +365,6 @@ struct FwdIo {
     int w_layout; float temperature;
     float* logp_out; float* lse_out; int32_t* dev_status;
     bf16_t* zc = nullptr;   // if set: [row_cap, ldv], the forward also stores the ratios p_v / p_y there
-    int64_t keep_rows = 0;  // > 0: zc is the dz chunk of the backward without a cache, and the forward keeps its
-                            // exponentials of the compact rows [0, keep_rows) there (see launch_kept_dz)
     int64_t row_cap = INT64_MAX;   // compact rows the caller's buffers hold (the cache may be sized for fewer than N*T)
     const float* ref_logp = nullptr;    // with zc: the behaviour log-probs, for the reference of the stored values
     const void* rms_weight = nullptr;   // if set (bf16 only): hidden is normalised while it is packed
@@ -401,15 +399,6 @@ WInPlace w_in_place(const Plan& p, const void* W, int w_layout, WReader reader) 
     const int64_t most = reader == W_FOR_LOGITS ? (vd ? 131072 : 16384) : (vd ? 12288 : 16384);
     if (p.Mmax <= most) w.mode = vd ? W_VD : W_DV;
     return w;
-}
-
-// Whether the forward of a backward without a cache keeps its exponentials in the (then idle) dz chunk: the rows of the
-// first row chunk, all of them in most batches, are spared the second contraction that forms their logits again.
-// That contraction takes time in proportion to d, the passes over rows x V that replace it do not.  Whole step, 32
-// generations of about 288 tokens, without and with: V = 151936, d = 256 3.31 / 3.77 ms, 384 5.86 / 5.97, 512 6.42 / 6.24,
-// 896 10.5 / 9.5; V = 8192, d = 256 350 / 353 us, 384 435 / 399, 512 486 / 463, 896 614 / 559.
-bool keeps_logits(const Plan& p) {
-    return p.dtype == RAPID_DTYPE_BF16 && p.d >= 448 && !p.two_wg && default_waves();
 }
 
 // packs W as [Vpad, ldk] (the operand of the logits kernels)
@@ -468,7 +457,7 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
     a.ld_part = p.ld_part; a.zy = at<float>(ws, p.zy); a.gi = g_gi_fwd;
     a.zc = io.zc; a.ldz = p.ldv; a.dev_status = io.dev_status;
     a.refz = at<float>(ws, p.refz); a.ref_logp = io.ref_logp; a.row_index = row_index;
-    a.part_row0 = base; a.zc_row0 = base; a.zc_keep = io.keep_rows > 0;
+    a.part_row0 = base; a.zc_row0 = base;
     a.WvdB = p.two_wg ? at<bf16_t>(ws, p.Wvd32) : nullptr;
     a.k32_mode = g_fwd_two_wg.load();
     {   // the sampled tokens' logits first: a storing forward uses them as its per-row reference
@@ -479,12 +468,8 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
     // hidden rows stay in the memory-side cache while every XCD sweeps its share of W over them
     // (one launch over all rows re-reads the hidden rows from HBM once per group of W panels).
     const int64_t block_rows = (int64_t)g_fwd_block_tiles.load() * 256;
-    for (int64_t r0 = 0, nrows; r0 < rows; r0 += nrows) {
-        nrows = (rows - r0) < block_rows ? (rows - r0) : block_rows;
-        if (a.zc_keep) {   // a block is kept whole or not at all
-            if (r0 >= io.keep_rows) a.zc = nullptr;
-            else if (r0 + nrows > io.keep_rows) nrows = io.keep_rows - r0;
-        }
+    for (int64_t r0 = 0; r0 < rows; r0 += block_rows) {
+        const int64_t nrows = (rows - r0) < block_rows ? (rows - r0) : block_rows;
         a.row0 = base + r0;
         a.tilesM = (int)(nrows / 256);
         Span sp(ST_FWD_LSE, st);
@@ -1218,11 +1203,6 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         io.idle.cu_live = at<int32_t>(ws, p.cu_live); io.idle.live_group = at<int32_t>(ws, p.live_group);
         bwd_counts = at<int32_t>(ws, p.tab) + CH_LIVE;
     }
-    const int64_t keep_rows = keeps_logits(p) ? p.Mc : 0;   // a multiple of ROW_TILE: the first row chunk
-    if (keep_rows) {
-        io.zc = at<bf16_t>(ws, p.chunk0);
-        io.keep_rows = keep_rows;
-    }
     run_forward(p, ws, io, st);
 
     // generation-level log ratios, clipped-weight group baseline, coefficients and loss
@@ -1272,11 +1252,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             za.tilesV = (int)(p.Vpad / 256); za.tilesM = (int)(rows / 256);
             za.V = p.V; za.Vpad = p.Vpad; za.inv_temp = inv_temp; za.m0 = m0;
             za.tokc = tokc; za.lse_c = lse_c; za.rowg = rowg; za.counts = bwd_counts; za.dz = dz; za.gi = g_gi_fwd;
-            if (m0 < keep_rows) {
-                za.part_max = at<float>(ws, p.part_max); za.ld_part = p.ld_part; za.zy = at<float>(ws, p.zy);
-                Span sp(ST_DZ, st);
-                launch_kept_dz(za, st);
-            } else {
+            {
                 // like the forward, in sub-blocks of rows whose hidden rows stay in the memory-side cache
                 const int64_t sub = (int64_t)g_fwd_block_tiles.load() * 256;
                 for (int64_t r0 = 0; r0 < rows; r0 += sub) {

@@ -223,8 +223,6 @@ struct FwdArgs {          // logits tile -> per-slot (max, sumexp) and gathered 
     int32_t* dev_status;  // may be NULL
     int64_t part_row0 = 0;   // compact row whose partials sit in column 0 of part_max / part_sum
     int64_t zc_row0 = 0;     // compact row stored in row 0 of zc
-    bool zc_keep = false;    // zc receives exp(logit - maximum of the partials' slot) in the 16-bit code of launch_kept_dz
-                             // instead (refz is not needed then)
     const bf16_t* WvdB = nullptr;   // if set: W blocked per (256-row tile, K step of 32) (launch_block_w32); selects the
                                     // kernel that runs two workgroups per CU
     int k32_mode = 1;               // with WvdB: 1 = two 4-wave workgroups per CU on 256 x 128 tiles, 2 = one 8-wave
@@ -253,13 +251,8 @@ struct DzArgs {           // logits tile -> dz = g (onehot - p) / temperature, b
     const int32_t* counts;
     bf16_t* dz;           // [Mc, Vpad]
     int gi;               // tiles along i that share one j before the order moves on (L2 blocking)
-    const float* part_max = nullptr;   // launch_kept_dz only: the forward's partials [P][ld_part] and the sampled
-    int64_t ld_part = 0;               // tokens' logits
-    const float* zy = nullptr;
 };
 void launch_dz(const DzArgs& a, hipStream_t st);
-// the same from what a forward with zc_keep left in dz (its rows m0, m0 + 1, ..)
-void launch_kept_dz(const DzArgs& a, hipStream_t st);
 // turns the ratios a storing forward left in u [rows_max, ldz] (row 0 = compact row row0) into the
 // backward's operands: the sampled token's element of each row, the row factors rowc, and Hc scaled by
 // them in place (Hc, tokc, zy, refz, lse_c, rowg, rowc are indexed by compact row)

@@ -1,5 +1,6 @@
 """GPU parity at the sizes where the kernels' tiles, cuts and dispatch rules change over, against the float64 oracle with
 the bounds of test_gpu_parity."""
+import numpy as np
 import pytest
 import torch
 
@@ -107,12 +108,11 @@ def test_w_read_in_place(rb, d, V, layout, cache):
 ])
 @pytest.mark.parametrize("layout", ["dv", "vd"])
 @pytest.mark.parametrize("scale", [1.0, 100.0])
-def test_probabilities_kept_by_the_forward(rb, d, V, prompts, length, layout, scale):
-    """Backward without a cache from the forward's kept probabilities (d >= 448), all rows or (smallest workspace) the first
-    256 with the others' logits formed again: the oracle's bounds, and no further from it than logits formed again for
-    all rows (tuning key 2 = 8); scale: logits hundreds of nats apart."""
-    print(f"kept probabilities d {d} V {V} {layout} scale {scale}", flush=True)
-    spec = wl.small_spec("kept", "bf16", d=d, V=V, prompts=prompts, G=4, len_lo=length - 9, len_hi=length, reward="uniform")
+def test_backward_without_a_cache(rb, d, V, prompts, length, layout, scale):
+    """Backward without a cache, all rows in one chunk or (smallest workspace) in chunks of 256: the oracle's bounds, and in
+    every chunk as close to it as with the packed copies of W (tuning key 2 = 8); scale: logits hundreds of nats apart."""
+    print(f"no cache d {d} V {V} {layout} scale {scale}", flush=True)
+    spec = wl.small_spec("no_cache", "bf16", d=d, V=V, prompts=prompts, G=4, len_lo=length - 9, len_hi=length, reward="uniform")
     w, g = _make(spec)
     W = (w["W"].float() * scale).to(torch.bfloat16)
     Wg = (W if layout == "dv" else W.t().contiguous()).cuda()
@@ -126,8 +126,8 @@ def test_probabilities_kept_by_the_forward(rb, d, V, prompts, length, layout, sc
     ref = orc.iw_pg_loss_fwd_bwd(H, _np(W), tok, mask, _np(logp_b), _np(w["rewards"]), _np(w["group_ids"]), w["K"])
     far = {}
     try:
-        for again, min_ws in ((False, False), (False, True), (True, False)):
-            rb.rapid_set_tuning(2, 8 if again else 0)
+        for packed, min_ws in ((False, False), (False, True), (True, False)):
+            rb.rapid_set_tuning(2, 8 if packed else 0)
             buf = rb.IwPgBuffers(g["hidden"], Wg, w["K"], lay, minimum_workspace=min_ws)
             out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], Wg, g["tokens"], g["mask"], logp_b, g["rewards"], g["group_ids"],
                                               w["K"], buffers=buf, w_layout=lay)
@@ -136,13 +136,32 @@ def test_probabilities_kept_by_the_forward(rb, d, V, prompts, length, layout, sc
             assert out.dev_status.item() == 0
             _dh_ok(out.dhidden, ref["dH"])
             _dw_ok(dW, ref["dW"])
-            far[again, min_ws] = _rel(dW, ref["dW"]), _rel(_np(out.dhidden), ref["dH"])
+            far[packed, min_ws] = _rel(dW, ref["dW"]), _rel(_np(out.dhidden), ref["dH"])
     finally:
         rb.rapid_set_tuning(2, 0)
     print("relative errors (dW, dHidden): " + str(far), flush=True)
-    for kept in ((False, False), (False, True)):
-        # both round dz to bf16 (8 bits); 11 bits before that add 1 / 64 of its variance at most
-        assert all(a <= b * 1.02 for a, b in zip(far[kept], far[True, False]))
+    for in_place in ((False, False), (False, True)):
+        # the same products summed in another order, which moves some of the roundings of dz and dHidden to bf16
+        assert all(a <= b * 1.02 for a, b in zip(far[in_place], far[True, False]))
+
+
+@pytest.mark.parametrize("d", [256, 448])
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("cache", [False, True])
+def test_nan_weight_is_not_hidden(rb, d, layout, cache):
+    """One weight that is not a number: the vocabulary column's gradient and every token's dHidden are not numbers either."""
+    print(f"NaN weight d {d} {layout} cache {cache}", flush=True)
+    w, g = _make(wl.small_spec("nan", "bf16", d=d, V=600, prompts=4, G=4, len_lo=20, len_hi=30, reward="uniform"))
+    g["tokens"][g["tokens"] == 333] = 7     # the log-probs themselves stay finite: the column's slot drops out of the sum
+    W = g["W"].clone()
+    W[5, 333] = float("nan")
+    W, lay = (W, rb.W_DV) if layout == "dv" else (W.t().contiguous(), rb.W_VD)
+    out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], W, g["tokens"], g["mask"], None, g["rewards"], g["group_ids"], w["K"],
+                                      w_layout=lay, logits_cache=cache)
+    torch.cuda.synchronize()
+    dW = out.dW if layout == "dv" else out.dW.t()
+    assert dW[:, 333].isnan().all()
+    assert out.dhidden[g["mask"] != 0].isnan().all() and (out.dhidden[g["mask"] == 0] == 0).all()
 
 
 @pytest.mark.parametrize("d", [136, 192, 200, 384, 448, 568])     # tiles of 192 (one, whole, two, three) and, dHidden, of 224
