@@ -1030,12 +1030,23 @@ __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the spare tile request of the last step
     __syncthreads();                                    // every wave is done with both stages
     // dz = -g p here; the +g of the sampled token's column is added by a separate small kernel, so
-    // the per-element work is one fma, one exp, one multiply and half a convert.  Rows past the last
-    // token get g = 0; columns past V are zero (dHidden may meet repeated weights there).
+    // the per-element work is one fma, one exp, one multiply and half a convert.  Rows past the last token are
+    // zero (they may belong to generations without gradient, whose logits are any size: exp of one of them
+    // times g = 0 would be NaN), columns past V too (dHidden may meet repeated weights there).
     const Lane<S> L;
     const int64_t i_base = (int64_t)t.ti * S::BI + L.wave_i * (WI * 32);
     const int64_t jl_base = (int64_t)t.tj * S::BJ + L.wave_j * (WJ * 32);   // row in chunk
     const float zs = a.inv_temp * LOG2E;
+    if (a.m0 + jl_base + WJ * 32 > M) {
+#pragma unroll
+        for (int jb = 0; jb < WJ; ++jb) {
+            const bool live = a.m0 + jl_base + jb * 32 + L.lj < M;
+#pragma unroll
+            for (int ib = 0; ib < WI; ++ib)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[ib][jb][v] = live ? acc[ib][jb][v] : 0.f;
+        }
+    }
     mask_padding<S>(acc, (int)(a.V - i_base), L.hi);
     float ngj[WJ], nlse[WJ];
 #pragma unroll

@@ -211,3 +211,29 @@ def test_short_contractions_in_tiles_of_128(rb, d, V, prompts, length, layout, c
     spec = wl.small_spec("short", "bf16", d=d, V=V, prompts=prompts, G=4, len_lo=max(1, length - 9), len_hi=length, reward="uniform")
     w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
     _check_pair(rb, spec, out, ref, layout)
+
+
+@pytest.mark.parametrize("d,min_ws", [(64, False), (448, True)])
+@pytest.mark.parametrize("cache", [False, True])
+def test_idle_generations_with_large_logits(rb, d, min_ws, cache):
+    """Generations without gradient fill the last row tile up behind those that have one: exp of their logits, which
+    overflows here, must not reach dW."""
+    print(f"idle generations with large logits d {d} min_ws {min_ws} cache {cache}", flush=True)
+    w, g = _make(wl.small_spec("idle", "bf16", d=d, V=300, prompts=6, G=4, len_lo=12, len_hi=18, reward="uniform"))
+    idle = w["group_ids"] == 2
+    w["rewards"][idle] = 0.0
+    w["hidden"][idle] *= 4000.0
+    live_rows = int(w["mask"][~idle].sum())
+    assert live_rows % 256 and live_rows > 256
+    g = {k: (v.cuda() if torch.is_tensor(v) else v) for k, v in w.items()}
+    logp_b, _ = rb.rapid_logprob_fwd(g["hidden"], g["W"], g["tokens"], g["mask"])
+    H, W, tok, mask = _oracle_inputs(w)
+    assert (H[_np(idle.float()) != 0] @ W).max() > 200
+    ref = orc.iw_pg_loss_fwd_bwd(H, W, tok, mask, _np(logp_b), _np(w["rewards"]), _np(w["group_ids"]), w["K"])
+    buf = rb.IwPgBuffers(g["hidden"], g["W"], w["K"], logits_cache=cache, minimum_workspace=min_ws)
+    out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], g["W"], g["tokens"], g["mask"], logp_b, g["rewards"], g["group_ids"],
+                                      w["K"], buffers=buf, logits_cache=cache)
+    torch.cuda.synchronize()
+    assert out.dev_status.item() == 0
+    _dh_ok(out.dhidden, ref["dH"])
+    _dw_ok(out.dW, ref["dW"])
