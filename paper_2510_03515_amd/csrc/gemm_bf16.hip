@@ -408,11 +408,12 @@ __device__ __forceinline__ void mainloop(const Operand& A, const Operand& B, int
     dst = lds + S::STAGE_BYTES;
     if constexpr (TAIL) {
         if (wave_j * (WJ * 32) >= live_j) {     // the wave only makes its share of the requests (those that others read)
+            const int read_j = (live_j + WJ * 32 - 1) / (WJ * 32) * (WJ * 32);     // a wave with tokens reads its whole share
             auto requests = [&](int kt) {
                 advance(kt < ktiles, kt < ktiles ? kt : ktiles - 1);
 #pragma unroll
                 for (int r = 0; r < T; ++r)
-                    if (r < NRA || (r - NRA) * (8 * S::NW) < live_j) request(r);
+                    if (r < NRA || (r - NRA) * (8 * S::NW) < read_j) request(r);
             };
             requests(1);
             for (int kt = 0; kt < ktiles; ++kt) {

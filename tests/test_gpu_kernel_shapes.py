@@ -237,3 +237,32 @@ def test_idle_generations_with_large_logits(rb, d, min_ws, cache):
     assert out.dev_status.item() == 0
     _dh_ok(out.dhidden, ref["dH"])
     _dw_ok(out.dW, ref["dW"])
+
+
+@pytest.mark.parametrize("waves", [4, 16])
+def test_short_last_row_tile_in_other_geometries(rb, waves):
+    """A last row tile of 40 tokens behind a whole one whose rows 64 to 127 have logits in the hundreds, several tiles per
+    workgroup: what the cache holds for rows past the last token is formed from rows of zeros whatever the geometry."""
+    print(f"short last row tile, {waves} waves", flush=True)
+    gen = torch.Generator().manual_seed(1)
+    N, T, d, V = 4, 74, 128, 70000
+    hidden = torch.randn((N * T, d), generator=gen)
+    hidden[64:128] *= 400.0
+    hidden = hidden.view(N, T, d).to(torch.bfloat16).cuda()
+    W = (torch.randn((d, V), generator=gen) * 0.02).to(torch.bfloat16).cuda()
+    tokens = torch.randint(0, V, (N, T), generator=gen, dtype=torch.int32).cuda()
+    mask = torch.ones((N, T), dtype=torch.uint8).cuda()
+    logp_b, _ = rb.rapid_logprob_fwd(hidden, W, tokens, mask)
+    rewards, group = torch.tensor([1.0, 0.0, 0.5, 0.0]).cuda(), torch.zeros(N, dtype=torch.int32).cuda()
+    got = {}
+    try:
+        for w in (8, waves):
+            rb.rapid_set_tuning(2, w)
+            out = rb.rapid_iw_pg_loss_fwd_bwd(hidden, W, tokens, mask, logp_b, rewards, group, 1, logits_cache=True)
+            torch.cuda.synchronize()
+            assert out.dev_status.item() == 0
+            got[w] = _np(out.dW)
+    finally:
+        rb.rapid_set_tuning(2, 0)
+    assert np.isfinite(got[waves]).all()
+    assert _rel(got[waves], got[8]) <= 1e-5         # the same bf16 operands, fp32 sums of 296 terms in another order
