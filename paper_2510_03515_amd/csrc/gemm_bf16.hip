@@ -1082,14 +1082,15 @@ struct TileShare {     // how a launch of `grid` workgroups works through `total
     __device__ __forceinline__ TileShare(int total, int grid, int ktiles, bool can_cut) {
         wgs = grid / 8; full_rounds = total / grid; rem = total - full_rounds * grid;
         // S with the shortest last round, counted in K steps of a workgroup: the segments of its units, about 5 steps for
-        // filling the pipeline and storing the accumulators, and the second pass over 256 KiB per unit (1 / 25 step each)
+        // filling the pipeline and storing the accumulators, and the second pass over 256 KiB per unit (1 / 25 step each).
+        // In whole numbers (25 S times the cost), so that the kernel that cuts and the one that adds the pieces agree.
         segs = 1;
-        float best = (float)ktiles + 4.f;
+        int64_t best = 25 * ((int64_t)ktiles + 4);
         if (can_cut && rem > 0) {
             for (int sg = 2; sg <= 64 && rem * sg <= MAX_UNITS && sg * 4 <= ktiles; sg += sg < 8 ? 1 : sg / 4) {
                 const int rounds = (rem * sg + grid - 1) / grid;
-                const float cost = (float)rounds * ((float)ktiles / (float)sg + 5.f) + (float)(rem * sg) * 0.04f;
-                if (cost < best) { best = cost; segs = sg; }
+                const int64_t cost = 25 * (int64_t)rounds * (ktiles + 5 * sg) + rem * sg * sg;
+                if (cost * segs < best * sg) { best = cost; segs = sg; }
             }
         }
         cut = segs > 1;
