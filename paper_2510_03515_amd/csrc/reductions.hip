@@ -356,11 +356,14 @@ __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
 }
 
 // lse[j] = log sum_p part_sum[p][j] exp(part_max[p][j]) ; logp = zy - lse, scattered to [N,T].
-// A block of 1024 threads takes 32 columns (a line of each slot): half a wave, one column per lane, is one of 32 groups
-// that fold P / 32 slots each, then the 32 (max, sum) pairs of a column are merged in a fixed tree: the two of a
-// wave in registers, the 16 waves through LDS.  A group's loads are a chain of batches, each a trip to memory: with 4
-// groups per column a few hundred rows took 50 us at P = 1188 (37 batches), now 13; 74 000 rows 166, now 138.
-// How P is shared out does not depend on the number of rows: every call forms a row's sum in the same order.
+// A block of NW waves takes 32 columns (a line of each slot): half a wave, one column per lane, is one of 2 NW groups
+// that fold P / (2 NW) slots each, then the (max, sum) pairs of a column are merged in a fixed tree: the two of a
+// wave in registers, the waves through LDS.  A group's loads are a chain of batches, each a trip to memory: with 4
+// groups per column a few hundred rows took 50 us at P = 1188 (37 batches), with 32 groups 13; 74 000 rows 166 and 138.
+// With few slots most of 32 groups are empty and their waves are all the time goes into; 131 072 rows, with the
+// sampled tokens' logits, 1 / 4 / 16 waves: P = 2 33 / 36 / 53 us, P = 16 34 / 37 / 55, P = 32 38 / 38 / 55, P = 128 58 / 54 / 61,
+// P = 256 83 / 79 / 83; 300 rows: P = 16 12 us with any, P = 128 20 / 14 / 13, P = 256 28 / 16 / 13.
+// How P is shared out depends on P alone: every call forms a row's sum in the same order.
 struct MaxSum { float mx; double acc; };
 // the lower-numbered operand first
 __device__ inline MaxSum merge_pair(const MaxSum& a, const MaxSum& b) {
@@ -371,13 +374,15 @@ __device__ inline MaxSum merge_pair(const MaxSum& a, const MaxSum& b) {
     if (b.acc > 0.0) r.acc += b.acc * (double)__expf(b.mx - r.mx);
     return r;
 }
-__global__ __launch_bounds__(1024) void merge_lse_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
                                  int64_t ld_part, const float* __restrict__ zy,
                                  const int32_t* __restrict__ row_index, const int32_t* __restrict__ counts,
                                  int64_t row0, float* __restrict__ lse_c, float* __restrict__ logp_out,
                                  float* __restrict__ lse_out) {
-    __shared__ float s_mx[16][32];
-    __shared__ double s_acc[16][32];
+    constexpr int GROUPS = 2 * NW;
+    __shared__ float s_mx[NW][32];
+    __shared__ double s_acc[NW][32];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = wave * 2 + (lane >> 5), col = lane & 31;
     const int64_t jl = (int64_t)blockIdx.x * 32 + col;
     const int64_t j = row0 + jl;
@@ -389,7 +394,7 @@ __global__ __launch_bounds__(1024) void merge_lse_kernel(const float* __restrict
     // partial sums themselves), the accumulation fp64.
     MaxSum m{-INFINITY, 0.0};
     constexpr int UN = 10;   // slots loaded ahead of the fold: the loads of a batch are in flight together
-    const int p_begin = (int)((int64_t)P * q / 32), p_end = (int)((int64_t)P * (q + 1) / 32);
+    const int p_begin = (int)((int64_t)P * q / GROUPS), p_end = (int)((int64_t)P * (q + 1) / GROUPS);
     if (live) {
         for (int p0 = p_begin; p0 < p_end; p0 += UN) {
             float pmv[UN], psv[UN];
@@ -417,17 +422,20 @@ __global__ __launch_bounds__(1024) void merge_lse_kernel(const float* __restrict
         m = lane < 32 ? merge_pair(m, o) : merge_pair(o, m);
     };
     merge_halves();
-    if (lane < 32) {
-        s_mx[wave][col] = m.mx;
-        s_acc[wave][col] = m.acc;
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    const int g = lane >> 5;   // wave 0: its halves fold the results of waves 0 .. 7 and 8 .. 15
-    m = MaxSum{s_mx[g * 8][col], s_acc[g * 8][col]};
+    const int g = lane >> 5;
+    if constexpr (NW > 1) {
+        if (lane < 32) {
+            s_mx[wave][col] = m.mx;
+            s_acc[wave][col] = m.acc;
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        constexpr int H = NW / 2;   // wave 0: its halves fold the results of the first and of the second half of the waves
+        m = MaxSum{s_mx[g * H][col], s_acc[g * H][col]};
 #pragma unroll
-    for (int w = 1; w < 8; ++w) m = merge_pair(m, MaxSum{s_mx[g * 8 + w][col], s_acc[g * 8 + w][col]});
-    merge_halves();
+        for (int w = 1; w < H; ++w) m = merge_pair(m, MaxSum{s_mx[g * H + w][col], s_acc[g * H + w][col]});
+        merge_halves();
+    }
     if (!live || g != 0) return;
     const double lse = (double)m.mx + log(m.acc);
     const float lse_f = (float)lse;
@@ -772,9 +780,10 @@ void launch_f32_add(const float* src, float* dst, int64_t n, hipStream_t st) {
 void launch_merge_lse(const float* part_max, const float* part_sum, int P, int64_t ld_part, const float* zy,
                       const int32_t* row_index, const int32_t* counts, int64_t row0, int64_t rows_max, float* lse_c,
                       float* logp_out, float* lse_out, hipStream_t st) {
-    if (rows_max > 0)
-        merge_lse_kernel<<<blocks_for(rows_max, 32), 1024, 0, st>>>(part_max, part_sum, P, ld_part, zy, row_index,
-                                                                    counts, row0, lse_c, logp_out, lse_out);
+    if (rows_max <= 0) return;
+    auto* kernel = P <= 16 ? &merge_lse_kernel<1> : P <= 128 ? &merge_lse_kernel<4> : &merge_lse_kernel<16>;
+    kernel<<<blocks_for(rows_max, 32), P <= 16 ? 64 : P <= 128 ? 256 : 1024, 0, st>>>(part_max, part_sum, P, ld_part, zy, row_index,
+                                                                                     counts, row0, lse_c, logp_out, lse_out);
 }
 
 void launch_seq_logratio(const float* logp_cur, const float* logp_behav, const uint8_t* mask, int64_t N,

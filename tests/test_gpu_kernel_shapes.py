@@ -266,3 +266,20 @@ def test_short_last_row_tile_in_other_geometries(rb, waves):
         rb.rapid_set_tuning(2, 0)
     assert np.isfinite(got[waves]).all()
     assert _rel(got[waves], got[8]) <= 1e-5         # the same bf16 operands, fp32 sums of 296 terms in another order
+
+
+@pytest.mark.parametrize("V", [8, 256, 257, 2048, 2049, 16384, 16385])     # 2 slots per 256 entries: 1, 4 or 16 waves fold them
+@pytest.mark.parametrize("rows", [1, 32, 77])
+def test_log_sum_exp_over_few_and_many_slots(rb, V, rows):
+    print(f"log-sum-exp V {V} rows {rows}", flush=True)
+    gen = torch.Generator().manual_seed(V + rows)
+    hidden = torch.randn((1, rows, 64), generator=gen).to(torch.bfloat16)
+    W = (torch.randn((64, V), generator=gen) * 0.5).to(torch.bfloat16)
+    tokens = torch.randint(0, V, (1, rows), generator=gen, dtype=torch.int32)
+    z = hidden[0].double() @ W.double()
+    lse = torch.logsumexp(z, -1)
+    want = z.gather(1, tokens[0].long()[:, None])[:, 0] - lse
+    logp, got = rb.rapid_logprob_fwd(hidden.cuda(), W.cuda(), tokens.cuda(), torch.ones((1, rows), dtype=torch.uint8).cuda(), want_lse=True)
+    torch.cuda.synchronize()
+    # fp32 sums of 64 products of magnitude up to about 6, and of the exponentials
+    assert (logp.cpu().double()[0] - want).abs().max() <= 2e-5 and (got.cpu().double()[0] - lse).abs().max() <= 2e-5
