@@ -77,32 +77,55 @@ inline unsigned block_threads(int64_t N, unsigned most) {
 // Three launches whatever is asked for: a small batch's call is a matter of launches (about 5 us each), and these
 // kernels have next to nothing to do.  Before (one kernel per array): 8 launches for a forward, 13 for a cached step.
 
-// One wave per generation: number of valid tokens, and zeros in its rows of the per-token outputs; the waves together
-// clear the plan's counters.
-__global__ __launch_bounds__(64) void seq_len_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
-                                                     int32_t* __restrict__ seq_len, float* __restrict__ zero_a,
-                                                     float* __restrict__ zero_b, ZeroWords z) {
-    const int64_t n = blockIdx.x;
-    const int lane = threadIdx.x;
+// One block per generation; its waves take stretches of the sequence of the same length.  One wave where a sequence has
+// fewer than 512 positions: 256 positions are about four trips to memory, and a second wave costs a barrier.
+inline unsigned row_threads(int64_t T) { return WAVE * (T < 512 ? 1u : T < 256 * 16 ? (unsigned)(T / 256) : 16u); }
+struct Stretch { int64_t begin, end; };
+__device__ inline Stretch wave_stretch(int64_t T) {
+    const int64_t span = (T + blockDim.x - 1) / blockDim.x * WAVE, begin = threadIdx.x / WAVE * span;
+    return {begin, begin + span < T ? begin + span : T};
+}
+// the wave's valid tokens in its stretch (all lanes get the sum)
+__device__ inline int count_valid(const uint8_t* mask, int64_t row0, int64_t T, const Stretch& s) {
+    const int lane = threadIdx.x & (WAVE - 1);
+    const uint8_t* row = mask + row0;
     int cnt = 0;
-    const uint8_t* row = mask + n * T;
     if ((T & 3) == 0 && ((uintptr_t)mask & 3) == 0) {
-        for (int64_t t = lane; t < T / 4; t += WAVE) {
+#pragma unroll 4
+        for (int64_t t = s.begin / 4 + lane; t < s.end / 4; t += WAVE) {
             const uint32_t w = ((const uint32_t*)row)[t];
             cnt += __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);   // top bit of every byte that is not 0
         }
     } else {
-        for (int64_t t = lane; t < T; t += WAVE) cnt += row[t] != 0;
+#pragma unroll 4
+        for (int64_t t = s.begin + lane; t < s.end; t += WAVE) cnt += row[t] != 0;
     }
-    for (int64_t t = lane; t < T; t += WAVE) {
+    return wave_sum_i(cnt);
+}
+
+// Number of valid tokens of each generation, and zeros in its rows of the per-token outputs; the blocks together
+// clear the plan's counters.
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void seq_len_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
+                                                       int32_t* __restrict__ seq_len, float* __restrict__ zero_a,
+                                                       float* __restrict__ zero_b, ZeroWords z) {
+    const int64_t n = blockIdx.x;
+    int cnt = count_valid(mask, n * T, T, ONE_WAVE ? Stretch{0, T} : wave_stretch(T));
+    for (int64_t t = threadIdx.x; t < T; t += blockDim.x) {
         if (zero_a) zero_a[n * T + t] = 0.f;
         if (zero_b) zero_b[n * T + t] = 0.f;
     }
 #pragma unroll
     for (int k = 0; k < 3; ++k)
-        for (int64_t i = n * WAVE + lane; i < z.n[k]; i += N * WAVE) z.p[k][i] = 0;
-    cnt = wave_sum_i(cnt);
-    if (lane == 0) seq_len[n] = cnt;
+        for (int64_t i = n * blockDim.x + threadIdx.x; i < z.n[k]; i += N * blockDim.x) z.p[k][i] = 0;
+    if constexpr (!ONE_WAVE) {
+        __shared__ int s_cnt[16];
+        if (threadIdx.x % WAVE == 0) s_cnt[threadIdx.x / WAVE] = cnt;
+        __syncthreads();
+        cnt = 0;
+        for (unsigned w = 0; w < blockDim.x / WAVE; ++w) cnt += s_cnt[w];
+    }
+    if (threadIdx.x == 0) seq_len[n] = cnt;
 }
 
 // exclusive prefix sum of v [N] -> cu [N + 1] by a block of up to 1024 threads; returns the total to every thread
@@ -300,47 +323,66 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     if (status && a.dev_status) atomicOr(a.dev_status, status);
 }
 
-// One wave per generation: flat positions of its valid tokens, in order, from compact row first_row[n]
+// One block per generation: flat positions of its valid tokens, in order, from compact row first_row[n]
 // on (a negative first row: the generation was left out), and their token ids and generation (out-of-range ids are flagged
 // and replaced by 0).  The compact rows come in regions of `region` rows; a generation never writes past the end of the
 // region its first row lies in.  Rows that fill a region's last row tile up (its counters: limits[e * stride]) get token 0.
-__global__ __launch_bounds__(64) void row_index_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
-                                                       const int32_t* __restrict__ first_row, int64_t region,
-                                                       int32_t* __restrict__ row_index, const int32_t* __restrict__ tokens,
-                                                       int64_t V, int32_t* __restrict__ tokc, int32_t* __restrict__ seqc,
-                                                       const int32_t* __restrict__ limits, int stride, int entries,
-                                                       int32_t* __restrict__ dev_status) {
+// A wave's loop is a chain of trips to memory, so it takes 4 x 64 positions at a time, mask and tokens together, and the
+// waves of a long sequence share it (each counts its stretch first).  One wave, one load after the other: 1 x 131 072
+// positions 500 us, 64 x 2048 19 us.
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void row_index_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
+                                                         const int32_t* __restrict__ first_row, int64_t region,
+                                                         int32_t* __restrict__ row_index, const int32_t* __restrict__ tokens,
+                                                         int64_t V, int32_t* __restrict__ tokc, int32_t* __restrict__ seqc,
+                                                         const int32_t* __restrict__ limits, int stride, int entries,
+                                                         int32_t* __restrict__ dev_status) {
     const int64_t n = blockIdx.x;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (WAVE - 1);
     if (tokc)
         for (int64_t e = n; e < entries; e += N)
-            for (int j = limits[e * stride + CNT_M] + lane; j < limits[e * stride + CNT_MR]; j += WAVE) {
+            for (int j = limits[e * stride + CNT_M] + (int)threadIdx.x; j < limits[e * stride + CNT_MR]; j += blockDim.x) {
                 tokc[j] = 0;
                 seqc[j] = 0;
             }
     int64_t base = first_row[n];
     if (base < 0) return;
     const int64_t limit = (base / region + 1) * region;
+    const Stretch s = ONE_WAVE ? Stretch{0, T} : wave_stretch(T);
+    if constexpr (!ONE_WAVE) {
+        __shared__ int s_cnt[16];
+        const int cnt = count_valid(mask, n * T, T, s), wave = threadIdx.x / WAVE;
+        if (lane == 0) s_cnt[wave] = cnt;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) base += s_cnt[w];
+    }
     bool bad = false;
-    for (int64_t t0 = 0; t0 < T; t0 += WAVE) {
-        const int64_t t = t0 + lane;
-        const bool v = t < T && mask[n * T + t] != 0;
-        const unsigned long long b = __ballot(v);
-        const int before = __popcll(b & ((1ull << lane) - 1ull));
-        if (v && base + before < limit) {
-            const int64_t j = base + before;
-            row_index[j] = (int32_t)(n * T + t);
-            if (tokc) {
-                int tok = tokens[n * T + t];
-                if (tok < 0 || tok >= V) {
-                    tok = 0;
-                    bad = true;
-                }
-                tokc[j] = tok;
-                seqc[j] = (int32_t)n;
-            }
+    constexpr int U = 4;
+    for (int64_t t0 = s.begin; t0 < s.end; t0 += U * WAVE) {
+        bool v[U];
+        int tok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t t = t0 + u * WAVE + lane;
+            v[u] = t < s.end && mask[n * T + t] != 0;
+            tok[u] = t < s.end && tokc ? tokens[n * T + t] : 0;
         }
-        base += __popcll(b);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t0 + u * WAVE >= s.end) break;
+            const unsigned long long b = __ballot(v[u]);
+            const int64_t j = base + __popcll(b & ((1ull << lane) - 1ull));
+            if (v[u] && j < limit) {
+                row_index[j] = (int32_t)(n * T + t0 + u * WAVE + lane);
+                if (tokc) {
+                    const bool in = tok[u] >= 0 && tok[u] < V;
+                    bad = bad || !in;
+                    tokc[j] = in ? tok[u] : 0;
+                    seqc[j] = (int32_t)n;
+                }
+            }
+            base += __popcll(b);
+        }
     }
     if (bad && dev_status) atomicOr(dev_status, RAPID_STATUS_BAD_TOKEN);
 }
@@ -761,10 +803,11 @@ void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs
     if (plan.runs) { z.p[0] = plan.runs; z.n[0] = 3 * plan.K + 1; }
     if (plan.idle.idle && !plan.idle.coef_override) { z.p[1] = plan.idle.live_group; z.n[1] = plan.K; }
     if (plan.tab && plan.Cmax > 1) { z.p[2] = plan.gseen; z.n[2] = plan.K; }
-    seq_len_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, plan.seq_len, zero_a, zero_b, z);
+    const unsigned threads = row_threads(T);
+    (threads == WAVE ? &seq_len_kernel<true> : &seq_len_kernel<false>)<<<(unsigned)N, threads, 0, st>>>(mask, N, T, plan.seq_len, zero_a, zero_b, z);
     plan_kernel<<<1, block_threads(plan.N, 1024), 0, st>>>(plan);
     if (row_index)
-        row_index_kernel<<<(unsigned)N, WAVE, 0, st>>>(mask, N, T, plan.tab ? plan.gen_row0 : plan.cu, plan.tab ? plan.Rcap : INT64_MAX / 4,
+        (threads == WAVE ? &row_index_kernel<true> : &row_index_kernel<false>)<<<(unsigned)N, threads, 0, st>>>(mask, N, T, plan.tab ? plan.gen_row0 : plan.cu, plan.tab ? plan.Rcap : INT64_MAX / 4,
                                                        row_index, tok.tokens, tok.V, tok.tokc, tok.seqc,
                                                        plan.tab ? plan.tab : plan.counts, plan.tab ? (int)CH_WORDS : 0,
                                                        plan.tab ? plan.Cmax : 1, plan.dev_status);

@@ -283,3 +283,29 @@ def test_log_sum_exp_over_few_and_many_slots(rb, V, rows):
     torch.cuda.synchronize()
     # fp32 sums of 64 products of magnitude up to about 6, and of the exponentials
     assert (logp.cpu().double()[0] - want).abs().max() <= 2e-5 and (got.cpu().double()[0] - lse).abs().max() <= 2e-5
+
+
+@pytest.mark.parametrize("N,T", [(2, 511), (3, 512), (2, 513), (2, 767), (5, 1028), (3, 4095), (2, 4096), (1, 8197)])   # 1, 2, .. 16 waves
+@pytest.mark.parametrize("p", [0.5, 1.0])
+def test_long_sequences_are_compacted_by_several_waves(rb, N, T, p):
+    print(f"several waves N {N} T {T} p {p}", flush=True)
+    gen = torch.Generator().manual_seed(N * T)
+    mask = (torch.rand((N, T), generator=gen) < p).to(torch.uint8)
+    mask[:, -1] = 1
+    seq_len, cu, row_index = rb.rapid_compaction(mask.cuda())
+    o_len, o_cu, o_rows = orc.compaction(_np(mask))
+    assert np.array_equal(_np(seq_len), o_len) and np.array_equal(_np(cu), o_cu) and np.array_equal(_np(row_index)[:o_cu[-1]], o_rows)
+    hidden = torch.randn((N, T, 8), generator=gen).to(torch.bfloat16)
+    W = torch.randn((8, 24), generator=gen).to(torch.bfloat16)
+    tokens = torch.randint(0, 24, (N, T), generator=gen, dtype=torch.int32)
+    want = torch.log_softmax(hidden.double() @ W.double(), -1).gather(2, tokens.long()[:, :, None])[:, :, 0] * mask
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    logp, _ = rb.rapid_logprob_fwd(hidden.cuda(), W.cuda(), tokens.cuda(), mask.cuda(), dev_status=status)
+    torch.cuda.synchronize()
+    assert status.item() == 0
+    # fp32 sums of 8 products of magnitude up to about 16
+    assert (logp.cpu().double() - want).abs().max() <= 2e-5 and (logp.cpu()[mask == 0] == 0).all()
+    tokens[-1, -1] = 24
+    rb.rapid_logprob_fwd(hidden.cuda(), W.cuda(), tokens.cuda(), mask.cuda(), dev_status=status)
+    torch.cuda.synchronize()
+    assert status.item() == rb.STATUS_BAD_TOKEN
