@@ -540,18 +540,11 @@ __device__ inline double clipped_weight(const float* s32, const double* s64, int
     return exp(fmin((double)s32[n], log_eta));
 }
 
-// data checks of one generation
-__device__ inline int generation_status(const float* rewards, const float* s32, const double* s64, int64_t n) {
-    int bits = 0;
-    if (!isfinite(rewards[n])) bits |= RAPID_STATUS_NONFINITE_REWARD;
-    if (s64 ? isnan(s64[n]) : (s32 && isnan(s32[n]))) bits |= RAPID_STATUS_NONFINITE_LOGP;
-    return bits;
-}
-
 // one block per group: size, mean/std of R, clipped-weight baseline, advantages of its members.
 // With gen_range only the generations in the range are looked at (the caller guarantees that a group
 // lies inside or outside the range as a whole); a group without a member there writes nothing.
-// Generations that no group owns get their defaults from the block whose share of the batch they lie in.
+// The blocks behind those of the K groups take a generation per thread: its checks and weight, and the defaults of one
+// that no group owns.  (By the groups' own blocks, one group of 20 000 generations took 76 us, now 57; 20 000 of one 334, 305.)
 __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __restrict__ rewards, const int32_t* __restrict__ group_ids,
                                        const float* __restrict__ s32, const double* __restrict__ s64, int64_t N,
                                        double log_eta, int baseline_mode, float* __restrict__ adv,
@@ -562,17 +555,21 @@ __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __res
     __shared__ double sm[16 * 3];
     const int k = blockIdx.x;
     int64_t n_begin = gen_range ? gen_range[0] : 0, n_end = gen_range ? gen_range[1] : N;
-    int bits = 0;
-    {
-        const int64_t b0 = N * k / K, b1 = N * (k + 1) / K;
-        for (int64_t n = (b0 > n_begin ? b0 : n_begin) + threadIdx.x; n < (b1 < n_end ? b1 : n_end); n += blockDim.x) {
-            const int32_t g = group_ids[n];
-            if (g >= 0 && g < K) continue;
-            bits |= RAPID_STATUS_BAD_GROUP | generation_status(rewards, s32, s64, n);
+    if (k >= K) {
+        const int64_t n = (int64_t)(k - (int)K) * blockDim.x + threadIdx.x;
+        if (n < n_begin || n >= n_end) return;
+        int bits = 0;
+        const int32_t g = group_ids[n];
+        if (g < 0 || g >= K) {
+            bits |= RAPID_STATUS_BAD_GROUP;
             adv[n] = 0.f;
             if (adv64) adv64[n] = 0.0;
-            if (weight) weight[n] = (float)clipped_weight(s32, s64, n, log_eta);
         }
+        if (!isfinite(rewards[n])) bits |= RAPID_STATUS_NONFINITE_REWARD;
+        if (s64 ? isnan(s64[n]) : (s32 && isnan(s32[n]))) bits |= RAPID_STATUS_NONFINITE_LOGP;
+        if (bits && dev_status) atomicOr(dev_status, bits);
+        if (weight) weight[n] = (float)clipped_weight(s32, s64, n, log_eta);
+        return;
     }
     if (runs && runs[3 * K] == 0) {   // every group is one run of the batch: look at that run only
         const int64_t r0 = runs[k] ? runs[K + k] : 0, r1 = runs[k] ? runs[2 * K + k] : 0;
@@ -584,15 +581,11 @@ __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __res
         if (group_ids[n] == k) {
             float r = rewards[n];
             if (!isfinite(r)) r = 0.f;
-            const double cw = clipped_weight(s32, s64, n, log_eta);
             cnt += 1.0;
             sum_r += (double)r;
-            sum_wr += cw * (double)r;
-            bits |= generation_status(rewards, s32, s64, n);
-            if (weight) weight[n] = (float)cw;
+            sum_wr += clipped_weight(s32, s64, n, log_eta) * (double)r;
         }
     }
-    if (bits && dev_status) atomicOr(dev_status, bits);
     double sums[3] = {cnt, sum_r, sum_wr};
     block_sums<3>(sums, sm);
     cnt = sums[0]; sum_r = sums[1]; sum_wr = sums[2];
@@ -842,7 +835,8 @@ void launch_group_advantage(const float* rewards, const int32_t* group_ids, cons
                             float* weight, float* gmean, float* gstd, int32_t* gsize, const int32_t* gen_range,
                             int32_t* dev_status, hipStream_t st, float adv_eps, int std_ddof, const int32_t* runs) {
     const double log_eta = (eta > 0.f && std::isfinite(eta)) ? log((double)eta) : (double)INFINITY;
-    group_advantage_kernel<<<(unsigned)K, block_threads(N, 256), 0, st>>>(rewards, group_ids, s32, s64, N, log_eta, baseline_mode, adv,
+    const unsigned threads = block_threads(N, 256);
+    group_advantage_kernel<<<(unsigned)K + blocks_for(N, (int)threads), threads, 0, st>>>(rewards, group_ids, s32, s64, N, log_eta, baseline_mode, adv,
                                                         adv64, weight, gmean, gstd, gsize, gen_range, (double)adv_eps,
                                                         std_ddof, runs, K, dev_status);
 }

@@ -309,3 +309,24 @@ def test_long_sequences_are_compacted_by_several_waves(rb, N, T, p):
     rb.rapid_logprob_fwd(hidden.cuda(), W.cuda(), tokens.cuda(), mask.cuda(), dev_status=status)
     torch.cuda.synchronize()
     assert status.item() == rb.STATUS_BAD_TOKEN
+
+
+@pytest.mark.parametrize("N,K", [(1, 1), (64, 3), (255, 1), (257, 5), (1025, 300)])     # one block of checks and several, a last short one
+def test_generations_without_a_group(rb, N, K):
+    """Group ids out of range at both ends of the batch and in between: advantage 0, their own weight, the status bits."""
+    print(f"generations without a group N {N} K {K}", flush=True)
+    rng = np.random.default_rng(N)
+    R, s = rng.random(N).astype(np.float32), rng.normal(size=N).astype(np.float32)
+    gid = rng.integers(0, K, size=N).astype(np.int32)
+    lost = np.unique([0, N // 2, N - 1])
+    gid[lost] = [-1, K, K + 7][:len(lost)]
+    keep = np.setdiff1d(np.arange(N), lost)
+    status = torch.zeros(1, dtype=torch.int32).cuda()
+    out = rb.rapid_group_advantage(torch.from_numpy(R).cuda(), torch.from_numpy(gid).cuda(), K, seq_logratio=torch.from_numpy(s).cuda(),
+                                   eta=2.0, dev_status=status)
+    torch.cuda.synchronize()
+    ref = orc.group_advantage(R[keep], gid[keep], K, s=s[keep], eta=2.0)
+    assert status.item() == rb.STATUS_BAD_GROUP
+    assert np.array_equal(_np(out["group_size"]), ref["group_size"])
+    assert (_np(out["adv"])[lost] == 0.0).all() and np.allclose(_np(out["adv"])[keep], ref["adv"], atol=2e-6)
+    assert np.allclose(_np(out["weight"]), orc.clipped_weight(s.astype(np.float64), 2.0), rtol=1e-6)
