@@ -28,8 +28,8 @@ def test_fp64_matrix_tiles(rb, d, V, prompts, length, layout, min_ws):
 
 @pytest.mark.parametrize("d,V,prompts,length", [
     (64, 2100, 1, 40),       # one tile of dHidden, its contraction cut into many segments
-    (640, 1300, 5, 60),      # d padded to 768: a few tiles, fewer than workgroups
-    (384, 3000, 2, 30),      # d padded to 384: tiles of 128 x 256
+    (640, 1300, 5, 60),      # a few tiles, fewer than workgroups, none of them ragged in d
+    (384, 3000, 2, 30),      # more tiles along d than rows
     (136, 70, 2, 30),        # a contraction of two steps: nothing to cut
 ])
 @pytest.mark.parametrize("cache", [False, True])
@@ -41,7 +41,7 @@ def test_dhidden_of_few_tiles(rb, d, V, prompts, length, cache):
 
 
 def test_dhidden_pacing_over_whole_rounds(rb):
-    """280 tiles on 256 workgroups: the whole round meets every 4 of its 12 K steps (tuning key 16), the cut last round
+    """280 tiles on 256 workgroups: the whole round meets every 4 of its 9 K steps (tuning key 16), the cut last round
     does not; same bits as unpaced."""
     spec = wl.small_spec("pace_whole", "bf16", d=512, V=520, prompts=35, G=4, len_lo=256, len_hi=256, sigma=0.02, reward="uniform")
     got = []
@@ -56,6 +56,23 @@ def test_dhidden_pacing_over_whole_rounds(rb):
     assert torch.equal(got[0], got[1])
 
 
+def _dw_in_every_form(rb, w, layout, cache):
+    """dW rounded to bf16 and added to what is there, against plain fp32 dW of the same call."""
+    g = {k: (v.cuda() if torch.is_tensor(v) else v) for k, v in w.items()}
+    lay = rb.W_DV if layout == "dv" else rb.W_VD
+    W = g["W"] if layout == "dv" else g["W"].t().contiguous()
+    args = (g["hidden"], W, g["tokens"], g["mask"], None, g["rewards"], g["group_ids"], w["K"])
+    base = rb.rapid_iw_pg_loss_fwd_bwd(*args, w_layout=lay, logits_cache=cache).dW
+    buf = rb.IwPgBuffers(g["hidden"], W, w["K"], lay, dw_dtype=torch.bfloat16, logits_cache=cache)
+    half = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=buf, w_layout=lay, logits_cache=cache).dW
+    assert torch.equal(half, base.to(torch.bfloat16))                       # one rounding of the same sum
+    buf = rb.IwPgBuffers(g["hidden"], W, w["K"], lay, logits_cache=cache)
+    old = torch.randn_like(buf.dW)
+    buf.dW.copy_(old)
+    added = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=buf, w_layout=lay, logits_cache=cache, accumulate_dw=True).dW
+    assert torch.equal(added, old + base)
+
+
 @pytest.mark.parametrize("d,V", [(256, 1024), (264, 1027), (72, 259)])     # whole tiles; rows off 16 bytes and ragged tiles
 @pytest.mark.parametrize("layout", ["dv", "vd"])
 @pytest.mark.parametrize("cache", [False, True])
@@ -68,16 +85,7 @@ def test_dw_leaves_in_every_form(rb, d, V, layout, cache):
         _check_pair(rb, spec, out, ref, layout)
         w, half, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache, min_ws=min_ws, dw_dtype=torch.bfloat16)
         assert torch.equal(half.dW, out.dW.to(torch.bfloat16))              # one rounding of the same sum
-    g = {k: (v.cuda() if torch.is_tensor(v) else v) for k, v in w.items()}
-    lay = rb.W_DV if layout == "dv" else rb.W_VD
-    W = g["W"] if layout == "dv" else g["W"].t().contiguous()
-    args = (g["hidden"], W, g["tokens"], g["mask"], None, g["rewards"], g["group_ids"], w["K"])
-    base = rb.rapid_iw_pg_loss_fwd_bwd(*args, w_layout=lay, logits_cache=cache).dW
-    buf = rb.IwPgBuffers(g["hidden"], W, w["K"], lay, logits_cache=cache)
-    old = torch.randn_like(buf.dW)
-    buf.dW.copy_(old)
-    added = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=buf, w_layout=lay, logits_cache=cache, accumulate_dw=True).dW
-    assert torch.equal(added, old + base)
+    _dw_in_every_form(rb, w, layout, cache)
 
 
 @pytest.mark.parametrize("d,V", [(64, 512), (72, 264), (200, 1000), (328, 776), (8, 8), (136, 1003)])
@@ -164,17 +172,36 @@ def test_nan_weight_is_not_hidden(rb, d, layout, cache):
     assert out.dhidden[g["mask"] != 0].isnan().all() and (out.dhidden[g["mask"] == 0] == 0).all()
 
 
-@pytest.mark.parametrize("d", [136, 192, 200, 384, 448, 568])     # tiles of 192 (one, whole, two, three) and, dHidden, of 224
+@pytest.mark.parametrize("d", [136, 192, 200, 384, 448, 568])     # tiles of 192 (one, whole, two, three) and of 224
 @pytest.mark.parametrize("layout", ["dv", "vd"])
 @pytest.mark.parametrize("packed", [False, True])
 def test_hidden_tiles_of_192_and_224(rb, d, layout, packed):
-    """dHidden and dW in tiles of the hidden dimension that are no power of two, with few tiles (cut) and with the head read
-    in place or, in a batch padded to more positions than that is done for, packed."""
+    """dHidden in tiles of the hidden dimension that are no power of two, with few tiles (cut): the head packed, in a batch
+    padded to more positions than it is read in place for; read in place (short contractions: tiles of 128 instead)."""
     print(f"hidden tiles d {d} {layout} packed {packed}", flush=True)
     spec = wl.small_spec("tiles", "bf16", d=d, V=520, prompts=8, G=5, len_lo=10, len_hi=420 if packed else 40, reward="uniform")
     for cache in (False, True):
         w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
         _check_pair(rb, spec, out, ref, layout)
+
+
+# Past the bounds of the tiles of 128 x 128: more than 4096 row tiles x K steps for dHidden (9 row tiles of positions, few
+# of them tokens; the head read in place), more than 128 tiles for dW.
+@pytest.mark.parametrize("d,V", [
+    (128, 33000), (256, 33000),     # tiles of 128 and of 256
+    (136, 33000), (192, 33000),     # one tile of 192, ragged and whole
+    (576, 11104),                   # three of 192
+    (200, 33000), (448, 16704),     # dHidden one and two tiles of 224, dW of 256
+])
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+def test_hidden_tiles_of_long_contractions(rb, d, V, layout):
+    cache = layout == "vd"
+    print(f"hidden tiles, long contractions d {d} V {V} {layout}", flush=True)
+    spec = wl.small_spec("long", "bf16", d=d, V=V, prompts=3, G=3, len_lo=8, len_hi=256, reward="uniform")
+    assert -(-d // 256) * 9 * -(-V // 64) > 4096 and -(-d // 256) * -(-V // 256) > 128
+    w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache)
+    _check_pair(rb, spec, out, ref, layout)
+    _dw_in_every_form(rb, w, layout, cache)
 
 
 @pytest.mark.parametrize("rows", [1, 64, 65, 192, 193, 257, 300, 1030])    # tokens of the last row tile: one to all waves' shares
