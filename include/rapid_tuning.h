@@ -1,7 +1,7 @@
 /*
  * rapid_tuning.h -- benchmark and tuning hooks of librapid_hip.so.  NOT part of the product ABI in
  * rapid.h: nothing here is needed to compute anything, the results of every call in rapid.h are the
- * same whatever is set here (up to the fp32 rounding noted at keys 17 and 20), and two of the calls below
+ * same whatever is set here (up to the fp32 rounding noted at keys 2, 15, 17, 19 and 20), and two of the calls below
  * wait for the device, which no call in rapid.h ever does.  bench.py and the tests of the kernels'
  * launch geometries use them.
  */
@@ -19,8 +19,11 @@ extern "C" {
  * key 1: per-stage event timing on (1) / off (0, default); see rapid_profile_read.
  * key 2: waves per workgroup of the contraction kernels: 0 (default) = each kernel's own choice (8,
  *        i.e. 2 x 4 waves of 128 x 64, for the logits kernels and dW; 4, i.e. 2 x 2 waves of 128 x 128,
- *        for dHidden), or 4 / 8 / 16 for all of them.  Same 256 x 256 tile and same results either way.  A value other than 0
- *        also makes them read W from its packed copies always, not in place as a small batch otherwise does.
+ *        for dHidden), or 4 / 8 / 16 for all of them.  A value other than 0 also leaves out what the default adds to
+ *        that geometry: tiles of 192, 224 and (where there is little to contract) 128 x 128 in dHidden and dW, and
+ *        reading W in place, which a small batch otherwise does instead of packing copies.  Log-probs are identical
+ *        with 8 and 16; the sums of dHidden and dW are taken in another order: they differ by the fp32 rounding of the
+ *        accumulators.  Workspace sizes follow the tiles: set it before asking for them.
  * keys 10, 11, 12: tile-order blocking (tiles along the first tile dimension that share one tile of
  *        the second before the order moves on) of the logits kernels, the dHidden kernel (0 = all)
  *        and the dW kernel; defaults 4, 0, 2 were measured best on MI355X.  Results are identical.
@@ -38,10 +41,11 @@ extern "C" {
  *        for a bounded time, for the others, so that all XCDs sweep W together and share it through
  *        the memory-side cache.  A timing hint only: results are identical, and a meeting that runs
  *        out of time switches the pacing off for the rest of the launch.
- * key 17: 1 (default) / 0: the dHidden kernel cuts the contraction of the tiles of a partly filled last round of
- *        workgroups into equal segments and deals the (tile, segment) units out in short rounds (the pieces of a
+ * key 17: 1 (default) / 0: the dHidden and dW kernels cut the contraction of the tiles of a partly filled last round
+ *        of workgroups into equal segments and deal the (segment, tile) units out (the pieces of a
  *        tile are summed in a fixed order by a small second kernel), instead of leaving workgroups idle for a
- *        whole tile.  The sums are taken in another order: results differ by fp32 rounding of the accumulators.
+ *        whole tile; 0 also turns the 128 x 128 tiles of short contractions off, which rely on it.  The sums are taken
+ *        in another order: results differ by fp32 rounding of the accumulators.
  * key 18: cache rows (a multiple of 256, default 90112) of the size rapid_workspace_bytes recommends for
  *        RAPID_OP_IW_PG_FWD_BWD_CACHED.  A call uses whatever its workspace affords; this only moves the
  *        recommendation.
@@ -57,7 +61,9 @@ extern "C" {
  *        workgroup per CU on 256 x 256 tiles, four stages, requests three steps ahead; 3 = the same with 4 waves
  *        of 128 x 128.  Identical results; measured slower or equal, kept for those measurements.
  * key 22: 0 (default) / 1: the dW kernel with K steps of 32 rows through four LDS stages, requests three steps
- *        ahead.  Identical results; measured 2 % slower, kept for that measurement. */
+ *        ahead, on a [d, V] head where dW runs in tiles of 256 x 256 or 256 x 128 by 8 waves (with key 2 = 8 always;
+ *        by default not in tiles of 192 and not in the 128 x 128 ones).  Identical results; measured 2 % slower,
+ *        kept for that measurement. */
 int rapid_set_tuning(int key, int value);
 
 /* Per-stage timing for benchmarks.  rapid_set_tuning(1, 1) makes every later call bracket each of
