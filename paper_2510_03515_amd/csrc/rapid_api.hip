@@ -364,8 +364,7 @@ struct FwdIo {
     const void* hidden; const void* W; const int32_t* tokens; const uint8_t* mask;
     int w_layout; float temperature;
     float* logp_out; float* lse_out; int32_t* dev_status;
-    bf16_t* zc = nullptr;   // if set: [row_cap, ldv], the forward also stores the ratios p_v / p_y there
-    int64_t row_cap = INT64_MAX;   // compact rows the caller's buffers hold (the cache may be sized for fewer than N*T)
+    bf16_t* zc = nullptr;   // if set: [rows, ldv], the forward also stores exp(logit - reference) there
     const float* ref_logp = nullptr;    // with zc: the behaviour log-probs, for the reference of the stored values
     const void* rms_weight = nullptr;   // if set (bf16 only): hidden is normalised while it is packed
     float rms_eps = 0.f;
@@ -497,11 +496,9 @@ void run_forward(const Plan& p, void* ws, const FwdIo& io, hipStream_t st) {
         plan.idle = io.idle;
         plan.runs = io.runs;
         if (io.idle.idle) {
-            plan.Rcap = io.row_cap < p.Mmax_pad ? io.row_cap : p.Mmax_pad;
+            plan.Rcap = p.Mmax_pad;
             plan.tab = at<int32_t>(ws, p.tab);
             plan.Cmax = 1;
-        } else {
-            plan.Rcap = io.row_cap;
         }
         launch_compaction(io.mask, p.N, p.T, plan, io.logp_out, io.lse_out, row_index, RowTokens{io.tokens, p.V, tokc, seqc}, st);
     }

@@ -49,8 +49,8 @@ struct IdleArgs {
     int32_t* live_group = nullptr;         // scratch [K]
 };
 // What the plan of a batch is made from and what it fills in (see plan_kernel).  cu [N + 1]: prefix sum of seq_len [N].
-// tab NULL: one region; counts (optional) = M and M rounded up to a row tile, both clipped to Rcap (sets
-// RAPID_STATUS_TOKEN_BOUND).  With tab the generations are dealt to at most Cmax chunks of at most Rcap compact rows
+// tab NULL: one region; counts (optional) = M and M rounded up to a row tile.
+// With tab the generations are dealt to at most Cmax chunks of at most Rcap compact rows
 // each, whole groups (maximal runs of equal group id) at a time, in order, each chunk as full as it gets; chunk c's
 // rows start at compact row c * Rcap.  Writes the chunk table `tab` [Cmax][CH_WORDS], gen_row0 [N]
 // (compact row of each generation's first token, -1 for a generation that was left out),
@@ -64,7 +64,7 @@ struct PlanArgs {
     int64_t N = 0, K = 0;
     const int32_t* gid = nullptr;
     int32_t *seq_len = nullptr, *cu = nullptr, *counts = nullptr;
-    int64_t Rcap = INT64_MAX;
+    int64_t Rcap = 0;     // with tab
     int32_t* tab = nullptr;
     int Cmax = 0;
     int32_t *gen_row0 = nullptr, *gen_chunk = nullptr, *gseen = nullptr, *runs = nullptr;

@@ -227,16 +227,9 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     if (a.idle.idle) block_scan(a.idle.len_live, N, a.idle.cu_live);
     if (threadIdx.x == 0 && a.lam_state) a.lam_state[0] = -INFINITY;
     if (!a.tab) {
-        // The counters never exceed row_cap (the rows the caller's buffers hold): tokens past it are left
-        // out of everything downstream and RAPID_STATUS_TOKEN_BOUND is set.
         if (threadIdx.x == 0 && a.counts) {
-            int m = (int)total;
-            if (total > a.Rcap) {
-                m = (int)a.Rcap;
-                if (a.dev_status) atomicOr(a.dev_status, RAPID_STATUS_TOKEN_BOUND);
-            }
-            a.counts[CNT_M] = m;
-            a.counts[CNT_MR] = (m + ROW_TILE - 1) / ROW_TILE * ROW_TILE;
+            a.counts[CNT_M] = (int32_t)total;
+            a.counts[CNT_MR] = (int32_t)((total + ROW_TILE - 1) / ROW_TILE * ROW_TILE);
         }
         return;
     }
