@@ -6,7 +6,8 @@
 //   dw      : dW (+)= H^T . dz       (contraction over the tokens of a row chunk)
 //
 // Tiling.  C[i][j] = sum_k A(i,k) B(j,k); operands are zero padded to whole tiles, so the loop has
-// no bounds checks.  A workgroup of NWI x NWJ 64-lane waves owns a 256 x 256 tile (the largest whose
+// no bounds checks, but for W read in place (a small batch), whose addresses are clamped to the matrix (see
+// Loader).  A workgroup of NWI x NWJ 64-lane waves owns a 256 x 256 tile (the largest whose
 // fp32 accumulators a CU's registers hold, which minimises L2 -> LDS bytes per flop), each wave
 // WI x WJ blocks of 32 x 32 computed with v_mfma_f32_32x32x16_bf16 (a lane feeds 8 consecutive k of
 // one row).  The default is 2 x 4 waves of 128 x 64, two waves per SIMD.  K advances 64 elements
@@ -21,8 +22,8 @@
 //  * row-major operands ([row][k], k contiguous): a tile row of a step is 128 bytes = 8 chunks of
 //    16 bytes; chunk c of row r sits at position c ^ ((r >> 1) & 7); fragments are read with
 //    ds_read_b128.
-//  * k-major operands ([k][column], used by dW where the contraction index is the token row): see
-//    the comment above KMajor below; fragments are read with the LDS transpose read.
+//  * k-major operands ([k][column]; both of dW, whose contraction index is the token row, and W in place where
+//    its other index is the contiguous one): see the comment above KMajor below; fragments are read with the LDS transpose read.
 //
 // Accumulator layout of a 32 x 32 block (lane l, register v): j = l % 32,
 // i = 8 (v / 4) + 4 (l / 32) + v % 4: a lane owns runs of 4 consecutive i for one j, so every
@@ -831,8 +832,9 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     auto opW = [&](const TileId& t) { return logits_w<S, WM>(a.w, a.Wvd, a.ldk, t.ti); };
     auto opH = [&](const TileId& t) { return Operand{a.Hc + (a.row0 + (int64_t)t.tj * S::BJ) * a.ldk, a.ldk, 128}; };
     // The next tile's first step is on its way while this tile's epilogue runs (in stage 1, if its waves' regions fit): a
-    // trip to memory per tile of a few dozen steps.  Worth 1 % of a step at d = 896 (53.4 -> 52.8 ms) and 1 to 2 % at
-    // d = 1536 (333 -> 327 ms); the chip is near its power limit there.
+    // trip to memory per tile of d / 64 steps.  The kernel's time without and with it, three runs of each in turn: d = 256
+    // 573-580 -> 553-558 us, 290 tokens at d = 1536 180 -> 176 us, d = 896 18.56 -> 18.39 ms, d = 1536 28.26 -> 28.12 ms (the chip is near
+    // its power limit there); a whole step changes by less than its spread.
     // In-place reads with a store have no registers left for it (11 spilled; small head's forward 15.5 -> 17.6 us).
     constexpr bool AHEAD = !STORE || (WM == W_PACKED && S::NW * (32 * 256) <= S::STAGE_BYTES);
     TileId t = tile(0);

@@ -1,6 +1,6 @@
-// Operand packing for the MFMA kernels: every contraction reads zero-padded, tile-aligned bf16
-// matrices whose contraction index is contiguous, so the hot loops need no bounds checks.  These
-// kernels are pure HBM copies (read once, write once).
+// Operand packing for the MFMA kernels: zero-padded, tile-aligned bf16 copies of the hidden rows and, unless the batch is
+// small enough to read it in place, of W with its contraction index contiguous, so that the hot loops need no bounds
+// checks.  These kernels are pure HBM copies (read once, write once).
 #include "rapid_internal.h"
 
 namespace rapid {
