@@ -116,6 +116,7 @@ struct Plan {
     int64_t Rcap;
     int Cmax;
     bool two_wg;        // the forward runs two workgroups per CU and reads W from its K-blocked copy (Wvd32)
+    bool default_waves; // tuning key 2 as this call found it
     int64_t ld_part;    // columns of the log-sum-exp partials
     int64_t rms_blocks; // row blocks of the final norm's dweight partial sums
     size_t per_row;     // chunk bytes per row
@@ -171,7 +172,8 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
     p.ld_part = Cmax > 0 ? Rcap : p.Mmax_pad;
     if (p.Mmax_pad > (int64_t)2100000000) return false;   // compact row indices are int32
     p.dpad = round_up(d, K_TILE);
-    const bool any_width = op == RAPID_OP_IW_PG_FWD_BWD && default_waves();
+    p.default_waves = default_waves();
+    const bool any_width = op == RAPID_OP_IW_PG_FWD_BWD && p.default_waves;
     p.dh = hidden_tile(d, any_width ? TILES_DH : TILES_256_128);
     p.dw = hidden_tile(d, any_width ? TILES_DW : TILES_256_128);
     p.hpad = p.dw.padded > p.dpad ? p.dw.padded : p.dpad;
@@ -388,13 +390,14 @@ PlanArgs plan_args(const Plan& p, void* ws, const int32_t* group_ids, int32_t* d
 // with 13 000 to 300 000 tokens, the logits kernels lose 0.5 % on a [V, d] head (its rows are the operand's) and 3 % on
 // a [d, V] head (read k-major; and the sampled tokens' logits gather columns), dHidden 2 % on [d, V] (rows far apart instead
 // of the copy's blocks) and 7 % on [V, d] (k-major).  The bounds are about where the two sides meet if half of the
-// N * T positions hold tokens.  (About 2100 rows: step 4.75 -> 4.45 ms at d = 1536; 290 rows, forward only: 432 -> 280 us.)
+// N * T positions hold tokens.  The packing passes and the readers all ask here, so the answer hangs on the call's plan
+// and arguments alone.  (About 2100 rows: step 4.75 -> 4.45 ms at d = 1536; 290 rows, forward only: 432 -> 280 us.)
 enum WReader { W_FOR_LOGITS, W_FOR_DHIDDEN };
 WInPlace w_in_place(const Plan& p, const void* W, int w_layout, WReader reader) {
     WInPlace w{(const bf16_t*)W, p.d, p.V, W_PACKED};
     const bool vd = w_layout == RAPID_W_VD;
     // whole 16-byte chunks of a row have to exist (d % 8 == 0 holds for every bf16 call)
-    if (p.two_wg || !default_waves() || (!vd && p.V % 8 != 0)) return w;
+    if (p.two_wg || !p.default_waves || (!vd && p.V % 8 != 0)) return w;
     const int64_t most = reader == W_FOR_LOGITS ? (vd ? 131072 : 16384) : (vd ? 12288 : 16384);
     if (p.Mmax <= most) w.mode = vd ? W_VD : W_DV;
     return w;
