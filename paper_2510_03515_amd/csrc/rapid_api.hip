@@ -414,14 +414,13 @@ void pack_w_for_logits(const Plan& p, void* ws, const void* W, int w_layout, hip
     if (p.two_wg) launch_block_w32(Wvd, p.ldk, at<bf16_t>(ws, p.Wvd32), p.Vpad, p.dpad, st);
 }
 
-// packs W as [dh.padded, Vpad], in tile blocks or row-major (tuning key 14) (the operand of dHidden)
-void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, hipStream_t st) {
+// packs W as [dh.padded, Vpad], in tile blocks or row-major (tuning key 14): the operand of dHidden
+void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, bool blocked, hipStream_t st) {
     if (w_in_place(p, W, w_layout, W_FOR_DHIDDEN).mode != W_PACKED) return;
     bf16_t* Wdv = at<bf16_t>(ws, p.Wdv);
     bf16_t* WdvB = at<bf16_t>(ws, p.WdvB);
     const int RB = p.dh.tile;
     const int64_t dpadR = p.dh.padded;
-    const bool blocked = g_blocked_wdv.load() != 0;
     if (w_layout == RAPID_W_DV) {
         if (blocked) launch_block_rows_bf16((const bf16_t*)W, p.V, WdvB, p.d, p.V, dpadR, p.Vpad, RB, st);
         else launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, dpadR, p.Vpad, nullptr, 0, st);
@@ -1078,7 +1077,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         {
             Span sp(ST_PACK, st);
             pack_w_for_logits(p, ws, W, o.w_layout, st);
-            pack_w_for_dhidden(p, ws, W, o.w_layout, st);
+            pack_w_for_dhidden(p, ws, W, o.w_layout, blocked_wdv, st);
         }
         {
             Span sp(ST_ZERO, st);
@@ -1239,7 +1238,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         const bool blocked_wdv = g_blocked_wdv.load() != 0;
         {
             Span sp(ST_PACK, st);
-            pack_w_for_dhidden(p, ws, W, o.w_layout, st);
+            pack_w_for_dhidden(p, ws, W, o.w_layout, blocked_wdv, st);
         }
         const int64_t step = p.Mc;
         int chunk = 0;
