@@ -154,9 +154,11 @@ size_t take(size_t& cur, size_t bytes) {
 }
 
 // lays the workspace out; chunk sizing is done by the caller through `avail`.  Cmax > 0: the layout of the
-// cached backward with Cmax regions of Rcap rows (bf16, RAPID_OP_IW_PG_FWD_BWD only).
+// cached backward with Cmax regions of Rcap rows (bf16, RAPID_OP_IW_PG_FWD_BWD only).  any_tile false: tiles of the
+// hidden dimension of 256 or 128 only, for a workspace that is too small for the others (for some d, 640 or 1040 for
+// instance, the fastest tiles pad further: up to 5 % more bytes at least).
 bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int dtype, int64_t Rcap = 0,
-               int Cmax = 0) {
+               int Cmax = 0, bool any_tile = true) {
     memset(&p, 0, sizeof(p));
     if (N <= 0 || T <= 0 || d <= 0 || V <= 0) return false;
     if (dtype != RAPID_DTYPE_F32 && dtype != RAPID_DTYPE_BF16) return false;
@@ -173,7 +175,7 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
     if (p.Mmax_pad > (int64_t)2100000000) return false;   // compact row indices are int32
     p.dpad = round_up(d, K_TILE);
     p.default_waves = default_waves();
-    const bool any_width = op == RAPID_OP_IW_PG_FWD_BWD && p.default_waves;
+    const bool any_width = any_tile && op == RAPID_OP_IW_PG_FWD_BWD && p.default_waves;
     p.dh = hidden_tile(d, any_width ? TILES_DH : TILES_256_128);
     p.dw = hidden_tile(d, any_width ? TILES_DW : TILES_256_128);
     p.hpad = p.dw.padded > p.dpad ? p.dw.padded : p.dpad;
@@ -292,10 +294,11 @@ int cached_chunks(int64_t rows, int64_t Rcap) { return Rcap >= rows ? 1 : (int)(
 std::atomic<int> g_cached_rcap{90112};
 
 // workspace bytes of the cached backward with a cache of Rcap rows for a batch of at most `rows` tokens; 0 if invalid
-size_t cached_total(int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int64_t rows, int64_t Rcap, Plan* out = nullptr) {
+size_t cached_total(int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int64_t rows, int64_t Rcap, Plan* out = nullptr,
+                    bool any_tile = true) {
     Plan p;
     if (Rcap > rows) Rcap = rows;
-    if (!make_plan(p, RAPID_OP_IW_PG_FWD_BWD, N, T, d, V, K, RAPID_DTYPE_BF16, Rcap, cached_chunks(rows, Rcap))) return 0;
+    if (!make_plan(p, RAPID_OP_IW_PG_FWD_BWD, N, T, d, V, K, RAPID_DTYPE_BF16, Rcap, cached_chunks(rows, Rcap), any_tile)) return 0;
     size_chunks(p, Rcap);
     if (out) *out = p;
     return p.total + 1024;
@@ -303,18 +306,20 @@ size_t cached_total(int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int64
 
 // Cache rows a call with this workspace works with: every row of the batch if that fits (one chunk), otherwise the
 // largest window that does; 0 if not even one row tile fits.  Fills `out` with the plan of that geometry.
-int64_t choose_cache(int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int64_t rows, size_t workspace_bytes, Plan* out) {
-    size_t need = cached_total(N, T, d, V, K, rows, rows, out);
+int64_t choose_cache(int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int64_t rows, size_t workspace_bytes, Plan* out,
+                     bool any_tile = true) {
+    size_t need = cached_total(N, T, d, V, K, rows, rows, out, any_tile);
     if (need != 0 && need <= workspace_bytes) return rows;
     int64_t lo = 1, hi = rows / ROW_TILE - 1, best = 0;     // cache rows in row tiles
     while (lo <= hi) {
         const int64_t mid = (lo + hi) / 2;
-        need = cached_total(N, T, d, V, K, rows, mid * ROW_TILE);
+        need = cached_total(N, T, d, V, K, rows, mid * ROW_TILE, nullptr, any_tile);
         if (need != 0 && need <= workspace_bytes) { best = mid; lo = mid + 1; } else { hi = mid - 1; }
     }
     // the size is not monotone everywhere (the number of regions steps down as the cache grows)
-    while (best > 0 && ((need = cached_total(N, T, d, V, K, rows, best * ROW_TILE, out)) == 0 || need > workspace_bytes))
+    while (best > 0 && ((need = cached_total(N, T, d, V, K, rows, best * ROW_TILE, out, any_tile)) == 0 || need > workspace_bytes))
         --best;
+    if (best == 0 && any_tile) return choose_cache(N, T, d, V, K, rows, workspace_bytes, out, false);
     return best * ROW_TILE;
 }
 
@@ -823,14 +828,21 @@ size_t rapid_workspace_bytes(int op, int64_t N, int64_t T, int64_t d, int64_t V,
 size_t rapid_workspace_min_bytes(int op, int64_t N, int64_t T, int64_t d, int64_t V, int64_t K, int dtype) {
     if (op == RAPID_OP_GROUP_ADVANTAGE) return 0;
     Plan p;
-    if (op == RAPID_OP_IW_PG_FWD_BWD_CACHED) {   // a cache of one row tile (every group must fit into it)
-        if (dtype != RAPID_DTYPE_BF16 || !make_plan(p, RAPID_OP_IW_PG_FWD_BWD, N, T, d, V, K, dtype)) return 0;
-        return cached_total(N, T, d, V, K, p.Mmax_pad, ROW_TILE);
+    size_t least = 0;
+    for (const bool any_tile : {true, false}) {
+        size_t need;
+        if (op == RAPID_OP_IW_PG_FWD_BWD_CACHED) {   // a cache of one row tile (every group must fit into it)
+            if (dtype != RAPID_DTYPE_BF16 || !make_plan(p, RAPID_OP_IW_PG_FWD_BWD, N, T, d, V, K, dtype)) return 0;
+            need = cached_total(N, T, d, V, K, p.Mmax_pad, ROW_TILE, nullptr, any_tile);
+        } else {
+            if (op != RAPID_OP_LOGPROB_FWD && op != RAPID_OP_IW_PG_FWD_BWD) return 0;
+            if (!make_plan(p, op, N, T, d, V, K, dtype, 0, 0, any_tile)) return 0;
+            size_chunks(p, ROW_TILE);
+            need = p.total + 1024;
+        }
+        if (least == 0 || need < least) least = need;
     }
-    if (op != RAPID_OP_LOGPROB_FWD && op != RAPID_OP_IW_PG_FWD_BWD) return 0;
-    if (!make_plan(p, op, N, T, d, V, K, dtype)) return 0;
-    size_chunks(p, ROW_TILE);
-    return p.total + 1024;
+    return least;
 }
 
 int rapid_compaction(const uint8_t* mask, int64_t N, int64_t T, int32_t* seq_len_out, int32_t* cu_seqlen_out,
@@ -984,7 +996,9 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             return RAPID_ERR_WORKSPACE;
         }
     } else {
-        const int64_t Mfit = fit_chunk(p, workspace_bytes);
+        int64_t Mfit = fit_chunk(p, workspace_bytes);
+        if (Mfit < ROW_TILE && make_plan(p, RAPID_OP_IW_PG_FWD_BWD, N, T, d, V, K, dtype, 0, 0, false))
+            Mfit = fit_chunk(p, workspace_bytes);
         if (Mfit < ROW_TILE) {
             set_error("workspace of %zu bytes is below the minimum %zu", workspace_bytes,
                       rapid_workspace_min_bytes(RAPID_OP_IW_PG_FWD_BWD, N, T, d, V, K, dtype));

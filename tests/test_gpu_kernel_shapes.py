@@ -357,3 +357,13 @@ def test_generations_without_a_group(rb, N, K):
     assert np.array_equal(_np(out["group_size"]), ref["group_size"])
     assert (_np(out["adv"])[lost] == 0.0).all() and np.allclose(_np(out["adv"])[keep], ref["adv"], atol=2e-6)
     assert np.allclose(_np(out["weight"]), orc.clipped_weight(s.astype(np.float64), 2.0), rtol=1e-6)
+
+
+@pytest.mark.parametrize("d", [640, 1040])      # their fastest tiles pad further than the smallest workspace has room for
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("cache", [False, True])
+def test_smallest_workspace_has_room_for_other_tiles_only(rb, d, layout, cache):
+    print(f"smallest workspace d {d} {layout} cache {cache}", flush=True)
+    spec = wl.small_spec("min_ws", "bf16", d=d, V=1500, prompts=6, G=4, len_lo=20, len_hi=60, reward="uniform")
+    w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache, min_ws=True)
+    _check_pair(rb, spec, out, ref, layout)

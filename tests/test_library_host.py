@@ -229,3 +229,19 @@ def test_header_is_plain_c_and_links(tmp_path):
     assert r.returncode == 0, r.stderr
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.split()[0] == str(len(names))
+
+
+@pytest.mark.parametrize("V", [1000, 151936])
+def test_minimum_workspace_does_not_grow_with_the_tiles(rb, V):
+    """Where the fastest tiles of the hidden dimension pad further than tiles of 256 and 128 do (d = 584 .. 640, 776 .. 872, ..),
+    the smallest workspace is still that of the latter (tuning key 2 = 8 allows only those)."""
+    sizes = {}
+    try:
+        for waves in (0, 8):
+            rb.rapid_set_tuning(2, waves)
+            sizes[waves] = {(op, d): rb.rapid_workspace_bytes(op, 32, 256, d, V, 8, rb.DTYPE_BF16, minimum=True)
+                            for op in (rb.OP_LOGPROB_FWD, rb.OP_IW_PG_FWD_BWD, rb.OP_IW_PG_FWD_BWD_CACHED) for d in range(8, 2049, 8)}
+    finally:
+        rb.rapid_set_tuning(2, 0)
+    assert all(0 < sizes[0][k] <= sizes[8][k] for k in sizes[0])
+    assert any(sizes[0][k] < sizes[8][k] for k in sizes[0])
