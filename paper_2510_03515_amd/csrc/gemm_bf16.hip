@@ -1431,49 +1431,6 @@ __global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_
         out.put(off + q * 8, left - q * 8, cur[q], f32x4u{sum[q * 4], sum[q * 4 + 1], sum[q * 4 + 2], sum[q * 4 + 3]});
 }
 
-// Logit of the sampled token: zy[j] = inv_temp * <Hc[j, :], W[tok_j, :]>, one wave per token row
-// (16-byte loads, fp32 accumulation, fixed reduction tree).  W has a token's weights in a row, or (GATHER) in a
-// column: 64 bytes are then read for each, which a small batch can afford; the sum is formed in the same order.
-// If refz is given it receives the reference of the storing forward: zy[j] - ref_logp[row_index[j]]
-// (zy[j] alone without ref_logp or where that value is not finite).
-template <bool GATHER>
-__global__ __launch_bounds__(256) void token_logit_kernel(const bf16_t* __restrict__ Hc, int64_t ldk, const bf16_t* __restrict__ W,
-                                                          int64_t ldw, int64_t d, const int32_t* __restrict__ tokc,
-                                                          const int32_t* __restrict__ counts, float inv_temp,
-                                                          float* __restrict__ zy, const float* __restrict__ ref_logp,
-                                                          const int32_t* __restrict__ row_index,
-                                                          float* __restrict__ refz, int64_t row0) {
-    const int64_t j = row0 + (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= counts[CNT_M]) return;
-    const int lane = threadIdx.x & 63;
-    const bf16x8* h = (const bf16x8*)(Hc + j * ldk);
-    const bf16_t* w = W + (GATHER ? (int64_t)tokc[j] : (int64_t)tokc[j] * ldw);
-    float acc = 0.f;
-    for (int64_t c = lane; c < d / 8; c += 64) {
-        const bf16x8 hv = h[c];
-        bf16x8 wv;
-        if (GATHER) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) wv[e] = __builtin_bit_cast(__bf16, w[(c * 8 + e) * ldw]);
-        } else {
-            wv = ((const bf16x8*)w)[c];
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc = fmaf((float)hv[e], (float)wv[e], acc);
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if (lane == 0) {
-        const float z = acc * inv_temp;
-        zy[j] = z;
-        if (refz) {
-            float lb = ref_logp ? ref_logp[row_index[j]] : 0.f;
-            if (!isfinite(lb)) lb = 0.f;
-            refz[j] = z - lb;
-        }
-    }
-}
-
 // dz[row][tok_row] += g: the one-hot part of dz = g (onehot - p)
 __global__ void token_onehot_kernel(bf16_t* __restrict__ dz, int64_t ldz, int64_t m0, int64_t rows,
                                     const int32_t* __restrict__ tokc, const float* __restrict__ rowg, float inv_temp,
@@ -1670,18 +1627,6 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
     if (w == 16) launch_fwd_lse_t<G16, W_PACKED>(a, st);
     else if (w == 8) launch_fwd_lse_t<G8, W_PACKED>(a, st);
     else launch_fwd_lse_t<G4, W_PACKED>(a, st);
-}
-void launch_token_logit(const FwdArgs& a, int64_t row0, int64_t rows_max, hipStream_t st) {
-    if (rows_max <= 0) return;
-    const unsigned blocks = (unsigned)((rows_max + 3) / 4);
-    float* refz = a.zc ? a.refz : nullptr;
-    if (a.w.mode == W_DV)
-        token_logit_kernel<true><<<blocks, 256, 0, st>>>(a.Hc, a.ldk, a.w.W, a.w.V, a.w.d, a.tokc, a.counts, a.inv_temp, a.zy,
-                                                         a.ref_logp, a.row_index, refz, row0);
-    else
-        token_logit_kernel<false><<<blocks, 256, 0, st>>>(a.Hc, a.ldk, a.w.mode == W_VD ? a.w.W : a.Wvd, a.w.mode == W_VD ? a.w.d : a.ldk,
-                                                          a.w.d, a.tokc, a.counts, a.inv_temp, a.zy, a.ref_logp, a.row_index,
-                                                          refz, row0);
 }
 int fwd_slots_per_tile() { return 2; }
 

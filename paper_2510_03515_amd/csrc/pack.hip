@@ -1,5 +1,5 @@
-// Operand packing for the MFMA kernels: zero-padded, tile-aligned bf16 copies of the hidden rows and, unless the batch is
-// small enough to read it in place, of W with its contraction index contiguous, so that the hot loops need no bounds
+// Operand packing for the MFMA kernels (hidden rows: rows.hip): zero-padded, tile-aligned bf16 copies of W, unless the batch is
+// small enough to read it in place, with its contraction index contiguous, so that the hot loops need no bounds
 // checks.  These kernels are pure HBM copies (read once, write once).
 #include "rapid_internal.h"
 
@@ -7,32 +7,14 @@ namespace rapid {
 
 namespace {
 
-struct RowLimits { int64_t R, Rpad; };
-
-__device__ inline RowLimits row_limits(const int32_t* counts, int64_t r0, int64_t R, int64_t Rpad) {
-    if (!counts) return {R, Rpad};
-    int64_t m = (int64_t)counts[CNT_M] - r0, mr = (int64_t)counts[CNT_MR] - r0;
-    m = m < 0 ? 0 : (m > R ? R : m);
-    mr = mr < 0 ? 0 : (mr > Rpad ? Rpad : mr);
-    return {m, mr};
-}
-
 // one block per destination row; 16-byte chunks (ld_dst, Cpad multiples of 8; src rows 16 B aligned
 // when C % 8 == 0, otherwise the element path is taken)
-__global__ void copy_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_src,
-                                     const int32_t* __restrict__ row_index, bf16_t* __restrict__ dst,
-                                     int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad,
-                                     const int32_t* __restrict__ counts, int64_t r0, int vec_ok) {
-    const RowLimits lim = row_limits(counts, r0, R, Rpad);
+__global__ void copy_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_src, bf16_t* __restrict__ dst,
+                                     int64_t ld_dst, int64_t R, int64_t C, int64_t Cpad, int vec_ok) {
     const int64_t r = blockIdx.x;
-    if (r >= lim.Rpad) return;
     bf16_t* drow = dst + r * ld_dst;
-    const bool live = r < lim.R;
-    const bf16_t* srow = nullptr;
-    if (live) {
-        const int64_t sr = row_index ? (int64_t)row_index[r0 + r] : r;
-        srow = src + sr * ld_src;
-    }
+    const bool live = r < R;
+    const bf16_t* srow = src + (live ? r : 0) * ld_src;
     if (vec_ok) {
         const int64_t chunks = Cpad / 8, live_chunks = C / 8;
         for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) {
@@ -53,12 +35,9 @@ __global__ void copy_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_
 // is conflict free.
 __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t ld_src,
                                                                  bf16_t* __restrict__ dst, int64_t ld_dst, int64_t R,
-                                                                 int64_t C, int64_t Rpad, int64_t Cpad,
-                                                                 const int32_t* __restrict__ counts, int64_t r0, int vec, int RB) {
+                                                                 int64_t C, int64_t Rpad, int64_t Cpad, int vec, int RB) {
     __shared__ bf16_t tile[64][66];
-    const RowLimits lim = row_limits(counts, r0, R, Rpad);
     const int64_t rb = (int64_t)blockIdx.x * 64, cb = (int64_t)blockIdx.y * 64;
-    if (rb >= lim.Rpad) return;
     auto at = [&](int64_t c, int64_t r) {
         return RB ? dst + (c / RB * (Rpad / 64) + r / 64) * (RB * 64) + c % RB * 64 + r % 64 : dst + c * ld_dst + r;
     };
@@ -67,9 +46,9 @@ __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* _
             const int rr = t >> 3, q = t & 7;
             const int64_t r = rb + rr, c = cb + q * 8;
             uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (r < lim.R && c + 8 <= C) {
+            if (r < R && c + 8 <= C) {
                 v = *(const uint4*)(src + r * ld_src + c);
-            } else if (r < lim.R && c < C) {
+            } else if (r < R && c < C) {
                 bf16_t e[8];
                 for (int i = 0; i < 8; ++i) e[i] = c + i < C ? src[r * ld_src + c + i] : (bf16_t)0;
                 v = *(const uint4*)e;
@@ -81,14 +60,14 @@ __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* _
         for (int t = threadIdx.x; t < 512; t += 256) {          // 64 destination rows x 8 chunks of 8
             const int cc = t >> 3, q = t & 7;
             const int64_t c = cb + cc, r = rb + q * 8;
-            if (c >= Cpad || r >= lim.Rpad) continue;
+            if (c >= Cpad || r >= Rpad) continue;
             bf16_t e[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) e[i] = tile[q * 8 + i][cc];
-            if (r + 8 <= lim.Rpad) {
+            if (r + 8 <= Rpad) {
                 *(uint4*)at(c, r) = *(const uint4*)e;
             } else {
-                for (int i = 0; i < 8 && r + i < lim.Rpad; ++i) *at(c, r + i) = e[i];
+                for (int i = 0; i < 8 && r + i < Rpad; ++i) *at(c, r + i) = e[i];
             }
         }
         return;
@@ -97,25 +76,23 @@ __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* _
     for (int rr = ty; rr < 64; rr += 4) {
         const int64_t r = rb + rr, c = cb + tx;
         bf16_t v = 0;
-        if (r < lim.R && c < C) v = src[r * ld_src + c];
+        if (r < R && c < C) v = src[r * ld_src + c];
         tile[rr][tx] = v;
     }
     __syncthreads();
     for (int cc = ty; cc < 64; cc += 4) {
         const int64_t c = cb + cc, r = rb + tx;
-        if (c < Cpad && r < lim.Rpad) *at(c, r) = tile[tx][cc];
+        if (c < Cpad && r < Rpad) *at(c, r) = tile[tx][cc];
     }
 }
 
 }  // namespace
 
-void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, const int32_t* row_index, bf16_t* dst,
-                          int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad,
-                          const int32_t* counts, int64_t r0, hipStream_t st) {
+void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad,
+                          int64_t Cpad, hipStream_t st) {
     if (Rpad <= 0) return;
     const int vec_ok = (C % 8 == 0) && (ld_src % 8 == 0) && (((uintptr_t)src) % 16 == 0);
-    copy_pad_bf16_kernel<<<(unsigned)Rpad, 256, 0, st>>>(src, ld_src, row_index, dst, ld_dst, R, C, Rpad, Cpad,
-                                                         counts, r0, vec_ok);
+    copy_pad_bf16_kernel<<<(unsigned)Rpad, 256, 0, st>>>(src, ld_src, dst, ld_dst, R, C, Cpad, vec_ok);
 }
 
 // [R, C] (row stride ld) -> tile-blocked [Rpad, Cpad] (multiples of RB and 64, zero padded): block (rt, kt) holds rows
@@ -152,16 +129,15 @@ void launch_transpose_blocks_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst
                                   int RB, hipStream_t st) {
     dim3 grid((unsigned)((Rpad + 63) / 64), (unsigned)((Cpad + 63) / 64));
     const int vec = (ld_src % 8 == 0) && (((uintptr_t)src) % 16 == 0);
-    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, 0, R, C, Rpad, Cpad, nullptr, 0, vec, RB);
+    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, 0, R, C, Rpad, Cpad, vec, RB);
 }
 
 void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R,
-                               int64_t C, int64_t Rpad, int64_t Cpad, const int32_t* counts, int64_t r0,
-                               hipStream_t st) {
+                               int64_t C, int64_t Rpad, int64_t Cpad, hipStream_t st) {
     if (Rpad <= 0 || Cpad <= 0) return;
     dim3 grid((unsigned)((Rpad + 63) / 64), (unsigned)((Cpad + 63) / 64));
     const int vec = (ld_src % 8 == 0) && (ld_dst % 8 == 0) && (((uintptr_t)src) % 16 == 0) && (((uintptr_t)dst) % 16 == 0);
-    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, ld_dst, R, C, Rpad, Cpad, counts, r0, vec, 0);
+    transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, ld_dst, R, C, Rpad, Cpad, vec, 0);
 }
 
 }  // namespace rapid

@@ -123,7 +123,7 @@ struct Plan {
     size_t fixed, total;
     // offsets into the workspace
     size_t counts, pace, seq_len, cu, row_index, tokc, seqc, zy, refz, lse_c, inv_rms, rms_part, rowc, rowg, logp_tmp, s64, s32, adv, adv64, g, g64, tsum, tmax,
-        Hc, Wvd, Wdv, WdvB, dh_part, part_max, part_sum, dw32, chunk0, tab, gen_row0, gen_chunk, gseen, lam_state, lam_chunk, beta_scale, idle, len_live, cu_live, live_group, gruns, Wvd32;
+        Hc, Wvd, Wdv, WdvB, dh_part, part_max, part_sum, dw32, chunk0, tab, gen_row0, gen_chunk, lam_state, lam_chunk, beta_scale, idle, len_live, cu_live, live_group, gruns, Wvd32;
 };
 
 // Tile of the hidden dimension in dHidden and dW, and d rounded up to whole tiles.  Tiles of 256 are the most efficient
@@ -208,7 +208,6 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
             p.tab = take(cur, (size_t)(Cmax > 0 ? Cmax : 1) * CH_WORDS * 4);
             p.gen_row0 = take(cur, (size_t)N * 4);
             p.gen_chunk = take(cur, (size_t)N * 4);
-            p.gseen = take(cur, (size_t)K * 4);
             p.idle = take(cur, (size_t)N * 4);
             p.len_live = take(cur, (size_t)N * 4);
             p.cu_live = take(cur, (size_t)(N + 1) * 4);
@@ -380,13 +379,14 @@ struct FwdIo {
     IdleArgs idle;
     const int32_t* group_ids = nullptr;
     int32_t* runs = nullptr;   // if set (with group_ids): where each group lies in the batch
+    void* dhidden = nullptr;   // if set: its rows without gradient are cleared
 };
 
 PlanArgs plan_args(const Plan& p, void* ws, const int32_t* group_ids, int32_t* dev_status) {
     PlanArgs a;
     a.N = p.N; a.K = p.K; a.gid = group_ids; a.dev_status = dev_status;
     a.seq_len = at<int32_t>(ws, p.seq_len); a.cu = at<int32_t>(ws, p.cu); a.counts = at<int32_t>(ws, p.counts);
-    a.gen_row0 = at<int32_t>(ws, p.gen_row0); a.gen_chunk = at<int32_t>(ws, p.gen_chunk); a.gseen = at<int32_t>(ws, p.gseen);
+    a.gen_row0 = at<int32_t>(ws, p.gen_row0); a.gen_chunk = at<int32_t>(ws, p.gen_chunk);
     return a;
 }
 
@@ -413,9 +413,9 @@ void pack_w_for_logits(const Plan& p, void* ws, const void* W, int w_layout, hip
     if (w_in_place(p, W, w_layout, W_FOR_LOGITS).mode != W_PACKED) return;
     bf16_t* Wvd = at<bf16_t>(ws, p.Wvd);
     if (w_layout == RAPID_W_VD)
-        launch_copy_pad_bf16((const bf16_t*)W, p.d, nullptr, Wvd, p.ldk, p.V, p.d, p.Vpad, p.dpad, nullptr, 0, st);
+        launch_copy_pad_bf16((const bf16_t*)W, p.d, Wvd, p.ldk, p.V, p.d, p.Vpad, p.dpad, st);
     else
-        launch_transpose_pad_bf16((const bf16_t*)W, p.V, Wvd, p.ldk, p.d, p.V, p.dpad, p.Vpad, nullptr, 0, st);
+        launch_transpose_pad_bf16((const bf16_t*)W, p.V, Wvd, p.ldk, p.d, p.V, p.dpad, p.Vpad, st);
     if (p.two_wg) launch_block_w32(Wvd, p.ldk, at<bf16_t>(ws, p.Wvd32), p.Vpad, p.dpad, st);
 }
 
@@ -428,48 +428,61 @@ void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, bo
     const int64_t dpadR = p.dh.padded;
     if (w_layout == RAPID_W_DV) {
         if (blocked) launch_block_rows_bf16((const bf16_t*)W, p.V, WdvB, p.d, p.V, dpadR, p.Vpad, RB, st);
-        else launch_copy_pad_bf16((const bf16_t*)W, p.V, nullptr, Wdv, p.ldv, p.d, p.V, dpadR, p.Vpad, nullptr, 0, st);
+        else launch_copy_pad_bf16((const bf16_t*)W, p.V, Wdv, p.ldv, p.d, p.V, dpadR, p.Vpad, st);
     } else {
         if (blocked) launch_transpose_blocks_bf16((const bf16_t*)W, p.d, WdvB, p.V, p.d, p.Vpad, dpadR, RB, st);
-        else launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, dpadR, nullptr, 0, st);
+        else launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, dpadR, st);
     }
 }
 
+// the compact rows of a planned batch: index, tokens and (bf16) packed hidden rows and sampled tokens' logits, which a
+// storing forward uses as its per-row reference; W is packed already
+void compact_rows(const Plan& p, void* ws, const FwdIo& io, const PlanArgs& plan, hipStream_t st) {
+    RowsArgs r;
+    r.mask = io.mask; r.N = p.N; r.T = p.T;
+    r.first_row = plan.tab ? plan.gen_row0 : plan.cu;
+    r.limits = plan.tab ? plan.tab : plan.counts;
+    r.region = plan.tab ? plan.Rcap : INT64_MAX / 4;
+    r.stride = plan.tab ? (int)CH_WORDS : 0;
+    r.entries = plan.tab ? plan.Cmax : 1;
+    r.row_index = at<int32_t>(ws, p.row_index);
+    r.tokens = io.tokens; r.V = p.V; r.tokc = at<int32_t>(ws, p.tokc); r.seqc = at<int32_t>(ws, p.seqc);
+    r.dev_status = io.dev_status;
+    r.zero_a = io.logp_out; r.zero_b = io.lse_out;
+    // d * (element size) is a multiple of 4 for every accepted shape (bf16 needs d % 8 == 0)
+    r.dhidden = (uint32_t*)io.dhidden; r.words_per_row = p.d * (p.dtype == RAPID_DTYPE_BF16 ? 2 : 4) / 4; r.idle = plan.idle.idle;
+    if (p.dtype == RAPID_DTYPE_BF16) {
+        const WInPlace w = w_in_place(p, io.W, io.w_layout, W_FOR_LOGITS);
+        r.hidden = (const bf16_t*)io.hidden; r.d = p.d; r.Hc = at<bf16_t>(ws, p.Hc); r.ldk = p.ldk; r.Cpad = p.hpad;
+        r.rms_weight = (const bf16_t*)io.rms_weight; r.rms_eps = io.rms_eps; r.inv_rms = at<float>(ws, p.inv_rms);
+        r.gather = w.mode == W_DV;
+        r.W = w.mode == W_PACKED ? at<bf16_t>(ws, p.Wvd) : w.W;
+        r.ldw = w.mode == W_PACKED ? p.ldk : w.mode == W_DV ? p.V : p.d;
+        r.inv_temp = 1.0f / io.temperature;
+        r.zy = at<float>(ws, p.zy); r.refz = io.zc ? at<float>(ws, p.refz) : nullptr; r.ref_logp = io.ref_logp;
+    }
+    launch_compact_rows(r, p.Mmax_pad, st);
+}
+
 // bf16 forward over the compact rows [base, base + rows) (rows a multiple of 256; `counts` holds the end of the
-// valid rows among them): packed hidden rows, sampled-token logits, streaming log-softmax, log-probs.
-// Leaves zy, lse_c (and Hc) of those rows in the workspace for the backward.  Wvd is packed already.
+// valid rows among them): streaming log-softmax, log-probs.  Leaves lse_c of those rows in the workspace for the backward.
 void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* counts, int64_t base, int64_t rows,
                        hipStream_t st) {
     int32_t* row_index = at<int32_t>(ws, p.row_index);
-    int32_t* tokc = at<int32_t>(ws, p.tokc);
-    bf16_t* Hc = at<bf16_t>(ws, p.Hc);
     const WInPlace w = w_in_place(p, io.W, io.w_layout, W_FOR_LOGITS);
     const float inv_temp = 1.0f / io.temperature;
-    {
-        Span sp(ST_PACK, st);
-        if (io.rms_weight)
-            launch_rmsnorm_pad_bf16((const bf16_t*)io.hidden, p.d, row_index, (const bf16_t*)io.rms_weight, io.rms_eps,
-                                    Hc, p.ldk, base, rows, p.hpad, counts, at<float>(ws, p.inv_rms), st);
-        else
-            launch_copy_pad_bf16((const bf16_t*)io.hidden, p.d, row_index, Hc + base * p.ldk, p.ldk, rows, p.d, rows,
-                                 p.hpad, counts, base, st);
-    }
     FwdArgs a;
     a.w = w;
-    a.Wvd = at<bf16_t>(ws, p.Wvd); a.Hc = Hc; a.dpad = p.dpad; a.ldk = p.ldk;
+    a.Wvd = at<bf16_t>(ws, p.Wvd); a.Hc = at<bf16_t>(ws, p.Hc); a.dpad = p.dpad; a.ldk = p.ldk;
     a.tilesV = (int)(p.Vpad / 256); a.tilesM = (int)(rows / 256);
-    a.V = p.V; a.inv_temp = inv_temp; a.tokc = tokc; a.counts = counts;
+    a.V = p.V; a.inv_temp = inv_temp; a.counts = counts;
     a.part_max = at<float>(ws, p.part_max); a.part_sum = at<float>(ws, p.part_sum);
-    a.ld_part = p.ld_part; a.zy = at<float>(ws, p.zy); a.gi = g_gi_fwd;
+    a.ld_part = p.ld_part; a.gi = g_gi_fwd;
     a.zc = io.zc; a.ldz = p.ldv; a.dev_status = io.dev_status;
-    a.refz = at<float>(ws, p.refz); a.ref_logp = io.ref_logp; a.row_index = row_index;
+    a.refz = at<float>(ws, p.refz);
     a.part_row0 = base; a.zc_row0 = base;
     a.WvdB = p.two_wg ? at<bf16_t>(ws, p.Wvd32) : nullptr;
     a.k32_mode = g_fwd_two_wg.load();
-    {   // the sampled tokens' logits first: a storing forward uses them as its per-row reference
-        Span sp(ST_MERGE, st);
-        launch_token_logit(a, base, rows, st);
-    }
     // The forward runs in blocks of token rows, all vocabulary tiles per block, so that a block's
     // hidden rows stay in the memory-side cache while every XCD sweeps its share of W over them
     // (one launch over all rows re-reads the hidden rows from HBM once per group of W panels).
@@ -483,7 +496,7 @@ void forward_rows_bf16(const Plan& p, void* ws, const FwdIo& io, const int32_t* 
     }
     {
         Span sp(ST_MERGE, st);
-        launch_merge_lse(a.part_max, a.part_sum, p.P, a.ld_part, a.zy, row_index, counts, base, rows,
+        launch_merge_lse(a.part_max, a.part_sum, p.P, a.ld_part, at<float>(ws, p.zy), row_index, counts, base, rows,
                          at<float>(ws, p.lse_c), io.logp_out, io.lse_out, st);
     }
 }
@@ -494,26 +507,26 @@ void run_forward(const Plan& p, void* ws, const FwdIo& io, hipStream_t st) {
     int32_t* counts = at<int32_t>(ws, p.counts);
     int32_t* row_index = at<int32_t>(ws, p.row_index);
     int32_t* tokc = at<int32_t>(ws, p.tokc);
-    int32_t* seqc = at<int32_t>(ws, p.seqc);
     float* lse_c = at<float>(ws, p.lse_c);
     const float inv_temp = 1.0f / io.temperature;
+    PlanArgs plan = plan_args(p, ws, io.group_ids, io.dev_status);
+    plan.idle = io.idle;
+    plan.runs = io.runs;
+    if (io.idle.idle) {
+        plan.Rcap = p.Mmax_pad;
+        plan.tab = at<int32_t>(ws, p.tab);
+        plan.Cmax = 1;
+    }
     {
         Span sp(ST_COMPACT, st);
-        PlanArgs plan = plan_args(p, ws, io.group_ids, io.dev_status);
-        plan.idle = io.idle;
-        plan.runs = io.runs;
-        if (io.idle.idle) {
-            plan.Rcap = p.Mmax_pad;
-            plan.tab = at<int32_t>(ws, p.tab);
-            plan.Cmax = 1;
-        }
-        launch_compaction(io.mask, p.N, p.T, plan, io.logp_out, io.lse_out, row_index, RowTokens{io.tokens, p.V, tokc, seqc}, st);
+        launch_plan(io.mask, p.N, p.T, plan, st);
+    }
+    {
+        Span sp(ST_PACK, st);
+        if (p.dtype == RAPID_DTYPE_BF16) pack_w_for_logits(p, ws, io.W, io.w_layout, st);
+        compact_rows(p, ws, io, plan, st);
     }
     if (p.dtype == RAPID_DTYPE_BF16) {
-        {
-            Span sp(ST_PACK, st);
-            pack_w_for_logits(p, ws, io.W, io.w_layout, st);
-        }
         forward_rows_bf16(p, ws, io, counts, 0, p.Mmax_pad, st);
     } else {
         float* z = at<float>(ws, p.chunk0);
@@ -859,7 +872,12 @@ int rapid_compaction(const uint8_t* mask, int64_t N, int64_t T, int32_t* seq_len
     if (rc) return rc;
     PlanArgs plan;
     plan.N = N; plan.seq_len = seq_len_out; plan.cu = cu_seqlen_out;
-    launch_compaction(mask, N, T, plan, nullptr, nullptr, row_index_out, RowTokens(), (hipStream_t)stream);
+    launch_plan(mask, N, T, plan, (hipStream_t)stream);
+    if (row_index_out) {
+        RowsArgs r;
+        r.mask = mask; r.N = N; r.T = T; r.first_row = cu_seqlen_out; r.region = INT64_MAX / 4; r.row_index = row_index_out;
+        launch_compact_rows(r, N * T, (hipStream_t)stream);
+    }
     return check_launch("rapid_compaction");
 }
 
@@ -1026,7 +1044,6 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     float* g = at<float>(ws, p.g);
     float* rowg = at<float>(ws, p.rowg);
     const float inv_temp = 1.0f / o.temperature;
-    const int elem = dtype == RAPID_DTYPE_BF16 ? 2 : 4;
     // token-level outer weight: per generation the sum and the log-maximum of its tokens' ratios
     const bool per_token = o.ratio_level == 1 && !o.coef_override;
     double* tsum = per_token ? at<double>(ws, p.tsum) : nullptr;
@@ -1080,22 +1097,20 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             idle_args.idle = at<int32_t>(ws, p.idle); idle_args.len_live = at<int32_t>(ws, p.len_live);
             idle_args.cu_live = at<int32_t>(ws, p.cu_live); idle_args.live_group = at<int32_t>(ws, p.live_group);
         }
+        io.dhidden = dhidden_out;
+        PlanArgs plan = plan_args(p, ws, group_ids, dev_status);
+        plan.Rcap = p.Rcap; plan.Cmax = p.Cmax; plan.tab = tab; plan.runs = gruns; plan.idle = idle_args;
+        plan.lam_state = lam_state;
         {
             Span sp(ST_COMPACT, st);
-            PlanArgs plan = plan_args(p, ws, group_ids, dev_status);
-            plan.Rcap = p.Rcap; plan.Cmax = p.Cmax; plan.tab = tab; plan.runs = gruns; plan.idle = idle_args;
-            plan.lam_state = lam_state;
-            launch_compaction(mask, N, T, plan, logp_cur, nullptr, row_index, RowTokens{tokens, V, tokc, seqc}, st);
+            launch_plan(mask, N, T, plan, st);
         }
         const bool blocked_wdv = g_blocked_wdv.load() != 0;
         {
             Span sp(ST_PACK, st);
             pack_w_for_logits(p, ws, W, o.w_layout, st);
+            compact_rows(p, ws, io, plan, st);
             pack_w_for_dhidden(p, ws, W, o.w_layout, blocked_wdv, st);
-        }
-        {
-            Span sp(ST_ZERO, st);
-            launch_zero_masked_rows(dhidden_out, mask, p.Mmax, d, elem, idle_args.idle, T, st);
         }
         const int cst = g_cached_step_tiles.load();
         const int64_t cstep = cst > 0 ? ((int64_t)cst * ROW_TILE < p.Rcap ? (int64_t)cst * ROW_TILE : p.Rcap) : p.Rcap;
@@ -1216,6 +1231,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         io.idle.cu_live = at<int32_t>(ws, p.cu_live); io.idle.live_group = at<int32_t>(ws, p.live_group);
         bwd_counts = at<int32_t>(ws, p.tab) + CH_LIVE;
     }
+    io.dhidden = dhidden_out;
     run_forward(p, ws, io, st);
 
     // generation-level log ratios, clipped-weight group baseline, coefficients and loss
@@ -1238,10 +1254,6 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     }
 
     // backward, in row chunks
-    {
-        Span sp(ST_ZERO, st);
-        launch_zero_masked_rows(dhidden_out, mask, p.Mmax, d, elem, io.idle.idle, T, st);
-    }
     const bool dw_staged = o.dw_dtype == RAPID_DTYPE_BF16;
     float* dW32 = dw_staged ? at<float>(ws, p.dw32) : (float*)dW_out;
 

@@ -58,7 +58,7 @@ struct IdleArgs {
 // Cmax == 1: one chunk takes every generation, groups may lie anywhere; tokens past Rcap are left
 // out (RAPID_STATUS_TOKEN_BOUND).  Cmax > 1: a group whose members are not adjacent, or whose tokens
 // exceed Rcap, sets RAPID_STATUS_GROUP_LAYOUT; more chunks than Cmax sets RAPID_STATUS_TOKEN_BOUND.
-// gseen [K] is scratch.  runs [3K + 1] (optional): where each group lies in the batch; given to launch_group_advantage
+// runs [3K + 1] (optional): where each group lies in the batch; given to launch_group_advantage
 // it lets a group that is one run of the batch look at that run alone.  lam_state (optional): set to -infinity.
 struct PlanArgs {
     int64_t N = 0, K = 0;
@@ -67,22 +67,50 @@ struct PlanArgs {
     int64_t Rcap = 0;     // with tab
     int32_t* tab = nullptr;
     int Cmax = 0;
-    int32_t *gen_row0 = nullptr, *gen_chunk = nullptr, *gseen = nullptr, *runs = nullptr;
+    int32_t *gen_row0 = nullptr, *gen_chunk = nullptr, *runs = nullptr;
     double* lam_state = nullptr;
     IdleArgs idle;
     int32_t* dev_status = nullptr;
 };
-struct ZeroWords { int32_t* p[3] = {nullptr, nullptr, nullptr}; int64_t n[3] = {0, 0, 0}; };
-// token ids of the compact rows, if wanted
-struct RowTokens {
-    const int32_t* tokens = nullptr;
+struct ZeroWords { int32_t* p[2] = {nullptr, nullptr}; int64_t n[2] = {0, 0}; };
+void launch_plan(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, hipStream_t st);
+// The compact rows of a planned batch (rows.hip): what is not wanted is NULL.
+struct RowsArgs {
+    const uint8_t* mask = nullptr;
+    int64_t N = 0, T = 0;
+    // generation n's rows begin at first_row[n] (negative: left out), inside its region of `region` rows; limits[e * stride]:
+    // counters of region e < entries
+    const int32_t *first_row = nullptr, *limits = nullptr;
+    int64_t region = 0;
+    int stride = 0, entries = 0;
+    int32_t* row_index = nullptr;               // out: flat position of every row
+    const int32_t* tokens = nullptr;            // [N, T]
     int64_t V = 0;
-    int32_t *tokc = nullptr, *seqc = nullptr;   // token id and generation per compact row
+    int32_t *tokc = nullptr, *seqc = nullptr;   // out: token id and generation of every row
+    int32_t* dev_status = nullptr;
+    float *zero_a = nullptr, *zero_b = nullptr;   // [N, T]: zeros at the positions without a row
+    uint32_t* dhidden = nullptr;                // [N, T] rows of words_per_row: zeros at masked positions and those of generations
+    int64_t words_per_row = 0;                  // that idle [N] marks
+    const int32_t* idle = nullptr;
+    // packed hidden rows (bf16), zeros in columns d .. Cpad and in the rows that fill a region's last row tile up
+    const bf16_t* hidden = nullptr;
+    int64_t d = 0;
+    bf16_t* Hc = nullptr;
+    int64_t ldk = 0, Cpad = 0;
+    const bf16_t* rms_weight = nullptr;         // normalised on the way; inv_rms: 1 / sqrt(mean(x^2) + eps) of every row
+    float rms_eps = 0.f;
+    float* inv_rms = nullptr;
+    // logit of the sampled token (W: a token's weights in a row of ldw, or with `gather` in a column)
+    const bf16_t* W = nullptr;
+    int64_t ldw = 0;
+    bool gather = false;
+    float inv_temp = 1.f;
+    float *zy = nullptr, *refz = nullptr;
+    const float* ref_logp = nullptr;            // [N, T]
 };
-// Lengths, plan, and (row_index not NULL) the flat position, token and generation of every compact row, three launches.
-// zero_a, zero_b (optional): [N * T] outputs set to 0.
-void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, float* zero_a, float* zero_b,
-                       int32_t* row_index, const RowTokens& tok, hipStream_t st);
+// rows: upper bound of the compact rows, padding included
+void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st);
+void launch_rows(const RowsArgs& a, bool by_position, int64_t rows, hipStream_t st);   // its part in rows.hip
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t st);
 // lse/logp from per-slot partial (max, sumexp) and the gathered logit, compact rows [row0, row0 + rows_max);
 // the partials of row j sit at column j - row0
@@ -147,19 +175,12 @@ void launch_rescale_rows(void* dhidden, const uint8_t* mask, int64_t N, int64_t 
                          const double* lam_chunk, const double* lam_state, hipStream_t st);
 // dst[i] += src[i]
 void launch_f32_add(const float* src, float* dst, int64_t n, hipStream_t st);
-// rows of masked positions, and (idle != NULL) of every position of an idle generation, set to zero
-void launch_zero_masked_rows(void* dhidden, const uint8_t* mask, int64_t rows, int64_t d, int elem_bytes,
-                             const int32_t* idle, int64_t T, hipStream_t st);
 void launch_f32_to_bf16(const float* src, bf16_t* dst, int64_t n, hipStream_t st);
 
 // ---- pack.hip ---------------------------------------------------------------------------------
-// dst[r][c] (ld_dst) = src[srow(r)][c] for r < R, c < C else 0, over r < Rpad, c < Cpad.
-// R may come from the device: if counts != NULL, R = counts[CNT_M] - r0 clipped to [0, R] and
-// Rpad = counts[CNT_MR] - r0 clipped to [0, Rpad].  Source row of r is row_index[r0 + r] if
-// row_index is given, else r (the caller offsets `src`).
-void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, const int32_t* row_index, bf16_t* dst,
-                          int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad,
-                          const int32_t* counts, int64_t r0, hipStream_t st);
+// dst[r][c] (ld_dst) = src[r][c] for r < R, c < C else 0, over r < Rpad, c < Cpad.
+void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad,
+                          int64_t Cpad, hipStream_t st);
 // dst = src [R, C] in zero-padded tile blocks of RB rows x 64 columns (see block_rows_bf16_kernel); the second one takes
 // the transpose of src [R, C], so that the blocks run over src's columns.
 void launch_block_rows_bf16(const bf16_t* src, int64_t ld, bf16_t* dst, int64_t R, int64_t C, int64_t Rpad, int64_t Cpad, int RB,
@@ -168,16 +189,9 @@ void launch_transpose_blocks_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst
                                   int RB, hipStream_t st);
 // dst[c][r] (ld_dst) = src[r][c] for r < R, c < C else 0, over r < Rpad, c < Cpad.
 void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R,
-                               int64_t C, int64_t Rpad, int64_t Cpad, const int32_t* counts, int64_t r0,
-                               hipStream_t st);
+                               int64_t C, int64_t Rpad, int64_t Cpad, hipStream_t st);
 
 // ---- rmsnorm.hip ------------------------------------------------------------------------------
-// dst row r in [r0, r0 + Rpad) below counts[CNT_MR] = bf16(src[row_index[r]] * weight / rms) for r < counts[CNT_M],
-// zero otherwise and in columns C .. Cpad; inv_rms[r] = 1 / sqrt(mean(x^2) + eps).  C % 8 == 0.  dst and
-// inv_rms are indexed by compact row.
-void launch_rmsnorm_pad_bf16(const bf16_t* src, int64_t C, const int32_t* row_index, const bf16_t* weight, float eps,
-                             bf16_t* dst, int64_t ld_dst, int64_t r0, int64_t Rpad, int64_t Cpad, const int32_t* counts,
-                             float* inv_rms, hipStream_t st);
 // dh [N*T, d] holds dL/dh at the valid positions of the compact rows [row0, row0 + rows_max) below
 // counts[CNT_M]: if part != NULL, partial sums of dL/dweight over blocks of those rows go to
 // part [rmsnorm_dweight_blocks(rows_max)][d] (zeroed beforehand: a block without rows writes nothing); then dh
@@ -208,18 +222,14 @@ struct FwdArgs {          // logits tile -> per-slot (max, sumexp) and gathered 
     int64_t row0;         // first compact token row of this launch
     int64_t V;
     float inv_temp;
-    const int32_t* tokc;
     const int32_t* counts;
     float* part_max;      // [P][ld_part], P = tilesV * 2
     float* part_sum;
     int64_t ld_part;
-    float* zy;            // [Mmax_pad]
     int gi;               // tiles along i that share one j before the order moves on (L2 blocking)
     bf16_t* zc;           // NULL, or [rows, ldz]: the kernel also stores exp(logit - refz[row]) there; refz must be set
     int64_t ldz;
-    float* refz;          // [Mmax_pad] reference of the stored exponentials, written by launch_token_logit if zc is set
-    const float* ref_logp;   // NULL, or [N*T] log-probs subtracted from zy to form refz
-    const int32_t* row_index;
+    const float* refz;    // [Mmax_pad] reference of the stored exponentials
     int32_t* dev_status;  // may be NULL
     int64_t part_row0 = 0;   // compact row whose partials sit in column 0 of part_max / part_sum
     int64_t zc_row0 = 0;     // compact row stored in row 0 of zc
@@ -231,8 +241,6 @@ struct FwdArgs {          // logits tile -> per-slot (max, sumexp) and gathered 
 void launch_fwd_lse(const FwdArgs& a, hipStream_t st);
 // out [Vpad * dpad]: Wvd [Vpad, ldk] in blocks of 256 rows x 32 columns, in the LDS order of the two-workgroup forward
 void launch_block_w32(const bf16_t* Wvd, int64_t ldk, bf16_t* out, int64_t Vpad, int64_t dpad, hipStream_t st);
-// zy (and refz) for the compact rows [row0, row0 + rows_max)
-void launch_token_logit(const FwdArgs& a, int64_t row0, int64_t rows_max, hipStream_t st);
 int fwd_slots_per_tile();
 
 struct DzArgs {           // logits tile -> dz = g (onehot - p) / temperature, bf16 [Mc, Vpad]

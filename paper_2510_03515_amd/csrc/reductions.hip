@@ -74,8 +74,8 @@ inline unsigned block_threads(int64_t N, unsigned most) {
 }
 
 // ------------------------------------------------------------------ compaction of the padding mask
-// Three launches whatever is asked for: a small batch's call is a matter of launches (about 5 us each), and these
-// kernels have next to nothing to do.  Before (one kernel per array): 8 launches for a forward, 13 for a cached step.
+// Lengths and plan here, the rows in rows.hip: two launches for a small batch, three for the others.  A small batch's call is a
+// matter of launches, and these have next to nothing to do.
 
 // One block per generation; its waves take stretches of the sequence of the same length.  One wave where a sequence has
 // fewer than 512 positions: 256 positions are about four trips to memory, and a second wave costs a barrier.
@@ -103,20 +103,14 @@ __device__ inline int count_valid(const uint8_t* mask, int64_t row0, int64_t T, 
     return wave_sum_i(cnt);
 }
 
-// Number of valid tokens of each generation, and zeros in its rows of the per-token outputs; the blocks together
-// clear the plan's counters.
+// Number of valid tokens of each generation; the blocks together clear the plan's counters.
 template <bool ONE_WAVE>
 __global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void seq_len_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
-                                                       int32_t* __restrict__ seq_len, float* __restrict__ zero_a,
-                                                       float* __restrict__ zero_b, ZeroWords z) {
+                                                       int32_t* __restrict__ seq_len, ZeroWords z) {
     const int64_t n = blockIdx.x;
     int cnt = count_valid(mask, n * T, T, ONE_WAVE ? Stretch{0, T} : wave_stretch(T));
-    for (int64_t t = threadIdx.x; t < T; t += blockDim.x) {
-        if (zero_a) zero_a[n * T + t] = 0.f;
-        if (zero_b) zero_b[n * T + t] = 0.f;
-    }
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 2; ++k)
         for (int64_t i = n * blockDim.x + threadIdx.x; i < z.n[k]; i += N * blockDim.x) z.p[k][i] = 0;
     if constexpr (!ONE_WAVE) {
         __shared__ int s_cnt[16];
@@ -129,7 +123,7 @@ __global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void seq_len_kernel(const u
 }
 
 // exclusive prefix sum of v [N] -> cu [N + 1] by a block of up to 1024 threads; returns the total to every thread
-__device__ int block_scan(const int32_t* v, int64_t N, int32_t* cu) {
+__device__ __forceinline__ int block_scan(const int32_t* v, int64_t N, int32_t* cu) {
     constexpr int PER = 8;   // consecutive entries per thread: 8192 per sweep of the block
     __shared__ int s_wave[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -177,36 +171,101 @@ __device__ int block_scan(const int32_t* v, int64_t N, int32_t* cu) {
 // The plan of a batch, by one block: where each group lies (runs), which generations are idle, the prefix sums of the
 // lengths, and either the counters of one region (tab NULL) or the chunk table.
 // Thread 0 walks the runs of equal group id in order and fills chunk after chunk; then all threads
-// give every generation its chunk and first compact row and count each run's group id once.
+// give every generation its chunk and first compact row.
 // With idle generations (cu_live = prefix sum of the other generations' lengths) a chunk's
 // rows are ordered: the generations that carry gradient first, in batch order, then the idle ones, so that the
 // two gradient contractions stop at CH_LIVE.
 // runs[k] = number of maximal runs of group id k, runs[K + k] / runs[2K + k] = begin / end of (the last of) them,
 // runs[3K] = 1 if some group has more than one run.  With one run per group, which is how a sampler that draws G
 // generations per prompt lays a batch out, the per-group pass below visits each generation once instead of once
-// per group.  runs, live_group and gseen are zero on entry (seq_len_kernel).
-__global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
+// per group.
+//
+// IN_LDS: N and K at most PLAN_LDS; what the plan makes for itself stays in the LDS, so that the steps between its
+// barriers are not trips to memory (64 generations 6.4 -> 4.0 us, a step in 7 chunks 66 -> 13 us).  LENGTHS: it counts
+// the generations' tokens too, a launch less; one block reads the whole mask then, which up to PLAN_MASK positions
+// takes it no longer than the launch would.  Else seq_len_kernel has counted them, and has cleared runs and live_group
+// where they are in memory.
+constexpr int PLAN_LDS = 1024, PLAN_MASK = 32768;
+template <bool IN_LDS, bool LENGTHS>
+__global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a, const uint8_t* __restrict__ mask, int64_t T) {
+    static_assert(IN_LDS || !LENGTHS, "lengths are counted into the LDS");
+    constexpr int L = IN_LDS ? PLAN_LDS : 0;
     __shared__ int s_status;
+    __shared__ int32_t s_len[L + 1], s_cu[L + 1], s_live_len[L + 1], s_cu_live[L + 1], s_live_group[L + 1], s_run_first[L + 1],
+        s_run_end[L + 1], s_run_count[L + 1], s_gid[L + 1];
     const int64_t N = a.N, K = a.K;
-    const int32_t* gid = a.gid;
-    if (a.runs || (a.idle.idle && !a.idle.coef_override)) {
-        for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
-            const int32_t g = gid[n];
-            if (g < 0 || g >= K) continue;
-            if (a.runs) {
-                if (n == 0 || gid[n - 1] != g) {
-                    if (atomicAdd(&a.runs[g], 1) > 0) a.runs[3 * K] = 1;
-                    a.runs[K + g] = (int32_t)n;
+    const int32_t* const gid = IN_LDS ? s_gid : a.gid;
+    int32_t* const seq_len = IN_LDS ? s_len : a.seq_len;
+    int32_t* const cu = IN_LDS ? s_cu : a.cu;
+    int32_t* const len_live = IN_LDS ? s_live_len : a.idle.len_live;
+    int32_t* const cu_live_out = IN_LDS ? s_cu_live : a.idle.cu_live;
+    int32_t* const live_group = IN_LDS ? s_live_group : a.idle.live_group;
+    int32_t* const run_count = IN_LDS ? s_run_count : a.runs;
+    int32_t* const run_first = IN_LDS ? s_run_first : a.runs + K;
+    int32_t* const run_end = IN_LDS ? s_run_end : a.runs + 2 * K;
+    __shared__ int s_split;      // some group has more than one run
+    if (threadIdx.x == 0) s_split = 0;
+    const bool by_reward = a.idle.idle && !a.idle.coef_override;
+    float my_reward = 0.f;       // in the LDS a thread has one generation at most
+    if constexpr (IN_LDS) {
+        if (by_reward && threadIdx.x < N) my_reward = a.idle.rewards[threadIdx.x];
+        for (int k = threadIdx.x; k < K; k += blockDim.x) s_live_group[k] = s_run_count[k] = s_run_first[k] = s_run_end[k] = 0;
+        if (a.gid)
+            for (int n = threadIdx.x; n < N; n += blockDim.x) s_gid[n] = a.gid[n];
+    }
+    if constexpr (LENGTHS) {
+        // 2^lanes_log2 lanes per generation, four loads of each in flight
+        const bool words = (T & 3) == 0 && ((uintptr_t)mask & 3) == 0;
+        const int per = (int)(words ? T / 4 : T), lanes_log2 = per <= 32 ? 3 : per <= 64 ? 4 : per <= 128 ? 5 : 6, lanes = 1 << lanes_log2;
+        for (int64_t n = threadIdx.x >> lanes_log2; n < N; n += blockDim.x >> lanes_log2) {
+            const uint8_t* row = mask + n * T;
+            int cnt = 0;
+            if (words) {
+#pragma unroll 4
+                for (int t = threadIdx.x & (lanes - 1); t < per; t += lanes) {
+                    const uint32_t w = ((const uint32_t*)row)[t];
+                    cnt += __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);
                 }
-                if (n == N - 1 || gid[n + 1] != g) a.runs[2 * K + g] = (int32_t)(n + 1);
+            } else {
+#pragma unroll 4
+                for (int t = threadIdx.x & (lanes - 1); t < per; t += lanes) cnt += row[t] != 0;
             }
-            if (a.idle.idle && !a.idle.coef_override) {
-                // a reward that is not finite counts as 0 in the estimator as well; equal values from several threads
-                const float R = a.idle.rewards[n];
-                if (isfinite(R) && R != 0.f) a.idle.live_group[g] = 1;
+            for (int o = lanes >> 1; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, WAVE);
+            if ((threadIdx.x & (lanes - 1)) == 0) {
+                s_len[n] = cnt;
+                a.seq_len[n] = cnt;
             }
         }
+    } else if constexpr (IN_LDS) {
+        for (int n = threadIdx.x; n < N; n += blockDim.x) s_len[n] = a.seq_len[n];
+    }
+    __syncthreads();
+    if (a.runs || by_reward) {
+        for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
+            const int32_t g = gid[n], before = n > 0 ? gid[n - 1] : -1, after = n < N - 1 ? gid[n + 1] : -1;
+            // a reward that is not finite counts as 0 in the estimator as well; equal values from several threads
+            const float R = IN_LDS ? my_reward : by_reward ? a.idle.rewards[n] : 0.f;
+            if (g < 0 || g >= K) continue;
+            if (a.runs) {
+                if (before != g) {
+                    if (atomicAdd(&run_count[g], 1) > 0) s_split = 1;
+                    run_first[g] = (int32_t)n;
+                }
+                if (after != g) run_end[g] = (int32_t)(n + 1);
+            }
+            if (isfinite(R) && R != 0.f) live_group[g] = 1;
+        }
         __syncthreads();
+        if (a.runs) {
+            if constexpr (IN_LDS) {
+                for (int k = threadIdx.x; k < K; k += blockDim.x) {
+                    a.runs[k] = s_run_count[k];
+                    a.runs[K + k] = s_run_first[k];
+                    a.runs[2 * K + k] = s_run_end[k];
+                }
+            }
+            if (threadIdx.x == 0) a.runs[3 * K] = s_split;
+        }
     }
     if (a.idle.idle) {
         for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
@@ -215,21 +274,25 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
                 z = a.idle.coef_override[n] == 0.f;
             } else {
                 const int32_t g = gid[n];
-                z = g >= 0 && g < K && a.idle.live_group[g] == 0;
+                z = g >= 0 && g < K && live_group[g] == 0;
             }
             a.idle.idle[n] = z ? 1 : 0;
-            a.idle.len_live[n] = z ? 0 : a.seq_len[n];
+            len_live[n] = z ? 0 : seq_len[n];
         }
         __syncthreads();
     }
-    const int32_t* cu_live = a.idle.idle ? a.idle.cu_live : nullptr;
-    const int64_t total = block_scan(a.seq_len, N, a.cu);
-    if (a.idle.idle) block_scan(a.idle.len_live, N, a.idle.cu_live);
+    const int32_t* cu_live = a.idle.idle ? cu_live_out : nullptr;
+    const int64_t total = block_scan(seq_len, N, cu);
+    if (a.idle.idle) block_scan(len_live, N, cu_live_out);
     if (threadIdx.x == 0 && a.lam_state) a.lam_state[0] = -INFINITY;
     if (!a.tab) {
         if (threadIdx.x == 0 && a.counts) {
             a.counts[CNT_M] = (int32_t)total;
             a.counts[CNT_MR] = (int32_t)((total + ROW_TILE - 1) / ROW_TILE * ROW_TILE);
+        }
+        if constexpr (IN_LDS) {
+            __syncthreads();
+            for (int n = threadIdx.x; n <= N; n += blockDim.x) a.cu[n] = s_cu[n];
         }
         return;
     }
@@ -237,7 +300,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     const int64_t Rcap = a.Rcap;
     const int Cmax = a.Cmax;
     int32_t* tab = a.tab;
-    const int32_t* cu = a.cu;
     if (threadIdx.x == 0) {
         int status = 0, c = 0;
         int64_t placed = 0;
@@ -288,67 +350,56 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
         s_status = status;
     }
     __syncthreads();
-    int status = 0;
     for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
         int c = -1;
-        for (int k = 0; k < Cmax; ++k)
-            if (n >= tab[k * CH_WORDS + CH_G0] && n < tab[k * CH_WORDS + CH_G1]) { c = k; break; }
+        int64_t g0 = 0, g1 = N;
+        for (int k = 0; k < Cmax; ++k) {
+            if (Cmax > 1) { g0 = tab[k * CH_WORDS + CH_G0]; g1 = tab[k * CH_WORDS + CH_G1]; }
+            if (n >= g0 && n < g1) { c = k; break; }
+        }
         a.gen_chunk[n] = c;
         int64_t row0 = -1;
         if (c >= 0) {
-            const int64_t g0 = tab[c * CH_WORDS + CH_G0], g1 = tab[c * CH_WORDS + CH_G1];
             const int64_t before = (int64_t)cu[n] - (int64_t)cu[g0];            // tokens of the chunk's earlier generations
             if (cu_live) {
                 const int64_t live_before = (int64_t)cu_live[n] - (int64_t)cu_live[g0];
                 const int64_t live_all = (int64_t)cu_live[g1] - (int64_t)cu_live[g0];
-                row0 = (int64_t)c * Rcap + (a.idle.idle[n] ? live_all + (before - live_before) : live_before);
+                // (an idle generation without tokens has no row to place)
+                row0 = (int64_t)c * Rcap + (len_live[n] != seq_len[n] ? live_all + (before - live_before) : live_before);
             } else {
                 row0 = (int64_t)c * Rcap + before;
             }
         }
         a.gen_row0[n] = (int32_t)row0;
-        if (Cmax > 1 && (n == 0 || gid[n] != gid[n - 1])) {       // first generation of a run
-            const int32_t g = gid[n];
-            if (g >= 0 && g < K && atomicAdd(&a.gseen[g], 1) > 0) status |= RAPID_STATUS_GROUP_LAYOUT;
-        }
     }
-    if (threadIdx.x == 0) status |= s_status;
-    if (status && a.dev_status) atomicOr(a.dev_status, status);
+    if (threadIdx.x == 0 && a.dev_status) {
+        const int status = s_status | (Cmax > 1 && s_split ? RAPID_STATUS_GROUP_LAYOUT : 0);
+        if (status) atomicOr(a.dev_status, status);
+    }
 }
 
-// One block per generation: flat positions of its valid tokens, in order, from compact row first_row[n]
-// on (a negative first row: the generation was left out), and their token ids and generation (out-of-range ids are flagged
-// and replaced by 0).  The compact rows come in regions of `region` rows; a generation never writes past the end of the
-// region its first row lies in.  Rows that fill a region's last row tile up (its counters: limits[e * stride]) get token 0.
+// The rows' positions, tokens and generations for batches of long sequences (see rows_by_position_kernel, which does the same
+// for the others); one block per generation.
 // A wave's loop is a chain of trips to memory, so it takes 4 x 64 positions at a time, mask and tokens together, and the
-// waves of a long sequence share it (each counts its stretch first).  One wave, one load after the other: 1 x 131 072
-// positions 500 us, 64 x 2048 19 us.
-template <bool ONE_WAVE>
-__global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void row_index_kernel(const uint8_t* __restrict__ mask, int64_t N, int64_t T,
-                                                         const int32_t* __restrict__ first_row, int64_t region,
-                                                         int32_t* __restrict__ row_index, const int32_t* __restrict__ tokens,
-                                                         int64_t V, int32_t* __restrict__ tokc, int32_t* __restrict__ seqc,
-                                                         const int32_t* __restrict__ limits, int stride, int entries,
-                                                         int32_t* __restrict__ dev_status) {
-    const int64_t n = blockIdx.x;
-    const int lane = threadIdx.x & (WAVE - 1);
-    if (tokc)
-        for (int64_t e = n; e < entries; e += N)
-            for (int j = limits[e * stride + CNT_M] + (int)threadIdx.x; j < limits[e * stride + CNT_MR]; j += blockDim.x) {
-                tokc[j] = 0;
-                seqc[j] = 0;
+// waves of the sequence share it (each counts its stretch first).  One wave, one load after the other: 1 x 131 072
+// positions 500 us, 19 now.
+__global__ __launch_bounds__(1024) void row_index_kernel(RowsArgs a) {
+    const int64_t n = blockIdx.x, T = a.T;
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    if (a.tokc)
+        for (int64_t e = n; e < a.entries; e += a.N)
+            for (int j = a.limits[e * a.stride + CNT_M] + (int)threadIdx.x; j < a.limits[e * a.stride + CNT_MR]; j += blockDim.x) {
+                a.tokc[j] = 0;
+                a.seqc[j] = 0;
             }
-    int64_t base = first_row[n];
-    if (base < 0) return;
-    const int64_t limit = (base / region + 1) * region;
-    const Stretch s = ONE_WAVE ? Stretch{0, T} : wave_stretch(T);
-    if constexpr (!ONE_WAVE) {
-        __shared__ int s_cnt[16];
-        const int cnt = count_valid(mask, n * T, T, s), wave = threadIdx.x / WAVE;
-        if (lane == 0) s_cnt[wave] = cnt;
-        __syncthreads();
-        for (int w = 0; w < wave; ++w) base += s_cnt[w];
-    }
+    int64_t base = a.first_row[n];
+    const int64_t limit = base < 0 ? 0 : (base / a.region + 1) * a.region;
+    const Stretch s = wave_stretch(T);
+    __shared__ int s_cnt[16];
+    const int cnt = count_valid(a.mask, n * T, T, s);
+    if (lane == 0) s_cnt[wave] = cnt;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) base += s_cnt[w];
     bool bad = false;
     constexpr int U = 4;
     for (int64_t t0 = s.begin; t0 < s.end; t0 += U * WAVE) {
@@ -357,27 +408,31 @@ __global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void row_index_kernel(const
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t t = t0 + u * WAVE + lane;
-            v[u] = t < s.end && mask[n * T + t] != 0;
-            tok[u] = t < s.end && tokc ? tokens[n * T + t] : 0;
+            v[u] = t < s.end && a.mask[n * T + t] != 0;
+            tok[u] = t < s.end && a.tokc ? a.tokens[n * T + t] : 0;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            const int64_t t = t0 + u * WAVE + lane, i = n * T + t;
             if (t0 + u * WAVE >= s.end) break;
             const unsigned long long b = __ballot(v[u]);
             const int64_t j = base + __popcll(b & ((1ull << lane) - 1ull));
             if (v[u] && j < limit) {
-                row_index[j] = (int32_t)(n * T + t0 + u * WAVE + lane);
-                if (tokc) {
-                    const bool in = tok[u] >= 0 && tok[u] < V;
+                a.row_index[j] = (int32_t)i;
+                if (a.tokc) {
+                    const bool in = tok[u] >= 0 && tok[u] < a.V;
                     bad = bad || !in;
-                    tokc[j] = in ? tok[u] : 0;
-                    seqc[j] = (int32_t)n;
+                    a.tokc[j] = in ? tok[u] : 0;
+                    a.seqc[j] = (int32_t)n;
                 }
+            } else if (t < s.end) {
+                if (a.zero_a) a.zero_a[i] = 0.f;
+                if (a.zero_b) a.zero_b[i] = 0.f;
             }
             base += __popcll(b);
         }
     }
-    if (bad && dev_status) atomicOr(dev_status, RAPID_STATUS_BAD_TOKEN);
+    if (bad && a.dev_status) atomicOr(a.dev_status, RAPID_STATUS_BAD_TOKEN);
 }
 
 __global__ void f32_add_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t n) {
@@ -783,20 +838,33 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 
 }  // namespace
 
-void launch_compaction(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, float* zero_a, float* zero_b,
-                       int32_t* row_index, const RowTokens& tok, hipStream_t st) {
+void launch_plan(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, hipStream_t st) {
+    const bool in_lds = N <= PLAN_LDS && plan.K <= PLAN_LDS;
+    if (in_lds && N * T <= PLAN_MASK) {
+        const int64_t lanes = T <= 64 ? 8 : T <= 256 ? 16 : 64;      // about what the kernel gives a generation
+        plan_kernel<true, true><<<1, block_threads(N * lanes, 1024), 0, st>>>(plan, mask, T);
+        return;
+    }
     ZeroWords z;
-    if (plan.runs) { z.p[0] = plan.runs; z.n[0] = 3 * plan.K + 1; }
-    if (plan.idle.idle && !plan.idle.coef_override) { z.p[1] = plan.idle.live_group; z.n[1] = plan.K; }
-    if (plan.tab && plan.Cmax > 1) { z.p[2] = plan.gseen; z.n[2] = plan.K; }
+    if (!in_lds && plan.runs) { z.p[0] = plan.runs; z.n[0] = 3 * plan.K; }
+    if (!in_lds && plan.idle.idle && !plan.idle.coef_override) { z.p[1] = plan.idle.live_group; z.n[1] = plan.K; }
     const unsigned threads = row_threads(T);
-    (threads == WAVE ? &seq_len_kernel<true> : &seq_len_kernel<false>)<<<(unsigned)N, threads, 0, st>>>(mask, N, T, plan.seq_len, zero_a, zero_b, z);
-    plan_kernel<<<1, block_threads(plan.N, 1024), 0, st>>>(plan);
-    if (row_index)
-        (threads == WAVE ? &row_index_kernel<true> : &row_index_kernel<false>)<<<(unsigned)N, threads, 0, st>>>(mask, N, T, plan.tab ? plan.gen_row0 : plan.cu, plan.tab ? plan.Rcap : INT64_MAX / 4,
-                                                       row_index, tok.tokens, tok.V, tok.tokc, tok.seqc,
-                                                       plan.tab ? plan.tab : plan.counts, plan.tab ? (int)CH_WORDS : 0,
-                                                       plan.tab ? plan.Cmax : 1, plan.dev_status);
+    (threads == WAVE ? &seq_len_kernel<true> : &seq_len_kernel<false>)<<<(unsigned)N, threads, 0, st>>>(mask, N, T, plan.seq_len, z);
+    if (in_lds) plan_kernel<true, false><<<1, block_threads(N, 1024), 0, st>>>(plan, mask, T);
+    else plan_kernel<false, false><<<1, 1024, 0, st>>>(plan, mask, T);
+}
+
+// Above this many positions per generation the waves of rows_by_position_kernel would spend their time on counting.
+constexpr int64_t BY_POSITION_T = 4096;
+void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st) {
+    if (a.T <= BY_POSITION_T) {
+        launch_rows(a, true, rows, st);
+        return;
+    }
+    const unsigned threads = row_threads(a.T);
+    row_index_kernel<<<(unsigned)a.N, threads, 0, st>>>(a);
+    if (a.dhidden) zero_masked_rows_kernel<<<(unsigned)(a.N * a.T), 128, 0, st>>>(a.dhidden, a.mask, a.N * a.T, a.words_per_row, a.idle, a.T);
+    if (a.Hc) launch_rows(a, false, rows, st);
 }
 
 void launch_fill_f32(float* p, int64_t n, float v, hipStream_t st) {
@@ -983,13 +1051,6 @@ void launch_row_coefficients(const float* g, const double* g64, const int32_t* s
 void launch_rescale_rows(void* dhidden, const uint8_t* mask, int64_t N, int64_t T, int64_t d, const int32_t* gen_chunk,
                          const double* lam_chunk, const double* lam_state, hipStream_t st) {
     rescale_rows_kernel<<<(unsigned)(N * T), 128, 0, st>>>((bf16_t*)dhidden, mask, T, d, gen_chunk, lam_chunk, lam_state);
-}
-
-void launch_zero_masked_rows(void* dhidden, const uint8_t* mask, int64_t rows, int64_t d, int elem_bytes,
-                             const int32_t* idle, int64_t T, hipStream_t st) {
-    // d * elem_bytes is a multiple of 4 for every accepted shape (bf16 needs d % 8 == 0)
-    zero_masked_rows_kernel<<<(unsigned)rows, 128, 0, st>>>((uint32_t*)dhidden, mask, rows,
-                                                            d * elem_bytes / 4, idle, T);
 }
 
 // master -= lr * grad; optionally also the updated weights in the contraction dtype

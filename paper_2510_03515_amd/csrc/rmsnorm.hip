@@ -1,20 +1,19 @@
 // Final RMSNorm folded into the operand pack of the fused call (not part of the paper's method: its
 // path starts at the hidden state; the Qwen2.5 models it trains end in this norm, and the pack pass
-// reads every hidden row anyway).  Forward: the packed, zero-padded bf16 operand holds
+// reads every hidden row anyway).  Forward (rows.hip): the packed, zero-padded bf16 operand holds
 // h = x * weight / sqrt(mean(x^2) + eps) instead of a copy of x.  Backward: the dHidden kernel has
 // written dL/dh (bf16) into the caller's dhidden buffer; two passes over the valid rows turn it into
 // dL/dweight (fixed-order partial sums) and, in place, dL/dx.
 #include "rapid_internal.h"
+#include "row_math.h"
 
 namespace rapid {
 
 namespace {
 
-constexpr int WAVE = 64;
-
 __device__ inline float wave_sum_f(float v) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 
@@ -22,102 +21,9 @@ __device__ inline float wave_sum_f(float v) {
 __device__ inline float block_sum_f(float v, float* sm) {
     v = wave_sum_f(v);
     __syncthreads();
-    if ((threadIdx.x & (WAVE - 1)) == 0) sm[threadIdx.x / WAVE] = v;
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x / 64] = v;
     __syncthreads();
     return (sm[0] + sm[1]) + (sm[2] + sm[3]);
-}
-
-__device__ inline void unpack8(const uint4& v, float (&f)[8]) {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        f[2 * e] = __builtin_bit_cast(float, w[e] << 16);
-        f[2 * e + 1] = __builtin_bit_cast(float, w[e] & 0xffff0000u);
-    }
-}
-
-// double -> float such that rounding the float to bf16 (nearest even) gives what rounding the double
-// to bf16 directly would: truncate, and set the last bit if anything was cut off ("round to odd"; the
-// sticky bit keeps a value just off a bf16 midpoint from landing on it)
-__device__ inline float round_to_odd_f32(double v) {
-    float f = (float)v;                       // nearest; repaired below if it moved the value
-    if ((double)f != v && isfinite(f)) {
-        uint32_t b = __builtin_bit_cast(uint32_t, f);
-        const bool away = fabs((double)f) > fabs(v);   // rounded away from zero: step back to the truncation
-        if (away) b -= 1u;
-        b |= 1u;
-        f = __builtin_bit_cast(float, b);
-    }
-    return f;
-}
-
-__device__ inline uint32_t pack2(float a, float b) {
-    const __bf16 x = (__bf16)a, y = (__bf16)b;
-    return (uint32_t)__builtin_bit_cast(unsigned short, x) | ((uint32_t)__builtin_bit_cast(unsigned short, y) << 16);
-}
-
-__device__ inline uint4 pack8(const float (&f)[8]) {
-    return make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
-}
-
-__device__ inline double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-    return v;
-}
-__device__ inline double block_sum_d(double v, double* sm) {
-    v = wave_sum_d(v);
-    __syncthreads();
-    if ((threadIdx.x & (WAVE - 1)) == 0) sm[threadIdx.x / WAVE] = v;
-    __syncthreads();
-    return (sm[0] + sm[1]) + (sm[2] + sm[3]);
-}
-
-// one block per destination row r < Mr (device count): rows < M hold the normalised source row
-// row_index[r], the rest and the columns C .. Cpad are zero; inv_rms[r] = 1 / sqrt(mean(x^2) + eps).
-// The normalised value is formed in fp64 and rounded to bf16 once: which of two neighbouring bf16
-// values an element becomes is a decision, and taken from an fp32 product it would fall the other
-// way than the exact value's for about one element in 40 000, each moving its row's log-prob by
-// ~1e-4.  The pass is bound by its memory traffic either way.
-__global__ __launch_bounds__(256) void rmsnorm_pad_bf16_kernel(const bf16_t* __restrict__ src, int64_t C,
-                                                               const int32_t* __restrict__ row_index,
-                                                               const bf16_t* __restrict__ weight, float eps,
-                                                               bf16_t* __restrict__ dst, int64_t ld_dst, int64_t Cpad,
-                                                               const int32_t* __restrict__ counts,
-                                                               float* __restrict__ inv_rms, int64_t r0) {
-    __shared__ double sm[4];
-    const int64_t r = r0 + blockIdx.x;
-    const int M = counts[CNT_M], Mr = counts[CNT_MR];
-    if (r >= Mr) return;
-    bf16_t* drow = dst + r * ld_dst;
-    const int64_t chunks = Cpad / 8, live_chunks = C / 8;
-    if (r >= M) {
-        for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) *(uint4*)(drow + c * 8) = make_uint4(0u, 0u, 0u, 0u);
-        return;
-    }
-    const bf16_t* srow = src + (int64_t)row_index[r] * C;
-    double ss = 0.0;
-    for (int64_t c = threadIdx.x; c < live_chunks; c += blockDim.x) {
-        float x[8];
-        unpack8(*(const uint4*)(srow + c * 8), x);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fma((double)x[e], (double)x[e], ss);
-    }
-    ss = block_sum_d(ss, sm);
-    const double inv = 1.0 / sqrt(ss / (double)C + (double)eps);
-    if (threadIdx.x == 0) inv_rms[r] = (float)inv;
-    for (int64_t c = threadIdx.x; c < chunks; c += blockDim.x) {
-        uint4 out = make_uint4(0u, 0u, 0u, 0u);
-        if (c < live_chunks) {
-            float x[8], g[8], h[8];
-            unpack8(*(const uint4*)(srow + c * 8), x);
-            unpack8(*(const uint4*)(weight + c * 8), g);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = round_to_odd_f32((double)x[e] * inv * (double)g[e]);
-            out = pack8(h);
-        }
-        *(uint4*)(drow + c * 8) = out;
-    }
 }
 
 // dweight partials: block (rb, cb) sums dh[row][k] x[row][k] inv_rms[row] over the valid compact rows
@@ -196,14 +102,6 @@ __global__ __launch_bounds__(256) void rmsnorm_dx_kernel(const bf16_t* __restric
 }
 
 }  // namespace
-
-void launch_rmsnorm_pad_bf16(const bf16_t* src, int64_t C, const int32_t* row_index, const bf16_t* weight, float eps,
-                             bf16_t* dst, int64_t ld_dst, int64_t r0, int64_t Rpad, int64_t Cpad, const int32_t* counts,
-                             float* inv_rms, hipStream_t st) {
-    if (Rpad <= 0) return;
-    rmsnorm_pad_bf16_kernel<<<(unsigned)Rpad, 256, 0, st>>>(src, C, row_index, weight, eps, dst, ld_dst, Cpad, counts,
-                                                            inv_rms, r0);
-}
 
 int64_t rmsnorm_dweight_blocks(int64_t rows_max) { return (rows_max + RB - 1) / RB; }
 

@@ -367,3 +367,20 @@ def test_smallest_workspace_has_room_for_other_tiles_only(rb, d, layout, cache):
     spec = wl.small_spec("min_ws", "bf16", d=d, V=1500, prompts=6, G=4, len_lo=20, len_hi=60, reward="uniform")
     w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=cache, min_ws=True)
     _check_pair(rb, spec, out, ref, layout)
+
+
+@pytest.mark.parametrize("prompts,G,length", [
+    (256, 4, 32),      # 1024 generations, 32768 positions: the most whose lengths and plan one block makes in the LDS
+    (256, 4, 33),      # lengths counted in a launch of their own, odd rows; more than one position per wave
+    (257, 4, 9),       # plan in memory
+    (1, 3, 1),         # one position each
+    (2, 3, 130), (3, 5, 258), (1, 2, 519),     # 8 to 64 lanes per generation, rows that are no whole words
+])
+@pytest.mark.parametrize("mode", ["recompute", "cache", "chunks", "f32"])
+def test_plan_and_rows_of_a_batch(rb, prompts, G, length, mode):
+    print(f"plan and rows {prompts} x {G} x {length} {mode}", flush=True)
+    dtype = "f32" if mode == "f32" else "bf16"
+    spec = wl.small_spec("rows", dtype, d=24, V=40, prompts=prompts, G=G, len_lo=max(1, length // 3), len_hi=length)
+    kw = dict(recompute={}, cache=dict(logits_cache=True), chunks=dict(logits_cache=True), f32={})[mode]
+    w, out, ref = _run_pair(rb, spec, min_ws=mode == "chunks" and G * length <= 256, **kw)
+    _check_pair(rb, spec, out, ref)
