@@ -1071,6 +1071,32 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     io.rms_weight = o.rms_weight;
     io.rms_eps = o.rms_eps;
 
+    // RAPID's estimator over the rows of a region; in one launch, or with one for what concerns whole generations, where it fits
+    const int fits = p.Cmax <= 1 ? small_estimator_fits(N, T, K) : ESTIMATOR_LAUNCHES;
+    auto estimator = [&](const CoefArgs& cc, const int32_t* row_counts, const int32_t* gen_range, int64_t base, int64_t rows) {
+        Span sp(ST_ESTIMATOR, st);
+        EstimatorArgs e;
+        e.logp_cur = logp_cur; e.logp_behav = logp_behav; e.mask = mask; e.N = N; e.T = T; e.K = K;
+        e.rewards = rewards; e.group_ids = group_ids; e.baseline_mode = o.baseline_mode; e.clip_tokens = o.coef_mode == 1;
+        e.per_token = per_token; e.tok_lr = tok_logratio_out; e.s32 = s32; e.adv = adv;
+        e.seqc = seqc; e.row_index = row_index; e.row_counts = row_counts; e.rowg = rowg; e.dev_status = dev_status; e.coef = cc;
+        if (fits == ESTIMATOR_ONE) {
+            launch_small_estimator(e, true, st);
+            return;
+        }
+        launch_seq_logratio(logp_cur, logp_behav, mask, N, T, tok_logratio_out, s64, s32, o.eta, o.coef_mode == 1,
+                            tsum, tmax, gen_range, dev_status, st);
+        if (fits == ESTIMATOR_GENERATIONS) {
+            launch_small_estimator(e, false, st);
+        } else {
+            launch_group_advantage(rewards, group_ids, nullptr, logp_behav ? s64 : nullptr, N, K, o.eta, o.baseline_mode,
+                                   adv, adv64, nullptr, nullptr, nullptr, nullptr, gen_range, dev_status, st, 0.f, 0, gruns);
+            launch_coefficients(cc, st);
+        }
+        launch_row_coefficients(g, cc.g64, seqc, row_index, row_counts, logp_cur, logp_behav, per_token, o.eta,
+                                o.coef_mode == 1, base, rows, rowg, st);
+    };
+
     if (cached) {
         // ---- cached backward: chunk after chunk of whole groups; forward with store, estimator, dHidden, dW
         bf16_t* Hc = at<bf16_t>(ws, p.Hc);
@@ -1130,18 +1156,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                                         dev_status, st);
                 launch_clip_rows(cl, seqc, row_index, cnt, base, p.Rcap, rowg, st);
             } else {
-                Span sp(ST_ESTIMATOR, st);
-                launch_seq_logratio(logp_cur, logp_behav, mask, N, T, tok_logratio_out, s64, s32, o.eta, o.coef_mode == 1,
-                                    tsum, tmax, gen_range, dev_status, st);
-                launch_group_advantage(rewards, group_ids, nullptr, logp_behav ? s64 : nullptr, N, K, o.eta, o.baseline_mode,
-                                       adv, adv64, nullptr, nullptr, nullptr, nullptr, gen_range, dev_status, st, 0.f, 0, gruns);
                 CoefArgs cc = ca;
                 if (p.Cmax > 1) {   // one chunk is the whole batch: coefficients and loss in one pass
                     cc.gen_range = gen_range; cc.lam_state = lam_state; cc.lam_chunk = lam_chunk + c; cc.beta_out = beta_scale;
                 }
-                launch_coefficients(cc, st);
-                launch_row_coefficients(g, ca.g64, seqc, row_index, cnt, logp_cur, logp_behav, per_token, o.eta,
-                                        o.coef_mode == 1, base, p.Rcap, rowg, st);
+                estimator(cc, cnt, gen_range, base, p.Rcap);
             }
             {   // row factors, the sampled tokens' elements, hidden rows scaled by the factors
                 Span sp(ST_DZ, st);
@@ -1243,14 +1262,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         launch_clip_finish(at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), N, counts, loss_out, clip->diag, st);
         launch_clip_rows(cl, seqc, row_index, counts, 0, p.Mmax_pad, rowg, st);
     } else {
-        Span sp(ST_ESTIMATOR, st);
-        launch_seq_logratio(logp_cur, logp_behav, mask, N, T, tok_logratio_out, s64, s32, o.eta, o.coef_mode == 1,
-                            tsum, tmax, nullptr, dev_status, st);
-        launch_group_advantage(rewards, group_ids, nullptr, logp_behav ? s64 : nullptr, N, K, o.eta, o.baseline_mode, adv,
-                               adv64, nullptr, nullptr, nullptr, nullptr, nullptr, dev_status, st, 0.f, 0, gruns);
-        launch_coefficients(ca, st);
-        launch_row_coefficients(g, ca.g64, seqc, row_index, counts, logp_cur, logp_behav, per_token, o.eta,
-                                o.coef_mode == 1, 0, p.Mmax_pad, rowg, st);
+        estimator(ca, counts, nullptr, 0, p.Mmax_pad);
     }
 
     // backward, in row chunks

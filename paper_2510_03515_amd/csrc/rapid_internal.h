@@ -164,6 +164,25 @@ struct CoefArgs {
     const int32_t* gen_range; double* lam_state; double* lam_chunk; float* beta_out; int write_g;
 };
 void launch_coefficients(const CoefArgs& a, hipStream_t st);
+// The estimator of a call that works on one chunk of rows from row 0 on, in one block for a batch that fits (see
+// small_estimator_kernel): all of it, or what lies between the log ratios and the rows' coefficients.
+// tok_lr may be NULL; of coef, what the caller hands in and the outputs count, and (not all of it) s64, tsum, tmax, g, g64.
+struct EstimatorArgs {
+    const float *logp_cur, *logp_behav;    // behav NULL: ratios 1
+    const uint8_t* mask;
+    int64_t N, T, K;
+    const float* rewards;
+    const int32_t* group_ids;
+    int baseline_mode, clip_tokens, per_token;
+    float *tok_lr, *s32, *adv;
+    const int32_t *seqc, *row_index, *row_counts;
+    float* rowg;
+    int32_t* dev_status;
+    CoefArgs coef;
+};
+enum { ESTIMATOR_LAUNCHES = 0, ESTIMATOR_GENERATIONS, ESTIMATOR_ONE };
+int small_estimator_fits(int64_t N, int64_t T, int64_t K);
+void launch_small_estimator(const EstimatorArgs& a, bool tokens, hipStream_t st);
 // rowg[j] = dL/dlogp of compact row j in [row0, row0 + rows_max) (0 for padding rows): g of its generation,
 // times its own ratio if per_token
 void launch_row_coefficients(const float* g, const double* g64, const int32_t* seqc, const int32_t* row_index,

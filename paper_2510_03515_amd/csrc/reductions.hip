@@ -181,11 +181,11 @@ __device__ __forceinline__ int block_scan(const int32_t* v, int64_t N, int32_t* 
 // per group.
 //
 // IN_LDS: N and K at most PLAN_LDS; what the plan makes for itself stays in the LDS, so that the steps between its
-// barriers are not trips to memory (64 generations 6.4 -> 4.0 us, a step in 7 chunks 66 -> 13 us).  LENGTHS: it counts
-// the generations' tokens too, a launch less; one block reads the whole mask then, which up to PLAN_MASK positions
-// takes it no longer than the launch would.  Else seq_len_kernel has counted them, and has cleared runs and live_group
+// barriers are not trips to memory.  LENGTHS: it counts the generations' tokens too, a launch less; one block reads the
+// whole mask then, which up to PLAN_MASK positions takes it no longer than the launch would (whole steps with either: 64 x 250 positions 92
+// and 94 us, 216 x 104 122 and 122, 560 x 53 145 and 141, 1024 x 31 155 and 150).  Else seq_len_kernel has counted them, and has cleared runs and live_group
 // where they are in memory.
-constexpr int PLAN_LDS = 1024, PLAN_MASK = 32768;
+constexpr int PLAN_LDS = 1024, PLAN_MASK = 16384;
 template <bool IN_LDS, bool LENGTHS>
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a, const uint8_t* __restrict__ mask, int64_t T) {
     static_assert(IN_LDS || !LENGTHS, "lengths are counted into the LDS");
@@ -214,20 +214,20 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a, const uint8_t* _
             for (int n = threadIdx.x; n < N; n += blockDim.x) s_gid[n] = a.gid[n];
     }
     if constexpr (LENGTHS) {
-        // 2^lanes_log2 lanes per generation, four loads of each in flight
+        // 2^lanes_log2 lanes per generation, eight loads of each in flight
         const bool words = (T & 3) == 0 && ((uintptr_t)mask & 3) == 0;
-        const int per = (int)(words ? T / 4 : T), lanes_log2 = per <= 32 ? 3 : per <= 64 ? 4 : per <= 128 ? 5 : 6, lanes = 1 << lanes_log2;
+        const int per = (int)(words ? T / 4 : T), lanes_log2 = per <= 64 ? 3 : per <= 128 ? 4 : per <= 256 ? 5 : 6, lanes = 1 << lanes_log2;
         for (int64_t n = threadIdx.x >> lanes_log2; n < N; n += blockDim.x >> lanes_log2) {
             const uint8_t* row = mask + n * T;
             int cnt = 0;
             if (words) {
-#pragma unroll 4
+#pragma unroll 8
                 for (int t = threadIdx.x & (lanes - 1); t < per; t += lanes) {
                     const uint32_t w = ((const uint32_t*)row)[t];
                     cnt += __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);
                 }
             } else {
-#pragma unroll 4
+#pragma unroll 8
                 for (int t = threadIdx.x & (lanes - 1); t < per; t += lanes) cnt += row[t] != 0;
             }
             for (int o = lanes >> 1; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, WAVE);
@@ -535,42 +535,57 @@ __global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restr
     if (lse_out) lse_out[pos] = lse_f;
 }
 
-// one wave per generation: token-level log ratios and their sum over the generation; for the
+// one block per generation: token-level log ratios and their sum over the generation; for the
 // token-level outer weight also sum_t c_{n,t} and max_t log c_{n,t} of the generation's valid tokens
-// (c = the token's ratio, clipped at eta if clip_tokens), tsum/tmax may be NULL
-__global__ void seq_logratio_kernel(const float* __restrict__ logp_cur, const float* __restrict__ logp_behav,
+// (c = the token's ratio, clipped at eta if clip_tokens), tsum/tmax may be NULL.
+// A wave's loop is a chain of trips to memory (4 x 64 positions each), so the waves of a long sequence share it: 4 x 1024
+// positions by one wave each, one load after the other, 14.5 us, 5.4 now.  How a sequence is shared out depends on T alone.
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void seq_logratio_kernel(const float* __restrict__ logp_cur, const float* __restrict__ logp_behav,
                                     const uint8_t* __restrict__ mask, int64_t N, int64_t T,
                                     float* __restrict__ tok_lr, double* __restrict__ s64,
                                     float* __restrict__ s32, double log_eta, int clip_tokens,
                                     double* __restrict__ tsum, double* __restrict__ tmax,
                                     const int32_t* __restrict__ gen_range, int32_t* __restrict__ dev_status) {
+    __shared__ double sm[16];
     const int64_t n = blockIdx.x;
-    if (n >= N) return;
     if (gen_range && (n < gen_range[0] || n >= gen_range[1])) return;
     double acc = 0.0, csum = 0.0, cmax = -INFINITY;
     bool bad = false;
-    for (int64_t t = threadIdx.x; t < T; t += WAVE) {
-        const int64_t i = n * T + t;
-        double dlt = 0.0;
-        const bool valid = mask[i] != 0;
-        if (valid && logp_behav != nullptr) {   // no behaviour log-probs: on-policy, every ratio is 1
-            const float lb = logp_behav[i];
-            if (isfinite(lb)) dlt = (double)logp_cur[i] - (double)lb;
-            else bad = true;
+    constexpr int U = 4;
+    for (int64_t t0 = threadIdx.x; t0 < T; t0 += U * blockDim.x) {
+        bool valid[U];
+        float cur[U], beh[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t t = t0 + u * blockDim.x, i = n * T + (t < T ? t : t0);
+            valid[u] = mask[i] != 0;
+            cur[u] = logp_cur[i];
+            beh[u] = logp_behav ? logp_behav[i] : 0.f;
         }
-        if (tok_lr) tok_lr[i] = (float)dlt;
-        acc += dlt;
-        if (valid) {
-            const double lc = clip_tokens ? fmin(dlt, log_eta) : dlt;
-            csum += exp(lc);
-            cmax = fmax(cmax, lc);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t t = t0 + u * blockDim.x;
+            if (t >= T) break;
+            double dlt = 0.0;
+            if (valid[u] && logp_behav != nullptr) {   // no behaviour log-probs: on-policy, every ratio is 1
+                if (isfinite(beh[u])) dlt = (double)cur[u] - (double)beh[u];
+                else bad = true;
+            }
+            if (tok_lr) tok_lr[n * T + t] = (float)dlt;
+            acc += dlt;
+            if (tsum && valid[u]) {
+                const double lc = clip_tokens ? fmin(dlt, log_eta) : dlt;
+                csum += exp(lc);
+                cmax = fmax(cmax, lc);
+            }
         }
     }
-    acc = wave_sum(acc);
-    if (__any(bad) && threadIdx.x == 0 && dev_status) atomicOr(dev_status, RAPID_STATUS_NONFINITE_LOGP);
+    if (__any(bad) && threadIdx.x % WAVE == 0 && dev_status) atomicOr(dev_status, RAPID_STATUS_NONFINITE_LOGP);
+    acc = ONE_WAVE ? wave_sum(acc) : block_sum(acc, sm);
     if (tsum) {
-        csum = wave_sum(csum);
-        cmax = wave_max(cmax);
+        csum = ONE_WAVE ? wave_sum(csum) : block_sum(csum, sm);
+        cmax = ONE_WAVE ? wave_max(cmax) : block_max(cmax, sm);
     }
     if (threadIdx.x == 0) {
         if (s64) s64[n] = acc;
@@ -682,6 +697,26 @@ __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __res
     }
 }
 
+// g_n = -(loss_scale/N) c_n A_n exp(-lam), c_n the generation's (clipped) ratio; per_token: without the ratio
+__device__ inline double generation_coefficient(const CoefArgs& a, bool per_token, double s, double adv, double log_eta,
+                                                double log_loss_scale, double logN, double lam) {
+    if (adv == 0.0) return 0.0;
+    const double lc = per_token ? 0.0 : (a.coef_mode == 0 ? s : fmin(s, log_eta));
+    return (adv > 0.0 ? -1.0 : 1.0) * exp(lc + log(fabs(adv)) + log_loss_scale - logN - lam);
+}
+__device__ inline void write_diag(const CoefArgs& a, const double (&sums)[4], double maxs, double lam) {
+    a.loss_out[0] = (float)sums[0];
+    if (a.diag) {
+        a.diag->n_tokens = a.counts[CNT_M];
+        a.diag->n_clipped = (int32_t)sums[3];
+        a.diag->n_sequences = (int32_t)a.N;
+        a.diag->mean_log_w = (float)(sums[1] / (double)a.N);
+        a.diag->mean_abs_log_w = (float)(sums[2] / (double)a.N);
+        a.diag->max_abs_s = (float)maxs;
+        a.diag->grad_log_scale = (float)lam;
+    }
+}
+
 // single block: coefficients g_n, the loss, diagnostics (the three uses are described at CoefArgs).
 // Generation-level outer weight (tsum NULL): g_n = -(loss_scale/N) c_n A_n, loss = sum_n g_n.
 // Token-level (tsum, tmax given): g_n is the generation's factor -(loss_scale/N) A_n, a token's
@@ -730,13 +765,7 @@ __global__ __launch_bounds__(1024) void coefficients_kernel(CoefArgs a, double l
         if (a.coef_override) {
             gn = (double)a.coef_override[n];
         } else {
-            const double av = advantage(n);
-            if (av != 0.0) {
-                const double lc = per_token ? 0.0 : (a.coef_mode == 0 ? s : fmin(s, log_eta));
-                gn = (av > 0.0 ? -1.0 : 1.0) * exp(lc + log(fabs(av)) + log_loss_scale - logN - lam);
-            } else {
-                gn = 0.0;
-            }
+            gn = generation_coefficient(a, per_token, s, advantage(n), log_eta, log_loss_scale, logN, lam);
         }
         if (a.write_g) {
             a.g[n] = (float)gn;
@@ -752,19 +781,209 @@ __global__ __launch_bounds__(1024) void coefficients_kernel(CoefArgs a, double l
     if (chunk_pass) return;
     double sums[4] = {loss, slw, salw, nclip};
     block_sums<4>(sums, sm);
-    loss = sums[0]; slw = sums[1]; salw = sums[2]; nclip = sums[3];
     maxs = block_max(maxs, sm);
-    if (threadIdx.x == 0) {
-        a.loss_out[0] = (float)loss;
-        if (a.diag) {
-            a.diag->n_tokens = a.counts[CNT_M];
-            a.diag->n_clipped = (int32_t)nclip;
-            a.diag->n_sequences = (int32_t)N;
-            a.diag->mean_log_w = (float)(slw / (double)N);
-            a.diag->mean_abs_log_w = (float)(salw / (double)N);
-            a.diag->max_abs_s = (float)maxs;
-            a.diag->grad_log_scale = (float)lam;
+    if (threadIdx.x == 0) write_diag(a, sums, maxs, lam);
+}
+
+// The whole estimator of a small batch in one block: log ratios of the generations, group advantages, coefficients, loss and
+// diagnostics, the rows' coefficients; what seq_logratio_kernel, group_advantage_kernel, coefficients_kernel and
+// row_coefficients_kernel do (same order of summation over the generations) in four dependent launches of 3 to 5 us each, next
+// to nothing of it work.  At most ESTIMATOR_LDS generations and groups, which stay in the LDS, and ESTIMATOR_POSITIONS positions:
+// one compute unit takes about 1 us per 1000 of them.  TOKENS false: more positions; the log ratios are there (s64, and tsum,
+// tmax) and the rows' coefficients are left to row_coefficients_kernel, so that two launches become one.  Whole steps, in one
+// block against this split: 64 x 8 positions 46 and 52 us, 64 x 64 58 and 61, 128 x 64 69 and 70, 64 x 250 96 and 92.
+constexpr int ESTIMATOR_LDS = 1024, ESTIMATOR_POSITIONS = 8192;
+template <bool PER_TOKEN, bool TOKENS>
+__global__ __launch_bounds__(1024) void small_estimator_kernel(EstimatorArgs a, double log_eta, double log_loss_scale) {
+    constexpr int L = ESTIMATOR_LDS, LT = PER_TOKEN ? L : 1;
+    __shared__ double sm[16 * 4], s_s[L], s_w[L], s_adv[L], s_tsum[LT], s_tmax[LT], s_part[3][16];
+    double* const s_g = s_w;     // the coefficients take the weights' place
+    __shared__ float s_r[L];
+    __shared__ int32_t s_gid[L], s_first[L], s_end[L];
+    __shared__ int s_split, s_longest, s_bits;
+    const int N = (int)a.N, K = (int)a.K, tid = threadIdx.x, threads = blockDim.x;
+    const int64_t T = a.T;
+    for (int n = tid; n < N; n += threads) {
+        s_gid[n] = a.group_ids[n];
+        s_r[n] = a.rewards[n];
+    }
+    for (int k = tid; k < K; k += threads) s_first[k] = s_end[k] = -1;
+    if (tid == 0) s_split = s_longest = s_bits = 0;
+    int bits = 0;
+
+    // log ratios: teams of 8 to 64 lanes, or (few generations) several waves per generation
+    int waves_log2 = 0;
+    if constexpr (TOKENS) {
+        const int lanes_log2 = T <= 64 ? 3 : T <= 128 ? 4 : T <= 256 ? 5 : 6, lanes = 1 << lanes_log2;
+        while (waves_log2 < 4 && (N << (waves_log2 + 1)) <= threads / WAVE && T >= (512 << waves_log2)) ++waves_log2;
+        for (int u = tid >> lanes_log2; u < N << waves_log2; u += threads >> lanes_log2) {
+            const int n = u >> waves_log2, part = u & ((1 << waves_log2) - 1);
+            const int64_t begin = T * part >> waves_log2, end = T * (part + 1) >> waves_log2;
+            double acc = 0.0, csum = 0.0, cmax = -INFINITY;
+            constexpr int U = 8;     // positions per lane whose loads are in flight together
+            for (int64_t t0 = begin + (tid & (lanes - 1)); t0 < end; t0 += U * lanes) {
+                bool valid[U];
+                float cur[U], beh[U];
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int64_t t = t0 + q * lanes, i = n * T + (t < end ? t : t0);
+                    valid[q] = a.mask[i] != 0;
+                    cur[q] = a.logp_cur[i];
+                    beh[q] = a.logp_behav ? a.logp_behav[i] : 0.f;      // none: on-policy, every ratio is 1
+                }
+#pragma unroll
+                for (int q = 0; q < U; ++q) {
+                    const int64_t t = t0 + q * lanes;
+                    if (t >= end) break;
+                    double dlt = 0.0;
+                    if (valid[q] && a.logp_behav) {
+                        if (isfinite(beh[q])) dlt = (double)cur[q] - (double)beh[q];
+                        else bits |= RAPID_STATUS_NONFINITE_LOGP;
+                    }
+                    if (a.tok_lr) a.tok_lr[n * T + t] = (float)dlt;
+                    acc += dlt;
+                    if constexpr (PER_TOKEN) {
+                        if (valid[q]) {
+                            const double lc = a.clip_tokens ? fmin(dlt, log_eta) : dlt;
+                            csum += exp(lc);
+                            cmax = fmax(cmax, lc);
+                        }
+                    }
+                }
+            }
+            for (int o = lanes >> 1; o > 0; o >>= 1) {
+                acc += __shfl_xor(acc, o, WAVE);
+                if constexpr (PER_TOKEN) {
+                    csum += __shfl_xor(csum, o, WAVE);
+                    cmax = fmax(cmax, __shfl_xor(cmax, o, WAVE));
+                }
+            }
+            if ((tid & (lanes - 1)) == 0) {
+                if (waves_log2 == 0) s_s[n] = acc; else s_part[0][u] = acc;
+                if constexpr (PER_TOKEN) {
+                    if (waves_log2 == 0) { s_tsum[n] = csum; s_tmax[n] = cmax; } else { s_part[1][u] = csum; s_part[2][u] = cmax; }
+                }
+            }
         }
+    } else {
+        for (int n = tid; n < N; n += threads) {
+            s_s[n] = a.coef.s64[n];
+            if constexpr (PER_TOKEN) { s_tsum[n] = a.coef.tsum[n]; s_tmax[n] = a.coef.tmax[n]; }
+        }
+    }
+    __syncthreads();
+    for (int n = tid; n < N; n += threads) {
+        if (waves_log2 > 0) {
+            double acc = 0.0, csum = 0.0, cmax = -INFINITY;
+            for (int u = n << waves_log2; u < (n + 1) << waves_log2; ++u) {
+                acc += s_part[0][u];
+                csum += s_part[1][u];
+                cmax = fmax(cmax, s_part[2][u]);
+            }
+            s_s[n] = acc;
+            if constexpr (PER_TOKEN) { s_tsum[n] = csum; s_tmax[n] = cmax; }
+        }
+        const double s = s_s[n];
+        if (TOKENS && a.s32) a.s32[n] = (float)s;
+        s_w[n] = a.logp_behav ? exp(fmin(s, log_eta)) : 1.0;
+        s_adv[n] = 0.0;
+        // runs of equal group id
+        const int32_t g = s_gid[n];
+        if (!isfinite(s_r[n])) { bits |= RAPID_STATUS_NONFINITE_REWARD; s_r[n] = 0.f; }
+        if (a.logp_behav && isnan(s)) bits |= RAPID_STATUS_NONFINITE_LOGP;
+        if (g < 0 || g >= K) { bits |= RAPID_STATUS_BAD_GROUP; continue; }
+        if ((n == 0 || s_gid[n - 1] != g) && atomicExch(&s_first[g], n) >= 0) s_split = 1;
+        if (n == N - 1 || s_gid[n + 1] != g) s_end[g] = n + 1;
+    }
+    if (bits) atomicOr(&s_bits, bits);
+    __syncthreads();
+    for (int k = tid; k < K; k += threads)
+        if (s_first[k] >= 0) atomicMax(&s_longest, s_end[k] - s_first[k]);
+    __syncthreads();
+
+    // group advantages: a team of lanes per group, over its run or (some group has several) over the whole batch
+    const bool split = s_split != 0;
+    const int team_log2 = split || s_longest > 16 ? 6 : 4, team = 1 << team_log2;
+    for (int k = tid >> team_log2; k < K; k += threads >> team_log2) {
+        const int begin = split ? 0 : s_first[k] < 0 ? 0 : s_first[k], end = split ? N : s_end[k];
+        double cnt = 0.0, sum_wr = 0.0;
+        for (int n = begin + (tid & (team - 1)); n < end; n += team) {
+            if (s_gid[n] != k) continue;
+            cnt += 1.0;
+            sum_wr += s_w[n] * (double)s_r[n];
+        }
+        for (int o = team >> 1; o > 0; o >>= 1) {
+            cnt += __shfl_xor(cnt, o, WAVE);
+            sum_wr += __shfl_xor(sum_wr, o, WAVE);
+        }
+        for (int n = begin + (tid & (team - 1)); n < end; n += team) {
+            if (s_gid[n] != k) continue;
+            const double r = (double)s_r[n], rest = sum_wr - s_w[n] * r;
+            const double b = a.baseline_mode == 0 ? sum_wr / cnt : a.baseline_mode == 1 ? rest / cnt : cnt > 1.0 ? rest / (cnt - 1.0) : 0.0;
+            s_adv[n] = r - b;
+        }
+    }
+    __syncthreads();
+
+    // coefficients, loss, diagnostics (see coefficients_kernel)
+    const CoefArgs& c = a.coef;
+    const double logN = log((double)N);
+    const bool per_token = PER_TOKEN && !c.coef_override;
+    double lam = 0.0;
+    if (!c.coef_override && c.normalized) {
+        double mx = -INFINITY;
+        for (int n = tid; n < N; n += threads) {
+            const double av = s_adv[n];
+            if (av == 0.0) continue;
+            const double lc = per_token ? s_tmax[PER_TOKEN ? n : 0] : (c.coef_mode == 0 ? s_s[n] : fmin(s_s[n], log_eta));
+            mx = fmax(mx, lc + log(fabs(av)) + log_loss_scale - logN);
+        }
+        mx = block_max(mx, sm);
+        lam = (mx == -INFINITY) ? 0.0 : mx;
+    }
+    double sums[4] = {0.0, 0.0, 0.0, 0.0}, maxs = 0.0;
+    for (int n = tid; n < N; n += threads) {
+        const double s = s_s[n], lw = fmin(s, log_eta);
+        if (a.adv) a.adv[n] = (float)s_adv[n];
+        const double gn = c.coef_override ? (double)c.coef_override[n]
+                                          : generation_coefficient(c, per_token, s, s_adv[n], log_eta, log_loss_scale, logN, lam);
+        s_g[n] = gn;
+        if (!TOKENS) { c.g[n] = (float)gn; c.g64[n] = gn; }
+        sums[0] += per_token ? (gn != 0.0 ? gn * s_tsum[PER_TOKEN ? n : 0] : 0.0) : gn;
+        sums[1] += lw;
+        sums[2] += fabs(lw);
+        sums[3] += s > log_eta ? 1.0 : 0.0;
+        maxs = fmax(maxs, fabs(s));
+    }
+    block_sums<4>(sums, sm);     // its barriers also make s_g visible
+    // the rows' coefficients (rows past M up to the row tile: 0)
+    constexpr int UR = 8;
+    const int M = TOKENS ? a.row_counts[CNT_M] : 0, Mr = TOKENS ? a.row_counts[CNT_MR] : 0;
+    for (int j0 = tid; j0 < Mr; j0 += UR * threads) {
+        int32_t gen[UR];
+#pragma unroll
+        for (int q = 0; q < UR; ++q) gen[q] = a.seqc[j0 + q * threads < Mr ? j0 + q * threads : j0];
+#pragma unroll
+        for (int q = 0; q < UR; ++q) {
+            const int j = j0 + q * threads;
+            if (j >= Mr) break;
+            double v = j < M ? s_g[gen[q]] : 0.0;
+            if (per_token && j < M) {
+                double dlt = 0.0;
+                if (a.logp_behav) {
+                    const int32_t pos = a.row_index[j];
+                    const float lb = a.logp_behav[pos];
+                    if (isfinite(lb)) dlt = (double)a.logp_cur[pos] - (double)lb;
+                }
+                v *= exp(a.clip_tokens ? fmin(dlt, log_eta) : dlt);
+            }
+            a.rowg[j] = (float)v;
+        }
+    }
+    maxs = block_max(maxs, sm);
+    if (tid == 0) {
+        write_diag(c, sums, maxs, lam);
+        if (s_bits && a.dev_status) atomicOr(a.dev_status, s_bits);
     }
 }
 
@@ -841,7 +1060,7 @@ inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) /
 void launch_plan(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan, hipStream_t st) {
     const bool in_lds = N <= PLAN_LDS && plan.K <= PLAN_LDS;
     if (in_lds && N * T <= PLAN_MASK) {
-        const int64_t lanes = T <= 64 ? 8 : T <= 256 ? 16 : 64;      // about what the kernel gives a generation
+        const int64_t lanes = T <= 256 ? 8 : T <= 512 ? 16 : 64;     // about what the kernel gives a generation
         plan_kernel<true, true><<<1, block_threads(N * lanes, 1024), 0, st>>>(plan, mask, T);
         return;
     }
@@ -887,8 +1106,9 @@ void launch_seq_logratio(const float* logp_cur, const float* logp_behav, const u
                          int64_t T, float* tok_logratio_out, double* s64, float* s32, float eta, int clip_tokens,
                          double* tsum, double* tmax, const int32_t* gen_range, int32_t* dev_status, hipStream_t st) {
     const double log_eta = (eta > 0.f && std::isfinite(eta)) ? log((double)eta) : (double)INFINITY;
-    seq_logratio_kernel<<<(unsigned)N, WAVE, 0, st>>>(logp_cur, logp_behav, mask, N, T, tok_logratio_out, s64,
-                                                      s32, log_eta, clip_tokens, tsum, tmax, gen_range, dev_status);
+    const unsigned threads = row_threads(T);
+    (threads == WAVE ? &seq_logratio_kernel<true> : &seq_logratio_kernel<false>)<<<(unsigned)N, threads, 0, st>>>(
+        logp_cur, logp_behav, mask, N, T, tok_logratio_out, s64, s32, log_eta, clip_tokens, tsum, tmax, gen_range, dev_status);
 }
 
 void launch_group_advantage(const float* rewards, const int32_t* group_ids, const float* s32, const double* s64,
@@ -1036,6 +1256,20 @@ void launch_clip_finish(const double* loss_n, const double* clipped_n, const dou
 void launch_coefficients(const CoefArgs& a, hipStream_t st) {
     const double log_eta = (a.eta > 0.f && std::isfinite(a.eta)) ? log((double)a.eta) : (double)INFINITY;
     coefficients_kernel<<<1, block_threads(a.N, 1024), 0, st>>>(a, log_eta, log((double)a.loss_scale));
+}
+
+int small_estimator_fits(int64_t N, int64_t T, int64_t K) {
+    if (N > ESTIMATOR_LDS || K > ESTIMATOR_LDS) return ESTIMATOR_LAUNCHES;
+    return N * T <= ESTIMATOR_POSITIONS ? ESTIMATOR_ONE : ESTIMATOR_GENERATIONS;
+}
+void launch_small_estimator(const EstimatorArgs& a, bool tokens, hipStream_t st) {
+    const float eta = a.coef.eta;
+    const double log_eta = (eta > 0.f && std::isfinite(eta)) ? log((double)eta) : (double)INFINITY;
+    const int64_t want = tokens ? a.N * a.T / 4 : a.N;        // threads beyond this find next to nothing to do
+    const unsigned threads = want >= 1024 ? 1024u : want >= 512 ? 512u : 256u;
+    auto* kernel = tokens ? (a.per_token ? &small_estimator_kernel<true, true> : &small_estimator_kernel<false, true>)
+                          : (a.per_token ? &small_estimator_kernel<true, false> : &small_estimator_kernel<false, false>);
+    kernel<<<1, threads, 0, st>>>(a, log_eta, log((double)a.coef.loss_scale));
 }
 
 void launch_row_coefficients(const float* g, const double* g64, const int32_t* seqc, const int32_t* row_index,

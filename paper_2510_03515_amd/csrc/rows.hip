@@ -217,7 +217,8 @@ __global__ __launch_bounds__(256) void rows_by_row_kernel(RowsArgs a) {
 template <int PACK, bool GATHER>
 void launch_t(const RowsArgs& a, bool by_position, int64_t rows, hipStream_t st) {
     if (by_position) {
-        const int per_wave = a.N * a.T <= 32768 ? 1 : 4;      // small batches: a wave per position, all trips side by side
+        // small batches: a wave per position, all trips side by side; without rows to pack there is next to nothing per position
+        const int per_wave = PACK == PACK_NONE ? 16 : a.N * a.T <= 32768 ? 1 : 4;
         const int64_t per_generation = (a.T + 4 * per_wave - 1) / (4 * per_wave), fill = a.tokc ? (int64_t)a.entries * 16 : 0;
         rows_by_position_kernel<PACK, GATHER><<<(unsigned)(a.N * per_generation + fill), 256, 0, st>>>(a, per_wave, (int)per_generation);
     } else if constexpr (PACK != PACK_NONE) {

@@ -6,6 +6,7 @@ import torch
 
 from paper_2510_03515_amd import workloads as wl
 from oracle import rapid_oracle as orc
+import parity_bounds as pb
 from test_gpu_parity import _check_pair, _dh_ok, _dw_ok, _make, _np, _oracle_inputs, _rel, _run_pair, rb  # noqa: F401  (rb is the library fixture)
 
 pytestmark = pytest.mark.gpu
@@ -384,3 +385,34 @@ def test_plan_and_rows_of_a_batch(rb, prompts, G, length, mode):
     kw = dict(recompute={}, cache=dict(logits_cache=True), chunks=dict(logits_cache=True), f32={})[mode]
     w, out, ref = _run_pair(rb, spec, min_ws=mode == "chunks" and G * length <= 256, **kw)
     _check_pair(rb, spec, out, ref)
+
+
+@pytest.mark.parametrize("prompts,G,length", [
+    (7, 5, 40),       # the estimator in one block, teams of 8 lanes
+    (3, 17, 130),     # teams of 32 lanes, groups of more than 16
+    (1, 2, 1030),     # two waves per generation and more
+    (2, 3, 1500),     # 9000 positions: the log ratios in a launch of their own, by several waves each
+    (70, 4, 33),      # 9240 positions of short generations
+])
+@pytest.mark.parametrize("kw", [
+    dict(baseline_mode=2, coef_mode=1, eta=1.05), dict(baseline_mode=1, normalized_grads=True), dict(ratio_level=1, eta=1.1),
+    dict(ratio_level=1, normalized_grads=True, coef_mode=1),
+])
+@pytest.mark.parametrize("scattered", [False, True])
+def test_estimator_of_a_small_batch(rb, prompts, G, length, kw, scattered):
+    print(f"estimator {prompts} x {G} x {length} {kw} scattered {scattered}", flush=True)
+    spec = wl.small_spec("estimator", "bf16", d=24, V=40, prompts=prompts, G=G, len_lo=max(1, length // 2), len_hi=length, reward="uniform")
+    w, g = _make(spec)
+    gid = w["group_ids"]
+    if scattered:
+        gid = gid[torch.randperm(gid.numel(), generator=torch.Generator().manual_seed(1))].contiguous()
+    H, W, tok, mask = _oracle_inputs(w)
+    logp_b, _ = rb.rapid_logprob_fwd(g["hidden"], g["W_old"], g["tokens"], g["mask"])
+    out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], g["W"], g["tokens"], g["mask"], logp_b, g["rewards"], gid.cuda(), w["K"], **kw)
+    torch.cuda.synchronize()
+    ref = orc.iw_pg_loss_fwd_bwd(H, W, tok, mask, _np(logp_b), _np(w["rewards"]), _np(gid), w["K"], **kw)
+    ref["slack"] = pb.coefficient_slack(ref, _np(w["rewards"]), mask)
+    _check_pair(rb, spec, out, ref)
+    # the same call's outputs from the stand-alone entry points
+    s, tl = rb.rapid_seq_logratio(out.logp_cur, logp_b, g["mask"], want_tokens=True)
+    assert torch.equal(tl, out.tok_logratio) and torch.allclose(s, out.seq_logratio, rtol=2.0 ** -23, atol=0)
