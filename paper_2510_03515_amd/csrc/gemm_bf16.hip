@@ -987,7 +987,7 @@ __global__ __launch_bounds__(64 * F2::NW, (F2::NW == 4 && F2::S::WJ == 2) ? 2 : 
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.row0 >= Mr) return;
     // the order covers the row tiles that hold tokens only
-    const int tilesM = min(a.tilesM * (256 / S::BJ), (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
+    const int tilesM = min(a.tilesM, (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
     const int ksteps = (int)(a.dpad / F2::K_STEP);
     for (int pid = blockIdx.x, ids = ids_for(a.tilesV, tilesM); pid < ids; pid += gridDim.x) {
         const TileId t = map_tile(pid, a.tilesV, tilesM, a.gi);
@@ -1177,17 +1177,17 @@ __device__ __forceinline__ void dh_contract(const DhArgs& a, const TileId& t, in
     mainloop<S, false, false, false, false, Pace>(w, z, k1 - k0, lds, acc, pace);
 }
 
+// what workgroup `block` of `grid` does
 template <class S, int WM>
-__global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
+__device__ __forceinline__ void dh_work(const DhArgs& a, int block, int grid, char* lds) {
     constexpr int WI = S::WI, WJ = S::WJ;
-    extern __shared__ __attribute__((aligned(128))) char lds[];
     const int tilesD = (int)(a.dpadR / S::BI);
     const int M = a.counts[CNT_M];
     if (a.m0 >= M) return;
     // the order (and with it the split over the XCDs) covers the row tiles that hold tokens only: a
     // short last chunk would otherwise leave whole XCDs with nothing but empty tiles
     const int tilesM = dh_row_tiles<S>(a, M);
-    const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
+    const int x = block & 7, w = block >> 3;
     const int ktiles = dh_ksteps(a);
     const TileShare sh(tilesD * tilesM, grid, ktiles, a.part != nullptr);
     const int gi = a.gi > 0 ? a.gi : tilesD;
@@ -1219,18 +1219,23 @@ __global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
         store_unit<S>(a.part, u, acc);
     }
 }
+template <class S, int WM>
+__global__ __launch_bounds__(S::NT) void dh_kernel(DhArgs a) {
+    extern __shared__ __attribute__((aligned(128))) char lds[];
+    dh_work<S, WM>(a, blockIdx.x, gridDim.x, lds);
+}
 
-// adds the pieces of the tiles that dh_kernel cut (grid_of_dh: the number of workgroups of that launch) and stores
-// them; workgroup (t, b) does the 32 x 32 block b of every wave of tile t of the last round
+// adds the pieces of the tiles that dh_work cut (grid_of_dh: the number of its workgroups) and stores
+// them; workgroup (tpos, block) does the 32 x 32 block `block` of every wave of tile tpos of the last round
 template <class S>
-__global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_dh) {
-    constexpr int WI = S::WI, WJ = S::WJ;
+__device__ __forceinline__ void dh_add_pieces(const DhArgs& a, int grid_of_dh, int tpos, int block) {
+    constexpr int WJ = S::WJ, WI = S::WI;
     const int tilesD = (int)(a.dpadR / S::BI);
     const int M = a.counts[CNT_M];
     if (a.m0 >= M) return;
     const int tilesM = dh_row_tiles<S>(a, M);
     const TileShare sh(tilesD * tilesM, grid_of_dh, dh_ksteps(a), true);
-    const int tpos = blockIdx.x, ib = blockIdx.y / WJ, jb = blockIdx.y % WJ;
+    const int ib = block / WJ, jb = block % WJ;
     if (!sh.cut || tpos >= sh.rem) return;
     const TileId t = tile_of_vid(sh.full_rounds * grid_of_dh + tpos, tilesD, tilesM, a.gi > 0 ? a.gi : tilesD);
     const Lane<S> L;
@@ -1247,6 +1252,11 @@ __global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_
         if (i0 < a.d)
             *(uint2*)(out + i0) = pack_bf16x4(cj * sum[q * 4], cj * sum[q * 4 + 1], cj * sum[q * 4 + 2], cj * sum[q * 4 + 3]);
     }
+}
+
+template <class S>
+__global__ __launch_bounds__(S::NT) void dh_reduce_kernel(DhArgs a, int grid_of_dh) {
+    dh_add_pieces<S>(a, grid_of_dh, blockIdx.x, blockIdx.y);
 }
 
 // ------------------------------------------------------------------------------------------ dw
@@ -1363,15 +1373,14 @@ __device__ __forceinline__ void dw_store(char* lds, const DwOut& out, int64_t i_
 }
 
 template <class S, bool VD, bool DEEP = false>
-__global__ __launch_bounds__(S::NT) void dw_kernel(DwArgs a) {
+__device__ __forceinline__ void dw_work(const DwArgs& a, int block, int grid, char* lds) {
     constexpr int WI = S::WI, WJ = S::WJ;
-    extern __shared__ __attribute__((aligned(128))) char lds[];
     const int tilesV = (int)(a.Vpad / (VD ? S::BJ : S::BI)), tilesD = (int)(a.dpadR / (VD ? S::BI : S::BJ));
     const int Mr = a.counts[CNT_MR];
     int64_t rows = (int64_t)Mr - a.m0;
     rows = rows < 0 ? 0 : (rows > a.Mc ? a.Mc : rows);
     if (rows == 0 && a.beta && !a.dW16) return;   // nothing to add
-    const int x = blockIdx.x & 7, w = blockIdx.x >> 3, grid = gridDim.x;
+    const int x = block & 7, w = block >> 3;
     const int ktiles = (int)(rows / K_TILE);
     const TileShare sh(tilesV * tilesD, grid, ktiles, a.part != nullptr);
     const DwOut out(a, VD);
@@ -1403,16 +1412,21 @@ __global__ __launch_bounds__(S::NT) void dw_kernel(DwArgs a) {
         if (sh.cut) store_unit<S>(a.part, u, acc); else finish(t, acc);
     }
 }
+template <class S, bool VD, bool DEEP = false>
+__global__ __launch_bounds__(S::NT) void dw_kernel(DwArgs a) {
+    extern __shared__ __attribute__((aligned(128))) char lds[];
+    dw_work<S, VD, DEEP>(a, blockIdx.x, gridDim.x, lds);
+}
 
-// adds the pieces of the tiles that dw_kernel cut and stores them (see dh_reduce_kernel)
+// adds the pieces of the tiles that dw_work cut and stores them (see dh_add_pieces)
 template <class S, bool VD>
-__global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_dw) {
+__device__ __forceinline__ void dw_add_pieces(const DwArgs& a, int grid_of_dw, int tpos, int block) {
     const int tilesV = (int)(a.Vpad / (VD ? S::BJ : S::BI)), tilesD = (int)(a.dpadR / (VD ? S::BI : S::BJ));
     const int Mr = a.counts[CNT_MR];
     int64_t rows = (int64_t)Mr - a.m0;
     rows = rows < 0 ? 0 : (rows > a.Mc ? a.Mc : rows);
     const TileShare sh(tilesV * tilesD, grid_of_dw, (int)(rows / K_TILE), true);
-    const int tpos = blockIdx.x, ib = blockIdx.y / S::WJ, jb = blockIdx.y % S::WJ;
+    const int ib = block / S::WJ, jb = block % S::WJ;
     if (!sh.cut || tpos >= sh.rem) return;
     const TileId t = tile_of_vid(sh.full_rounds * grid_of_dw + tpos, tilesV, tilesD, a.gi);
     const DwOut out(a, VD);
@@ -1429,6 +1443,25 @@ __global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_
 #pragma unroll
     for (int q = 0; q < 4; ++q)
         out.put(off + q * 8, left - q * 8, cur[q], f32x4u{sum[q * 4], sum[q * 4 + 1], sum[q * 4 + 2], sum[q * 4 + 3]});
+}
+
+template <class S, bool VD>
+__global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_dw) {
+    dw_add_pieces<S, VD>(a, grid_of_dw, blockIdx.x, blockIdx.y);
+}
+
+// dHidden and dW of a small batch side by side: neither fills the chip for longer than it takes to get going, and they do
+// not depend on each other.  The first grid_dh workgroups are dHidden's.  `add`: their second passes, the first tiles_dh columns of the grid dHidden's.
+template <class S, int WM, bool VD>
+__global__ __launch_bounds__(S::NT, 2) void dh_dw_kernel(DhArgs h, DwArgs w, int grid_dh) {
+    extern __shared__ __attribute__((aligned(128))) char lds[];
+    if ((int)blockIdx.x < grid_dh) dh_work<S, WM>(h, blockIdx.x, grid_dh, lds);
+    else dw_work<S, VD>(w, blockIdx.x - grid_dh, gridDim.x - grid_dh, lds);
+}
+template <class S, bool VD>
+__global__ __launch_bounds__(S::NT) void dh_dw_reduce_kernel(DhArgs h, DwArgs w, int grid_dh, int grid_dw, int tiles_dh) {
+    if ((int)blockIdx.x < tiles_dh) dh_add_pieces<S>(h, grid_dh, blockIdx.x, blockIdx.y);
+    else dw_add_pieces<S, VD>(w, grid_dw, blockIdx.x - tiles_dh, blockIdx.y);
 }
 
 // dz[row][tok_row] += g: the one-hot part of dz = g (onehot - p)
@@ -1657,10 +1690,17 @@ void launch_cache_finish(bf16_t* u, int64_t ldz, bf16_t* Hc, int64_t ldk, const 
 // d = 1024, V = 2000 (8) 40 / 40 and 40 -> 32; d = 128, V = 30000 (13) 56 -> 54 and 39 -> 31; d = 768, V = 20000 (15) 56 -> 51, but
 // dW, whose 237 tiles fill the chip as they are, 43 -> 47; d = 512, V = 16000 (29) 71 -> 73 and 72 -> 63.
 static bool few_steps(int64_t tiles, int64_t ksteps, int most) { return tiles * ksteps <= (int64_t)most * g_num_cu.load(); }
+static bool short_dh(const DhArgs& a) {
+    return a.w.mode != W_PACKED && a.part && few_steps((a.d + 255) / 256 * a.tilesM, (a.w.V + K_TILE - 1) / K_TILE, 16);
+}
+static bool short_dw(const DwArgs& a) {
+    const int64_t tiles = (a.d + 255) / 256 * (a.Vpad / 256);
+    return default_waves() && a.part && tiles <= g_num_cu.load() / 2 && few_steps(tiles, a.Mc / K_TILE, 32);
+}
 void launch_dh(const DhArgs& a, hipStream_t st) {
     const int w = waves_for(4);
     const bool d256 = a.dtile == 256;   // else 128, or 192 or 224 in the default geometry
-    if (a.w.mode != W_PACKED && a.part && few_steps((a.d + 255) / 256 * a.tilesM, (a.w.V + K_TILE - 1) / K_TILE, 16)) {
+    if (short_dh(a)) {
         DhArgs b = a;
         b.dpadR = round_up(a.d, 128);
         a.w.mode == W_VD ? launch_dh_t<G4_128, W_VD>(b, st) : launch_dh_t<G4_128, W_DV>(b, st);
@@ -1682,8 +1722,7 @@ void set_dw_deep(int on) { g_dw_deep = on ? 1 : 0; }
 void launch_dw(const DwArgs& a, hipStream_t st) {
     const int w = waves_for(8);
     const bool d256 = a.dtile == 256;   // else 128, or 192 in the default geometry
-    const int64_t tiles = (a.d + 255) / 256 * (a.Vpad / 256);
-    if (default_waves() && a.part && tiles <= g_num_cu.load() / 2 && few_steps(tiles, a.Mc / K_TILE, 32)) {
+    if (short_dw(a)) {
         DwArgs b = a;
         b.dpadR = round_up(a.d, 128);
         a.w_layout == RAPID_W_VD ? launch_dw_t<G4_128, true>(b, st) : launch_dw_t<G4_128, false>(b, st);
@@ -1703,6 +1742,29 @@ void launch_dw(const DwArgs& a, hipStream_t st) {
     if (w == 16) d256 ? launch_dw_t<G16, false>(a, st) : launch_dw_t<G16_J128, false>(a, st);
     else if (w == 8) d256 ? launch_dw_t<G8, false>(a, st) : launch_dw_t<G8_J128, false>(a, st);
     else d256 ? launch_dw_t<G4, false>(a, st) : launch_dw_t<G4_J128, false>(a, st);
+}
+
+template <int WM, bool VD>
+static void launch_dh_dw_t(const DhArgs& h, const DwArgs& w, hipStream_t st) {
+    using S = G4_128;
+    allow_lds<&dh_dw_kernel<S, WM, VD>>(S::LDS_BYTES);
+    const unsigned each = grid_of_cut<S>() / 2;
+    const int64_t tiles_dh = h.dpadR / S::BI * h.tilesM * (256 / S::BJ), tiles_dw = w.Vpad / S::BI * (w.dpadR / S::BJ) % each;
+    const unsigned cols_dh = (unsigned)(tiles_dh < each ? tiles_dh : each);
+    dh_dw_kernel<S, WM, VD><<<2 * each, S::NT, S::LDS_BYTES, st>>>(h, w, (int)each);
+    dh_dw_reduce_kernel<S, VD><<<dim3(cols_dh + (unsigned)tiles_dw, S::WI * S::WJ), S::NT, 0, st>>>(h, w, (int)each, (int)each, (int)cols_dh);
+}
+bool launch_dh_dw(const DhArgs& h, const DwArgs& w, hipStream_t st) {
+    // where both take tiles of 128 x 128, two of whose workgroups share a compute unit: one of each
+    constexpr size_t part = (size_t)MAX_UNITS * G4_128::BI * G4_128::BJ * 4;
+    if (!short_dh(h) || !short_dw(w) || h.part_bytes < 2 * part || h.part != w.part) return false;
+    DhArgs a = h;
+    DwArgs b = w;
+    a.dpadR = b.dpadR = round_up(h.d, 128);
+    b.part = w.part + part / 4;
+    // dW has the layout of the head that dHidden reads in place
+    h.w.mode == W_VD ? launch_dh_dw_t<W_VD, true>(a, b, st) : launch_dh_dw_t<W_DV, false>(a, b, st);
+    return true;
 }
 
 }  // namespace rapid

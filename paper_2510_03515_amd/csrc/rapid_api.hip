@@ -1173,9 +1173,10 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             // so that it fills the compute units a short last round of dHidden tiles leaves idle, was tried: the
             // two kernels are dispatched side by side from the start, each XCD then holds half as many workgroups
             // of either, they share fewer operand panels in its L2, and the pair takes 4 % longer.)
+            const bool whole = cstep >= p.Rcap && wstep >= p.Rcap;
+            DhArgs ha;
             for (int64_t r0 = 0; r0 < p.Rcap; r0 += cstep) {
                 const int64_t rows = (p.Rcap - r0) < cstep ? (p.Rcap - r0) : cstep;
-                DhArgs ha;
                 ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
                 ha.Wdv = at<bf16_t>(ws, p.Wdv); ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = cache + r0 * p.ldv;
                 ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dh.padded; ha.dtile = p.dh.tile;
@@ -1185,6 +1186,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 if (ha.pace) launch_fill_f32((float*)ha.pace, 64, 0.f, st);
                 ha.dhidden = (bf16_t*)dhidden_out; ha.gi = g_gi_dh;
                 ha.part = g_dh_split.load() ? at<float>(ws, p.dh_part) : nullptr; ha.part_bytes = dh_part_bytes();
+                if (whole) break;        // launched with dW
                 Span sp(ST_DH, st);
                 launch_dh(ha, st);
             }
@@ -1201,6 +1203,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 // the last launch rounds a bf16 gradient on its way out
                 if (dw_bf16 && c == p.Cmax - 1 && r0 + wstep >= p.Rcap) wa.dW16 = (bf16_t*)dW_out;
                 wa.part = g_dh_split.load() ? at<float>(ws, p.dh_part) : nullptr; wa.part_bytes = dh_part_bytes();
+                if (whole && launch_dh_dw(ha, wa, st)) break;
+                if (whole) {
+                    Span sp(ST_DH, st);
+                    launch_dh(ha, st);
+                }
                 Span sp(ST_DW, st);
                 launch_dw(wa, st);
             }
@@ -1311,16 +1318,17 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             if (ha.pace) launch_fill_f32((float*)ha.pace, 64, 0.f, st);
             ha.dhidden = (bf16_t*)dhidden_out; ha.gi = g_gi_dh;
             ha.part = g_dh_split.load() ? at<float>(ws, p.dh_part) : nullptr; ha.part_bytes = dh_part_bytes();
-            {
-                Span sp(ST_DH, st);
-                launch_dh(ha, st);
-            }
             DwArgs wa;
             wa.dz = dz; wa.Hc = Hc + m0 * p.ldk; wa.Mc = step; wa.ldz = p.ldv; wa.ldH = p.ldk;
             wa.d = p.d; wa.dpadR = p.dw.padded; wa.dtile = p.dw.tile; wa.V = p.V; wa.Vpad = p.Vpad; wa.m0 = m0; wa.counts = bwd_counts;
             wa.dW = dW32; wa.w_layout = o.w_layout; wa.beta = (chunk > 0 || o.accumulate_dw) ? 1 : 0; wa.gi = g_gi_dw;
             if (dw_staged && m0 + step >= p.Mmax_pad) wa.dW16 = (bf16_t*)dW_out;   // the last launch rounds it on its way out
             wa.part = ha.part; wa.part_bytes = ha.part_bytes;
+            if (launch_dh_dw(ha, wa, st)) continue;
+            {
+                Span sp(ST_DH, st);
+                launch_dh(ha, st);
+            }
             {
                 Span sp(ST_DW, st);
                 launch_dw(wa, st);
