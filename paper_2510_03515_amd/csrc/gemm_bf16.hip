@@ -817,7 +817,7 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.row0 >= Mr) return;
     // the order (and with it the split over the XCDs) covers the row tiles that hold tokens only
-    const int tilesM = min(a.tilesM, (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
+    const int tilesM = min(a.tilesM * (256 / S::BJ), (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
     const int per = ids_for(a.tilesV, tilesM) / 8, wgs = gridDim.x / 8, x = blockIdx.x & 7, w = blockIdx.x >> 3;
     // The last row tile is the cheaper the fewer tokens it holds (waves without any do no products: 260 to 300 tokens at
     // d = 1536, V = 151936 241 -> 212 us a call, 16 to 100 tokens 174 -> 153 us).  Where a round of workgroups covers whole groups of the
@@ -987,7 +987,7 @@ __global__ __launch_bounds__(64 * F2::NW, (F2::NW == 4 && F2::S::WJ == 2) ? 2 : 
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.row0 >= Mr) return;
     // the order covers the row tiles that hold tokens only
-    const int tilesM = min(a.tilesM, (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
+    const int tilesM = min(a.tilesM * (256 / S::BJ), (int)((Mr - a.row0 + S::BJ - 1) / S::BJ));
     const int ksteps = (int)(a.dpad / F2::K_STEP);
     for (int pid = blockIdx.x, ids = ids_for(a.tilesV, tilesM); pid < ids; pid += gridDim.x) {
         const TileId t = map_tile(pid, a.tilesV, tilesM, a.gi);
@@ -1023,7 +1023,7 @@ __global__ __launch_bounds__(S::NT) void dz_kernel(DzArgs a) {
     extern __shared__ __attribute__((aligned(128))) char lds[];
     const int M = a.counts[CNT_M], Mr = a.counts[CNT_MR];
     if (a.m0 >= Mr) return;
-    const int tilesM = min(a.tilesM, (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));   // row tiles that hold tokens
+    const int tilesM = min(a.tilesM * (256 / S::BJ), (int)((Mr - a.m0 + S::BJ - 1) / S::BJ));   // row tiles that hold tokens
     for (int pid = blockIdx.x, ids = ids_for(a.tilesV, tilesM); pid < ids; pid += gridDim.x) {
     const TileId t = map_tile(pid, a.tilesV, tilesM, a.gi);
     if (!t.valid) continue;
@@ -1567,16 +1567,16 @@ template <class S, int WM>
 void launch_fwd_lse_t(const FwdArgs& a, hipStream_t st) {
     if (a.zc) {
         allow_lds<&fwd_lse_kernel<S, true, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, true, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+        fwd_lse_kernel<S, true, WM><<<grid_for(a.tilesV, a.tilesM * (256 / S::BJ)), S::NT, S::LDS_BYTES, st>>>(a);
     } else {
         allow_lds<&fwd_lse_kernel<S, false, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, false, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+        fwd_lse_kernel<S, false, WM><<<grid_for(a.tilesV, a.tilesM * (256 / S::BJ)), S::NT, S::LDS_BYTES, st>>>(a);
     }
 }
 template <class S, int WM>
 void launch_dz_t(const DzArgs& a, hipStream_t st) {
     allow_lds<&dz_kernel<S, WM>>(S::LDS_BYTES);
-    dz_kernel<S, WM><<<grid_for(a.tilesV, a.tilesM), S::NT, S::LDS_BYTES, st>>>(a);
+    dz_kernel<S, WM><<<grid_for(a.tilesV, a.tilesM * (256 / S::BJ)), S::NT, S::LDS_BYTES, st>>>(a);
 }
 // workgroups of a launch that may cut tiles: as many as the chip holds
 template <class S>
@@ -1619,6 +1619,9 @@ void launch_block_w32(const bf16_t* Wvd, int64_t ldk, bf16_t* out, int64_t Vpad,
     const int64_t chunks = Vpad * (dpad / 32) * 4;
     block_w32_kernel<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(Wvd, ldk, out, Vpad, dpad);
 }
+// Logits of a small batch on a small head: tiles of half the token rows where the whole ones would leave half the chip
+// without any; same bits (a tile's columns and its order of summation stay the same).
+static bool half_tiles(int tilesV, int tilesM) { return (int64_t)tilesV * tilesM <= g_num_cu.load() / 2; }
 void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
     if (a.WvdB && a.k32_mode == 3) {   // one workgroup of 4 waves per CU, K steps of 32 requested three steps ahead
         const unsigned grid = grid_for(a.tilesV, a.tilesM);
@@ -1654,6 +1657,10 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
         }
         return;
     }
+    if (half_tiles(a.tilesV, a.tilesM)) {
+        if (a.w.mode == W_VD) { launch_fwd_lse_t<G8_J128, W_VD>(a, st); return; }
+        if (a.w.mode == W_DV) { launch_fwd_lse_t<G8_J128, W_DV>(a, st); return; }
+    }
     if (a.w.mode == W_VD) { launch_fwd_lse_t<G8, W_VD>(a, st); return; }
     if (a.w.mode == W_DV) { launch_fwd_lse_t<G8, W_DV>(a, st); return; }
     const int w = waves_for(8);
@@ -1665,7 +1672,10 @@ int fwd_slots_per_tile() { return 2; }
 
 void launch_dz(const DzArgs& a, hipStream_t st) {
     const int w = waves_for(8);
-    if (a.w.mode == W_VD) launch_dz_t<G8, W_VD>(a, st);
+    const bool half = half_tiles(a.tilesV, a.tilesM);
+    if (half && a.w.mode == W_VD) launch_dz_t<G8_J128, W_VD>(a, st);
+    else if (half && a.w.mode == W_DV) launch_dz_t<G8_J128, W_DV>(a, st);
+    else if (a.w.mode == W_VD) launch_dz_t<G8, W_VD>(a, st);
     else if (a.w.mode == W_DV) launch_dz_t<G8, W_DV>(a, st);
     else if (w == 16) launch_dz_t<G16, W_PACKED>(a, st);
     else if (w == 8) launch_dz_t<G8, W_PACKED>(a, st);
