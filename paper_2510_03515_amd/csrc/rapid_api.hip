@@ -118,11 +118,10 @@ struct Plan {
     bool two_wg;        // the forward runs two workgroups per CU and reads W from its K-blocked copy (Wvd32)
     bool default_waves; // tuning key 2 as this call found it
     int64_t ld_part;    // columns of the log-sum-exp partials
-    int64_t rms_blocks; // row blocks of the final norm's dweight partial sums
     size_t per_row;     // chunk bytes per row
     size_t fixed, total;
     // offsets into the workspace
-    size_t counts, pace, seq_len, cu, row_index, tokc, seqc, zy, refz, lse_c, inv_rms, rms_part, rowc, rowg, logp_tmp, s64, s32, adv, adv64, g, g64, tsum, tmax,
+    size_t counts, pace, seq_len, cu, row_index, tokc, seqc, zy, refz, lse_c, inv_rms, rowc, rowg, logp_tmp, s64, s32, adv, adv64, g, g64, tsum, tmax,
         Hc, Wvd, Wdv, WdvB, dh_part, part_max, part_sum, dw32, chunk0, tab, gen_row0, gen_chunk, lam_state, lam_chunk, beta_scale, idle, len_live, cu_live, live_group, gruns, Wvd32;
 };
 
@@ -199,8 +198,6 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
     if (dtype == RAPID_DTYPE_BF16) p.inv_rms = take(cur, (size_t)p.Mmax_pad * 4);   // final-norm option
     if (bwd) {
         p.rowc = take(cur, (size_t)p.Mmax_pad * 4);
-        p.rms_blocks = Cmax > 0 ? (int64_t)Cmax * rmsnorm_dweight_blocks(Rcap) : rmsnorm_dweight_blocks(p.Mmax_pad);
-        if (dtype == RAPID_DTYPE_BF16) p.rms_part = take(cur, (size_t)p.rms_blocks * d * 4);
         p.rowg = take(cur, (size_t)p.Mmax_pad * 4);
         p.adv64 = take(cur, (size_t)N * 8);
         p.gruns = take(cur, (size_t)(3 * K + 1) * 4);
@@ -1229,14 +1226,9 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         }
         if (o.rms_weight) {   // dhidden holds dL/dh of the normalised state: on to dL/dweight and dL/dx
             Span sp(ST_ZERO, st);
-            float* part = o.drms_weight_out ? at<float>(ws, p.rms_part) : nullptr;
-            if (part) launch_fill_f32(part, p.rms_blocks * d, 0.f, st);
-            const int64_t blocks_per_region = rmsnorm_dweight_blocks(p.Rcap);
-            for (int c = 0; c < p.Cmax; ++c)
-                launch_rmsnorm_backward((const bf16_t*)hidden, (bf16_t*)dhidden_out, d, (const bf16_t*)o.rms_weight, row_index,
-                                        tab + (int64_t)c * CH_WORDS, at<float>(ws, p.inv_rms), (int64_t)c * p.Rcap, p.Rcap,
-                                        part ? part + (int64_t)c * blocks_per_region * d : nullptr, st);
-            if (part) launch_rmsnorm_dweight_reduce(part, d, p.rms_blocks, o.drms_weight_out, st);
+            // the scratch of the cut tiles is idle by now
+            launch_rmsnorm_backward((const bf16_t*)hidden, (bf16_t*)dhidden_out, d, (const bf16_t*)o.rms_weight, row_index, tab, CH_WORDS,
+                                    p.Cmax, p.Rcap, at<float>(ws, p.inv_rms), at<float>(ws, p.dh_part), dh_part_bytes(), o.drms_weight_out, st);
         }
         if (dw_staged && !dw_bf16) {
             Span sp(ST_CONVERT, st);
@@ -1336,11 +1328,8 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         }
         if (o.rms_weight) {   // dhidden holds dL/dh of the normalised state: on to dL/dweight and dL/dx
             Span sp(ST_ZERO, st);
-            float* part = o.drms_weight_out ? at<float>(ws, p.rms_part) : nullptr;
-            if (part) launch_fill_f32(part, p.rms_blocks * d, 0.f, st);
-            launch_rmsnorm_backward((const bf16_t*)hidden, (bf16_t*)dhidden_out, d, (const bf16_t*)o.rms_weight, row_index,
-                                    counts, at<float>(ws, p.inv_rms), 0, p.Mmax_pad, part, st);
-            if (part) launch_rmsnorm_dweight_reduce(part, d, p.rms_blocks, o.drms_weight_out, st);
+            launch_rmsnorm_backward((const bf16_t*)hidden, (bf16_t*)dhidden_out, d, (const bf16_t*)o.rms_weight, row_index, counts, 0, 1,
+                                    p.Mmax_pad, at<float>(ws, p.inv_rms), at<float>(ws, p.dh_part), dh_part_bytes(), o.drms_weight_out, st);
         }
     } else {
         float* z = at<float>(ws, p.chunk0);

@@ -211,15 +211,12 @@ void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, i
                                int64_t C, int64_t Rpad, int64_t Cpad, hipStream_t st);
 
 // ---- rmsnorm.hip ------------------------------------------------------------------------------
-// dh [N*T, d] holds dL/dh at the valid positions of the compact rows [row0, row0 + rows_max) below
-// counts[CNT_M]: if part != NULL, partial sums of dL/dweight over blocks of those rows go to
-// part [rmsnorm_dweight_blocks(rows_max)][d] (zeroed beforehand: a block without rows writes nothing); then dh
-// becomes dL/dx in place.  launch_rmsnorm_dweight_reduce sums nblk blocks of partial sums in order.
-int64_t rmsnorm_dweight_blocks(int64_t rows_max);
+// dh [N*T, d] holds dL/dh at the valid positions of the compact rows, which come in regions of region_rows rows with their
+// counters at counts[g * stride]; it becomes dL/dx in place, and dweight [d] (may be NULL) dL/dweight.  part: scratch of part_bytes
+// (128 MiB) for the partial sums.
 void launch_rmsnorm_backward(const bf16_t* x, bf16_t* dh, int64_t d, const bf16_t* weight, const int32_t* row_index,
-                             const int32_t* counts, const float* inv_rms, int64_t row0, int64_t rows_max, float* part,
-                             hipStream_t st);
-void launch_rmsnorm_dweight_reduce(const float* part, int64_t d, int64_t nblk, float* dweight, hipStream_t st);
+                             const int32_t* counts, int stride, int regions, int64_t region_rows, const float* inv_rms, float* part,
+                             size_t part_bytes, float* dweight, hipStream_t st);
 
 // ---- gemm_bf16.hip ----------------------------------------------------------------------------
 // The head as the caller has it.  mode says how a kernel reads it: from a packed copy (the argument structs hold those),

@@ -416,3 +416,27 @@ def test_estimator_of_a_small_batch(rb, prompts, G, length, kw, scattered):
     # the same call's outputs from the stand-alone entry points
     s, tl = rb.rapid_seq_logratio(out.logp_cur, logp_b, g["mask"], want_tokens=True)
     assert torch.equal(tl, out.tok_logratio) and torch.allclose(s, out.seq_logratio, rtol=2.0 ** -23, atol=0)
+
+
+@pytest.mark.parametrize("d", [8, 512, 520, 1032, 1544, 2048, 2056])      # 1 to 4 chunks of 16 bytes per lane, and wider rows
+@pytest.mark.parametrize("mode", ["recompute", "chunks"])
+def test_final_norm_backward_by_width(rb, d, mode):
+    print(f"final norm d {d} {mode}", flush=True)
+    spec = wl.small_spec("norm", "bf16", d=d, V=72, prompts=5, G=3, len_lo=9, len_hi=40, reward="uniform")
+    w, g = _make(spec)
+    gen = torch.Generator().manual_seed(d)
+    x = (g["hidden"].cpu().float() * torch.exp(torch.randn((*g["hidden"].shape[:2], 1), generator=gen))).to(torch.bfloat16).cuda()
+    wgt = (1.0 + 0.3 * torch.randn(d, generator=gen)).to(torch.bfloat16).cuda()
+    logp_b, _ = rb.rapid_logprob_fwd(x, g["W_old"], g["tokens"], g["mask"], rms_weight=wgt)
+    buf = rb.IwPgBuffers(x, g["W"], w["K"], minimum_workspace=mode == "chunks", logits_cache=mode == "chunks")
+    out = rb.rapid_iw_pg_loss_fwd_bwd(x, g["W"], g["tokens"], g["mask"], logp_b, g["rewards"], g["group_ids"], w["K"],
+                                      buffers=buf, logits_cache=mode == "chunks", rms_weight=wgt)
+    torch.cuda.synchronize()
+    _, W, tok, mask = _oracle_inputs(w)
+    ref = orc.iw_pg_loss_fwd_bwd(_np(x), W, tok, mask, _np(logp_b), _np(w["rewards"]), _np(w["group_ids"]), w["K"],
+                                 rms_weight=_np(wgt), rms_eps=1e-6, round_normed_hidden=True)
+    assert out.dev_status.item() == 0
+    # as test_fwd_bwd_with_final_rmsnorm: dL/dx is formed from a dL/dh that is rounded to bf16 first
+    assert _rel(_np(out.dhidden), ref["dH"]) <= 2e-2 and _rel(_np(out.dW), ref["dW"]) <= 2e-2
+    assert _rel(_np(out.drms_weight), ref["d_rms_weight"]) <= 2e-2
+    assert np.abs(_np(out.drms_weight) - ref["d_rms_weight"]).max() <= 2.0 ** -6 * np.abs(ref["d_rms_weight"]).max()
