@@ -494,6 +494,147 @@ __device__ __forceinline__ void prefetch_tile(const Operand& A, const Operand& B
     for (int r = 0; r < Loader<S, EB, BK, false>::ROUNDS; ++r) lb.request(r, lds + S::LI * 128);
 }
 
+// The same contraction (same fragments, same order of summation: same bits) with three LDS stages for A, whose steps are
+// requested two ahead, beside two for B.  For a batch of few rows: W streams through the chip once and every step of it
+// comes from HBM, a longer trip than a step takes, while the few hidden rows are in the L2.  All 160 KiB of LDS.
+// A group of requests is B's step k and A's step k + 1, in this order, so "all but the last NRA have landed" leaves A's
+// step under way.
+template <class S>
+constexpr int deep_lds_bytes() { return (3 * S::LI + 2 * S::LJ) * 128; }
+template <class S, bool AK, bool CLAMP, bool TAIL>
+__device__ __forceinline__ void mainloop_deep(const Operand& A, const Operand& B, int ktiles, char* lds, f32x16 (&acc)[S::WI][S::WJ],
+                                              int live_j, bool first_requested) {
+    constexpr int WI = S::WI, WJ = S::WJ, A_STAGE = S::LI * 128, B_STAGE = S::LJ * 128, B0 = 3 * A_STAGE;
+    constexpr int EA = AK ? S::LI : S::BI, EB = S::BJ;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_i = wave % S::NWI, wave_j = wave / S::NWI;
+    Loader<S, EA, AK, CLAMP> la(A, wave, lane);
+    Loader<S, EB, false, false> lb(B, wave, lane);
+    const Reader<S, EA, WI, AK> ra(lane, wave_i * WI, 0);
+    const Reader<S, EB, WJ, false> rb(lane, wave_j * WJ, 0);
+    constexpr int NRA = Loader<S, EA, AK, CLAMP>::ROUNDS, NRB = Loader<S, EB, false, false>::ROUNDS, T = NRA + NRB;
+#pragma unroll
+    for (int ib = 0; ib < WI; ++ib)
+#pragma unroll
+        for (int jb = 0; jb < WJ; ++jb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[ib][jb][v] = 0.f;
+
+    char *dst_a = lds, *dst_b = lds + B0;
+    auto request = [&](int r) {
+        if (r < NRB) lb.request(r, dst_b); else la.request(r - NRB, dst_a);
+    };
+    int step_a = 0;                                 // step that la stands at (steps past the last one repeat it, into idle stages)
+    auto advance_a = [&]() {
+        if (step_a + 1 < ktiles) { ++step_a; la.g += A.step; }
+        la.at_step(step_a);
+    };
+    la.start();
+    if (!first_requested) {
+        lds_barrier();      // see mainloop
+#pragma unroll
+        for (int r = 0; r < T; ++r) request(r);     // B's and A's step 0
+    }
+    advance_a();
+    dst_a = lds + A_STAGE;
+    if (!first_requested) {
+#pragma unroll
+        for (int r = 0; r < NRA; ++r) la.request(r, dst_a);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NRA) : "memory");
+    lds_barrier();
+    int a_cur = 0, a_fill = 2;                      // A's stages: of step kt, and of the step requested next
+    // the group for step kt + 1: B's step kt + 1 and A's step kt + 2
+    auto next_group = [&](int kt) {
+        lb.g += kt + 1 < ktiles ? B.step : 0;
+        advance_a();
+        dst_b = lds + B0 + ((kt + 1) & 1) * B_STAGE;
+        dst_a = lds + a_fill * A_STAGE;
+        a_fill = a_fill == 2 ? 0 : a_fill + 1;
+    };
+    next_group(0);
+    if constexpr (TAIL) {
+        if (wave_j * (WJ * 32) >= live_j) {         // see mainloop
+            const int read_j = (live_j + WJ * 32 - 1) / (WJ * 32) * (WJ * 32);
+            auto requests = [&]() {
+#pragma unroll
+                for (int r = 0; r < T; ++r)
+                    if (r >= NRB || r * (8 * S::NW) < read_j) request(r);
+            };
+            requests();
+            for (int kt = 0; kt < ktiles; ++kt) {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NRA) : "memory");
+                lds_barrier();
+                next_group(kt + 1);
+                requests();
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            return;
+        }
+    }
+    Frags<WI, WJ> f0, f1;
+    constexpr int NR = Reader<S, EA, WI, AK>::READS + Reader<S, EB, WJ, false>::READS;
+    {
+        ra.template load<0>(f0.a, lds_addr(lds));
+        rb.template load<0>(f0.b, lds_addr(lds + B0));
+        request_first_half<S, T>(request);
+        wait_frags<0>(f0);
+    }
+    for (int kt = 0; kt < ktiles; ++kt) {
+        const int a_next = a_cur == 2 ? 0 : a_cur + 1;
+        const uint32_t ca = lds_addr(lds + a_cur * A_STAGE), na = lds_addr(lds + a_next * A_STAGE);
+        const uint32_t cb = lds_addr(lds + B0 + (kt & 1) * B_STAGE), nb = lds_addr(lds + B0 + ((kt + 1) & 1) * B_STAGE);
+        fence();
+        ra.template load<1>(f1.a, ca);
+        rb.template load<1>(f1.b, cb);
+        fence();
+        mma_block_requesting<S, 1, T>(f0, acc, request);
+        fence();
+        ra.template load<2>(f0.a, ca);
+        rb.template load<2>(f0.b, cb);
+        wait_frags<NR>(f1);
+        fence();
+        mma_block<WI, WJ>(f1, acc);
+        fence();
+        ra.template load<3>(f1.a, ca);
+        rb.template load<3>(f1.b, cb);
+        wait_frags<NR>(f0);
+        fence();
+        mma_block<WI, WJ>(f0, acc);
+        fence();
+        wait_frags<0>(f1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NRA) : "memory");
+        lds_barrier();
+        ra.template load<0>(f0.a, na);
+        rb.template load<0>(f0.b, nb);
+        fence();
+        next_group(kt + 1);
+        mma_block_requesting<S, 0, T>(f1, acc, request);
+        fence();
+        wait_frags<0>(f0);
+        a_cur = a_next;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+// the requests before the loop, for the next tile (see prefetch_tile; the epilogue that covers them keeps off the LDS)
+template <class S, bool AK, bool CLAMP>
+__device__ __forceinline__ void prefetch_tile_deep(const Operand& A, const Operand& B, int ktiles, char* lds) {
+    constexpr int EA = AK ? S::LI : S::BI;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Loader<S, EA, AK, CLAMP> la(A, wave, lane);
+    const Loader<S, S::BJ, false, false> lb(B, wave, lane);
+    la.start();
+#pragma unroll
+    for (int r = 0; r < Loader<S, S::BJ, false, false>::ROUNDS; ++r) lb.request(r, lds + 3 * S::LI * 128);
+#pragma unroll
+    for (int r = 0; r < Loader<S, EA, AK, CLAMP>::ROUNDS; ++r) la.request(r, lds);
+    if (ktiles > 1) la.g += A.step;
+    la.at_step(ktiles > 1 ? 1 : 0);
+#pragma unroll
+    for (int r = 0; r < Loader<S, EA, AK, CLAMP>::ROUNDS; ++r) la.request(r, lds + S::LI * 128);
+}
+
 // The same contraction with K steps of 32 rows through NST LDS stages (NST x 32 rows = the same LDS as two
 // steps of 64), the requests NST - 1 steps ahead of the MFMAs: the streamed operand of dW comes from HBM, and
 // one step of lead is less than a trip there.  Same LDS layout per row, same fragments, same order of
@@ -810,7 +951,7 @@ __device__ __forceinline__ void fwd_epilogue(const FwdArgs& a, const TileId& t, 
 }
 
 // one workgroup per CU on 256 x 256 tiles: the logits tile on MFMA, then the epilogue above
-template <class S, bool STORE, int WM>
+template <class S, bool STORE, int WM, bool DEEP = false>
 __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     constexpr int WI = S::WI, WJ = S::WJ;
     extern __shared__ __attribute__((aligned(128))) char lds[];
@@ -836,7 +977,7 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
     // 573-580 -> 553-558 us, 290 tokens at d = 1536 180 -> 176 us, d = 896 18.56 -> 18.39 ms, d = 1536 28.26 -> 28.12 ms (the chip is near
     // its power limit there); a whole step changes by less than its spread.
     // In-place reads with a store have no registers left for it (11 spilled; small head's forward 15.5 -> 17.6 us).
-    constexpr bool AHEAD = !STORE || (WM == W_PACKED && S::NW * (32 * 256) <= S::STAGE_BYTES);
+    constexpr bool AHEAD = !STORE || (!DEEP && WM == W_PACKED && S::NW * (32 * 256) <= S::STAGE_BYTES);
     TileId t = tile(0);
     for (int r = 0; t.valid; ++r) {
         const int64_t j_tile = a.row0 + (int64_t)t.tj * S::BJ;   // first token row of the tile
@@ -844,15 +985,19 @@ __global__ __launch_bounds__(S::NT) void fwd_lse_kernel(FwdArgs a) {
         f32x16 acc[WI][WJ];
         float ref[WJ];
         if (STORE && AHEAD) load_references<S>(a, j_tile, M, ref);
-        mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(opW(t), opH(t), (int)(a.dpad / K_TILE), lds, acc, NoPace(), live,
-                                                             AHEAD && r > 0);
+        const int ktiles = (int)(a.dpad / K_TILE);
+        if constexpr (DEEP) mainloop_deep<S, WM == W_DV, WM != W_PACKED, true>(opW(t), opH(t), ktiles, lds, acc, live, AHEAD && r > 0);
+        else mainloop<S, WM == W_DV, false, WM != W_PACKED, true>(opW(t), opH(t), ktiles, lds, acc, NoPace(), live, AHEAD && r > 0);
         const TileId next = tile(r + 1);
         if (STORE && !AHEAD) load_references<S>(a, j_tile, M, ref);
         if (STORE && AHEAD) {     // they are here: the compiler shall see that before the requests below
 #pragma unroll
             for (int jb = 0; jb < WJ; ++jb) asm volatile("" : "+v"(ref[jb]));
         }
-        if (AHEAD && next.valid) prefetch_tile<S, WM == W_DV, false, WM != W_PACKED>(opW(next), opH(next), lds);
+        if (AHEAD && next.valid) {
+            if constexpr (DEEP) prefetch_tile_deep<S, WM == W_DV, WM != W_PACKED>(opW(next), opH(next), ktiles, lds);
+            else prefetch_tile<S, WM == W_DV, false, WM != W_PACKED>(opW(next), opH(next), lds);
+        }
         if (STORE || (int)(threadIdx.x >> 6) / S::NWI * (WJ * 32) < live)      // else: no token of this wave's
             fwd_epilogue<S, STORE>(a, t, j_tile, M, lds + (AHEAD ? S::STAGE_BYTES : 0), acc, ref);
         t = next;
@@ -1563,14 +1708,16 @@ using G4_128 = Geo<2, 2, 2, 2>;    // 128 x 128, for a launch with little to con
 using G4_I192 = Geo<2, 2, 3, 4>;   // 192 x 256, waves of 96 x 128
 using G4_J192 = Geo<2, 2, 4, 3>;   // 256 x 192
 
-template <class S, int WM>
+template <class S, int WM, bool DEEP = false>
 void launch_fwd_lse_t(const FwdArgs& a, hipStream_t st) {
+    constexpr int bytes = DEEP ? deep_lds_bytes<S>() : S::LDS_BYTES;
+    const unsigned grid = grid_for(a.tilesV, a.tilesM * (256 / S::BJ));
     if (a.zc) {
-        allow_lds<&fwd_lse_kernel<S, true, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, true, WM><<<grid_for(a.tilesV, a.tilesM * (256 / S::BJ)), S::NT, S::LDS_BYTES, st>>>(a);
+        allow_lds<&fwd_lse_kernel<S, true, WM, DEEP>>(bytes);
+        fwd_lse_kernel<S, true, WM, DEEP><<<grid, S::NT, bytes, st>>>(a);
     } else {
-        allow_lds<&fwd_lse_kernel<S, false, WM>>(S::LDS_BYTES);
-        fwd_lse_kernel<S, false, WM><<<grid_for(a.tilesV, a.tilesM * (256 / S::BJ)), S::NT, S::LDS_BYTES, st>>>(a);
+        allow_lds<&fwd_lse_kernel<S, false, WM, DEEP>>(bytes);
+        fwd_lse_kernel<S, false, WM, DEEP><<<grid, S::NT, bytes, st>>>(a);
     }
 }
 template <class S, int WM>
@@ -1660,6 +1807,14 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
     if (half_tiles(a.tilesV, a.tilesM)) {
         if (a.w.mode == W_VD) { launch_fwd_lse_t<G8_J128, W_VD>(a, st); return; }
         if (a.w.mode == W_DV) { launch_fwd_lse_t<G8_J128, W_DV>(a, st); return; }
+    }
+    // W's steps two ahead (mainloop_deep) where the few rows leave little else to do; a short tile is over before it pays,
+    // the steps past its end are fetched for nothing.  Calls at V = 151936, without and with it: 100 tokens at d = 512 64 -> 59 us, d = 1024
+    // 105 -> 96, d = 1536 147 -> 134; 290 tokens (two row tiles) d = 512 86 -> 90, d = 768 109 -> 111, d = 1024 144 -> 137,
+    // d = 1536 208 -> 195; 900 tokens as before.
+    if (a.tilesM <= 2 && a.dpad >= (int64_t)a.tilesM * 8 * K_TILE) {
+        if (a.w.mode == W_VD) { launch_fwd_lse_t<G8, W_VD, true>(a, st); return; }
+        if (a.w.mode == W_DV) { launch_fwd_lse_t<G8, W_DV, true>(a, st); return; }
     }
     if (a.w.mode == W_VD) { launch_fwd_lse_t<G8, W_VD>(a, st); return; }
     if (a.w.mode == W_DV) { launch_fwd_lse_t<G8, W_DV>(a, st); return; }
