@@ -31,12 +31,14 @@ struct F64Operand {
 // These are template arguments because a branch around a load keeps the loads of a step from being in flight together.
 // Global loads run two steps ahead of the MFMAs (two register sets; a step's MFMAs take less than a trip to memory).
 // LDS rows are KS + 2 doubles apart (an odd multiple of 16 bytes): a fragment read is free of bank conflicts.
+template <int TI, int TJ, int KS, bool SPLIT>
+constexpr int f64_lds_bytes() { return (2 * (TI + TJ) * (KS + 2) + (SPLIT ? 4 * TI * TJ : 0)) * 8; }
 template <int TI, int TJ, int KS, bool SPLIT, bool KA, bool KB, bool MA, bool MB>
-__global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand B, F32Gemm g) {
+__device__ __forceinline__ void f64_work(const F64Operand& A, const F64Operand& B, const F32Gemm& g, unsigned tile_i, unsigned tile_j, double* lds) {
     constexpr int WI = SPLIT ? TI / 16 : TI / 32, WJ = SPLIT ? TJ / 16 : TJ / 32, LD = KS + 2;
     constexpr int QA = TI * KS / 256, QB = TJ * KS / 256;   // elements per thread and step
     static_assert(KS <= 64 && 256 % KS == 0 && 256 % TI == 0 && 256 % TJ == 0, "thread layout of the loads");
-    __shared__ double As[2][TI * LD], Bs[2][TJ * LD];
+    double *const As[2] = {lds, lds + TI * LD}, *const Bs[2] = {lds + 2 * TI * LD, lds + (2 * TI + TJ) * LD};
     int64_t I = g.I, Kd = g.Kd;
     if (g.counts) {
         const int64_t M = g.counts[CNT_M], left = M > g.i0 ? M - g.i0 : 0;
@@ -44,7 +46,7 @@ __global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand 
         if (g.limit_k) Kd = left < Kd ? left : Kd;
         else I = left < I ? left : I;
     }
-    const int64_t ib = (int64_t)blockIdx.y * TI, jb = (int64_t)blockIdx.x * TJ;
+    const int64_t ib = (int64_t)tile_i * TI, jb = (int64_t)tile_j * TJ;
     if (ib >= I) return;
     if (g.limit_k && Kd == 0 && g.beta) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -173,16 +175,16 @@ __global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand 
         *p = (float)(g.beta ? (double)*p + v : v);
     };
     if constexpr (SPLIT) {
-        __shared__ double sum[4][TI * TJ];
+        double* const sum = lds + 2 * (TI + TJ) * LD;      // [4][TI * TJ]
 #pragma unroll
         for (int x = 0; x < WI; ++x)
 #pragma unroll
             for (int y = 0; y < WJ; ++y)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) sum[wave][(x * 16 + v * 4 + fk) * TJ + y * 16 + fo] = acc[x][y][v];
+                for (int v = 0; v < 4; ++v) sum[wave * (TI * TJ) + (x * 16 + v * 4 + fk) * TJ + y * 16 + fo] = acc[x][y][v];
         __syncthreads();
         for (int e = tid; e < TI * TJ; e += 256)
-            write(ib + e / TJ, jb + e % TJ, (sum[0][e] + sum[1][e]) + (sum[2][e] + sum[3][e]));
+            write(ib + e / TJ, jb + e % TJ, (sum[e] + sum[TI * TJ + e]) + (sum[2 * TI * TJ + e] + sum[3 * TI * TJ + e]));
     } else {
 #pragma unroll
         for (int x = 0; x < WI; ++x)
@@ -191,6 +193,23 @@ __global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand 
 #pragma unroll
                 for (int v = 0; v < 4; ++v) write(ib + wi + x * 16 + v * 4 + fk, jb + wj + y * 16 + fo, acc[x][y][v]);
     }
+}
+
+template <int TI, int TJ, int KS, bool SPLIT, bool KA, bool KB, bool MA, bool MB>
+__global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand B, F32Gemm g) {
+    __shared__ double lds[f64_lds_bytes<TI, TJ, KS, SPLIT>() / 8];
+    f64_work<TI, TJ, KS, SPLIT, KA, KB, MA, MB>(A, B, g, blockIdx.y, blockIdx.x, lds);
+}
+
+// dHidden and dW of a small shape side by side: two chains of a few trips to memory each that do not depend on each
+// other (640 rows x V = 1000 x d = 64: 10.8 and 8.8 us one after the other, 12.1 together).  The first h_blocks blocks are dHidden's.
+template <bool KB, bool MA>
+__global__ __launch_bounds__(256) void f64_pair_kernel(F64Operand hA, F64Operand hB, F32Gemm h, unsigned h_cols, unsigned h_blocks,
+                                                       F64Operand wA, F64Operand wB, F32Gemm w, unsigned w_cols) {
+    __shared__ double lds[f64_lds_bytes<16, 16, 64, true>() / 8];
+    const unsigned b = blockIdx.x;
+    if (b < h_blocks) f64_work<16, 16, 64, true, true, KB, false, false>(hA, hB, h, b / h_cols, b % h_cols, lds);
+    else f64_work<16, 16, 64, true, false, false, MA, !MA>(wA, wB, w, (b - h_blocks) / w_cols, (b - h_blocks) % w_cols, lds);
 }
 
 __device__ inline double block_reduce(double v, double* sm, bool is_max) {
@@ -249,31 +268,52 @@ __global__ void f32_dz_kernel(float* __restrict__ z, int64_t V, int64_t m0, cons
 // Tile: 64 x 64 where that gives every CU two workgroups (a SIMD needs two waves at least to keep the instruction
 // going: 35 TFLOP/s with one, 46 with two), else 32 x 32, else (dHidden and dW of small shapes, fewer tiles than CUs)
 // 16 x 16 with the contraction shared out over the waves: 10 us for 640 rows x V = 1000 x d = 64, 31 us before.
+int64_t tiles_of(const F32Gemm& g, int T) { return ((g.I + T - 1) / T) * ((g.J + T - 1) / T); }
+bool tile_64(const F32Gemm& g) { return tiles_of(g, 64) >= 512; }
+bool tile_32(const F32Gemm& g) { return tiles_of(g, 32) >= 256 || !g.may_split; }
 template <bool KA, bool KB, bool MA, bool MB>
 void launch_tiles(const F64Operand& A, const F64Operand& B, const F32Gemm& g, hipStream_t st) {
-    auto tiles = [&](int T) { return ((g.I + T - 1) / T) * ((g.J + T - 1) / T); };
     auto grid = [&](int T) { return dim3((unsigned)((g.J + T - 1) / T), (unsigned)((g.I + T - 1) / T)); };
-    if (tiles(64) >= 512) f64_mfma_kernel<64, 64, 16, false, KA, KB, MA, MB><<<grid(64), 256, 0, st>>>(A, B, g);
-    else if (tiles(32) >= 256 || !g.may_split) f64_mfma_kernel<32, 32, 32, false, KA, KB, MA, MB><<<grid(32), 256, 0, st>>>(A, B, g);
+    if (tile_64(g)) f64_mfma_kernel<64, 64, 16, false, KA, KB, MA, MB><<<grid(64), 256, 0, st>>>(A, B, g);
+    else if (tile_32(g)) f64_mfma_kernel<32, 32, 32, false, KA, KB, MA, MB><<<grid(32), 256, 0, st>>>(A, B, g);
     else f64_mfma_kernel<16, 16, 64, true, KA, KB, MA, MB><<<grid(16), 256, 0, st>>>(A, B, g);
+}
+struct F64Call { F64Operand A, B; F32Gemm g; };
+F64Call f64_call(const F32Gemm& in) {
+    F64Call c{{in.A, in.sa_i, in.sa_k, in.a_imap ? in.a_imap + in.i0 : nullptr, in.a_kmap ? in.a_kmap + in.i0 : nullptr},
+              {in.B, in.sb_j, in.sb_k, nullptr, nullptr}, in};
+    if (in.sc_i == 1 && in.limit_k) {   // C is contiguous along i: form its transpose, so that a store covers whole lines
+        const F64Operand t = c.A; c.A = c.B; c.B = t;
+        c.g.I = in.J; c.g.J = in.I;
+        c.g.sc_i = in.sc_j; c.g.sc_j = 1;
+    }
+    return c;
 }
 
 }  // namespace
 
 void launch_f32_gemm(const F32Gemm& in, hipStream_t st) {
     if (in.I <= 0 || in.J <= 0) return;
-    F32Gemm g = in;
-    F64Operand A{g.A, g.sa_i, g.sa_k, g.a_imap ? g.a_imap + g.i0 : nullptr, g.a_kmap ? g.a_kmap + g.i0 : nullptr};
-    F64Operand B{g.B, g.sb_j, g.sb_k, nullptr, nullptr};
-    if (g.sc_i == 1 && g.limit_k) {   // C is contiguous along i: form its transpose, so that a store covers whole lines
-        const F64Operand t = A; A = B; B = t;
-        const int64_t n = g.I; g.I = g.J; g.J = n;
-        g.sc_i = g.sc_j; g.sc_j = 1;
+    const F64Call c = f64_call(in);
+    if (c.A.kmap) launch_tiles<false, false, true, false>(c.A, c.B, c.g, st);        // dW: both operands contiguous along their outer index
+    else if (c.B.kmap) launch_tiles<false, false, false, true>(c.A, c.B, c.g, st);
+    else if (c.B.sk == 1) launch_tiles<true, true, false, false>(c.A, c.B, c.g, st);
+    else launch_tiles<true, false, false, false>(c.A, c.B, c.g, st);
+}
+
+void launch_f32_gemm_pair(const F32Gemm& dh, const F32Gemm& dw, hipStream_t st) {
+    const F64Call h = f64_call(dh), w = f64_call(dw);
+    auto small = [](const F32Gemm& g) { return g.I > 0 && g.J > 0 && !tile_64(g) && !tile_32(g); };
+    if (!small(h.g) || !small(w.g)) {
+        launch_f32_gemm(dh, st);
+        launch_f32_gemm(dw, st);
+        return;
     }
-    if (A.kmap) launch_tiles<false, false, true, false>(A, B, g, st);        // dW: both operands contiguous along their outer index
-    else if (B.kmap) launch_tiles<false, false, false, true>(A, B, g, st);
-    else if (B.sk == 1) launch_tiles<true, true, false, false>(A, B, g, st);
-    else launch_tiles<true, false, false, false>(A, B, g, st);
+    auto cols = [](const F32Gemm& g) { return (unsigned)((g.J + 15) / 16); };
+    const unsigned nh = (unsigned)tiles_of(h.g, 16), nw = (unsigned)tiles_of(w.g, 16);
+    auto* kernel = h.B.sk == 1 ? (w.A.kmap ? &f64_pair_kernel<true, true> : &f64_pair_kernel<true, false>)
+                               : (w.A.kmap ? &f64_pair_kernel<false, true> : &f64_pair_kernel<false, false>);
+    kernel<<<nh + nw, 256, 0, st>>>(h.A, h.B, h.g, cols(h.g), nh, w.A, w.B, w.g, cols(w.g));
 }
 
 void launch_f32_row_lse(const float* z, int64_t V, int64_t rows, int64_t m0, const int32_t* tokc,

@@ -1356,7 +1356,6 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             if (o.w_layout == RAPID_W_DV) { gh.sb_k = 1; gh.sb_j = V; } else { gh.sb_k = d; gh.sb_j = 1; }
             gh.C = (float*)dhidden_out; gh.sc_i = d; gh.sc_j = 1; gh.c_rows = row_index;
             gh.I = rows; gh.J = d; gh.Kd = V; gh.beta = 0; gh.counts = counts; gh.i0 = m0; gh.alpha = 1.f; gh.may_split = 1;
-            launch_f32_gemm(gh, st);
             // dW(k', v) += sum_rows H[row, k'] dz[row, v]
             F32Gemm gw;
             memset(&gw, 0, sizeof(gw));
@@ -1366,7 +1365,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             if (o.w_layout == RAPID_W_DV) { gw.sc_i = V; gw.sc_j = 1; } else { gw.sc_i = 1; gw.sc_j = d; }
             gw.I = d; gw.J = V; gw.Kd = rows; gw.beta = (chunk > 0 || o.accumulate_dw) ? 1 : 0;
             gw.counts = counts; gw.i0 = m0; gw.limit_k = 1; gw.alpha = 1.f; gw.may_split = 1;
-            launch_f32_gemm(gw, st);
+            launch_f32_gemm_pair(gh, gw, st);
         }
     }
     if (dw_staged && dtype == RAPID_DTYPE_F32) {

@@ -363,6 +363,8 @@ struct F32Gemm {
     int skip_last;           // 1: nothing to do if no row lies past this chunk (its C is still what this launch would form)
 };
 void launch_f32_gemm(const F32Gemm& g, hipStream_t st);
+// dHidden (no maps on its contraction index) and dW (with one) of the same rows, in one launch if both are small
+void launch_f32_gemm_pair(const F32Gemm& dh, const F32Gemm& dw, hipStream_t st);
 // row-wise: lse, logp, gathered logit from a materialised logits chunk z [rows, V]
 void launch_f32_row_lse(const float* z, int64_t V, int64_t rows, int64_t m0, const int32_t* tokc,
                         const int32_t* row_index, const int32_t* counts, float* lse_c, float* logp_out,
