@@ -377,6 +377,7 @@ struct FwdIo {
     const int32_t* group_ids = nullptr;
     int32_t* runs = nullptr;   // if set (with group_ids): where each group lies in the batch
     void* dhidden = nullptr;   // if set: its rows without gradient are cleared
+    bool plan_needed = true;   // lengths, runs or the order of the generations are used by what follows
 };
 
 PlanArgs plan_args(const Plan& p, void* ws, const int32_t* group_ids, int32_t* dev_status) {
@@ -432,12 +433,17 @@ void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, bo
     }
 }
 
+// A small batch whose rows come in the order of the positions, without more about it being asked for, needs no plan: its waves
+// count the mask from its start (rows.hip), a launch less.
+bool plan_left_out(const Plan& p, const FwdIo& io) { return !io.plan_needed && !io.idle.idle && p.Mmax <= ROWS_WITHOUT_PLAN && p.T <= BY_POSITION_T; }
+
 // the compact rows of a planned batch: index, tokens and (bf16) packed hidden rows and sampled tokens' logits, which a
 // storing forward uses as its per-row reference; W is packed already
 void compact_rows(const Plan& p, void* ws, const FwdIo& io, const PlanArgs& plan, hipStream_t st) {
     RowsArgs r;
     r.mask = io.mask; r.N = p.N; r.T = p.T;
-    r.first_row = plan.tab ? plan.gen_row0 : plan.cu;
+    if (plan_left_out(p, io)) r.counts_out = plan.counts;
+    else r.first_row = plan.tab ? plan.gen_row0 : plan.cu;
     r.limits = plan.tab ? plan.tab : plan.counts;
     r.region = plan.tab ? plan.Rcap : INT64_MAX / 4;
     r.stride = plan.tab ? (int)CH_WORDS : 0;
@@ -514,7 +520,7 @@ void run_forward(const Plan& p, void* ws, const FwdIo& io, hipStream_t st) {
         plan.tab = at<int32_t>(ws, p.tab);
         plan.Cmax = 1;
     }
-    {
+    if (!plan_left_out(p, io)) {
         Span sp(ST_COMPACT, st);
         launch_plan(io.mask, p.N, p.T, plan, st);
     }
@@ -616,6 +622,7 @@ int logprob_fwd(const void* hidden, const void* W, const int32_t* tokens, const 
     FwdIo io{hidden, W, tokens, mask, w_layout, temperature, logp_out, lse_out, dev_status};
     io.rms_weight = rms_weight;
     io.rms_eps = rms_eps;
+    io.plan_needed = false;
     run_forward(p, workspace, io, (hipStream_t)stream);
     return check_launch("rapid_logprob_fwd");
 }
@@ -1250,6 +1257,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         bwd_counts = at<int32_t>(ws, p.tab) + CH_LIVE;
     }
     io.dhidden = dhidden_out;
+    io.plan_needed = clip != nullptr || fits != ESTIMATOR_ONE;
     run_forward(p, ws, io, st);
 
     // generation-level log ratios, clipped-weight group baseline, coefficients and loss

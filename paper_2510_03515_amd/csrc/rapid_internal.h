@@ -79,10 +79,12 @@ struct RowsArgs {
     const uint8_t* mask = nullptr;
     int64_t N = 0, T = 0;
     // generation n's rows begin at first_row[n] (negative: left out), inside its region of `region` rows; limits[e * stride]:
-    // counters of region e < entries
+    // counters of region e < entries.  first_row NULL: no plan was made; the rows are the valid positions in order, and their
+    // number goes to counts_out
     const int32_t *first_row = nullptr, *limits = nullptr;
     int64_t region = 0;
     int stride = 0, entries = 0;
+    int32_t* counts_out = nullptr;
     int32_t* row_index = nullptr;               // out: flat position of every row
     const int32_t* tokens = nullptr;            // [N, T]
     int64_t V = 0;
@@ -108,6 +110,9 @@ struct RowsArgs {
     float *zy = nullptr, *refz = nullptr;
     const float* ref_logp = nullptr;            // [N, T]
 };
+constexpr int64_t ROWS_WITHOUT_PLAN = 8192;     // positions up to which the rows may do without a plan (first_row NULL)
+// Above this many positions per generation the waves of rows_by_position_kernel would spend their time on counting.
+constexpr int64_t BY_POSITION_T = 4096;
 // rows: upper bound of the compact rows, padding included
 void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st);
 void launch_rows(const RowsArgs& a, bool by_position, int64_t rows, hipStream_t st);   // its part in rows.hip

@@ -1073,8 +1073,6 @@ void launch_plan(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan
     else plan_kernel<false, false><<<1, 1024, 0, st>>>(plan, mask, T);
 }
 
-// Above this many positions per generation the waves of rows_by_position_kernel would spend their time on counting.
-constexpr int64_t BY_POSITION_T = 4096;
 void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st) {
     if (a.T <= BY_POSITION_T) {
         launch_rows(a, true, rows, st);

@@ -5,8 +5,8 @@
 // One launch, a wave per position (or few): a small batch's call is a matter of launches, and this replaces five of them
 // (index of the rows, copy, sampled tokens' logits, gradient rows without gradient, zeros of the per-token outputs) that
 // took 3 to 5 us each for next to nothing; a large batch reads its hidden rows once instead of twice.  A wave
-// finds the compact row of its first position by counting the mask from the start of the generation, which costs T / 256 loads
-// per lane; above BY_POSITION_T positions the rows are indexed by row_index_kernel first and the waves here take compact
+// finds the compact row of its first position by counting the mask from the start of the generation (at most T / 256 loads per
+// lane) or, without a plan, of the batch; above BY_POSITION_T positions the rows are indexed by row_index_kernel first and the waves here take compact
 // rows.
 #include "rapid_internal.h"
 #include "row_math.h"
@@ -137,6 +137,33 @@ __device__ __forceinline__ void fill_row(const RowsArgs& a, int64_t j, bool pack
     if (pack) zero_row(a.Hc + j * a.ldk, a.Cpad / 2);
 }
 
+// the wave's valid positions among the first n of `mask`
+__device__ __forceinline__ int count_before(const uint8_t* mask, int n) {
+    const int lane = threadIdx.x & 63;
+    int cnt = 0;
+    auto bytes = [](uint32_t w) { return __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u); };   // top bit of every byte that is not 0
+    if (((uintptr_t)mask & 15) == 0) {
+        const int whole = n >> 4;
+#pragma unroll 4
+        for (int c = lane; c < whole; c += 64) {
+            const uint4 w = ((const uint4*)mask)[c];
+            cnt += bytes(w.x) + bytes(w.y) + bytes(w.z) + bytes(w.w);
+        }
+        if (lane < (n & 15)) cnt += mask[whole * 16 + lane] != 0;
+    } else if (((uintptr_t)mask & 3) == 0) {
+        const int whole = n >> 2;
+#pragma unroll 4
+        for (int c = lane; c < whole; c += 64) cnt += bytes(((const uint32_t*)mask)[c]);
+        if (lane < (n & 3)) cnt += mask[whole * 4 + lane] != 0;
+    } else {
+#pragma unroll 4
+        for (int t = lane; t < n; t += 64) cnt += mask[t] != 0;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
+    return cnt;
+}
+
 // Compact rows: generation n's valid positions, in order, take the rows from first_row[n] on (a negative first row: the
 // generation was left out).  They come in regions of `region` rows, and a generation never writes past the end of the region its
 // first row lies in.  Token ids out of range are flagged and replaced by 0.
@@ -148,9 +175,20 @@ __global__ __launch_bounds__(256) void rows_by_position_kernel(RowsArgs a, int p
     const int64_t N = a.N, T = a.T;
     const int64_t b = blockIdx.x, main_blocks = N * blocks_per_generation;
     if (b >= main_blocks) {
-        const int64_t e = (b - main_blocks) / 16;
-        const int32_t* lim = a.limits + e * a.stride;
-        const int64_t first = (int64_t)lim[CNT_M] + (b - main_blocks) % 16 * 16 + wave * 4, end = lim[CNT_MR];
+        const int64_t e = (b - main_blocks) / 16, part = (b - main_blocks) % 16;
+        int64_t M, end;
+        if (a.first_row) {
+            M = a.limits[e * a.stride + CNT_M];
+            end = a.limits[e * a.stride + CNT_MR];
+        } else {
+            M = count_before(a.mask, (int)(N * T));
+            end = (M + ROW_TILE - 1) / ROW_TILE * ROW_TILE;
+            if (part == 0 && threadIdx.x == 0) {
+                a.counts_out[CNT_M] = (int32_t)M;
+                a.counts_out[CNT_MR] = (int32_t)end;
+            }
+        }
+        const int64_t first = M + part * 16 + wave * 4;
         for (int64_t j = first; j < first + 4 && j < end; ++j) fill_row(a, j, PACK != PACK_NONE);
         return;
     }
@@ -158,25 +196,12 @@ __global__ __launch_bounds__(256) void rows_by_position_kernel(RowsArgs a, int p
     const int64_t t0 = (b - n * blocks_per_generation) * 4 * per_wave + wave * per_wave;
     if (t0 >= T) return;
     const uint8_t* row = a.mask + n * T;
-    const int64_t first = a.first_row[n], i_mine = n * T + t0 + lane;
+    const int64_t first = a.first_row ? a.first_row[n] : 0, i_mine = n * T + t0 + lane;
     const bool here = lane < per_wave && t0 + lane < T, valid = here && row[t0 + lane] != 0;
     int tok = valid && a.tokc ? a.tokens[i_mine] : 0;
     const bool idle = a.idle && a.idle[n];
-    int before = 0;       // valid positions of the generation in front of t0
-    if ((T & 3) == 0 && ((uintptr_t)a.mask & 3) == 0) {
-        const int words = (int)(t0 >> 2), rest = (int)(t0 & 3);
-#pragma unroll 4
-        for (int t = lane; t < words + (rest != 0); t += 64) {
-            uint32_t w = ((const uint32_t*)row)[t];
-            if (t == words) w &= (1u << (8 * rest)) - 1u;
-            before += __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);   // top bit of every byte that is not 0
-        }
-    } else {
-#pragma unroll 4
-        for (int t = lane; t < (int)t0; t += 64) before += row[t] != 0;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+    // valid positions in front of t0, of the generation or (no plan) of the batch
+    const int before = a.first_row ? count_before(row, (int)t0) : count_before(a.mask, (int)(n * T + t0));
     const unsigned long long votes = __ballot(valid);
     const int64_t limit = first < 0 ? 0 : (first / a.region + 1) * a.region;
     const int64_t j_mine = first + before + __popcll(votes & ((1ull << lane) - 1ull));
