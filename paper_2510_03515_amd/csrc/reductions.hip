@@ -449,7 +449,8 @@ __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
 // A block of NW waves takes 32 columns (a line of each slot): half a wave, one column per lane, is one of 2 NW groups
 // that fold P / (2 NW) slots each, then the (max, sum) pairs of a column are merged in a fixed tree: the two of a
 // wave in registers, the waves through LDS.  A group's loads are a chain of batches, each a trip to memory: with 4
-// groups per column a few hundred rows took 50 us at P = 1188 (37 batches), with 32 groups 13; 74 000 rows 166 and 138.
+// groups per column a few hundred rows took 50 us at P = 1188, with 32 groups 13; 74 000 rows 166 and 138 (151 with batches of 20 slots
+// instead of 10, which the few rows want).
 // With few slots most of 32 groups are empty and their waves are all the time goes into; 131 072 rows, with the
 // sampled tokens' logits, 1 / 4 / 16 waves: P = 2 33 / 36 / 53 us, P = 16 34 / 37 / 55, P = 32 38 / 38 / 55, P = 128 58 / 54 / 61,
 // P = 256 83 / 79 / 83; 300 rows: P = 16 12 us with any, P = 128 20 / 14 / 13, P = 256 28 / 16 / 13.
@@ -463,6 +464,34 @@ __device__ inline MaxSum merge_pair(const MaxSum& a, const MaxSum& b) {
     if (a.acc > 0.0) r.acc += a.acc * (double)__expf(a.mx - r.mx);
     if (b.acc > 0.0) r.acc += b.acc * (double)__expf(b.mx - r.mx);
     return r;
+}
+// Slots [p_begin, p_end) of a column in batches of UN, whose loads are in flight together; a batch is brought to its own maximum
+// and the sum so far, so that its exponentials do not wait for each other.  A slot without a positive sum counts for nothing.
+constexpr int SLOT_BATCH = 20;
+__device__ __forceinline__ MaxSum fold_slots(const float* __restrict__ part_max, const float* __restrict__ part_sum, int p_begin, int p_end,
+                                             int64_t ld_part, int64_t jl) {
+    constexpr int UN = SLOT_BATCH;
+    MaxSum m{-INFINITY, 0.0};
+    for (int p0 = p_begin; p0 < p_end; p0 += UN) {
+        float pm[UN], ps[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int64_t at = (int64_t)(p0 + u < p_end ? p0 + u : p_end - 1) * ld_part + jl;
+            pm[u] = part_max[at];
+            ps[u] = part_sum[at];
+        }
+        float mx = m.mx;
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            if (p0 + u >= p_end || !(ps[u] > 0.f)) { ps[u] = 0.f; pm[u] = -INFINITY; }
+            mx = fmaxf(mx, pm[u]);
+        }
+        if (m.acc > 0.0) m.acc *= (double)__expf(m.mx - mx);
+#pragma unroll
+        for (int u = 0; u < UN; ++u) m.acc += ps[u] > 0.f ? (double)ps[u] * (double)__expf(pm[u] - mx) : 0.0;
+        m.mx = mx;
+    }
+    return m;
 }
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
@@ -483,30 +512,8 @@ __global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restr
     // The weights exp(pm - mx) are fp32 (relative error 1e-7, far below the fp32 rounding of the
     // partial sums themselves), the accumulation fp64.
     MaxSum m{-INFINITY, 0.0};
-    constexpr int UN = 10;   // slots loaded ahead of the fold: the loads of a batch are in flight together
     const int p_begin = (int)((int64_t)P * q / GROUPS), p_end = (int)((int64_t)P * (q + 1) / GROUPS);
-    if (live) {
-        for (int p0 = p_begin; p0 < p_end; p0 += UN) {
-            float pmv[UN], psv[UN];
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const bool in = p0 + u < p_end;
-                pmv[u] = in ? part_max[(int64_t)(p0 + u) * ld_part + jl] : 0.f;
-                psv[u] = in ? part_sum[(int64_t)(p0 + u) * ld_part + jl] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const float pm = pmv[u], ps = psv[u];
-                if (!(ps > 0.f)) continue;
-                if (pm > m.mx) {
-                    m.acc = m.acc * (double)__expf(m.mx - pm) + (double)ps;   // exp(-inf) = 0 on the first slot
-                    m.mx = pm;
-                } else {
-                    m.acc += (double)ps * (double)__expf(pm - m.mx);
-                }
-            }
-        }
-    }
+    if (live) m = fold_slots(part_max, part_sum, p_begin, p_end, ld_part, jl);
     auto merge_halves = [&]() {   // both partners compute the same pair
         const MaxSum o{__shfl_xor(m.mx, 32, 64), __shfl_xor(m.acc, 32, 64)};
         m = lane < 32 ? merge_pair(m, o) : merge_pair(o, m);
@@ -527,6 +534,46 @@ __global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restr
         merge_halves();
     }
     if (!live || g != 0) return;
+    const double lse = (double)m.mx + log(m.acc);
+    const float lse_f = (float)lse;
+    lse_c[j] = lse_f;
+    const int32_t pos = row_index[j];
+    logp_out[pos] = (float)((double)zy[j] - lse);
+    if (lse_out) lse_out[pos] = lse_f;
+}
+
+// The same for few rows and many slots (what merge_lse_kernel<16> does, same order): 8 columns per block and a thread for each
+// of the 32 groups, so that four times as many compute units read the partials.  290 rows at P = 1188 14.4 -> 11.5 us; 2200 rows 14 and 15.
+__global__ __launch_bounds__(256) void merge_lse_few_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
+                                 int64_t ld_part, const float* __restrict__ zy,
+                                 const int32_t* __restrict__ row_index, const int32_t* __restrict__ counts,
+                                 int64_t row0, float* __restrict__ lse_c, float* __restrict__ logp_out,
+                                 float* __restrict__ lse_out) {
+    constexpr int GROUPS = 32, COLS = 8;
+    __shared__ float s_mx[GROUPS][COLS];
+    __shared__ double s_acc[GROUPS][COLS];
+    const int col = threadIdx.x % COLS, q = threadIdx.x / COLS;
+    const int64_t jl = (int64_t)blockIdx.x * COLS + col, j = row0 + jl;
+    const int M = counts[CNT_M];
+    if (j - col >= M) return;
+    const bool live = j < M;
+    MaxSum m{-INFINITY, 0.0};
+    if (live) m = fold_slots(part_max, part_sum, (int)((int64_t)P * q / GROUPS), (int)((int64_t)P * (q + 1) / GROUPS), ld_part, jl);
+    s_mx[q][col] = m.mx;
+    s_acc[q][col] = m.acc;
+    __syncthreads();
+    auto at = [&](int g) { return MaxSum{s_mx[g][col], s_acc[g][col]}; };
+    if (q < 16) m = merge_pair(at(2 * q), at(2 * q + 1));
+    __syncthreads();
+    if (q < 16) { s_mx[q][col] = m.mx; s_acc[q][col] = m.acc; }
+    __syncthreads();
+    if (q >= 2) return;
+    m = at(8 * q);
+#pragma unroll
+    for (int w = 1; w < 8; ++w) m = merge_pair(m, at(8 * q + w));
+    const MaxSum o{__shfl_down(m.mx, COLS, 64), __shfl_down(m.acc, COLS, 64)};
+    if (q != 0 || !live) return;
+    m = merge_pair(m, o);
     const double lse = (double)m.mx + log(m.acc);
     const float lse_f = (float)lse;
     lse_c[j] = lse_f;
@@ -1095,6 +1142,10 @@ void launch_merge_lse(const float* part_max, const float* part_sum, int P, int64
                       const int32_t* row_index, const int32_t* counts, int64_t row0, int64_t rows_max, float* lse_c,
                       float* logp_out, float* lse_out, hipStream_t st) {
     if (rows_max <= 0) return;
+    if (P > 128 && rows_max <= 1024) {
+        merge_lse_few_kernel<<<blocks_for(rows_max, 8), 256, 0, st>>>(part_max, part_sum, P, ld_part, zy, row_index, counts, row0, lse_c, logp_out, lse_out);
+        return;
+    }
     auto* kernel = P <= 16 ? &merge_lse_kernel<1> : P <= 128 ? &merge_lse_kernel<4> : &merge_lse_kernel<16>;
     kernel<<<blocks_for(rows_max, 32), P <= 16 ? 64 : P <= 128 ? 256 : 1024, 0, st>>>(part_max, part_sum, P, ld_part, zy, row_index,
                                                                                      counts, row0, lse_c, logp_out, lse_out);

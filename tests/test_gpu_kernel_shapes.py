@@ -440,3 +440,67 @@ def test_final_norm_backward_by_width(rb, d, mode):
     assert _rel(_np(out.dhidden), ref["dH"]) <= 2e-2 and _rel(_np(out.dW), ref["dW"]) <= 2e-2
     assert _rel(_np(out.drms_weight), ref["d_rms_weight"]) <= 2e-2
     assert np.abs(_np(out.drms_weight) - ref["d_rms_weight"]).max() <= 2.0 ** -6 * np.abs(ref["d_rms_weight"]).max()
+
+
+@pytest.mark.parametrize("N,T", [(1, 1), (3, 5), (7, 33), (1, 4096), (1, 4097), (2, 4096), (64, 128), (73, 113)])   # up to 8192 positions, T <= 4096: no plan
+@pytest.mark.parametrize("dtype,layout", [("bf16", "dv"), ("bf16", "vd"), ("f32", "dv")])
+def test_rows_without_a_plan(rb, N, T, dtype, layout):
+    print(f"rows without a plan {N} x {T} {dtype} {layout}", flush=True)
+    gen = torch.Generator().manual_seed(N * T)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    mask = (torch.rand((N, T), generator=gen) < 0.6).to(torch.uint8)
+    hidden = torch.randn((N, T, 24), generator=gen).to(dt)
+    W = (torch.randn((24, 40), generator=gen) * 0.3).to(dt)
+    tokens = torch.randint(0, 40, (N, T), generator=gen, dtype=torch.int32)
+    z = hidden.double() @ W.double()
+    lse = torch.logsumexp(z, -1)
+    want = (z.gather(2, tokens.long()[:, :, None])[:, :, 0] - lse) * mask
+    Wg = (W if layout == "dv" else W.t().contiguous()).cuda()
+    for at in (0, 1, 4):            # the mask's alignment decides how it is read
+        buf = torch.zeros(N * T + 16, dtype=torch.uint8, device="cuda")
+        m = buf[at:at + N * T].view(N, T)
+        m.copy_(mask)
+        logp, got = rb.rapid_logprob_fwd(hidden.cuda(), Wg, tokens.cuda(), m, w_layout=rb.W_DV if layout == "dv" else rb.W_VD, want_lse=True)
+        torch.cuda.synchronize()
+        # fp32 sums of 24 products (bf16 path) and of 40 exponentials
+        assert (logp.cpu().double() - want).abs().max() <= 2e-5 and (got.cpu().double() - lse * mask).abs().max() <= 2e-5
+
+
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 300, 1024, 1025])       # 8 columns per block up to 1024 rows, 32 above
+def test_log_sum_exp_of_few_rows(rb, rows):
+    """One order of summation whatever the launch: the rows of a short call have the bits of the same rows in a long one."""
+    print(f"log-sum-exp of {rows} rows", flush=True)
+    gen = torch.Generator().manual_seed(rows)
+    hidden = torch.randn((1, 4097, 64), generator=gen).to(torch.bfloat16).cuda()
+    W = (torch.randn((64, 16700), generator=gen) * 0.5).to(torch.bfloat16).cuda()
+    tokens = torch.randint(0, 16700, (1, 4097), generator=gen, dtype=torch.int32).cuda()
+    ones = torch.ones((1, 4097), dtype=torch.uint8).cuda()
+    full, full_lse = rb.rapid_logprob_fwd(hidden, W, tokens, ones, want_lse=True)
+    lp, lse = rb.rapid_logprob_fwd(hidden[:, :rows].contiguous(), W, tokens[:, :rows].contiguous(), ones[:, :rows].contiguous(), want_lse=True)
+    assert torch.equal(lp, full[:, :rows]) and torch.equal(lse, full_lse[:, :rows])
+
+
+@pytest.mark.parametrize("d", [448, 512, 1024, 1032])        # 7, 8, 16, 17 steps: W requested two steps ahead from 8 per row tile on
+@pytest.mark.parametrize("rows", [5, 256, 257, 512, 513])
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+def test_few_rows_request_w_two_steps_ahead(rb, d, rows, layout):
+    """The same bits as from the packed copies (tuning key 2 = 8), plain and storing forward."""
+    print(f"W two steps ahead d {d} rows {rows} {layout}", flush=True)
+    spec = wl.small_spec("deep", "bf16", d=d, V=33000, prompts=1, G=1, len_lo=rows, len_hi=rows)
+    w, g = _make(spec)
+    W, lay = (g["W"], rb.W_DV) if layout == "dv" else (g["W"].t().contiguous(), rb.W_VD)
+    got = []
+    try:
+        for waves in (0, 8):
+            rb.rapid_set_tuning(2, waves)
+            lp, _ = rb.rapid_logprob_fwd(g["hidden"], W, g["tokens"], g["mask"], w_layout=lay)
+            out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], W, g["tokens"], g["mask"], lp, torch.ones(1, device="cuda"), g["group_ids"], 1,
+                                              w_layout=lay, logits_cache=True)
+            torch.cuda.synchronize()
+            assert out.dev_status.item() == 0 and torch.equal(out.logp_cur, lp)
+            got.append((lp, out.dW.clone(), out.dhidden.clone()))
+    finally:
+        rb.rapid_set_tuning(2, 0)
+    assert torch.equal(got[0][0], got[1][0])
+    for a, b in zip(got[0][1:], got[1][1:]):      # dHidden and dW sum in another order
+        assert _rel(_np(a), _np(b)) <= 4e-3
