@@ -126,12 +126,22 @@ def _check(rc):
         raise RapidError(rc, load().rapid_last_error().decode())
 
 
+# A small call is as long as its Python: pointers are passed as plain integers (the argument types make them void*), and the
+# current stream's handle is asked for without the object around it.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current device's current stream."""
+    return _raw_stream(_current_device()) if torch.cuda.is_initialized() else torch.cuda.current_stream().cuda_stream
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is None or _current_device is None:
+    def _stream():  # noqa: F811
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype_code(t):
@@ -348,17 +358,9 @@ def rapid_iw_pg_loss_fwd_bwd(hidden, W, tokens, mask, logp_behav, rewards, group
     if buffers is None:
         buffers = IwPgBuffers(hidden, W, K, w_layout, logits_cache=logits_cache, max_tokens=max_tokens)
     b = buffers
-    o = default_opts()
-    o.eta = float(eta) if math.isfinite(eta) else float("inf")
-    o.coef_mode, o.baseline_mode = int(coef_mode), int(baseline_mode)
-    o.loss_scale, o.temperature = float(loss_scale), float(temperature)
-    o.w_layout = int(w_layout)
-    o.dw_dtype = _dtype_code(b.dW)
-    o.accumulate_dw = int(bool(accumulate_dw))
-    o.normalized_grads = int(bool(normalized_grads))
-    o.logits_cache = int(bool(logits_cache))
-    o.ratio_level = int(ratio_level)
-    o.max_tokens = int(max_tokens)
+    o = IwPgOpts(float(eta) if math.isfinite(eta) else float("inf"), int(coef_mode), int(baseline_mode), float(loss_scale),
+                 float(temperature), int(w_layout), _dtype_code(b.dW), int(bool(accumulate_dw)), int(bool(normalized_grads)),
+                 int(bool(logits_cache)), int(ratio_level), int(max_tokens))
     if rms_weight is not None:          # hidden is the input of the final RMSNorm; dhidden is dLoss/d(that input)
         _need(rms_weight, hidden.dtype, "rms_weight")
         if getattr(b, "drms_weight", None) is None:
