@@ -14,19 +14,14 @@ __device__ inline void unpack8(const uint4& v, float (&f)[8]) {
     }
 }
 
-// double -> float such that rounding the float to bf16 (nearest even) gives what rounding the double
-// to bf16 directly would: truncate, and set the last bit if anything was cut off ("round to odd"; the
-// sticky bit keeps a value just off a bf16 midpoint from landing on it)
-__device__ inline float round_to_odd_f32(double v) {
-    float f = (float)v;                       // nearest; repaired below if it moved the value
-    if ((double)f != v && isfinite(f)) {
-        uint32_t b = __builtin_bit_cast(uint32_t, f);
-        const bool away = fabs((double)f) > fabs(v);   // rounded away from zero: step back to the truncation
-        if (away) b -= 1u;
-        b |= 1u;
-        f = __builtin_bit_cast(float, b);
-    }
-    return f;
+// double -> float such that rounding the float to bf16 (nearest even) gives what rounding the double to bf16 directly
+// would.  The float nearest to v lies on the same side of every midpoint of two bf16 values as v does, or on it: there, and if
+// v itself is not the midpoint, it is moved off towards v (about one element in 65536).
+__device__ inline float round_for_bf16(double v) {
+    const float f = (float)v;
+    const uint32_t b = __builtin_bit_cast(uint32_t, f);
+    if ((b & 0xffffu) != 0x8000u || (double)f == v || !isfinite(f)) return f;
+    return __builtin_bit_cast(float, fabs((double)f) > fabs(v) ? b - 1u : b + 1u);
 }
 
 __device__ inline uint32_t pack2(float a, float b) {

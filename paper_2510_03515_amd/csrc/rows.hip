@@ -102,7 +102,7 @@ __device__ __forceinline__ void pack_row(const RowsArgs& a, int64_t j, int64_t p
                 float gf[8];
                 unpack8(g[u], gf);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) hf[e] = round_to_odd_f32((double)hf[e] * inv * (double)gf[e]);
+                for (int e = 0; e < 8; ++e) hf[e] = round_for_bf16((double)hf[e] * inv * (double)gf[e]);
                 h[u] = pack8(hf);
                 unpack8(h[u], hf);
             }
