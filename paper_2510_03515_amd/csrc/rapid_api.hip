@@ -1063,7 +1063,10 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     memset(&cl, 0, sizeof(cl));
     if (clip) {
         cl.logp_cur = logp_cur; cl.logp_old = logp_behav; cl.logp_ref = clip->o.kl_beta != 0.f ? clip->logp_ref : nullptr;
-        cl.mask = mask; cl.adv64 = adv64; cl.seq_len = at<int32_t>(ws, p.seq_len); cl.counts = counts; cl.N = N; cl.T = T;
+        cl.seq_len = at<int32_t>(ws, p.seq_len); cl.counts = counts; cl.N = N; cl.T = T; cl.K = K;
+        cl.rewards = rewards; cl.group_ids = group_ids; cl.runs = at<int32_t>(ws, p.gruns); cl.adv = adv;
+        cl.adv_eps = clip->o.adv_eps; cl.std_ddof = clip->o.std_ddof;
+        cl.row_index = row_index; cl.rowg = rowg; cl.dev_status = dev_status;
         cl.eps_low = clip->o.eps_low; cl.eps_high = clip->o.eps_high; cl.kl_beta = clip->o.kl_beta;
         cl.loss_scale = clip->o.loss_scale; cl.norm_mode = clip->o.norm_mode;
     }
@@ -1094,7 +1097,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             launch_small_estimator(e, false, st);
         } else {
             launch_group_advantage(rewards, group_ids, nullptr, logp_behav ? s64 : nullptr, N, K, o.eta, o.baseline_mode,
-                                   adv, adv64, nullptr, nullptr, nullptr, nullptr, gen_range, dev_status, st, 0.f, 0, gruns);
+                                   adv, adv64, nullptr, nullptr, nullptr, nullptr, gen_range, dev_status, st, gruns);
             launch_coefficients(cc, st);
         }
         launch_row_coefficients(g, cc.g64, seqc, row_index, row_counts, logp_cur, logp_behav, per_token, o.eta,
@@ -1154,11 +1157,8 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             forward_rows_bf16(p, ws, io, cnt, base, p.Rcap, st);
             if (clip) {
                 Span sp(ST_ESTIMATOR, st);
-                launch_group_advantage(rewards, group_ids, nullptr, nullptr, N, K, 2.f, BASELINE_NORMALIZED, adv, adv64, nullptr,
-                                       nullptr, nullptr, nullptr, gen_range, dev_status, st, clip->o.adv_eps, clip->o.std_ddof, gruns);
-                launch_clip_generations(cl, gen_range, at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax),
-                                        dev_status, st);
-                launch_clip_rows(cl, seqc, row_index, cnt, base, p.Rcap, rowg, st);
+                cl.first_row = plan.gen_row0; cl.region = p.Rcap; cl.row_counts = cnt;
+                launch_clip_generations(cl, gen_range, at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), st);
             } else {
                 CoefArgs cc = ca;
                 if (p.Cmax > 1) {   // one chunk is the whole batch: coefficients and loss in one pass
@@ -1263,11 +1263,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     // generation-level log ratios, clipped-weight group baseline, coefficients and loss
     if (clip) {
         Span sp(ST_ESTIMATOR, st);
-        launch_group_advantage(rewards, group_ids, nullptr, nullptr, N, K, 2.f, BASELINE_NORMALIZED, adv, adv64, nullptr, nullptr,
-                               nullptr, nullptr, nullptr, dev_status, st, clip->o.adv_eps, clip->o.std_ddof, gruns);
-        launch_clip_generations(cl, nullptr, at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), dev_status, st);
+        // as the plan of run_forward has them
+        cl.first_row = io.idle.idle ? at<int32_t>(ws, p.gen_row0) : at<int32_t>(ws, p.cu);
+        cl.region = io.idle.idle ? p.Mmax_pad : INT64_MAX / 4; cl.row_counts = counts;
+        launch_clip_generations(cl, nullptr, at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), st);
         launch_clip_finish(at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), N, counts, loss_out, clip->diag, st);
-        launch_clip_rows(cl, seqc, row_index, counts, 0, p.Mmax_pad, rowg, st);
     } else {
         estimator(ca, counts, nullptr, 0, p.Mmax_pad);
     }

@@ -660,7 +660,7 @@ __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __res
                                        double log_eta, int baseline_mode, float* __restrict__ adv,
                                        double* __restrict__ adv64, float* __restrict__ weight, float* __restrict__ gmean,
                                        float* __restrict__ gstd, int32_t* __restrict__ gsize,
-                                       const int32_t* __restrict__ gen_range, double adv_eps, int std_ddof,
+                                       const int32_t* __restrict__ gen_range,
                                        const int32_t* __restrict__ runs, int64_t K, int32_t* __restrict__ dev_status) {
     __shared__ double sm[16 * 3];
     const int k = blockIdx.x;
@@ -709,9 +709,7 @@ __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __res
             const double dlt = (double)r - mean;
             sq += dlt * dlt;
             double b;
-            if (baseline_mode == BASELINE_NORMALIZED) {
-                continue;                      // needs the group's std: third pass below
-            } else if (baseline_mode == 0) {
+            if (baseline_mode == 0) {
                 b = sum_wr / cnt;
             } else {
                 const double rest = sum_wr - clipped_weight(s32, s64, n, log_eta) * (double)r;
@@ -723,20 +721,6 @@ __global__ __launch_bounds__(256) void group_advantage_kernel(const float* __res
         }
     }
     sq = block_sum(sq, sm);
-    if (baseline_mode == BASELINE_NORMALIZED) {   // (R - mean) / (std + eps); equal rewards give 0
-        const double den = cnt - (double)std_ddof;
-        const double sd = den > 0.0 ? sqrt(sq / den) : 0.0;
-        for (int64_t n = n_begin + threadIdx.x; n < n_end; n += blockDim.x) {
-            if (group_ids[n] == k) {
-                float r = rewards[n];
-                if (!isfinite(r)) r = 0.f;
-                const double num = (double)r - mean;
-                const double a = num != 0.0 ? num / (sd + adv_eps) : 0.0;
-                adv[n] = (float)a;
-                if (adv64) adv64[n] = a;
-            }
-        }
-    }
     if (threadIdx.x == 0) {
         if (gsize) gsize[k] = (int32_t)cnt;
         if (gmean) gmean[k] = (float)mean;
@@ -1163,12 +1147,11 @@ void launch_seq_logratio(const float* logp_cur, const float* logp_behav, const u
 void launch_group_advantage(const float* rewards, const int32_t* group_ids, const float* s32, const double* s64,
                             int64_t N, int64_t K, float eta, int baseline_mode, float* adv, double* adv64,
                             float* weight, float* gmean, float* gstd, int32_t* gsize, const int32_t* gen_range,
-                            int32_t* dev_status, hipStream_t st, float adv_eps, int std_ddof, const int32_t* runs) {
+                            int32_t* dev_status, hipStream_t st, const int32_t* runs) {
     const double log_eta = (eta > 0.f && std::isfinite(eta)) ? log((double)eta) : (double)INFINITY;
     const unsigned threads = block_threads(N, 256);
     group_advantage_kernel<<<(unsigned)K + blocks_for(N, (int)threads), threads, 0, st>>>(rewards, group_ids, s32, s64, N, log_eta, baseline_mode, adv,
-                                                        adv64, weight, gmean, gstd, gsize, gen_range, (double)adv_eps,
-                                                        std_ddof, runs, K, dev_status);
+                                                        adv64, weight, gmean, gstd, gsize, gen_range, runs, K, dev_status);
 }
 
 // ---- the token-level clipped surrogate of the GRPO / DAPO loss steps ---------------------------
@@ -1218,62 +1201,88 @@ __device__ inline double clip_omega(const ClipArgs& a, int64_t n) {
     return M > 0 ? (double)a.loss_scale / (double)M : 0.0;
 }
 
-__global__ void clip_rows_kernel(ClipArgs a, const int32_t* __restrict__ seqc, const int32_t* __restrict__ row_index,
-                                 const int32_t* __restrict__ row_counts, int64_t row0, float* __restrict__ rowg) {
-    const int64_t j = row0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int M = row_counts[CNT_M], Mr = row_counts[CNT_MR];
-    if (j >= Mr) return;
-    float v = 0.f;
-    if (j < M) {
-        const int32_t n = seqc[j];
-        bool bad = false;
-        v = (float)clip_token(a, row_index[j], a.adv64[n], clip_omega(a, n), &bad).dlogp;
-    }
-    rowg[j] = v;
-}
-
-// one wave per generation
-__global__ void clip_generations_kernel(ClipArgs a, const int32_t* __restrict__ gen_range, double* __restrict__ loss_n,
-                                        double* __restrict__ clipped_n, double* __restrict__ kl_n,
-                                        int32_t* __restrict__ dev_status) {
+// One block per generation: its normalised advantage (every generation works its group's mean and deviation out by itself:
+// a group is a handful of rewards, and a launch is 5 us), its tokens' terms, each formed once for the sums of the generation and
+// for the row's coefficient.  The last block: the rows that fill the row tile up.  (One after the other, group_advantage_kernel, this one and
+// one for the rows took 16 us of a small step.)
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void clip_generations_kernel(ClipArgs a, const int32_t* __restrict__ gen_range, double* __restrict__ loss_n,
+                                        double* __restrict__ clipped_n, double* __restrict__ kl_n) {
+    __shared__ double sm[16 * 3];
     const int64_t n = blockIdx.x;
-    if (n >= a.N) return;
-    if (gen_range && (n < gen_range[0] || n >= gen_range[1])) return;
-    const double omega = clip_omega(a, n), adv = a.adv64[n];
-    double loss = 0.0, ncl = 0.0, kl = 0.0;
-    bool bad = false;
-    for (int64_t t = threadIdx.x; t < a.T; t += WAVE) {
-        const int64_t i = n * a.T + t;
-        if (a.mask[i] == 0) continue;
-        const ClipToken tk = clip_token(a, i, adv, omega, &bad);
-        loss += tk.loss;
-        ncl += tk.clipped ? 1.0 : 0.0;
-        kl += tk.kl;
+    if (n == a.N) {
+        for (int j = a.row_counts[CNT_M] + (int)threadIdx.x; j < a.row_counts[CNT_MR]; j += blockDim.x) a.rowg[j] = 0.f;
+        return;
     }
-    loss = wave_sum(loss);
-    ncl = wave_sum(ncl);
-    kl = wave_sum(kl);
-    if (__any(bad) && threadIdx.x == 0 && dev_status) atomicOr(dev_status, RAPID_STATUS_NONFINITE_LOGP);
+    const int64_t n_first = gen_range ? gen_range[0] : 0, n_last = gen_range ? gen_range[1] : a.N;
+    if (n < n_first || n >= n_last) return;
+    // (R - mean) / (std + eps) over the group, equal rewards give 0
+    const int32_t k = a.group_ids[n];
+    const float mine = a.rewards[n];
+    const int len = a.seq_len[n];
+    const int64_t row0 = a.first_row[n];
+    int bits = isfinite(mine) ? 0 : RAPID_STATUS_NONFINITE_REWARD;
+    double adv = 0.0;
+    if (k < 0 || k >= a.K) {
+        bits |= RAPID_STATUS_BAD_GROUP;
+    } else {
+        int64_t begin = n_first, end = n_last;
+        if (a.runs[3 * a.K] == 0) {      // every group is one run of the batch
+            begin = a.runs[a.K + k] > begin ? a.runs[a.K + k] : begin;
+            end = a.runs[2 * a.K + k] < end ? a.runs[2 * a.K + k] : end;
+        }
+        double cnt = 0.0, sum = 0.0, sq = 0.0;
+        auto reward = [&](int64_t m) { const float r = a.rewards[m]; return isfinite(r) ? (double)r : 0.0; };
+        const int lane = threadIdx.x & (WAVE - 1);
+        for (int64_t m = begin + lane; m < end; m += WAVE)
+            if (a.group_ids[m] == k) { cnt += 1.0; sum += reward(m); }
+        cnt = wave_sum(cnt);
+        const double mean = wave_sum(sum) / cnt;
+        for (int64_t m = begin + lane; m < end; m += WAVE)
+            if (a.group_ids[m] == k) { const double dlt = reward(m) - mean; sq += dlt * dlt; }
+        sq = wave_sum(sq);
+        const double den = cnt - (double)a.std_ddof, sd = den > 0.0 ? sqrt(sq / den) : 0.0, num = reward(n) - mean;
+        adv = num != 0.0 ? num / (sd + (double)a.adv_eps) : 0.0;
+    }
+    if (threadIdx.x == 0) a.adv[n] = (float)adv;
+    const double omega = clip_omega(a, n);
+    double sums[3] = {0.0, 0.0, 0.0};
+    bool bad = false;
+    const int64_t limit = row0 < 0 ? 0 : (row0 / a.region + 1) * a.region, rows = row0 < 0 ? 0 : row0 + len < limit ? len : limit - row0;
+    for (int64_t i = threadIdx.x; i < rows; i += blockDim.x) {
+        const ClipToken tk = clip_token(a, a.row_index[row0 + i], adv, omega, &bad);
+        a.rowg[row0 + i] = (float)tk.dlogp;
+        sums[0] += tk.loss;
+        sums[1] += tk.clipped ? 1.0 : 0.0;
+        sums[2] += tk.kl;
+    }
+    if (__any(bad)) bits |= RAPID_STATUS_NONFINITE_LOGP;
+    if (bits && threadIdx.x % WAVE == 0 && a.dev_status) atomicOr(a.dev_status, bits);
+    if constexpr (ONE_WAVE) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) sums[q] = wave_sum(sums[q]);
+    } else {
+        block_sums<3>(sums, sm);
+    }
     if (threadIdx.x == 0) {
-        loss_n[n] = loss;
-        clipped_n[n] = ncl;
-        kl_n[n] = kl;
+        loss_n[n] = sums[0];
+        clipped_n[n] = sums[1];
+        kl_n[n] = sums[2];
     }
 }
 
 __global__ void clip_finish_kernel(const double* __restrict__ loss_n, const double* __restrict__ clipped_n,
                                    const double* __restrict__ kl_n, int64_t N, const int32_t* __restrict__ counts,
                                    float* __restrict__ loss_out, rapid_clip_pg_diag* __restrict__ diag) {
-    __shared__ double sm[16];
-    double loss = 0.0, ncl = 0.0, kl = 0.0;
+    __shared__ double sm[16 * 3];
+    double sums[3] = {0.0, 0.0, 0.0};
     for (int64_t n = threadIdx.x; n < N; n += blockDim.x) {
-        loss += loss_n[n];
-        ncl += clipped_n[n];
-        kl += kl_n[n];
+        sums[0] += loss_n[n];
+        sums[1] += clipped_n[n];
+        sums[2] += kl_n[n];
     }
-    loss = block_sum(loss, sm);
-    ncl = block_sum(ncl, sm);
-    kl = block_sum(kl, sm);
+    block_sums<3>(sums, sm);
+    const double loss = sums[0], ncl = sums[1], kl = sums[2];
     if (threadIdx.x == 0) {
         loss_out[0] = (float)loss;
         if (diag) {
@@ -1288,18 +1297,13 @@ __global__ void clip_finish_kernel(const double* __restrict__ loss_n, const doub
 
 }  // namespace
 
-void launch_clip_rows(const ClipArgs& a, const int32_t* seqc, const int32_t* row_index, const int32_t* row_counts,
-                      int64_t row0, int64_t rows_max, float* rowg, hipStream_t st) {
-    if (rows_max > 0)
-        clip_rows_kernel<<<blocks_for(rows_max, 256), 256, 0, st>>>(a, seqc, row_index, row_counts, row0, rowg);
-}
-void launch_clip_generations(const ClipArgs& a, const int32_t* gen_range, double* loss_n, double* clipped_n, double* kl_n,
-                             int32_t* dev_status, hipStream_t st) {
-    clip_generations_kernel<<<(unsigned)a.N, WAVE, 0, st>>>(a, gen_range, loss_n, clipped_n, kl_n, dev_status);
+void launch_clip_generations(const ClipArgs& a, const int32_t* gen_range, double* loss_n, double* clipped_n, double* kl_n, hipStream_t st) {
+    const unsigned threads = row_threads(a.T);
+    (threads == WAVE ? &clip_generations_kernel<true> : &clip_generations_kernel<false>)<<<(unsigned)a.N + 1, threads, 0, st>>>(a, gen_range, loss_n, clipped_n, kl_n);
 }
 void launch_clip_finish(const double* loss_n, const double* clipped_n, const double* kl_n, int64_t N, const int32_t* counts,
                         float* loss_out, rapid_clip_pg_diag* diag, hipStream_t st) {
-    clip_finish_kernel<<<1, 1024, 0, st>>>(loss_n, clipped_n, kl_n, N, counts, loss_out, diag);
+    clip_finish_kernel<<<1, block_threads(N, 1024), 0, st>>>(loss_n, clipped_n, kl_n, N, counts, loss_out, diag);
 }
 
 void launch_coefficients(const CoefArgs& a, hipStream_t st) {
