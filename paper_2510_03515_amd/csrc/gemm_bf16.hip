@@ -30,6 +30,7 @@
 // epilogue keeps j = the token row (per-lane scalars: lse, coefficient, token id, output row) and
 // stores 4 consecutive i with one 8- or 16-byte access.
 #include <atomic>
+#include <type_traits>
 #include <utility>
 
 #include "rapid_internal.h"
@@ -1259,19 +1260,30 @@ __device__ __forceinline__ void store_unit(float* part, int unit, const f32x16 (
             off += 16 * S::NT;
         }
 }
-// sum[16] = block (ib, jb) of tile tpos of the cut round, its pieces added in segment order (16 loads in flight together)
+// sum[16] = block (ib, jb) of tile tpos of the cut round, its pieces added in segment order (one after the other, 42 pieces
+// of a tile were 23 us of trips to memory)
 template <class S>
 __device__ __forceinline__ void sum_units(const float* part, const TileShare& sh, int tpos, int ib, int jb, float (&sum)[16]) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) sum[v] = 0.f;
     const float* in = part + (int64_t)tpos * (S::BI * S::BJ) + threadIdx.x + (int64_t)((ib * S::WJ + jb) * 16) * S::NT;
-    for (int seg = 0; seg < sh.segs; ++seg, in += (int64_t)sh.rem * (S::BI * S::BJ)) {
-        float got[16];
+    const int64_t next = (int64_t)sh.rem * (S::BI * S::BJ);
+    auto add = [&](auto pieces) {      // that many pieces, their loads in flight together
+        constexpr int P = decltype(pieces)::value;
+        float got[P][16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) got[v] = in[v * S::NT];
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sum[v] += got[v];
-    }
+            for (int v = 0; v < 16; ++v) got[p][v] = in[p * next + v * S::NT];
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] += got[p][v];
+        in += P * next;
+    };
+    int seg = 0;
+    for (; seg + 4 <= sh.segs; seg += 4) add(std::integral_constant<int, 4>{});
+    for (; seg < sh.segs; ++seg) add(std::integral_constant<int, 1>{});
 }
 
 // ------------------------------------------------------------------------------------------ dh

@@ -841,6 +841,15 @@ __global__ __launch_bounds__(1024) void small_estimator_kernel(EstimatorArgs a, 
     for (int k = tid; k < K; k += threads) s_first[k] = s_end[k] = -1;
     if (tid == 0) s_split = s_longest = s_bits = 0;
     int bits = 0;
+    // generations of the thread's first rows: asked for now, used last
+    constexpr int UR = 8;
+    int32_t gen[UR];
+    const int M = TOKENS ? a.row_counts[CNT_M] : 0, Mr = TOKENS ? a.row_counts[CNT_MR] : 0;
+    auto generations_of = [&](int j0) {
+#pragma unroll
+        for (int q = 0; q < UR; ++q) gen[q] = a.seqc[j0 + q * threads < Mr ? j0 + q * threads : j0];
+    };
+    if (tid < Mr) generations_of(tid);
 
     // log ratios: teams of 8 to 64 lanes, or (few generations) several waves per generation
     int waves_log2 = 0;
@@ -988,12 +997,8 @@ __global__ __launch_bounds__(1024) void small_estimator_kernel(EstimatorArgs a, 
     }
     block_sums<4>(sums, sm);     // its barriers also make s_g visible
     // the rows' coefficients (rows past M up to the row tile: 0)
-    constexpr int UR = 8;
-    const int M = TOKENS ? a.row_counts[CNT_M] : 0, Mr = TOKENS ? a.row_counts[CNT_MR] : 0;
     for (int j0 = tid; j0 < Mr; j0 += UR * threads) {
-        int32_t gen[UR];
-#pragma unroll
-        for (int q = 0; q < UR; ++q) gen[q] = a.seqc[j0 + q * threads < Mr ? j0 + q * threads : j0];
+        if (j0 != tid) generations_of(j0);
 #pragma unroll
         for (int q = 0; q < UR; ++q) {
             const int j = j0 + q * threads;
