@@ -1819,6 +1819,7 @@ void launch_fwd_lse(const FwdArgs& a, hipStream_t st) {
     if (half_tiles(a.tilesV, a.tilesM)) {
         if (a.w.mode == W_VD) { launch_fwd_lse_t<G8_J128, W_VD>(a, st); return; }
         if (a.w.mode == W_DV) { launch_fwd_lse_t<G8_J128, W_DV>(a, st); return; }
+        if (waves_for(8) == 8) { launch_fwd_lse_t<G8_J128, W_PACKED>(a, st); return; }
     }
     // W's steps two ahead (mainloop_deep) where the few rows leave little else to do; a short tile is over before it pays,
     // the steps past its end are fetched for nothing.  Calls at V = 151936, without and with it: 100 tokens at d = 512 64 -> 59 us, d = 1024
@@ -1842,6 +1843,7 @@ void launch_dz(const DzArgs& a, hipStream_t st) {
     const bool half = half_tiles(a.tilesV, a.tilesM);
     if (half && a.w.mode == W_VD) launch_dz_t<G8_J128, W_VD>(a, st);
     else if (half && a.w.mode == W_DV) launch_dz_t<G8_J128, W_DV>(a, st);
+    else if (half && w == 8) launch_dz_t<G8_J128, W_PACKED>(a, st);
     else if (a.w.mode == W_VD) launch_dz_t<G8, W_VD>(a, st);
     else if (a.w.mode == W_DV) launch_dz_t<G8, W_DV>(a, st);
     else if (w == 16) launch_dz_t<G16, W_PACKED>(a, st);
@@ -1867,8 +1869,14 @@ void launch_cache_finish(bf16_t* u, int64_t ldz, bf16_t* Hc, int64_t ldk, const 
 // d = 1024, V = 2000 (8) 40 / 40 and 40 -> 32; d = 128, V = 30000 (13) 56 -> 54 and 39 -> 31; d = 768, V = 20000 (15) 56 -> 51, but
 // dW, whose 237 tiles fill the chip as they are, 43 -> 47; d = 512, V = 16000 (29) 71 -> 73 and 72 -> 63.
 static bool few_steps(int64_t tiles, int64_t ksteps, int most) { return tiles * ksteps <= (int64_t)most * g_num_cu.load(); }
+static bool short_dh_steps(int64_t d, int64_t tilesM, int64_t V) { return few_steps((d + 255) / 256 * tilesM, (V + K_TILE - 1) / K_TILE, 16); }
+// a packed copy has to be laid out for it, and, with no bound on the rows as reading in place has, half the chip has to be without tiles
+bool short_dh_packed(int64_t d, int64_t tilesM, int64_t V) {
+    return default_waves() && (d + 255) / 256 * tilesM <= g_num_cu.load() / 2 && short_dh_steps(d, tilesM, V);
+}
 static bool short_dh(const DhArgs& a) {
-    return a.w.mode != W_PACKED && a.part && few_steps((a.d + 255) / 256 * a.tilesM, (a.w.V + K_TILE - 1) / K_TILE, 16);
+    if (!a.part) return false;
+    return a.w.mode != W_PACKED ? short_dh_steps(a.d, a.tilesM, a.w.V) : a.dtile == 128 && short_dh_packed(a.d, a.tilesM, a.w.V);
 }
 static bool short_dw(const DwArgs& a) {
     const int64_t tiles = (a.d + 255) / 256 * (a.Vpad / 256);
@@ -1880,7 +1888,7 @@ void launch_dh(const DhArgs& a, hipStream_t st) {
     if (short_dh(a)) {
         DhArgs b = a;
         b.dpadR = round_up(a.d, 128);
-        a.w.mode == W_VD ? launch_dh_t<G4_128, W_VD>(b, st) : launch_dh_t<G4_128, W_DV>(b, st);
+        a.w.mode == W_VD ? launch_dh_t<G4_128, W_VD>(b, st) : a.w.mode == W_DV ? launch_dh_t<G4_128, W_DV>(b, st) : launch_dh_t<G4_128, W_PACKED>(b, st);
         return;
     }
     if (a.dtile == 224)
@@ -1940,7 +1948,9 @@ bool launch_dh_dw(const DhArgs& h, const DwArgs& w, hipStream_t st) {
     a.dpadR = b.dpadR = round_up(h.d, 128);
     b.part = w.part + part / 4;
     // dW has the layout of the head that dHidden reads in place
-    h.w.mode == W_VD ? launch_dh_dw_t<W_VD, true>(a, b, st) : launch_dh_dw_t<W_DV, false>(a, b, st);
+    if (h.w.mode == W_VD) launch_dh_dw_t<W_VD, true>(a, b, st);
+    else if (h.w.mode == W_DV) launch_dh_dw_t<W_DV, false>(a, b, st);
+    else w.w_layout == RAPID_W_VD ? launch_dh_dw_t<W_PACKED, true>(a, b, st) : launch_dh_dw_t<W_PACKED, false>(a, b, st);
     return true;
 }
 

@@ -64,6 +64,39 @@ __global__ __launch_bounds__(256) void transpose_pad_bf16_kernel(const bf16_t* _
     }
 }
 
+// Both packed copies of W at once, a tile of 64 x 64 per block: Wvd [Vpad, ldk] (columns below dpad), the operand of the logits
+// kernels, and the tile blocks of RB rows x 64 that dHidden reads ([dpadR, Vpad], see block_rows_bf16_kernel).  W is read
+// once, and a small head's two launches (4 us each) are one: d = 1536, V = 151936 335 -> 250 us.
+template <bool VD>     // W is stored [V, d], else [d, V]
+__global__ __launch_bounds__(256) void pack_both_bf16_kernel(const bf16_t* __restrict__ W, int64_t d, int64_t V, bf16_t* __restrict__ Wvd,
+                                                             int64_t ldk, int64_t dpad, bf16_t* __restrict__ blocks, int64_t dpadR, int RB,
+                                                             int64_t KT) {
+    __shared__ bf16_t tile[64][66];       // rows 33 banks apart: the transposed read is conflict free
+    const int64_t v0 = (int64_t)blockIdx.x * 64, d0 = (int64_t)blockIdx.y * 64;
+    auto at_block = [&](int64_t dd, int64_t v) { return blocks + (dd / RB * KT + v / 64) * (RB * 64) + dd % RB * 64 + v % 64; };
+    auto at_row = [&](int64_t v, int64_t dd) { return Wvd + v * ldk + dd; };
+    for (int t = threadIdx.x; t < 512; t += 256) {
+        const int rr = t >> 3, q = t & 7;
+        const int64_t v = VD ? v0 + rr : v0 + q * 8, dd = VD ? d0 + q * 8 : d0 + rr;
+        const uint4 x = VD ? (v < V ? load_chunk(W + v * d, dd, d) : make_uint4(0u, 0u, 0u, 0u))
+                           : (dd < d ? load_chunk(W + dd * V, v, V) : make_uint4(0u, 0u, 0u, 0u));
+        if (VD) { if (dd < dpad) *(uint4*)at_row(v, dd) = x; }
+        else { if (dd < dpadR) *(uint4*)at_block(dd, v) = x; }
+        uint32_t* p = (uint32_t*)&tile[rr][q * 8];
+        p[0] = x.x; p[1] = x.y; p[2] = x.z; p[3] = x.w;
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < 512; t += 256) {
+        const int cc = t >> 3, q = t & 7;
+        bf16_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = tile[q * 8 + i][cc];
+        const int64_t v = VD ? v0 + q * 8 : v0 + cc, dd = VD ? d0 + cc : d0 + q * 8;
+        if (VD) { if (dd < dpadR) *(uint4*)at_block(dd, v) = *(const uint4*)e; }
+        else { if (dd < dpad) *(uint4*)at_row(v, dd) = *(const uint4*)e; }
+    }
+}
+
 }  // namespace
 
 void launch_copy_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R, int64_t C, int64_t Rpad,
@@ -102,6 +135,12 @@ void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, i
     if (Rpad <= 0 || Cpad <= 0) return;
     dim3 grid((unsigned)((Rpad + 63) / 64), (unsigned)((Cpad + 63) / 64));
     transpose_pad_bf16_kernel<<<grid, 256, 0, st>>>(src, ld_src, dst, ld_dst, R, C, Rpad, Cpad, 0);
+}
+
+void launch_pack_both_bf16(const bf16_t* W, bool vd, int64_t d, int64_t V, bf16_t* Wvd, int64_t ldk, int64_t dpad, bf16_t* blocks,
+                           int64_t dpadR, int RB, int64_t Vpad, hipStream_t st) {
+    const dim3 grid((unsigned)(Vpad / 64), (unsigned)(((dpad > dpadR ? dpad : dpadR) + 63) / 64));
+    (vd ? &pack_both_bf16_kernel<true> : &pack_both_bf16_kernel<false>)<<<grid, 256, 0, st>>>(W, d, V, Wvd, ldk, dpad, blocks, dpadR, RB, Vpad / 64);
 }
 
 }  // namespace rapid

@@ -363,6 +363,9 @@ int check_launch(const char* what) {
 template <class T>
 T* at(void* ws, size_t off) { return (T*)((char*)ws + off); }
 
+// What is packed of W: for the logits, and (a backward follows) for dHidden, in tile blocks or not
+struct PackW { bool backward = false, blocked = true; HiddenTile tile{256, 0}; };
+
 struct FwdIo {
     const void* hidden; const void* W; const int32_t* tokens; const uint8_t* mask;
     int w_layout; float temperature;
@@ -377,6 +380,7 @@ struct FwdIo {
     const int32_t* group_ids = nullptr;
     int32_t* runs = nullptr;   // if set (with group_ids): where each group lies in the batch
     void* dhidden = nullptr;   // if set: its rows without gradient are cleared
+    PackW pack;                // what of W is packed (bf16)
     bool plan_needed = true;   // lengths, runs or the order of the generations are used by what follows
 };
 
@@ -417,13 +421,20 @@ void pack_w_for_logits(const Plan& p, void* ws, const void* W, int w_layout, hip
     if (p.two_wg) launch_block_w32(Wvd, p.ldk, at<bf16_t>(ws, p.Wvd32), p.Vpad, p.dpad, st);
 }
 
-// packs W as [dh.padded, Vpad], in tile blocks or row-major (tuning key 14): the operand of dHidden
-void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, bool blocked, hipStream_t st) {
+// Tile of dHidden's hidden dimension in this call: the plan's, or 128 where few K steps call for it and a packed copy in blocks of
+// 128 rows takes no more room (W in place: the kernel's own choice).
+HiddenTile dh_tiling(const Plan& p, int64_t rows) {
+    const int64_t padded = round_up(p.d, 128);
+    return p.default_waves && padded <= p.dh.padded && short_dh_packed(p.d, rows / 256, p.V) ? HiddenTile{128, padded} : p.dh;
+}
+
+// packs W as [tile.padded, Vpad], in tile blocks or row-major (tuning key 14): the operand of dHidden
+void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, bool blocked, const HiddenTile& tile, hipStream_t st) {
     if (w_in_place(p, W, w_layout, W_FOR_DHIDDEN).mode != W_PACKED) return;
     bf16_t* Wdv = at<bf16_t>(ws, p.Wdv);
     bf16_t* WdvB = at<bf16_t>(ws, p.WdvB);
-    const int RB = p.dh.tile;
-    const int64_t dpadR = p.dh.padded;
+    const int RB = tile.tile;
+    const int64_t dpadR = tile.padded;
     if (w_layout == RAPID_W_DV) {
         if (blocked) launch_block_rows_bf16((const bf16_t*)W, p.V, WdvB, p.d, p.V, dpadR, p.Vpad, RB, st);
         else launch_copy_pad_bf16((const bf16_t*)W, p.V, Wdv, p.ldv, p.d, p.V, dpadR, p.Vpad, st);
@@ -431,6 +442,18 @@ void pack_w_for_dhidden(const Plan& p, void* ws, const void* W, int w_layout, bo
         if (blocked) launch_transpose_blocks_bf16((const bf16_t*)W, p.d, WdvB, p.V, p.d, p.Vpad, dpadR, RB, st);
         else launch_transpose_pad_bf16((const bf16_t*)W, p.d, Wdv, p.ldv, p.V, p.d, p.Vpad, dpadR, st);
     }
+}
+
+// W for the logits and for dHidden, in one pass if both are packed
+void pack_w(const Plan& p, void* ws, const void* W, int w_layout, const PackW& k, hipStream_t st) {
+    if (k.backward && k.blocked && !p.two_wg && w_in_place(p, W, w_layout, W_FOR_LOGITS).mode == W_PACKED &&
+        w_in_place(p, W, w_layout, W_FOR_DHIDDEN).mode == W_PACKED) {
+        launch_pack_both_bf16((const bf16_t*)W, w_layout == RAPID_W_VD, p.d, p.V, at<bf16_t>(ws, p.Wvd), p.ldk, p.dpad,
+                              at<bf16_t>(ws, p.WdvB), k.tile.padded, k.tile.tile, p.Vpad, st);
+        return;
+    }
+    pack_w_for_logits(p, ws, W, w_layout, st);
+    if (k.backward) pack_w_for_dhidden(p, ws, W, w_layout, k.blocked, k.tile, st);
 }
 
 // A small batch whose rows come in the order of the positions, without more about it being asked for, needs no plan: its waves
@@ -526,7 +549,7 @@ void run_forward(const Plan& p, void* ws, const FwdIo& io, hipStream_t st) {
     }
     {
         Span sp(ST_PACK, st);
-        if (p.dtype == RAPID_DTYPE_BF16) pack_w_for_logits(p, ws, io.W, io.w_layout, st);
+        if (p.dtype == RAPID_DTYPE_BF16) pack_w(p, ws, io.W, io.w_layout, io.pack, st);
         compact_rows(p, ws, io, plan, st);
     }
     if (p.dtype == RAPID_DTYPE_BF16) {
@@ -1077,6 +1100,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
     FwdIo io{hidden, W, tokens, mask, o.w_layout, o.temperature, logp_cur, nullptr, dev_status};
     io.rms_weight = o.rms_weight;
     io.rms_eps = o.rms_eps;
+    io.pack = PackW{true, g_blocked_wdv.load() != 0, dh_tiling(p, cached ? p.Rcap : p.Mmax_pad < p.Mc ? p.Mmax_pad : p.Mc)};
 
     // RAPID's estimator over the rows of a region; in one launch, or with one for what concerns whole generations, where it fits
     const int fits = p.Cmax <= 1 ? small_estimator_fits(N, T, K) : ESTIMATOR_LAUNCHES;
@@ -1138,12 +1162,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             Span sp(ST_COMPACT, st);
             launch_plan(mask, N, T, plan, st);
         }
-        const bool blocked_wdv = g_blocked_wdv.load() != 0;
+        const bool blocked_wdv = io.pack.blocked;
         {
             Span sp(ST_PACK, st);
-            pack_w_for_logits(p, ws, W, o.w_layout, st);
+            pack_w(p, ws, W, o.w_layout, io.pack, st);
             compact_rows(p, ws, io, plan, st);
-            pack_w_for_dhidden(p, ws, W, o.w_layout, blocked_wdv, st);
         }
         const int cst = g_cached_step_tiles.load();
         const int64_t cstep = cst > 0 ? ((int64_t)cst * ROW_TILE < p.Rcap ? (int64_t)cst * ROW_TILE : p.Rcap) : p.Rcap;
@@ -1183,7 +1206,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 const int64_t rows = (p.Rcap - r0) < cstep ? (p.Rcap - r0) : cstep;
                 ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
                 ha.Wdv = at<bf16_t>(ws, p.Wdv); ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = cache + r0 * p.ldv;
-                ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dh.padded; ha.dtile = p.dh.tile;
+                ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = io.pack.tile.padded; ha.dtile = io.pack.tile.tile;
                 ha.tilesM = (int)(rows / 256); ha.m0 = base + r0; ha.row_index = row_index; ha.counts = cnt + CH_LIVE;
                 ha.rowc = at<float>(ws, p.rowc);
                 ha.pace = pace_every > 0 ? at<unsigned>(ws, p.pace) : nullptr; ha.pace_every = pace_every;
@@ -1280,11 +1303,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         bf16_t* Hc = at<bf16_t>(ws, p.Hc);
         bf16_t* Wvd = at<bf16_t>(ws, p.Wvd);
         bf16_t* Wdv = at<bf16_t>(ws, p.Wdv);
-        const bool blocked_wdv = g_blocked_wdv.load() != 0;
-        {
-            Span sp(ST_PACK, st);
-            pack_w_for_dhidden(p, ws, W, o.w_layout, blocked_wdv, st);
-        }
+        const bool blocked_wdv = io.pack.blocked;
         const int64_t step = p.Mc;
         int chunk = 0;
         for (int64_t m0 = 0; m0 < p.Mmax_pad; m0 += step, ++chunk) {
@@ -1310,7 +1329,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             }
             DhArgs ha;
             ha.w = w_in_place(p, W, o.w_layout, W_FOR_DHIDDEN);
-            ha.Wdv = Wdv; ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = dz; ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = p.dh.padded; ha.dtile = p.dh.tile;
+            ha.Wdv = Wdv; ha.WdvB = blocked_wdv ? at<bf16_t>(ws, p.WdvB) : nullptr; ha.dz = dz; ha.Vpad = p.Vpad; ha.ldv = p.ldv; ha.d = p.d; ha.dpadR = io.pack.tile.padded; ha.dtile = io.pack.tile.tile;
             ha.tilesM = (int)(rows / 256); ha.m0 = m0; ha.row_index = row_index; ha.counts = bwd_counts;
             ha.rowc = nullptr;
             const int pace_every = g_pace_every.load();

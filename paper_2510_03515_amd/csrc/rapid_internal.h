@@ -216,6 +216,10 @@ void launch_transpose_blocks_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst
 void launch_transpose_pad_bf16(const bf16_t* src, int64_t ld_src, bf16_t* dst, int64_t ld_dst, int64_t R,
                                int64_t C, int64_t Rpad, int64_t Cpad, hipStream_t st);
 
+// both packed copies of W in one pass: Wvd (rows up to Vpad, columns up to dpad) and the tile blocks of RB rows x 64 columns
+void launch_pack_both_bf16(const bf16_t* W, bool vd, int64_t d, int64_t V, bf16_t* Wvd, int64_t ldk, int64_t dpad, bf16_t* blocks,
+                           int64_t dpadR, int RB, int64_t Vpad, hipStream_t st);
+
 // ---- rmsnorm.hip ------------------------------------------------------------------------------
 // dh [N*T, d] holds dL/dh at the valid positions of the compact rows, which come in regions of region_rows rows with their
 // counters at counts[g * stride]; it becomes dL/dx in place, and dweight [d] (may be NULL) dL/dweight.  part: scratch of part_bytes
@@ -313,6 +317,7 @@ struct DhArgs {           // dH[row, :] = dz[row, :] . Wdv^T
     size_t part_bytes = 0;    // tiles along the contraction
 };
 void launch_dh(const DhArgs& a, hipStream_t st);
+bool short_dh_packed(int64_t d, int64_t tilesM, int64_t V);   // whether dHidden wants tiles of 128 x 128 from a packed copy
 size_t dh_part_bytes();   // scratch that lets a dHidden or dW launch cut its last round
 
 struct DwArgs {           // dW (+)= Hc^T . dz over the chunk's rows

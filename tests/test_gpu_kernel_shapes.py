@@ -504,3 +504,23 @@ def test_few_rows_request_w_two_steps_ahead(rb, d, rows, layout):
     assert torch.equal(got[0][0], got[1][0])
     for a, b in zip(got[0][1:], got[1][1:]):      # dHidden and dW sum in another order
         assert _rel(_np(a), _np(b)) <= 4e-3
+
+
+@pytest.mark.parametrize("d,V", [(8, 9), (120, 1001), (192, 999), (328, 2047), (576, 1003), (1032, 259)])    # vocabularies that are not read in place
+@pytest.mark.parametrize("layout", ["dv", "vd"])
+@pytest.mark.parametrize("mode", ["recompute", "cache"])
+def test_packed_heads_of_small_batches(rb, d, V, layout, mode):
+    """Both packed copies in one pass, tiles of 128 for dHidden and of 256 x 128 for the logits: [d, V] with V % 8 != 0, and (as
+    more than 131072 positions would) a [V, d] head through tuning key 2 = 8, whose log-probs have the same bits."""
+    print(f"packed head d {d} V {V} {layout} {mode}", flush=True)
+    spec = wl.small_spec("packed", "bf16", d=d, V=V, prompts=5, G=3, len_lo=5, len_hi=40, reward="uniform")
+    got = []
+    try:
+        for waves in (0, 8):
+            rb.rapid_set_tuning(2, waves)
+            w, out, ref = _run_pair(rb, spec, layout=layout, logits_cache=mode == "cache")
+            _check_pair(rb, spec, out, ref, layout)
+            got.append(out.logp_cur.clone())
+    finally:
+        rb.rapid_set_tuning(2, 0)
+    assert torch.equal(got[0], got[1])
