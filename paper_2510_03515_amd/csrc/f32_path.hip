@@ -226,8 +226,10 @@ __device__ inline double block_reduce(double v, double* sm, bool is_max) {
     return r;
 }
 
-// one block per chunk row: lse over the V logits, log-prob of the sampled token
-__global__ void f32_row_lse_kernel(const float* __restrict__ z, int64_t V, int64_t m0,
+// one block per chunk row: lse over the V logits, log-prob of the sampled token.  PER > 0: V <= 256 PER, the row is loaded once
+// and stays in registers (in two passes over it 640 rows x V = 1000 took 6.2 us, now 4.8; 14 000 rows x 4096 104 -> 79).
+template <int PER>
+__global__ __launch_bounds__(256) void f32_row_lse_kernel(const float* __restrict__ z, int64_t V, int64_t m0,
                                    const int32_t* __restrict__ tokc, const int32_t* __restrict__ row_index,
                                    const int32_t* __restrict__ counts, float* __restrict__ lse_c,
                                    float* __restrict__ logp_out, float* __restrict__ lse_out) {
@@ -235,17 +237,32 @@ __global__ void f32_row_lse_kernel(const float* __restrict__ z, int64_t V, int64
     const int64_t jl = blockIdx.x, j = m0 + jl;
     if (j >= counts[CNT_M]) return;
     const float* row = z + jl * V;
-    double mx = -INFINITY;
-    for (int64_t v = threadIdx.x; v < V; v += blockDim.x) mx = fmax(mx, (double)row[v]);
-    mx = block_reduce(mx, sm, true);
-    double sum = 0.0;
-    for (int64_t v = threadIdx.x; v < V; v += blockDim.x) sum += exp((double)row[v] - mx);
+    const int32_t pos = row_index[j], tok = tokc[j];
+    double mx = -INFINITY, sum = 0.0;
+    if constexpr (PER > 0) {
+        float v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int at = threadIdx.x + 256 * i;
+            v[i] = row[at < V ? at : V - 1];
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (threadIdx.x + 256 * i < V) mx = fmax(mx, (double)v[i]);
+        mx = block_reduce(mx, sm, true);
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (threadIdx.x + 256 * i < V) sum += exp((double)v[i] - mx);
+    } else {
+        for (int64_t v = threadIdx.x; v < V; v += blockDim.x) mx = fmax(mx, (double)row[v]);
+        mx = block_reduce(mx, sm, true);
+        for (int64_t v = threadIdx.x; v < V; v += blockDim.x) sum += exp((double)row[v] - mx);
+    }
     sum = block_reduce(sum, sm, false);
     if (threadIdx.x == 0) {
         const double lse = mx + log(sum);
         lse_c[j] = (float)lse;
-        const int32_t pos = row_index[j];
-        logp_out[pos] = (float)((double)row[tokc[j]] - lse);
+        logp_out[pos] = (float)((double)row[tok] - lse);
         if (lse_out) lse_out[pos] = (float)lse;
     }
 }
@@ -319,9 +336,9 @@ void launch_f32_gemm_pair(const F32Gemm& dh, const F32Gemm& dw, hipStream_t st) 
 void launch_f32_row_lse(const float* z, int64_t V, int64_t rows, int64_t m0, const int32_t* tokc,
                         const int32_t* row_index, const int32_t* counts, float* lse_c, float* logp_out,
                         float* lse_out, hipStream_t st) {
-    if (rows > 0)
-        f32_row_lse_kernel<<<(unsigned)rows, 256, 0, st>>>(z, V, m0, tokc, row_index, counts, lse_c, logp_out,
-                                                           lse_out);
+    if (rows <= 0) return;
+    auto* kernel = V <= 1024 ? &f32_row_lse_kernel<4> : V <= 2048 ? &f32_row_lse_kernel<8> : V <= 4096 ? &f32_row_lse_kernel<16> : &f32_row_lse_kernel<0>;
+    kernel<<<(unsigned)rows, 256, 0, st>>>(z, V, m0, tokc, row_index, counts, lse_c, logp_out, lse_out);
 }
 
 void launch_f32_dz(float* z, int64_t V, int64_t rows, int64_t m0, const int32_t* tokc, const float* lse_c,

@@ -524,3 +524,18 @@ def test_packed_heads_of_small_batches(rb, d, V, layout, mode):
     finally:
         rb.rapid_set_tuning(2, 0)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("V", [1, 255, 257, 1024, 1025, 2048, 2049, 4096, 4097])       # 4, 8, 16 logits per thread, and a loop
+def test_fp32_log_sum_exp_by_vocabulary(rb, V):
+    print(f"fp32 log-sum-exp V {V}", flush=True)
+    gen = torch.Generator().manual_seed(V)
+    hidden, W = torch.randn((3, 11, 20), generator=gen), torch.randn((20, V), generator=gen)
+    tokens = torch.randint(0, V, (3, 11), generator=gen, dtype=torch.int32)
+    z = hidden.double() @ W.double()
+    lse = torch.logsumexp(z, -1)
+    logp, got = rb.rapid_logprob_fwd(hidden.cuda(), W.cuda(), tokens.cuda(), torch.ones((3, 11), dtype=torch.uint8).cuda(), want_lse=True)
+    torch.cuda.synchronize()
+    want = z.gather(2, tokens.long()[:, :, None])[:, :, 0] - lse
+    # logits of magnitude up to about 20 are stored as floats (2^-20 each), log-probs of up to 40 too
+    assert (logp.cpu().double() - want).abs().max() <= 6e-6 and (got.cpu().double() - lse).abs().max() <= 4e-6
