@@ -198,6 +198,8 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
     if (dtype == RAPID_DTYPE_BF16) p.inv_rms = take(cur, (size_t)p.Mmax_pad * 4);   // final-norm option
     if (bwd) {
         p.rowc = take(cur, (size_t)p.Mmax_pad * 4);
+        // Not used any more (the final norm's partial sums lie in dh_part): it keeps the sizes what callers have allocated by.
+        if (dtype == RAPID_DTYPE_BF16) take(cur, (size_t)(Cmax > 0 ? (int64_t)Cmax * ((Rcap + 511) / 512) : (p.Mmax_pad + 511) / 512) * d * 4);
         p.rowg = take(cur, (size_t)p.Mmax_pad * 4);
         p.adv64 = take(cur, (size_t)N * 8);
         p.gruns = take(cur, (size_t)(3 * K + 1) * 4);
