@@ -369,6 +369,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a, const uint8_t* _
             } else {
                 row0 = (int64_t)c * Rcap + before;
             }
+            // Past the chunk's end (the chunk was cut short): left out.  Its rows would be the next chunk's, or lie behind the last.
+            if (row0 >= (int64_t)(c + 1) * Rcap) row0 = -1;
         }
         a.gen_row0[n] = (int32_t)row0;
     }
@@ -393,7 +395,8 @@ __global__ __launch_bounds__(1024) void row_index_kernel(RowsArgs a) {
                 a.seqc[j] = 0;
             }
     int64_t base = a.first_row[n];
-    const int64_t limit = base < 0 ? 0 : (base / a.region + 1) * a.region;
+    const bool left_out = base < 0;
+    const int64_t limit = left_out ? 0 : (base / a.region + 1) * a.region;
     const Stretch s = wave_stretch(T);
     __shared__ int s_cnt[16];
     const int cnt = count_valid(a.mask, n * T, T, s);
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(1024) void row_index_kernel(RowsArgs a) {
             if (t0 + u * WAVE >= s.end) break;
             const unsigned long long b = __ballot(v[u]);
             const int64_t j = base + __popcll(b & ((1ull << lane) - 1ull));
-            if (v[u] && j < limit) {
+            if (v[u] && !left_out && j < limit) {
                 a.row_index[j] = (int32_t)i;
                 if (a.tokc) {
                     const bool in = tok[u] >= 0 && tok[u] < a.V;

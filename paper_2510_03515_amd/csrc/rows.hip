@@ -205,7 +205,7 @@ __global__ __launch_bounds__(256) void rows_by_position_kernel(RowsArgs a, int p
     const unsigned long long votes = __ballot(valid);
     const int64_t limit = first < 0 ? 0 : (first / a.region + 1) * a.region;
     const int64_t j_mine = first + before + __popcll(votes & ((1ull << lane) - 1ull));
-    const bool placed = valid && j_mine < limit;
+    const bool placed = valid && first >= 0 && j_mine < limit;
     if (placed) {
         if (a.row_index) a.row_index[j_mine] = (int32_t)i_mine;
         if (a.tokc) {

@@ -539,3 +539,49 @@ def test_fp32_log_sum_exp_by_vocabulary(rb, V):
     want = z.gather(2, tokens.long()[:, :, None])[:, :, 0] - lse
     # logits of magnitude up to about 20 are stored as floats (2^-20 each), log-probs of up to 40 too
     assert (logp.cpu().double() - want).abs().max() <= 6e-6 and (got.cpu().double() - lse).abs().max() <= 4e-6
+
+
+@pytest.mark.parametrize("T", [60, 4200])          # rows placed by position, and by row_index_kernel
+@pytest.mark.parametrize("chunks", [False, True])
+def test_generations_past_the_end_of_the_cache_place_no_rows(rb, T, chunks):
+    """A broken opts.max_tokens: what the cache has room for is computed as ever, the other positions read 0 and nothing
+    is written for them (a row of theirs would be another chunk's, or lie in front of or behind the buffers)."""
+    print(f"past the end of the cache T {T} chunks {chunks}", flush=True)
+    spec = wl.small_spec("past_end", "bf16", d=136, V=1100, prompts=20, G=3, len_lo=5, len_hi=60, sigma=0.02, reward="uniform")
+    w, g = _make(spec, seed=4)
+    N, T0, d = g["hidden"].shape
+    pad = lambda t: torch.cat([t, torch.zeros((N, T - T0, *t.shape[2:]), dtype=t.dtype, device=t.device)], 1).contiguous()
+    g = dict(g, **{k: pad(g[k]) for k in ("hidden", "tokens", "mask")})
+    K, promise = w["K"], 512
+    logp_b, _ = rb.rapid_logprob_fwd(g["hidden"], g["W_old"], g["tokens"], g["mask"])
+    rewards = torch.ones_like(g["rewards"])
+    args = (g["hidden"], g["W"], g["tokens"], g["mask"], logp_b, rewards, g["group_ids"], K)
+    whole = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=rb.IwPgBuffers(g["hidden"], g["W"], K, logits_cache=True, max_tokens=4096),
+                                        logits_cache=True, max_tokens=4096).logp_cur
+    nbytes = rb.rapid_workspace_bytes(rb.OP_IW_PG_FWD_BWD_CACHED, N, T, d, spec.V, K, rb.DTYPE_BF16, max_tokens=promise)
+    if chunks:
+        nbytes -= 256
+    Rcap = rb.rapid_logits_cache_rows(N, T, d, spec.V, K, promise, nbytes)
+    assert Rcap == (256 if chunks else 512)
+    per_group = g["mask"].long().sum(1).view(K, spec.G).sum(1).tolist()
+    if chunks:                      # whole groups, in 2 * (512 / 256) + 1 chunks
+        kept = rows = 0
+        left = 2 * (promise // Rcap) + 1
+        for n in per_group:
+            if rows + n > Rcap:
+                left, rows = left - 1, 0
+                if left == 0:
+                    break
+            rows, kept = rows + n, kept + n
+    else:
+        kept = Rcap
+    assert 0 < kept < sum(per_group)
+    buf = rb.IwPgBuffers(g["hidden"], g["W"], K, workspace_bytes=nbytes)
+    buf.logp_cur.fill_(float("nan"))
+    out = rb.rapid_iw_pg_loss_fwd_bwd(*args, buffers=buf, logits_cache=True, max_tokens=promise)
+    torch.cuda.synchronize()
+    assert out.dev_status.item() & rb.STATUS_TOKEN_BOUND
+    assert out.read_diag()["n_tokens"] == kept
+    flat = g["mask"].flatten().bool()
+    want = torch.where(flat & (flat.long().cumsum(0) <= kept), whole.flatten(), torch.zeros_like(whole.flatten()))
+    assert torch.equal(out.logp_cur.flatten(), want)
