@@ -121,7 +121,7 @@ struct Plan {
     size_t per_row;     // chunk bytes per row
     size_t fixed, total;
     // offsets into the workspace
-    size_t counts, pace, seq_len, cu, row_index, tokc, seqc, zy, refz, lse_c, inv_rms, rowc, rowg, logp_tmp, s64, s32, adv, adv64, g, g64, tsum, tmax,
+    size_t counts, pace, seq_len, cu, row_index, tokc, seqc, zy, refz, lse_c, inv_rms, rms_part, rowc, rowg, logp_tmp, s64, s32, adv, adv64, g, g64, tsum, tmax,
         Hc, Wvd, Wdv, WdvB, dh_part, part_max, part_sum, dw32, chunk0, tab, gen_row0, gen_chunk, lam_state, lam_chunk, beta_scale, idle, len_live, cu_live, live_group, gruns, Wvd32;
 };
 
@@ -198,8 +198,8 @@ bool make_plan(Plan& p, int op, int64_t N, int64_t T, int64_t d, int64_t V, int6
     if (dtype == RAPID_DTYPE_BF16) p.inv_rms = take(cur, (size_t)p.Mmax_pad * 4);   // final-norm option
     if (bwd) {
         p.rowc = take(cur, (size_t)p.Mmax_pad * 4);
-        // Not used any more (the final norm's partial sums lie in dh_part): it keeps the sizes what callers have allocated by.
-        if (dtype == RAPID_DTYPE_BF16) take(cur, (size_t)(Cmax > 0 ? (int64_t)Cmax * ((Rcap + 511) / 512) : (p.Mmax_pad + 511) / 512) * d * 4);
+        // the final norm's partial sums where dh_part has no room for them; it is counted for every bf16 call, as callers have allocated by
+        if (dtype == RAPID_DTYPE_BF16) p.rms_part = take(cur, (size_t)(Cmax > 0 ? (int64_t)Cmax * ((Rcap + 511) / 512) : (p.Mmax_pad + 511) / 512) * d * 4);
         p.rowg = take(cur, (size_t)p.Mmax_pad * 4);
         p.adv64 = take(cur, (size_t)N * 8);
         p.gruns = take(cur, (size_t)(3 * K + 1) * 4);
@@ -1260,7 +1260,8 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             Span sp(ST_ZERO, st);
             // the scratch of the cut tiles is idle by now
             launch_rmsnorm_backward((const bf16_t*)hidden, (bf16_t*)dhidden_out, d, (const bf16_t*)o.rms_weight, row_index, tab, CH_WORDS,
-                                    p.Cmax, p.Rcap, at<float>(ws, p.inv_rms), at<float>(ws, p.dh_part), dh_part_bytes(), o.drms_weight_out, st);
+                                    p.Cmax, p.Rcap, at<float>(ws, p.inv_rms), at<float>(ws, p.dh_part), dh_part_bytes(), at<float>(ws, p.rms_part),
+                                    o.drms_weight_out, st);
         }
         if (dw_staged && !dw_bf16) {
             Span sp(ST_CONVERT, st);
@@ -1358,7 +1359,8 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         if (o.rms_weight) {   // dhidden holds dL/dh of the normalised state: on to dL/dweight and dL/dx
             Span sp(ST_ZERO, st);
             launch_rmsnorm_backward((const bf16_t*)hidden, (bf16_t*)dhidden_out, d, (const bf16_t*)o.rms_weight, row_index, counts, 0, 1,
-                                    p.Mmax_pad, at<float>(ws, p.inv_rms), at<float>(ws, p.dh_part), dh_part_bytes(), o.drms_weight_out, st);
+                                    p.Mmax_pad, at<float>(ws, p.inv_rms), at<float>(ws, p.dh_part), dh_part_bytes(), at<float>(ws, p.rms_part),
+                                    o.drms_weight_out, st);
         }
     } else {
         float* z = at<float>(ws, p.chunk0);

@@ -223,10 +223,10 @@ void launch_pack_both_bf16(const bf16_t* W, bool vd, int64_t d, int64_t V, bf16_
 // ---- rmsnorm.hip ------------------------------------------------------------------------------
 // dh [N*T, d] holds dL/dh at the valid positions of the compact rows, which come in regions of region_rows rows with their
 // counters at counts[g * stride]; it becomes dL/dx in place, and dweight [d] (may be NULL) dL/dweight.  part: scratch of part_bytes
-// (128 MiB) for the partial sums.
+// (128 MiB) for the partial sums; part_512: scratch that has room for a row of d sums per 512 rows of every region.
 void launch_rmsnorm_backward(const bf16_t* x, bf16_t* dh, int64_t d, const bf16_t* weight, const int32_t* row_index,
                              const int32_t* counts, int stride, int regions, int64_t region_rows, const float* inv_rms, float* part,
-                             size_t part_bytes, float* dweight, hipStream_t st);
+                             size_t part_bytes, float* part_512, float* dweight, hipStream_t st);
 
 // ---- gemm_bf16.hip ----------------------------------------------------------------------------
 // The head as the caller has it.  mode says how a kernel reads it: from a packed copy (the argument structs hold those),

@@ -204,13 +204,14 @@ __global__ __launch_bounds__(256) void rmsnorm_dx_kernel(const bf16_t* __restric
 
 void launch_rmsnorm_backward(const bf16_t* x, bf16_t* dh, int64_t d, const bf16_t* weight, const int32_t* row_index,
                              const int32_t* counts, int stride, int regions, int64_t region_rows, const float* inv_rms, float* part,
-                             size_t part_bytes, float* dweight, hipStream_t st) {
+                             size_t part_bytes, float* part_512, float* dweight, hipStream_t st) {
     const int C = (int)((d / 8 + 63) / 64);
     const bool narrow = C <= 4;
     // rows per block: few for a small batch, whose rows then go side by side; more if the partial sums would not fit
     int rows = narrow ? ((int64_t)regions * region_rows <= 8192 ? 8 : 32) : 32;
     auto blocks = [&]() { return (region_rows + rows - 1) / rows; };
-    while ((size_t)(blocks() * regions * d) * 4 > part_bytes) rows *= 2;
+    while (rows < 512 && (size_t)(blocks() * regions * d) * 4 > part_bytes) rows *= 2;
+    if ((size_t)(blocks() * regions * d) * 4 > part_bytes) part = part_512;      // thousands of small regions, each with a block of its own
     for (int g = 0; g < regions; ++g) {
         const int32_t* cnt = counts + (int64_t)g * stride;
         const int64_t row0 = g * region_rows;
