@@ -1232,25 +1232,14 @@ struct TileShare {     // how a launch of `grid` workgroups works through `total
         // S with the shortest last round, counted in K steps of a workgroup: the segments of its units, about 5 steps for
         // filling the pipeline and storing the accumulators, and the second pass over 256 KiB per unit (1 / 25 step each).
         // In whole numbers (25 S times the cost), so that the kernel that cuts and the one that adds the pieces agree.
-        // A lane per candidate 1, 2 .. 8, 10, 12, .. 63 and a minimum over the wave (the shortest of equals is the smallest S): one after the
-        // other they took 2 us of every launch that asks.
         segs = 1;
+        int64_t best = 25 * ((int64_t)ktiles + 4);
         if (can_cut && rem > 0) {
-            constexpr unsigned char candidates[32] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 15, 18, 22, 27, 33, 41, 51, 63};   // 8, 8 + 8 / 4, ..
-            const int lane = threadIdx.x & 31;
-            int sg = candidates[lane];
-            const bool fits = sg == 1 || (sg > 1 && rem * sg <= MAX_UNITS && sg * 4 <= ktiles);
-            const int rounds = fits ? (rem * sg + grid - 1) / grid : 0;
-            int64_t cost = sg == 1 ? 25 * ((int64_t)ktiles + 4) : 25 * (int64_t)rounds * (ktiles + 5 * sg) + rem * sg * sg;
-            if (!fits) { sg = 1; cost = INT64_MAX / 128; }
-#pragma unroll
-            for (int o = 16; o > 0; o >>= 1) {
-                const int64_t oc = __shfl_xor(cost, o, 64);
-                const int os = __shfl_xor(sg, o, 64);
-                const int64_t mine = cost * os, other = oc * sg;
-                if (other < mine || (other == mine && os < sg)) { cost = oc; sg = os; }
+            for (int sg = 2; sg <= 64 && rem * sg <= MAX_UNITS && sg * 4 <= ktiles; sg += sg < 8 ? 1 : sg / 4) {
+                const int rounds = (rem * sg + grid - 1) / grid;
+                const int64_t cost = 25 * (int64_t)rounds * (ktiles + 5 * sg) + rem * sg * sg;
+                if (cost * segs < best * sg) { best = cost; segs = sg; }
             }
-            segs = __builtin_amdgcn_readfirstlane(sg);
         }
         cut = segs > 1;
         unit_share = (rem * segs + 7) / 8;
