@@ -452,8 +452,7 @@ __global__ void fill_f32_kernel(float* p, int64_t n, float v) {
 // A block of NW waves takes 32 columns (a line of each slot): half a wave, one column per lane, is one of 2 NW groups
 // that fold P / (2 NW) slots each, then the (max, sum) pairs of a column are merged in a fixed tree: the two of a
 // wave in registers, the waves through LDS.  A group's loads are a chain of batches, each a trip to memory: with 4
-// groups per column a few hundred rows took 50 us at P = 1188, with 32 groups 13; 74 000 rows 166 and 138 (151 with batches of 20 slots
-// instead of 10, which the few rows want).
+// groups per column a few hundred rows took 50 us at P = 1188, with 32 groups 13; 74 000 rows 166 and 138.
 // With few slots most of 32 groups are empty and their waves are all the time goes into; 131 072 rows, with the
 // sampled tokens' logits, 1 / 4 / 16 waves: P = 2 33 / 36 / 53 us, P = 16 34 / 37 / 55, P = 32 38 / 38 / 55, P = 128 58 / 54 / 61,
 // P = 256 83 / 79 / 83; 300 rows: P = 16 12 us with any, P = 128 20 / 14 / 13, P = 256 28 / 16 / 13.
@@ -468,31 +467,33 @@ __device__ inline MaxSum merge_pair(const MaxSum& a, const MaxSum& b) {
     if (b.acc > 0.0) r.acc += b.acc * (double)__expf(b.mx - r.mx);
     return r;
 }
-// Slots [p_begin, p_end) of a column in batches of UN, whose loads are in flight together; a batch is brought to its own maximum
-// and the sum so far, so that its exponentials do not wait for each other.  A slot without a positive sum counts for nothing.
-constexpr int SLOT_BATCH = 20;
+// Slots [p_begin, p_end) of a column, one after the other with a running maximum; a slot without a positive sum counts for
+// nothing.  The loads of a batch of UN are in flight together (a matter of time alone), and its exponentials do not wait for
+// each other: the running maximum is known in front of every slot, and a slot takes one exponential, of the sum so far if it
+// raises the maximum and of its own sum if not.
+template <int UN>
 __device__ __forceinline__ MaxSum fold_slots(const float* __restrict__ part_max, const float* __restrict__ part_sum, int p_begin, int p_end,
                                              int64_t ld_part, int64_t jl) {
-    constexpr int UN = SLOT_BATCH;
     MaxSum m{-INFINITY, 0.0};
     for (int p0 = p_begin; p0 < p_end; p0 += UN) {
-        float pm[UN], ps[UN];
+        float pm[UN], ps[UN], e[UN];
+        bool up[UN];
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int64_t at = (int64_t)(p0 + u < p_end ? p0 + u : p_end - 1) * ld_part + jl;
             pm[u] = part_max[at];
             ps[u] = part_sum[at];
         }
-        float mx = m.mx;
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            if (p0 + u >= p_end || !(ps[u] > 0.f)) { ps[u] = 0.f; pm[u] = -INFINITY; }
-            mx = fmaxf(mx, pm[u]);
+            const bool counts = p0 + u < p_end && ps[u] > 0.f;
+            up[u] = counts && pm[u] > m.mx;
+            e[u] = counts ? __expf(up[u] ? m.mx - pm[u] : pm[u] - m.mx) : 1.f;
+            if (!counts) ps[u] = 0.f;
+            if (up[u]) m.mx = pm[u];
         }
-        if (m.acc > 0.0) m.acc *= (double)__expf(m.mx - mx);
 #pragma unroll
-        for (int u = 0; u < UN; ++u) m.acc += ps[u] > 0.f ? (double)ps[u] * (double)__expf(pm[u] - mx) : 0.0;
-        m.mx = mx;
+        for (int u = 0; u < UN; ++u) m.acc = up[u] ? fma(m.acc, (double)e[u], (double)ps[u]) : fma((double)ps[u], (double)e[u], m.acc);
     }
     return m;
 }
@@ -511,12 +512,11 @@ __global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restr
     const int M = counts[CNT_M];
     if (row0 + (int64_t)blockIdx.x * 32 >= M) return;
     const bool live = j < M;
-    // one pass with a running maximum; slots are merged in a fixed order, so the result is reproducible.
     // The weights exp(pm - mx) are fp32 (relative error 1e-7, far below the fp32 rounding of the
     // partial sums themselves), the accumulation fp64.
     MaxSum m{-INFINITY, 0.0};
     const int p_begin = (int)((int64_t)P * q / GROUPS), p_end = (int)((int64_t)P * (q + 1) / GROUPS);
-    if (live) m = fold_slots(part_max, part_sum, p_begin, p_end, ld_part, jl);
+    if (live) m = fold_slots<10>(part_max, part_sum, p_begin, p_end, ld_part, jl);
     auto merge_halves = [&]() {   // both partners compute the same pair
         const MaxSum o{__shfl_xor(m.mx, 32, 64), __shfl_xor(m.acc, 32, 64)};
         m = lane < 32 ? merge_pair(m, o) : merge_pair(o, m);
@@ -546,7 +546,8 @@ __global__ __launch_bounds__(64 * NW) void merge_lse_kernel(const float* __restr
 }
 
 // The same for few rows and many slots (what merge_lse_kernel<16> does, same order): 8 columns per block and a thread for each
-// of the 32 groups, so that four times as many compute units read the partials.  290 rows at P = 1188 14.4 -> 11.5 us; 2200 rows 14 and 15.
+// of the 32 groups, so that four times as many compute units read the partials, twice as many slots ahead.  P = 1188, d = 64: 290
+// rows 11.6 -> 8.8 us; with 2200 rows the kernel above takes 11.4.
 __global__ __launch_bounds__(256) void merge_lse_few_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum, int P,
                                  int64_t ld_part, const float* __restrict__ zy,
                                  const int32_t* __restrict__ row_index, const int32_t* __restrict__ counts,
@@ -561,7 +562,7 @@ __global__ __launch_bounds__(256) void merge_lse_few_kernel(const float* __restr
     if (j - col >= M) return;
     const bool live = j < M;
     MaxSum m{-INFINITY, 0.0};
-    if (live) m = fold_slots(part_max, part_sum, (int)((int64_t)P * q / GROUPS), (int)((int64_t)P * (q + 1) / GROUPS), ld_part, jl);
+    if (live) m = fold_slots<20>(part_max, part_sum, (int)((int64_t)P * q / GROUPS), (int)((int64_t)P * (q + 1) / GROUPS), ld_part, jl);
     s_mx[q][col] = m.mx;
     s_acc[q][col] = m.acc;
     __syncthreads();
