@@ -112,7 +112,7 @@ struct RowsArgs {
 };
 constexpr int64_t ROWS_WITHOUT_PLAN = 8192;     // positions up to which the rows may do without a plan (first_row NULL)
 // Above this many positions per generation the waves of rows_by_position_kernel would spend their time on counting.
-constexpr int64_t BY_POSITION_T = 4096;
+constexpr int64_t BY_POSITION_T = 4096;         // (launch_compact_rows: which batches take it)
 // rows: upper bound of the compact rows, padding included
 void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st);
 void launch_rows(const RowsArgs& a, bool by_position, int64_t rows, hipStream_t st);   // its part in rows.hip

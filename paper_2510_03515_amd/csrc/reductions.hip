@@ -380,8 +380,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a, const uint8_t* _
     }
 }
 
-// The rows' positions, tokens and generations for batches of long sequences (see rows_by_position_kernel, which does the same
-// for the others); one block per generation.
+// The rows' positions, tokens and generations where rows_by_position_kernel does not find them (launch_compact_rows); one block
+// per generation.
 // A wave's loop is a chain of trips to memory, so it takes 4 x 64 positions at a time, mask and tokens together, and the
 // waves of the sequence share it (each counts its stretch first).  One wave, one load after the other: 1 x 131 072
 // positions 500 us, 19 now.
@@ -398,11 +398,13 @@ __global__ __launch_bounds__(1024) void row_index_kernel(RowsArgs a) {
     const bool left_out = base < 0;
     const int64_t limit = left_out ? 0 : (base / a.region + 1) * a.region;
     const Stretch s = wave_stretch(T);
-    __shared__ int s_cnt[16];
-    const int cnt = count_valid(a.mask, n * T, T, s);
-    if (lane == 0) s_cnt[wave] = cnt;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) base += s_cnt[w];
+    if (blockDim.x > WAVE) {
+        __shared__ int s_cnt[16];
+        const int cnt = count_valid(a.mask, n * T, T, s);
+        if (lane == 0) s_cnt[wave] = cnt;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) base += s_cnt[w];
+    }
     bool bad = false;
     constexpr int U = 4;
     for (int64_t t0 = s.begin; t0 < s.end; t0 += U * WAVE) {
@@ -1113,8 +1115,13 @@ void launch_plan(const uint8_t* mask, int64_t N, int64_t T, const PlanArgs& plan
     else plan_kernel<false, false><<<1, 1024, 0, st>>>(plan, mask, T);
 }
 
+// By position, in one launch, where that is a matter of launches or where gradient rows have to be cleared too, a launch with a block
+// per position; else with an index of the rows in front.  A wave that packs nothing has a few positions to place and counts
+// the whole generation for it: rapid_compaction of 256 x 4096 positions 64 us against 14, of 4096 x 512 117 and 19, of 20 000 x 100 156
+// and 40, of 4 x 1024 10 and 10.  Log-probs (d = 1536, V = 256), by position and with an index: 4 x 1024 54 and 60 us, 64 x 250 101
+// and 97, 4 x 4096 110 and 110, 64 x 1024 135 and 131, 1024 x 256 608 and 533, 256 x 4096 1979 and 1929.
 void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st) {
-    if (a.T <= BY_POSITION_T) {
+    if (a.T <= BY_POSITION_T && (a.dhidden || a.N * a.T <= ROWS_WITHOUT_PLAN)) {
         launch_rows(a, true, rows, st);
         return;
     }

@@ -6,8 +6,8 @@
 // (index of the rows, copy, sampled tokens' logits, gradient rows without gradient, zeros of the per-token outputs) that
 // took 3 to 5 us each for next to nothing; a large batch reads its hidden rows once instead of twice.  A wave
 // finds the compact row of its first position by counting the mask from the start of the generation (at most T / 256 loads per
-// lane) or, without a plan, of the batch; above BY_POSITION_T positions the rows are indexed by row_index_kernel first and the waves here take compact
-// rows.
+// lane) or, without a plan, of the batch; where that does not pay (launch_compact_rows) the rows are indexed by row_index_kernel first
+// and the waves here take compact rows.
 #include "rapid_internal.h"
 #include "row_math.h"
 

@@ -466,6 +466,56 @@ def test_rows_without_a_plan(rb, N, T, dtype, layout):
         assert (logp.cpu().double() - want).abs().max() <= 2e-5 and (got.cpu().double() - lse * mask).abs().max() <= 2e-5
 
 
+# more than 8192 positions and no gradient rows: an index in front of the rows; one wave per generation and (from 512 positions on) several
+@pytest.mark.parametrize("N,T", [(4100, 2), (130, 64), (33, 249), (17, 511), (16, 513), (9, 1024), (3, 2731), (3, 4096)])
+@pytest.mark.parametrize("dtype,layout", [("bf16", "dv"), ("bf16", "vd"), ("f32", "dv")])
+def test_rows_with_an_index(rb, N, T, dtype, layout):
+    print(f"rows with an index {N} x {T} {dtype} {layout}", flush=True)
+    gen = torch.Generator().manual_seed(N * T)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    mask = (torch.rand((N, T), generator=gen) < 0.6).to(torch.uint8)
+    hidden = torch.randn((N, T, 24), generator=gen).to(dt)
+    W = (torch.randn((24, 40), generator=gen) * 0.3).to(dt)
+    tokens = torch.randint(0, 40, (N, T), generator=gen, dtype=torch.int32)
+    z = hidden.double() @ W.double()
+    lse = torch.logsumexp(z, -1)
+    want = (z.gather(2, tokens.long()[:, :, None])[:, :, 0] - lse) * mask
+    Wg = (W if layout == "dv" else W.t().contiguous()).cuda()
+    for at in (0, 1, 4):            # the mask's alignment decides how it is read
+        buf = torch.zeros(N * T + 16, dtype=torch.uint8, device="cuda")
+        m = buf[at:at + N * T].view(N, T)
+        m.copy_(mask)
+        logp, got = rb.rapid_logprob_fwd(hidden.cuda(), Wg, tokens.cuda(), m, w_layout=rb.W_DV if layout == "dv" else rb.W_VD, want_lse=True)
+        sl, cu, ri = rb.rapid_compaction(m)
+        torch.cuda.synchronize()
+        # as test_rows_without_a_plan: fp32 sums of 24 products (bf16 path) and of 40 exponentials
+        assert (logp.cpu().double() - want).abs().max() <= 2e-5 and (got.cpu().double() - lse * mask).abs().max() <= 2e-5
+        count = int(mask.sum())
+        assert torch.equal(sl.cpu().long(), mask.long().sum(1)) and int(cu[N]) == count
+        assert torch.equal(ri.cpu()[:count].long(), torch.nonzero(mask.flatten()).flatten()) and bool((ri[count:] == -1).all())
+
+
+def test_compaction_time_is_that_of_the_positions(rb):
+    """The same two million positions in 256 long and in 4096 short generations: with a wave for every 16 positions, each counting
+    its generation up to there, the short ones took six times as long."""
+    def microseconds(N, T):
+        mask = torch.ones((N, T), dtype=torch.uint8, device="cuda")
+        rb.rapid_compaction(mask)
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                rb.rapid_compaction(mask)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 20 * 1e3)
+        return min(times)
+    long, short = microseconds(256, 8192), microseconds(4096, 512)
+    print(f"compaction: 256 x 8192 {long:.1f} us, 4096 x 512 {short:.1f} us", flush=True)
+    assert short <= 3.0 * long + 20.0
+
+
 @pytest.mark.parametrize("rows", [1, 7, 8, 9, 300, 1024, 1025])       # 8 columns per block up to 1024 rows, 32 above
 def test_log_sum_exp_of_few_rows(rb, rows):
     """One order of summation whatever the launch: the rows of a short call have the bits of the same rows in a long one."""
