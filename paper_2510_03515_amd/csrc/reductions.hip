@@ -385,9 +385,10 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a, const uint8_t* _
 // A wave's loop is a chain of trips to memory, so it takes 4 x 64 positions at a time, mask and tokens together, and the
 // waves of the sequence share it (each counts its stretch first).  One wave, one load after the other: 1 x 131 072
 // positions 500 us, 19 now.
-__global__ __launch_bounds__(1024) void row_index_kernel(RowsArgs a) {
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void row_index_kernel(RowsArgs a) {
     const int64_t n = blockIdx.x, T = a.T;
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    const int lane = threadIdx.x & (WAVE - 1);
     if (a.tokc)
         for (int64_t e = n; e < a.entries; e += a.N)
             for (int j = a.limits[e * a.stride + CNT_M] + (int)threadIdx.x; j < a.limits[e * a.stride + CNT_MR]; j += blockDim.x) {
@@ -397,10 +398,10 @@ __global__ __launch_bounds__(1024) void row_index_kernel(RowsArgs a) {
     int64_t base = a.first_row[n];
     const bool left_out = base < 0;
     const int64_t limit = left_out ? 0 : (base / a.region + 1) * a.region;
-    const Stretch s = wave_stretch(T);
-    if (blockDim.x > WAVE) {
+    const Stretch s = ONE_WAVE ? Stretch{0, T} : wave_stretch(T);
+    if constexpr (!ONE_WAVE) {
         __shared__ int s_cnt[16];
-        const int cnt = count_valid(a.mask, n * T, T, s);
+        const int cnt = count_valid(a.mask, n * T, T, s), wave = threadIdx.x / WAVE;
         if (lane == 0) s_cnt[wave] = cnt;
         __syncthreads();
         for (int w = 0; w < wave; ++w) base += s_cnt[w];
@@ -1126,7 +1127,7 @@ void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st) {
         return;
     }
     const unsigned threads = row_threads(a.T);
-    row_index_kernel<<<(unsigned)a.N, threads, 0, st>>>(a);
+    (threads == WAVE ? &row_index_kernel<true> : &row_index_kernel<false>)<<<(unsigned)a.N, threads, 0, st>>>(a);
     if (a.dhidden) zero_masked_rows_kernel<<<(unsigned)(a.N * a.T), 128, 0, st>>>(a.dhidden, a.mask, a.N * a.T, a.words_per_row, a.idle, a.T);
     if (a.Hc) launch_rows(a, false, rows, st);
 }
