@@ -111,8 +111,11 @@ struct RowsArgs {
     const float* ref_logp = nullptr;            // [N, T]
 };
 constexpr int64_t ROWS_WITHOUT_PLAN = 8192;     // positions up to which the rows may do without a plan (first_row NULL)
-// Above this many positions per generation the waves of rows_by_position_kernel would spend their time on counting.
-constexpr int64_t BY_POSITION_T = 4096;         // (launch_compact_rows: which batches take it)
+// Positions per generation up to which calls with gradient rows take rows_by_position_kernel, whose waves count a generation's
+// mask up to their place.  Steps of V = 256 by position and with an index of the rows, cached: 64 x 4095, d = 1024 961 and 975 us, 64 x 512
+// 192 and 197, 1024 x 250 1022 and 974; just past the bound by position is still ahead (64 x 4097 947 and 963, 16 x 8192 551 and
+// 555), but what a wave counts grows with the length.
+constexpr int64_t BY_POSITION_T = 4096;
 // rows: upper bound of the compact rows, padding included
 void launch_compact_rows(const RowsArgs& a, int64_t rows, hipStream_t st);
 void launch_rows(const RowsArgs& a, bool by_position, int64_t rows, hipStream_t st);   // its part in rows.hip

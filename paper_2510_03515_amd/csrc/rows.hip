@@ -5,9 +5,9 @@
 // One launch, a wave per position (or few): a small batch's call is a matter of launches, and this replaces five of them
 // (index of the rows, copy, sampled tokens' logits, gradient rows without gradient, zeros of the per-token outputs) that
 // took 3 to 5 us each for next to nothing; a large batch reads its hidden rows once instead of twice.  A wave
-// finds the compact row of its first position by counting the mask from the start of the generation (at most T / 256 loads per
-// lane) or, without a plan, of the batch; where that does not pay (launch_compact_rows) the rows are indexed by row_index_kernel first
-// and the waves here take compact rows.
+// finds the compact row of its first position by counting the mask from the start of the generation, 16 bytes per lane and
+// load wherever the mask starts (T / 1024 loads and one for the edges), or, without a plan, of the batch; where that does not
+// pay (launch_compact_rows) the rows are indexed by row_index_kernel first and the waves here take compact rows.
 #include "rapid_internal.h"
 #include "row_math.h"
 
@@ -137,28 +137,20 @@ __device__ __forceinline__ void fill_row(const RowsArgs& a, int64_t j, bool pack
     if (pack) zero_row(a.Hc + j * a.ldk, a.Cpad / 2);
 }
 
-// the wave's valid positions among the first n of `mask`
+// the wave's valid positions among the first n of `mask`: 16-byte words, and one lane each for the bytes in front of the first
+// and behind the last of them
 __device__ __forceinline__ int count_before(const uint8_t* mask, int n) {
     const int lane = threadIdx.x & 63;
-    int cnt = 0;
+    const int align = (int)(-(uintptr_t)mask & 15), head = align < n ? align : n, words = (n - head) >> 4;
     auto bytes = [](uint32_t w) { return __popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u); };   // top bit of every byte that is not 0
-    if (((uintptr_t)mask & 15) == 0) {
-        const int whole = n >> 4;
+    int cnt = 0;
 #pragma unroll 4
-        for (int c = lane; c < whole; c += 64) {
-            const uint4 w = ((const uint4*)mask)[c];
-            cnt += bytes(w.x) + bytes(w.y) + bytes(w.z) + bytes(w.w);
-        }
-        if (lane < (n & 15)) cnt += mask[whole * 16 + lane] != 0;
-    } else if (((uintptr_t)mask & 3) == 0) {
-        const int whole = n >> 2;
-#pragma unroll 4
-        for (int c = lane; c < whole; c += 64) cnt += bytes(((const uint32_t*)mask)[c]);
-        if (lane < (n & 3)) cnt += mask[whole * 4 + lane] != 0;
-    } else {
-#pragma unroll 4
-        for (int t = lane; t < n; t += 64) cnt += mask[t] != 0;
+    for (int c = lane; c < words; c += 64) {
+        const uint4 w = ((const uint4*)(mask + head))[c];
+        cnt += bytes(w.x) + bytes(w.y) + bytes(w.z) + bytes(w.w);
     }
+    const int edge = lane < 16 ? lane : head + words * 16 + lane - 16;
+    if (lane < 16 ? lane < head : lane < 32 && edge < n) cnt += mask[edge] != 0;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
     return cnt;

@@ -495,6 +495,27 @@ def test_rows_with_an_index(rb, N, T, dtype, layout):
         assert torch.equal(ri.cpu()[:count].long(), torch.nonzero(mask.flatten()).flatten()) and bool((ri[count:] == -1).all())
 
 
+@pytest.mark.parametrize("N,T", [(3, 37), (2, 300), (2, 1027)])
+def test_rows_by_position_wherever_the_mask_starts(rb, N, T):
+    """Every distance of the mask from a 16-byte boundary, counted up to every position: the same rows, the same bits."""
+    print(f"mask alignment {N} x {T}", flush=True)
+    gen = torch.Generator().manual_seed(T)
+    mask = (torch.rand((N, T), generator=gen) < 0.6).to(torch.uint8)
+    hidden = torch.randn((N, T, 8), generator=gen).to(torch.bfloat16).cuda()
+    W = torch.randn((8, 8), generator=gen).to(torch.bfloat16).cuda()
+    tokens = torch.randint(0, 8, (N, T), generator=gen, dtype=torch.int32).cuda()
+    every, _ = rb.rapid_logprob_fwd(hidden, W, tokens, torch.ones((N, T), dtype=torch.uint8, device="cuda"))
+    rows = torch.nonzero(mask.flatten()).flatten()
+    for at in range(16):
+        buf = torch.ones(N * T + 32, dtype=torch.uint8, device="cuda")      # ones around the mask: nothing of them may be counted
+        m = buf[at:at + N * T].view(N, T)
+        m.copy_(mask)
+        logp, _ = rb.rapid_logprob_fwd(hidden, W, tokens, m)
+        _, _, index = rb.rapid_compaction(m)
+        torch.cuda.synchronize()
+        assert torch.equal(logp, every * m) and torch.equal(index.cpu()[:len(rows)].long(), rows)
+
+
 def test_compaction_time_is_that_of_the_positions(rb):
     """The same two million positions in 256 long and in 4096 short generations: with a wave for every 16 positions, each counting
     its generation up to there, the short ones took six times as long."""
