@@ -163,7 +163,7 @@ __device__ __forceinline__ int count_before(const uint8_t* mask, int n) {
 // the regions' last row tiles up (16 blocks per region).
 template <int PACK, bool GATHER>
 __global__ __launch_bounds__(256) void rows_by_position_kernel(RowsArgs a, int per_wave, int blocks_per_generation) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     const int64_t N = a.N, T = a.T;
     const int64_t b = blockIdx.x, main_blocks = N * blocks_per_generation;
     if (b >= main_blocks) {
@@ -180,12 +180,11 @@ __global__ __launch_bounds__(256) void rows_by_position_kernel(RowsArgs a, int p
                 a.counts_out[CNT_MR] = (int32_t)end;
             }
         }
-        const int64_t first = M + part * 16 + wave * 4;
-        for (int64_t j = first; j < first + 4 && j < end; ++j) fill_row(a, j, PACK != PACK_NONE);
+        for (int64_t j = M + part * waves + wave; j < end; j += 16 * waves) fill_row(a, j, PACK != PACK_NONE);
         return;
     }
     const int64_t n = b / blocks_per_generation;
-    const int64_t t0 = (b - n * blocks_per_generation) * 4 * per_wave + wave * per_wave;
+    const int64_t t0 = ((b - n * blocks_per_generation) * waves + wave) * per_wave;
     if (t0 >= T) return;
     const uint8_t* row = a.mask + n * T;
     const int64_t first = a.first_row ? a.first_row[n] : 0, i_mine = n * T + t0 + lane;
@@ -236,8 +235,12 @@ void launch_t(const RowsArgs& a, bool by_position, int64_t rows, hipStream_t st)
     if (by_position) {
         // small batches: a wave per position, all trips side by side; without rows to pack there is next to nothing per position
         const int per_wave = PACK == PACK_NONE ? 16 : a.N * a.T <= 32768 ? 1 : 4;
-        const int64_t per_generation = (a.T + 4 * per_wave - 1) / (4 * per_wave), fill = a.tokc ? (int64_t)a.entries * 16 : 0;
-        rows_by_position_kernel<PACK, GATHER><<<(unsigned)(a.N * per_generation + fill), 256, 0, st>>>(a, per_wave, (int)per_generation);
+        // blocks of no more waves than a generation has work for: a launch holds less than 2^32 threads (a block of four waves for each
+        // generation of a few positions would be refused from 16.8 M generations on)
+        const int64_t wanted = (a.T + per_wave - 1) / per_wave;
+        const int waves = wanted < 4 ? (int)wanted : 4;
+        const int64_t per_generation = (wanted + waves - 1) / waves, fill = a.tokc ? (int64_t)a.entries * 16 : 0;
+        rows_by_position_kernel<PACK, GATHER><<<(unsigned)(a.N * per_generation + fill), 64 * waves, 0, st>>>(a, per_wave, (int)per_generation);
     } else if constexpr (PACK != PACK_NONE) {
         rows_by_row_kernel<PACK, GATHER><<<(unsigned)((rows + 3) / 4), 256, 0, st>>>(a);
     }

@@ -537,6 +537,35 @@ def test_compaction_time_is_that_of_the_positions(rb):
     assert short <= 3.0 * long + 20.0
 
 
+def test_as_many_short_generations_as_before(rb):
+    """2^24 + 5 generations of one position through the fp32 step: a launch of 2^32 threads is refused, so a generation's rows may
+    not take a block of 256 threads."""
+    N, K, d, V = 2 ** 24 + 5, 4, 8, 8
+    print(f"{N} generations of one position", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    hidden = torch.randn((N, 1, d), generator=gen, device="cuda")
+    W = torch.randn((d, V), generator=gen, device="cuda")
+    tokens = torch.randint(0, V, (N, 1), generator=gen, device="cuda", dtype=torch.int32)
+    mask = (torch.rand((N, 1), generator=gen, device="cuda") < 0.9).to(torch.uint8)
+    rewards = torch.rand(N, generator=gen, device="cuda")
+    gid = (torch.arange(N, device="cuda") * K // N).to(torch.int32)
+    out = rb.rapid_iw_pg_loss_fwd_bwd(hidden, W, tokens, mask, None, rewards, gid, K)
+    torch.cuda.synchronize()
+    assert out.dev_status.item() == 0 and out.read_diag()["n_tokens"] == int(mask.sum())
+    mean = torch.stack([rewards[gid == k].double().mean() for k in range(K)])
+    for at in (slice(0, 4096), slice(N // 2, N // 2 + 4096), slice(N - 4096, N)):
+        m = mask[at, 0].double()
+        z = hidden[at, 0].double() @ W.double()
+        logp = torch.log_softmax(z, -1)
+        onehot = torch.nn.functional.one_hot(tokens[at, 0].long(), V).double()
+        g = -(rewards[at].double() - mean[gid[at].long()]) / N
+        dh = (g * m)[:, None] * ((onehot - logp.exp()) @ W.double().t())
+        assert ((logp * onehot).sum(-1) * m - out.logp_cur[at, 0].double()).abs().max() <= 2e-6
+        # the tolerances of the fp32 path
+        assert (dh - out.dhidden[at, 0].double()).norm() <= 1e-5 * dh.norm()
+        assert not out.dhidden[at, 0][m == 0].any()
+
+
 @pytest.mark.parametrize("rows", [1, 7, 8, 9, 300, 1024, 1025])       # 8 columns per block up to 1024 rows, 32 above
 def test_log_sum_exp_of_few_rows(rb, rows):
     """One order of summation whatever the launch: the rows of a short call have the bits of the same rows in a long one."""
