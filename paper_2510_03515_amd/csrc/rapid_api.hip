@@ -1090,6 +1090,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         cl.logp_cur = logp_cur; cl.logp_old = logp_behav; cl.logp_ref = clip->o.kl_beta != 0.f ? clip->logp_ref : nullptr;
         cl.seq_len = at<int32_t>(ws, p.seq_len); cl.counts = counts; cl.N = N; cl.T = T; cl.K = K;
         cl.rewards = rewards; cl.group_ids = group_ids; cl.runs = at<int32_t>(ws, p.gruns); cl.adv = adv;
+        cl.adv64 = N > CLIP_SCAN ? adv64 : nullptr;
         cl.adv_eps = clip->o.adv_eps; cl.std_ddof = clip->o.std_ddof;
         cl.row_index = row_index; cl.rowg = rowg; cl.dev_status = dev_status;
         cl.eps_low = clip->o.eps_low; cl.eps_high = clip->o.eps_high; cl.kl_beta = clip->o.kl_beta;

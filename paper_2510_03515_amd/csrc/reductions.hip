@@ -1218,8 +1218,47 @@ __device__ inline double clip_omega(const ClipArgs& a, int64_t n) {
     return M > 0 ? (double)a.loss_scale / (double)M : 0.0;
 }
 
-// One block per generation: its normalised advantage (every generation works its group's mean and deviation out by itself:
-// a group is a handful of rewards, and a launch is 5 us), its tokens' terms, each formed once for the sums of the generation and
+// (R - mean) / (std + eps) of a group's generations in [n_first, n_last), equal rewards give 0.  Its sums are taken by one wave
+// (ONE_WAVE: any of a block's) or by the block, over the group's run of the batch or, where some group has several, over the whole range.
+struct GroupScan { int64_t begin, end; };
+__device__ inline GroupScan group_scan(const ClipArgs& a, int32_t k, int64_t n_first, int64_t n_last) {
+    if (a.runs[3 * a.K] != 0) return {n_first, n_last};
+    return {a.runs[a.K + k] > n_first ? a.runs[a.K + k] : n_first, a.runs[2 * a.K + k] < n_last ? a.runs[2 * a.K + k] : n_last};
+}
+__device__ inline double reward_of(const ClipArgs& a, int64_t n) { const float r = a.rewards[n]; return isfinite(r) ? (double)r : 0.0; }
+struct GroupStats {
+    double mean, scale;     // scale: std + eps
+    __device__ double advantage(double r) const { return r != mean ? (r - mean) / scale : 0.0; }
+};
+template <bool ONE_WAVE>
+__device__ inline GroupStats group_stats(const ClipArgs& a, int32_t k, const GroupScan& s, double* sm) {
+    const int first = ONE_WAVE ? threadIdx.x & (WAVE - 1) : threadIdx.x, step = ONE_WAVE ? WAVE : blockDim.x;
+    auto total = [&](double v) { return ONE_WAVE ? wave_sum(v) : block_sum(v, sm); };
+    double cnt = 0.0, sum = 0.0, sq = 0.0;
+    for (int64_t m = s.begin + first; m < s.end; m += step)
+        if (a.group_ids[m] == k) { cnt += 1.0; sum += reward_of(a, m); }
+    cnt = total(cnt);
+    const double mean = total(sum) / cnt;
+    for (int64_t m = s.begin + first; m < s.end; m += step)
+        if (a.group_ids[m] == k) { const double dlt = reward_of(a, m) - mean; sq += dlt * dlt; }
+    sq = total(sq);
+    const double den = cnt - (double)a.std_ddof;
+    return {mean, (den > 0.0 ? sqrt(sq / den) : 0.0) + (double)a.adv_eps};
+}
+
+// A block per group: the advantages of its generations, where there are too many generations for each to look for itself.
+__global__ __launch_bounds__(256) void clip_advantages_kernel(ClipArgs a, const int32_t* __restrict__ gen_range) {
+    __shared__ double sm[16];
+    const int32_t k = blockIdx.x;
+    const GroupScan s = group_scan(a, k, gen_range ? gen_range[0] : 0, gen_range ? gen_range[1] : a.N);
+    if (s.begin >= s.end) return;
+    const GroupStats g = group_stats<false>(a, k, s, sm);
+    for (int64_t n = s.begin + threadIdx.x; n < s.end; n += blockDim.x)
+        if (a.group_ids[n] == k) a.adv64[n] = g.advantage(reward_of(a, n));
+}
+
+// One block per generation: its normalised advantage (up to CLIP_SCAN generations every one works its group's mean and deviation
+// out by itself, a launch less), its tokens' terms, each formed once for the sums of the generation and
 // for the row's coefficient.  The last block: the rows that fill the row tile up.  (One after the other, group_advantage_kernel, this one and
 // one for the rows took 16 us of a small step.)
 template <bool ONE_WAVE>
@@ -1233,34 +1272,15 @@ __global__ __launch_bounds__(ONE_WAVE ? WAVE : 1024) void clip_generations_kerne
     }
     const int64_t n_first = gen_range ? gen_range[0] : 0, n_last = gen_range ? gen_range[1] : a.N;
     if (n < n_first || n >= n_last) return;
-    // (R - mean) / (std + eps) over the group, equal rewards give 0
     const int32_t k = a.group_ids[n];
     const float mine = a.rewards[n];
     const int len = a.seq_len[n];
     const int64_t row0 = a.first_row[n];
     int bits = isfinite(mine) ? 0 : RAPID_STATUS_NONFINITE_REWARD;
     double adv = 0.0;
-    if (k < 0 || k >= a.K) {
-        bits |= RAPID_STATUS_BAD_GROUP;
-    } else {
-        int64_t begin = n_first, end = n_last;
-        if (a.runs[3 * a.K] == 0) {      // every group is one run of the batch
-            begin = a.runs[a.K + k] > begin ? a.runs[a.K + k] : begin;
-            end = a.runs[2 * a.K + k] < end ? a.runs[2 * a.K + k] : end;
-        }
-        double cnt = 0.0, sum = 0.0, sq = 0.0;
-        auto reward = [&](int64_t m) { const float r = a.rewards[m]; return isfinite(r) ? (double)r : 0.0; };
-        const int lane = threadIdx.x & (WAVE - 1);
-        for (int64_t m = begin + lane; m < end; m += WAVE)
-            if (a.group_ids[m] == k) { cnt += 1.0; sum += reward(m); }
-        cnt = wave_sum(cnt);
-        const double mean = wave_sum(sum) / cnt;
-        for (int64_t m = begin + lane; m < end; m += WAVE)
-            if (a.group_ids[m] == k) { const double dlt = reward(m) - mean; sq += dlt * dlt; }
-        sq = wave_sum(sq);
-        const double den = cnt - (double)a.std_ddof, sd = den > 0.0 ? sqrt(sq / den) : 0.0, num = reward(n) - mean;
-        adv = num != 0.0 ? num / (sd + (double)a.adv_eps) : 0.0;
-    }
+    if (k < 0 || k >= a.K) bits |= RAPID_STATUS_BAD_GROUP;
+    else if (a.adv64) adv = a.adv64[n];
+    else adv = group_stats<true>(a, k, group_scan(a, k, n_first, n_last), sm).advantage(reward_of(a, n));
     if (threadIdx.x == 0) a.adv[n] = (float)adv;
     const double omega = clip_omega(a, n);
     double sums[3] = {0.0, 0.0, 0.0};
@@ -1315,6 +1335,7 @@ __global__ void clip_finish_kernel(const double* __restrict__ loss_n, const doub
 }  // namespace
 
 void launch_clip_generations(const ClipArgs& a, const int32_t* gen_range, double* loss_n, double* clipped_n, double* kl_n, hipStream_t st) {
+    if (a.adv64) clip_advantages_kernel<<<(unsigned)a.K, block_threads(a.N, 256), 0, st>>>(a, gen_range);
     const unsigned threads = row_threads(a.T);
     (threads == WAVE ? &clip_generations_kernel<true> : &clip_generations_kernel<false>)<<<(unsigned)a.N + 1, threads, 0, st>>>(a, gen_range, loss_n, clipped_n, kl_n);
 }

@@ -1250,6 +1250,91 @@ def test_clip_pg_special_cases_and_chunks(rb):
         _check_clip(rb, spec, w, out, ref, None)
 
 
+# up to 2048 generations each one works its group out by itself, above a launch does it per group; several waves per generation from
+# 512 positions on
+@pytest.mark.parametrize("dtype,prompts,G,len_hi", [("f32", 6, 5, 24), ("f32", 4, 3, 600), ("f32", 512, 4, 2), ("f32", 683, 3, 2), ("bf16", 12, 4, 24),
+                                                    ("bf16", 683, 3, 2)])
+@pytest.mark.parametrize("groups", ["adjacent", "scattered", "one", "faulty"])
+def test_clip_pg_groups_anywhere(rb, dtype, prompts, G, len_hi, groups):
+    """Groups that are one run of the batch, scattered ones, the whole batch as one group; "faulty": scattered, with group ids out of
+    range and rewards that are not finite, which are flagged and count as no group (advantage 0) and as 0.  Every output against
+    the oracle, in both backward modes, and adjacent groups through the smallest cache."""
+    spec = wl.small_spec("clip_groups", dtype, d=16, V=40, prompts=prompts, G=G, len_lo=max(1, len_hi // 3), len_hi=len_hi, reward="uniform")
+    w, g, lp_old, lp_ref = _clip_inputs(rb, spec, seed=5)
+    H, W, tok, mask = _oracle_inputs(w)
+    N, T, d = g["hidden"].shape
+    K = w["K"]
+    rng = np.random.default_rng(N)
+    gid, R = _np(w["group_ids"]).astype(np.int32), _np(w["rewards"]).astype(np.float32)
+    if groups == "one":
+        gid, K = np.zeros(N, np.int32), 1
+    elif groups != "adjacent":
+        gid = rng.permutation(gid)
+    ref_gid, ref_R, ref_K, bits = gid.copy(), R.copy(), K, 0
+    if groups == "faulty":
+        gid, R = gid.copy(), R.copy()
+        lost = rng.choice(N, 5, replace=False)                      # each a group of its own for the oracle: advantage 0
+        gid[lost] = [-1, K, -7, K + 3, 2 ** 31 - 1]
+        ref_gid[lost] = K + np.arange(5)
+        ref_K = K + 5
+        odd = rng.choice(np.setdiff1d(np.arange(N), lost), 3, replace=False)
+        R[odd] = [np.nan, np.inf, -np.inf]
+        ref_R[odd] = 0.0
+        bits = rb.STATUS_BAD_GROUP | rb.STATUS_NONFINITE_REWARD
+    gid_g, R_g = torch.from_numpy(gid).cuda(), torch.from_numpy(R).cuda()
+    for variant in ("grpo", "dapo"):
+        o = rb.clip_pg_default_opts(variant)
+        ref = orc.clipped_pg_loss_fwd_bwd(H, W, tok, mask, _np(lp_old), _np(lp_ref), ref_R, ref_gid, ref_K, eps_low=o.eps_low,
+                                          eps_high=o.eps_high, kl_beta=o.kl_beta, norm_mode=o.norm_mode)
+        ref["logp_old"], ref["eps"] = _np(lp_old), (o.eps_low, o.eps_high)
+        ref["coef_of_logp"] = lambda lp, o=o, ref=ref: orc.clipped_token_coefficients(
+            lp, _np(lp_old), _np(lp_ref), mask, ref["adv"], o.eps_low, o.eps_high, o.kl_beta, o.norm_mode)[0]
+        modes = [(False, None)]
+        if dtype == "bf16":
+            modes.append((True, None))
+            if groups == "adjacent":
+                modes.append((True, rb.rapid_workspace_bytes(rb.OP_IW_PG_FWD_BWD_CACHED, N, T, d, spec.V, K, rb.DTYPE_BF16, minimum=True)))
+        for cache, nbytes in modes:
+            print(f"clip groups {dtype} {N} x {T} {groups} {variant} cache {cache} workspace {nbytes}", flush=True)
+            buf = rb.IwPgBuffers(g["hidden"], g["W"], K, workspace_bytes=nbytes, logits_cache=cache)
+            out = rb.rapid_clip_pg_loss_fwd_bwd(g["hidden"], g["W"], g["tokens"], g["mask"], lp_old, lp_ref, R_g, gid_g, K,
+                                                variant=variant, buffers=buf, logits_cache=cache)
+            torch.cuda.synchronize()
+            assert out.dev_status.item() == bits
+            out.dev_status.zero_()
+            _check_clip(rb, spec, w, out, ref, None)
+
+
+def test_clip_pg_time_of_one_large_group(rb):
+    """Advantages are linear work: 32 768 generations of one token in one group take about as long as in groups of four (3.5 times
+    while every generation looked through the whole group)."""
+    N = 32768
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    hidden = torch.randn((N, 1, 16), generator=gen, device="cuda")
+    W = torch.randn((16, 40), generator=gen, device="cuda")
+    tokens = torch.randint(0, 40, (N, 1), generator=gen, device="cuda", dtype=torch.int32)
+    mask = torch.ones((N, 1), dtype=torch.uint8, device="cuda")
+    lp, _ = rb.rapid_logprob_fwd(hidden, W, tokens, mask)
+    rewards = torch.rand(N, generator=gen, device="cuda")
+
+    def microseconds(K):
+        gid = (torch.arange(N, device="cuda") * K // N).to(torch.int32)
+        buf = rb.IwPgBuffers(hidden, W, K)
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                rb.rapid_clip_pg_loss_fwd_bwd(hidden, W, tokens, mask, lp, lp, rewards, gid, K, buffers=buf)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 5 * 1e3)
+        return min(times)
+    fours, one = microseconds(N // 4), microseconds(1)
+    print(f"clip step of {N} generations: groups of four {fours:.0f} us, one group {one:.0f} us", flush=True)
+    assert one <= 2.0 * fours
+
+
 def test_seq_logratio_and_adamw_entry_points(rb):
     """The ratio reduction as a call of its own (arbitrary masks, a non-finite stored log-prob), and the
     AdamW update of the inner loop over a few steps, both against the oracle."""
