@@ -1939,19 +1939,19 @@ static void launch_dh_dw_t(const DhArgs& h, const DwArgs& w, hipStream_t st) {
     dh_dw_kernel<S, WM, VD><<<2 * each, S::NT, S::LDS_BYTES, st>>>(h, w, (int)each);
     dh_dw_reduce_kernel<S, VD><<<dim3(cols_dh + (unsigned)tiles_dw, S::WI * S::WJ), S::NT, 0, st>>>(h, w, (int)each, (int)each, (int)cols_dh);
 }
-bool launch_dh_dw(const DhArgs& h, const DwArgs& w, hipStream_t st) {
-    // where both take tiles of 128 x 128, two of whose workgroups share a compute unit: one of each
-    constexpr size_t part = (size_t)MAX_UNITS * G4_128::BI * G4_128::BJ * 4;
-    if (!short_dh(h) || !short_dw(w) || h.part_bytes < 2 * part || h.part != w.part) return false;
+// scratch that the pieces of one of the two take
+constexpr size_t PAIR_PART = (size_t)MAX_UNITS * G4_128::BI * G4_128::BJ * 4;
+// where both take tiles of 128 x 128, two of whose workgroups share a compute unit: one of each
+bool dh_dw_together(const DhArgs& h, const DwArgs& w) { return short_dh(h) && short_dw(w) && h.part_bytes >= 2 * PAIR_PART && h.part == w.part; }
+void launch_dh_dw(const DhArgs& h, const DwArgs& w, hipStream_t st) {
     DhArgs a = h;
     DwArgs b = w;
     a.dpadR = b.dpadR = round_up(h.d, 128);
-    b.part = w.part + part / 4;
+    b.part = w.part + PAIR_PART / 4;
     // dW has the layout of the head that dHidden reads in place
     if (h.w.mode == W_VD) launch_dh_dw_t<W_VD, true>(a, b, st);
     else if (h.w.mode == W_DV) launch_dh_dw_t<W_DV, false>(a, b, st);
     else w.w_layout == RAPID_W_VD ? launch_dh_dw_t<W_PACKED, true>(a, b, st) : launch_dh_dw_t<W_PACKED, false>(a, b, st);
-    return true;
 }
 
 }  // namespace rapid

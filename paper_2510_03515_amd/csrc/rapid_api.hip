@@ -72,7 +72,8 @@ int static_scratch(void** out) {
 
 // Optional per-stage timing with HIP events on the caller's stream (off by default).
 enum Stage { ST_COMPACT = 0, ST_PACK, ST_FWD_LSE, ST_MERGE, ST_ESTIMATOR, ST_ZERO, ST_DZ, ST_DZ_T, ST_DH, ST_DW,
-             ST_F32, ST_CONVERT, ST_COUNT };
+             ST_F32, ST_CONVERT, ST_COUNT,
+             ST_DH_DW = ST_COUNT };   // one launch for both: half of its time goes to each (they have the same products)
 struct Profiler {
     bool on = false;
     static constexpr int MAX_SPANS = 8192;
@@ -830,8 +831,11 @@ int rapid_profile_read(double* ms_by_stage, int64_t* spans_by_stage, int n_stage
             g_prof.used = 0;
             return RAPID_ERR_HIP;
         }
-        ms_by_stage[g_prof.stage[i]] += ms;
-        spans_by_stage[g_prof.stage[i]] += 1;
+        const int id = g_prof.stage[i], first = id == ST_DH_DW ? ST_DH : id, last = id == ST_DH_DW ? ST_DW : id;
+        for (int k = first; k <= last; ++k) {
+            ms_by_stage[k] += ms / (last - first + 1);
+            spans_by_stage[k] += 1;
+        }
     }
     g_prof.used = 0;
     return RAPID_OK;
@@ -1233,7 +1237,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
                 // the last launch rounds a bf16 gradient on its way out
                 if (dw_bf16 && c == p.Cmax - 1 && r0 + wstep >= p.Rcap) wa.dW16 = (bf16_t*)dW_out;
                 wa.part = g_dh_split.load() ? at<float>(ws, p.dh_part) : nullptr; wa.part_bytes = dh_part_bytes();
-                if (whole && launch_dh_dw(ha, wa, st)) break;
+                if (whole && dh_dw_together(ha, wa)) {
+                    Span sp(ST_DH_DW, st);
+                    launch_dh_dw(ha, wa, st);
+                    break;
+                }
                 if (whole) {
                     Span sp(ST_DH, st);
                     launch_dh(ha, st);
@@ -1347,7 +1355,11 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             wa.dW = dW32; wa.w_layout = o.w_layout; wa.beta = (chunk > 0 || o.accumulate_dw) ? 1 : 0; wa.gi = g_gi_dw;
             if (dw_staged && m0 + step >= p.Mmax_pad) wa.dW16 = (bf16_t*)dW_out;   // the last launch rounds it on its way out
             wa.part = ha.part; wa.part_bytes = ha.part_bytes;
-            if (launch_dh_dw(ha, wa, st)) continue;
+            if (dh_dw_together(ha, wa)) {
+                Span sp(ST_DH_DW, st);
+                launch_dh_dw(ha, wa, st);
+                continue;
+            }
             {
                 Span sp(ST_DH, st);
                 launch_dh(ha, st);

@@ -348,8 +348,9 @@ struct DwArgs {           // dW (+)= Hc^T . dz over the chunk's rows
     size_t part_bytes = 0;
 };
 void launch_dw(const DwArgs& a, hipStream_t st);
-// both, of the same rows, side by side, if the batch is small enough for that to pay; false: nothing was launched
-bool launch_dh_dw(const DhArgs& h, const DwArgs& w, hipStream_t st);
+// whether the batch is small enough for both, of the same rows, to run side by side in one launch, and that launch
+bool dh_dw_together(const DhArgs& h, const DwArgs& w);
+void launch_dh_dw(const DhArgs& h, const DwArgs& w, hipStream_t st);
 void set_waves_per_workgroup(int n);   // 4, 8 or 16 waves per contraction workgroup
 bool default_waves();                  // each kernel runs its own choice
 void set_dw_deep(int on);              // dW with K steps of 32 rows and requests three steps ahead

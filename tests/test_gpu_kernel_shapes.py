@@ -537,6 +537,27 @@ def test_compaction_time_is_that_of_the_positions(rb):
     assert short <= 3.0 * long + 20.0
 
 
+@pytest.mark.parametrize("prompts,V", [(3, 1000), (40, 20000)])       # dHidden and dW in one launch, and in two
+@pytest.mark.parametrize("cache", [False, True])
+def test_stage_times_cover_dhidden_and_dw(rb, prompts, V, cache):
+    print(f"stage times {prompts} prompts, V {V}, cache {cache}", flush=True)
+    spec = wl.small_spec("stages", "bf16", d=256, V=V, prompts=prompts, G=4, len_lo=20, len_hi=60)
+    w, g = _make(spec)
+    logp_b, _ = rb.rapid_logprob_fwd(g["hidden"], g["W_old"], g["tokens"], g["mask"])
+    buf = rb.IwPgBuffers(g["hidden"], g["W"], w["K"], logits_cache=cache)
+    try:
+        rb.rapid_set_tuning(1, 1)
+        for _ in range(3):
+            rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], g["W"], g["tokens"], g["mask"], logp_b, g["rewards"], g["group_ids"], w["K"],
+                                        buffers=buf, logits_cache=cache)
+        stages = rb.rapid_profile_read()
+    finally:
+        rb.rapid_set_tuning(1, 0)
+    for name in ("compaction", "pack", "fwd_lse", "merge_lse", "estimator", "dz", "dh", "dw"):
+        ms, spans = stages[name]
+        assert spans % 3 == 0 and spans > 0 and ms > 0.0, (name, ms, spans)
+
+
 def test_as_many_short_generations_as_before(rb):
     """2^24 + 5 generations of one position through the fp32 step: a launch of 2^32 threads is refused, so a generation's rows may
     not take a block of 256 threads."""
