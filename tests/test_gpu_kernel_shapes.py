@@ -371,8 +371,11 @@ def test_smallest_workspace_has_room_for_other_tiles_only(rb, d, layout, cache):
 
 
 @pytest.mark.parametrize("prompts,G,length", [
-    (256, 4, 32),      # 1024 generations, 32768 positions: the most whose lengths and plan one block makes in the LDS
-    (256, 4, 33),      # lengths counted in a launch of their own, odd rows; more than one position per wave
+    (256, 4, 16),      # 1024 generations, 16384 positions: the most whose lengths and plan one block makes in the LDS
+    (256, 4, 15),      # the same with odd rows
+    (256, 4, 17),      # lengths counted in a launch of their own, plan in the LDS
+    (256, 4, 32),      # 32768 positions: the most of which a wave packs one
+    (256, 4, 33),      # more than one position per wave, odd rows
     (257, 4, 9),       # plan in memory
     (1, 3, 1),         # one position each
     (2, 3, 130), (3, 5, 258), (1, 2, 519),     # 8 to 64 lanes per generation, rows that are no whole words
@@ -440,6 +443,41 @@ def test_final_norm_backward_by_width(rb, d, mode):
     assert _rel(_np(out.dhidden), ref["dH"]) <= 2e-2 and _rel(_np(out.dW), ref["dW"]) <= 2e-2
     assert _rel(_np(out.drms_weight), ref["d_rms_weight"]) <= 2e-2
     assert np.abs(_np(out.drms_weight) - ref["d_rms_weight"]).max() <= 2.0 ** -6 * np.abs(ref["d_rms_weight"]).max()
+
+
+@pytest.mark.parametrize("d", [2048, 2056])       # one pass over a row, and two
+def test_final_norm_backward_of_more_regions_than_the_partial_sums_have_room_for(rb, d):
+    """The smallest cache makes thousands of regions of 256 rows of a large batch, whose partial sums of dL/dweight (a row each) are
+    more than the 128 MiB they lie in otherwise.  Few positions hold tokens: the same tokens as a batch of their own, without a
+    cache, give the same gradients."""
+    N, T, V, K, length = 8193, 256, 131072, 8193, 1
+    print(f"final norm in {2 * N + 1} regions, d {d}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    small = torch.randn((N, length, d), generator=gen, device="cuda").to(torch.bfloat16)
+    W = (torch.randn((d, V), generator=gen, device="cuda") * d ** -0.5).to(torch.bfloat16)
+    wgt = (1.0 + 0.3 * torch.randn(d, generator=gen, device="cuda")).to(torch.bfloat16)
+    tokens = torch.randint(0, V, (N, length), generator=gen, device="cuda", dtype=torch.int32)
+    ones = torch.ones((N, length), dtype=torch.uint8, device="cuda")
+    rewards = torch.rand(N, generator=gen, device="cuda")
+    gid = torch.arange(N, device="cuda", dtype=torch.int32)
+    coef = ((rewards - 0.5) / N).contiguous()
+    wide = lambda t: torch.cat([t, torch.zeros((N, T - length, *t.shape[2:]), dtype=t.dtype, device="cuda")], 1)
+    hidden, mask = wide(small), wide(ones)
+    nbytes = rb.rapid_workspace_bytes(rb.OP_IW_PG_FWD_BWD_CACHED, N, T, d, V, K, rb.DTYPE_BF16, minimum=True)
+    assert rb.rapid_logits_cache_rows(N, T, d, V, K, 0, nbytes) == 256
+    assert (2 * (N * T // 256) + 1) * d * 4 > 128 << 20
+    buf = rb.IwPgBuffers(hidden, W, K, workspace_bytes=nbytes)
+    got = rb.rapid_iw_pg_loss_fwd_bwd(hidden, W, wide(tokens), mask, None, rewards, gid, K, buffers=buf, logits_cache=True,
+                                      coef_override=coef, rms_weight=wgt)
+    torch.cuda.synchronize()
+    assert got.dev_status.item() == 0 and got.read_diag()["n_tokens"] == N * length
+    want = rb.rapid_iw_pg_loss_fwd_bwd(small, W, tokens, ones, None, rewards, gid, K, coef_override=coef, rms_weight=wgt)
+    torch.cuda.synchronize()
+    assert torch.equal(got.logp_cur[:, :length], want.logp_cur)
+    # two backward modes: dL/dh of both is rounded to bf16 from sums taken in another order
+    assert _rel(_np(got.drms_weight), _np(want.drms_weight)) <= 4e-3
+    assert _rel(_np(got.dhidden[:, :length]), _np(want.dhidden)) <= 4e-3
+    assert not got.dhidden[:, length:].any()
 
 
 @pytest.mark.parametrize("N,T", [(1, 1), (3, 5), (7, 33), (1, 4096), (1, 4097), (2, 4096), (64, 128), (73, 113)])   # up to 8192 positions, T <= 4096: no plan
