@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void f64_mfma_kernel(F64Operand A, F64Operand 
 }
 
 // dHidden and dW of a small shape side by side: two chains of a few trips to memory each that do not depend on each
-// other (640 rows x V = 1000 x d = 64: 10.8 and 8.8 us one after the other, 12.1 together).  The first h_blocks blocks are dHidden's.
+// other (640 rows x V = 1000 x d = 64: 10.9 and 8.8 us one after the other, 12.6 to 14.0 together).  The first h_blocks blocks are dHidden's.
 template <bool KB, bool MA>
 __global__ __launch_bounds__(256) void f64_pair_kernel(F64Operand hA, F64Operand hB, F32Gemm h, unsigned h_cols, unsigned h_blocks,
                                                        F64Operand wA, F64Operand wB, F32Gemm w, unsigned w_cols) {
@@ -227,7 +227,8 @@ __device__ inline double block_reduce(double v, double* sm, bool is_max) {
 }
 
 // one block per chunk row: lse over the V logits, log-prob of the sampled token.  PER > 0: V <= 256 PER, the row is loaded once
-// and stays in registers (in two passes over it 640 rows x V = 1000 took 6.2 us, now 4.8; 14 000 rows x 4096 104 -> 79).
+// and stays in registers (in two passes over it 640 rows x V = 1000 took 6.2 us, now 4.8; 4096 rows x 4096 34.6 -> 28.0).  Past 16 per
+// thread the gain goes on (4096 rows x 6144 49.5 us in two passes, 37.0 with 24 per thread; x 8192 62 and 46 with 32).
 template <int PER>
 __global__ __launch_bounds__(256) void f32_row_lse_kernel(const float* __restrict__ z, int64_t V, int64_t m0,
                                    const int32_t* __restrict__ tokc, const int32_t* __restrict__ row_index,

@@ -1608,7 +1608,9 @@ __global__ __launch_bounds__(S::NT) void dw_reduce_kernel(DwArgs a, int grid_of_
 }
 
 // dHidden and dW of a small batch side by side: neither fills the chip for longer than it takes to get going, and they do
-// not depend on each other.  The first grid_dh workgroups are dHidden's.  `add`: their second passes, the first tiles_dh columns of the grid dHidden's.
+// not depend on each other.  The first grid_dh workgroups are dHidden's; of their second passes in one launch (dh_dw_reduce_kernel) the
+// first tiles_dh columns of the grid.  d = 256, V = 4096, about 1800 tokens: 17.1 and 16.6 us, second passes 7.2 and 6.4, one after the other;
+// 20.8 and 9.3 together.
 template <class S, int WM, bool VD>
 __global__ __launch_bounds__(S::NT, 2) void dh_dw_kernel(DhArgs h, DwArgs w, int grid_dh) {
     extern __shared__ __attribute__((aligned(128))) char lds[];

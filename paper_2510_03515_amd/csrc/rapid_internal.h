@@ -110,7 +110,10 @@ struct RowsArgs {
     float *zy = nullptr, *refz = nullptr;
     const float* ref_logp = nullptr;            // [N, T]
 };
-constexpr int64_t ROWS_WITHOUT_PLAN = 8192;     // positions up to which the rows may do without a plan (first_row NULL)
+// Positions up to which the rows may do without a plan (first_row NULL): every wave then counts the batch's mask up to its place.
+// Log-probs at d = 1024, V = 256 without a plan and with one: 64 x 32 positions 35 and 38 us, 64 x 64 42 and 45, 64 x 128 57 and 60;
+// past the bound it depends on the shape (64 x 250 78 and 84, 1024 x 16 98 and 81).
+constexpr int64_t ROWS_WITHOUT_PLAN = 8192;
 // Positions per generation up to which calls with gradient rows take rows_by_position_kernel, whose waves count a generation's
 // mask up to their place.  Steps of V = 256 by position and with an index of the rows, cached: 64 x 4095, d = 1024 961 and 975 us, 64 x 512
 // 192 and 197, 1024 x 250 1022 and 974; just past the bound by position is still ahead (64 x 4097 947 and 963, 16 x 8192 551 and

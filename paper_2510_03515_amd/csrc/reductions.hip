@@ -825,9 +825,10 @@ __global__ __launch_bounds__(1024) void coefficients_kernel(CoefArgs a, double l
 
 // The whole estimator of a small batch in one block: log ratios of the generations, group advantages, coefficients, loss and
 // diagnostics, the rows' coefficients; what seq_logratio_kernel, group_advantage_kernel, coefficients_kernel and
-// row_coefficients_kernel do (same order of summation over the generations) in four dependent launches of 3 to 5 us each, next
-// to nothing of it work.  At most ESTIMATOR_LDS generations and groups, which stay in the LDS, and ESTIMATOR_POSITIONS positions:
-// one compute unit takes about 1 us per 1000 of them.  TOKENS false: more positions; the log ratios are there (s64, and tsum,
+// row_coefficients_kernel do in four dependent launches of 3 to 5 us each, next to nothing of it work.  All sums are taken in 64
+// bits, in an order that is fixed for a shape; it is that of the four where every group is one run of at most 64 generations and
+// there are as many threads as generations, else their last bits differ.  At most ESTIMATOR_LDS generations and groups, which stay in the LDS, and ESTIMATOR_POSITIONS positions:
+// one compute unit takes about 1 us per 1000 of them (32 x 32 positions 7.5 us, 64 x 48 9.6, 4 x 1024 15.1).  TOKENS false: more positions; the log ratios are there (s64, and tsum,
 // tmax) and the rows' coefficients are left to row_coefficients_kernel, so that two launches become one.  Whole steps, in one
 // block against this split: 64 x 8 positions 46 and 52 us, 64 x 64 58 and 61, 128 x 64 69 and 70, 64 x 250 96 and 92.
 constexpr int ESTIMATOR_LDS = 1024, ESTIMATOR_POSITIONS = 8192;

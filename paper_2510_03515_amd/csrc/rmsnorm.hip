@@ -206,8 +206,12 @@ void launch_rmsnorm_backward(const bf16_t* x, bf16_t* dh, int64_t d, const bf16_
                              const int32_t* counts, int stride, int regions, int64_t region_rows, const float* inv_rms, float* part,
                              size_t part_bytes, float* part_512, float* dweight, hipStream_t st) {
     const int C = (int)((d / 8 + 63) / 64);
+    // One pass up to 4 chunks per lane, two past them.  The gain does not end there: with 7 chunks per lane 880 rows at d = 3584 take
+    // 15 us instead of 20, 40 000 181 instead of 296.
     const bool narrow = C <= 4;
-    // rows per block: few for a small batch, whose rows then go side by side; more if the partial sums would not fit
+    // Rows per block: few for a small batch, whose rows then go side by side; more if the partial sums would not fit.  Both kernels
+    // at d = 1536 with 8, 16, 32 and 64 rows: 880 rows 11, 13, 18 and 27 us, 3000 14, 15, 19 and 29, 8192 23, 20, 21 and 29, 16 384 39,
+    // 33, 31 and 33, 40 000 88, 82, 82 and 94.
     int rows = narrow ? ((int64_t)regions * region_rows <= 8192 ? 8 : 32) : 32;
     auto blocks = [&]() { return (region_rows + rows - 1) / rows; };
     while (rows < 512 && (size_t)(blocks() * regions * d) * 4 > part_bytes) rows *= 2;
