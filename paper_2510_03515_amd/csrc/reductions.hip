@@ -823,6 +823,59 @@ __global__ __launch_bounds__(1024) void coefficients_kernel(CoefArgs a, double l
     if (threadIdx.x == 0) write_diag(a, sums, maxs, lam);
 }
 
+constexpr int ESTIMATOR_LDS = 1024, ESTIMATOR_POSITIONS = 8192;
+// Scattered groups: generations times groups up to which a team of lanes per group looks through the batch instead of a list of the
+// members (fp32 steps with either: 64 x 64 positions in fours 71.4 and 73.8 us, 128 x 64 118.8 and 119.8, in pairs 122.8 and 121.4, 256 x 16 88.4
+// and 79.2, 1024 x 8 254.8 and 136.2; side by side 128.3).
+constexpr int LIST_MEMBERS = 8192;
+// The generations of every group k in batch order, order[first[k] .. end[k]), where groups lie scattered: a counting sort over pieces of
+// 128 generations, each a wave's.  count [ESTIMATOR_LDS] is zero; byte p of a group's word counts its members in piece p, place[n] those
+// of n's group in front of it in its piece.  Generations without a group are left out.  (Its loops stay rolled: unrolled, their ballots
+// spill scalar registers of the whole kernel, 0.7 us of every call.)
+__device__ inline void list_members(const int32_t* gid, int N, int K, double* count, int32_t* first, int32_t* end, uint8_t* place, uint16_t* order) {
+    constexpr int PIECE = 2 * WAVE;
+    static_assert(ESTIMATOR_LDS <= 8 * PIECE, "a byte of a group's word per piece");
+    auto members = [&](int k, int pieces) {       // of group k in that many first pieces
+        uint64_t w = __builtin_bit_cast(uint64_t, count[k]);
+        if (pieces < 8) w &= (1ull << 8 * pieces) - 1ull;
+        return (int)(((w & 0x00ff00ff00ff00ffull) + (w >> 8 & 0x00ff00ff00ff00ffull)) * 0x0001000100010001ull >> 48);
+    };
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE, waves = blockDim.x / WAVE;
+#pragma unroll 1
+    for (int n0 = wave * PIECE; n0 < N; n0 += waves * PIECE) {
+#pragma unroll 1
+        for (int n = n0 + lane; n - lane < n0 + PIECE && n - lane < N; n += WAVE) {
+            const int g = n < N ? gid[n] : -1;
+            const bool in = g >= 0 && g < K;
+            unsigned long long same = __ballot(in);      // lanes of the same group
+#pragma unroll 1
+            for (int bit = 1; bit < ESTIMATOR_LDS; bit <<= 1) {
+                const unsigned long long set = __ballot(g & bit);
+                same &= g & bit ? set : ~set;
+            }
+            if (in) {
+                uint8_t& here = ((uint8_t*)(count + g))[n0 / PIECE];
+                const int before = __popcll(same & ((1ull << lane) - 1ull)), seen = here;
+                place[n] = (uint8_t)(seen + before);
+                if (before == 0) here = (uint8_t)(seen + __popcll(same));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the second half reads what the first half's lanes wrote
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < K; k += blockDim.x) end[k] = members(k, 8);
+    __syncthreads();
+    block_scan(end, K, first);
+    __syncthreads();
+    for (int n = threadIdx.x; n < N; n += blockDim.x) {
+        const int g = gid[n];
+        if (g >= 0 && g < K) order[first[g] + members(g, n / PIECE) + place[n]] = (uint16_t)n;
+    }
+    for (int k = threadIdx.x; k < K; k += blockDim.x) end[k] = first[k + 1];
+    __syncthreads();
+}
+
 // The whole estimator of a small batch in one block: log ratios of the generations, group advantages, coefficients, loss and
 // diagnostics, the rows' coefficients; what seq_logratio_kernel, group_advantage_kernel, coefficients_kernel and
 // row_coefficients_kernel do in four dependent launches of 3 to 5 us each, next to nothing of it work.  All sums are taken in 64
@@ -831,14 +884,15 @@ __global__ __launch_bounds__(1024) void coefficients_kernel(CoefArgs a, double l
 // one compute unit takes about 1 us per 1000 of them (32 x 32 positions 7.5 us, 64 x 48 9.6, 4 x 1024 15.1).  TOKENS false: more positions; the log ratios are there (s64, and tsum,
 // tmax) and the rows' coefficients are left to row_coefficients_kernel, so that two launches become one.  Whole steps, in one
 // block against this split: 64 x 8 positions 46 and 52 us, 64 x 64 58 and 61, 128 x 64 69 and 70, 64 x 250 96 and 92.
-constexpr int ESTIMATOR_LDS = 1024, ESTIMATOR_POSITIONS = 8192;
 template <bool PER_TOKEN, bool TOKENS>
 __global__ __launch_bounds__(1024) void small_estimator_kernel(EstimatorArgs a, double log_eta, double log_loss_scale) {
     constexpr int L = ESTIMATOR_LDS, LT = PER_TOKEN ? L : 1;
     __shared__ double sm[16 * 4], s_s[L], s_w[L], s_adv[L], s_tsum[LT], s_tmax[LT], s_part[3][16];
     double* const s_g = s_w;     // the coefficients take the weights' place
     __shared__ float s_r[L];
-    __shared__ int32_t s_gid[L], s_first[L], s_end[L];
+    __shared__ int32_t s_gid[L], s_first[L + 1], s_end[L];
+    __shared__ uint16_t s_order[L];
+    __shared__ uint8_t s_place[L];
     __shared__ int s_split, s_longest, s_bits;
     const int N = (int)a.N, K = (int)a.K, tid = threadIdx.x, threads = blockDim.x;
     const int64_t T = a.T;
@@ -945,17 +999,25 @@ __global__ __launch_bounds__(1024) void small_estimator_kernel(EstimatorArgs a, 
     }
     if (bits) atomicOr(&s_bits, bits);
     __syncthreads();
+    const bool split = s_split != 0, listed = split && N * K > LIST_MEMBERS;
+    if (listed) {
+        for (int i = tid; i < L; i += threads) s_adv[i] = 0.0;
+        __syncthreads();
+        list_members(s_gid, N, K, s_adv, s_first, s_end, s_place, s_order);
+        for (int i = tid; i < L; i += threads) s_adv[i] = 0.0;
+    }
     for (int k = tid; k < K; k += threads)
         if (s_first[k] >= 0) atomicMax(&s_longest, s_end[k] - s_first[k]);
     __syncthreads();
 
-    // group advantages: a team of lanes per group, over its run or (some group has several) over the whole batch
-    const bool split = s_split != 0;
-    const int team_log2 = split || s_longest > 16 ? 6 : 4, team = 1 << team_log2;
+    // group advantages: a team of lanes per group, over its run or (some group has several) over its list of members or the batch
+    const bool scan = split && !listed;
+    const int team_log2 = scan || s_longest > 16 ? 6 : 4, team = 1 << team_log2;
     for (int k = tid >> team_log2; k < K; k += threads >> team_log2) {
-        const int begin = split ? 0 : s_first[k] < 0 ? 0 : s_first[k], end = split ? N : s_end[k];
+        const int begin = scan || s_first[k] < 0 ? 0 : s_first[k], end = scan ? N : s_end[k];
         double cnt = 0.0, sum_wr = 0.0;
-        for (int n = begin + (tid & (team - 1)); n < end; n += team) {
+        for (int i = begin + (tid & (team - 1)); i < end; i += team) {
+            const int n = listed ? s_order[i] : i;
             if (s_gid[n] != k) continue;
             cnt += 1.0;
             sum_wr += s_w[n] * (double)s_r[n];
@@ -964,7 +1026,8 @@ __global__ __launch_bounds__(1024) void small_estimator_kernel(EstimatorArgs a, 
             cnt += __shfl_xor(cnt, o, WAVE);
             sum_wr += __shfl_xor(sum_wr, o, WAVE);
         }
-        for (int n = begin + (tid & (team - 1)); n < end; n += team) {
+        for (int i = begin + (tid & (team - 1)); i < end; i += team) {
+            const int n = listed ? s_order[i] : i;
             if (s_gid[n] != k) continue;
             const double r = (double)s_r[n], rest = sum_wr - s_w[n] * r;
             const double b = a.baseline_mode == 0 ? sum_wr / cnt : a.baseline_mode == 1 ? rest / cnt : cnt > 1.0 ? rest / (cnt - 1.0) : 0.0;

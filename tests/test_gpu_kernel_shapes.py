@@ -421,6 +421,70 @@ def test_estimator_of_a_small_batch(rb, prompts, G, length, kw, scattered):
     assert torch.equal(tl, out.tok_logratio) and torch.allclose(s, out.seq_logratio, rtol=2.0 ** -23, atol=0)
 
 
+# pieces of 128 generations listed by a wave each; from 4 waves to 16 in the block
+@pytest.mark.parametrize("K,G,T", [(512, 2, 3), (2, 2, 3), (13, 5, 3), (43, 3, 20), (64, 2, 40), (3, 300, 8), (257, 3, 40), (1000, 1, 8)])
+@pytest.mark.parametrize("kw", [dict(baseline_mode=2, eta=1.05), dict(ratio_level=1, normalized_grads=True)])
+@pytest.mark.parametrize("faulty", [False, True])
+def test_estimator_of_scattered_groups(rb, K, G, T, kw, faulty):
+    """Groups whose members lie anywhere; "faulty": with group ids out of range, which are flagged and belong to no group (advantage
+    0: a group of its own with reward 0 for the oracle), and a reward that is not finite, which counts as 0."""
+    N = K * G
+    print(f"scattered groups {K} x {G} x {T} {kw} faulty {faulty}", flush=True)
+    spec = wl.small_spec("scattered", "bf16", d=24, V=40, prompts=K, G=G, len_lo=1, len_hi=T, reward="uniform")
+    w, g = _make(spec)
+    gid = np.random.default_rng(N).permutation(_np(w["group_ids"]).astype(np.int32))
+    rewards = _np(w["rewards"]).astype(np.float32)
+    ref_gid, ref_rewards, ref_K, bits = gid.copy(), rewards.copy(), K, 0
+    if faulty and N >= 8:
+        for i, (n, bad) in enumerate(zip(np.random.default_rng(7).choice(N, 3, replace=False), (-1, K, 2 ** 31 - 1))):
+            gid[n], ref_gid[n], ref_rewards[n] = bad, K + i, 0.0
+        odd = int(np.flatnonzero((gid >= 0) & (gid < K))[N // 3])
+        rewards[odd] = np.inf
+        ref_rewards[odd] = 0.0
+        ref_K, bits = K + 3, rb.STATUS_BAD_GROUP | rb.STATUS_NONFINITE_REWARD
+    H, W, tok, mask = _oracle_inputs(w)
+    logp_b, _ = rb.rapid_logprob_fwd(g["hidden"], g["W_old"], g["tokens"], g["mask"])
+    out = rb.rapid_iw_pg_loss_fwd_bwd(g["hidden"], g["W"], g["tokens"], g["mask"], logp_b, torch.from_numpy(rewards).cuda(),
+                                      torch.from_numpy(gid).cuda(), K, **kw)
+    torch.cuda.synchronize()
+    assert out.dev_status.item() == bits
+    out.dev_status.zero_()
+    ref = orc.iw_pg_loss_fwd_bwd(H, W, tok, mask, _np(logp_b), ref_rewards, ref_gid, ref_K, **kw)
+    ref["slack"] = pb.coefficient_slack(ref, ref_rewards, mask)
+    _check_pair(rb, spec, out, ref)
+
+
+def test_estimator_time_of_scattered_groups(rb):
+    """512 pairs among 1024 generations take about as long scattered as side by side (1.9 times as long while a team of lanes looked
+    through the batch for every group)."""
+    N, T = 1024, 8
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    hidden = torch.randn((N, T, 16), generator=gen, device="cuda")
+    W = torch.randn((16, 40), generator=gen, device="cuda")
+    tokens = torch.randint(0, 40, (N, T), generator=gen, device="cuda", dtype=torch.int32)
+    mask = torch.ones((N, T), dtype=torch.uint8, device="cuda")
+    lp, _ = rb.rapid_logprob_fwd(hidden, W, tokens, mask)
+    rewards = torch.rand(N, generator=gen, device="cuda")
+    buf = rb.IwPgBuffers(hidden, W, N // 2)
+
+    def microseconds(gid):
+        times = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                rb.rapid_iw_pg_loss_fwd_bwd(hidden, W, tokens, mask, lp, rewards, gid, N // 2, buffers=buf)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) / 10 * 1e3)
+        return min(times)
+    adjacent = (torch.arange(N, device="cuda") // 2).to(torch.int32)
+    side_by_side = microseconds(adjacent)
+    scattered = microseconds(adjacent[torch.randperm(N, generator=gen, device="cuda")].contiguous())
+    print(f"step of 512 pairs: side by side {side_by_side:.0f} us, scattered {scattered:.0f} us", flush=True)
+    assert scattered <= 1.4 * side_by_side
+
+
 @pytest.mark.parametrize("d", [8, 512, 520, 1032, 1544, 2048, 2056])      # 1 to 4 chunks of 16 bytes per lane, and wider rows
 @pytest.mark.parametrize("mode", ["recompute", "chunks"])
 def test_final_norm_backward_by_width(rb, d, mode):
