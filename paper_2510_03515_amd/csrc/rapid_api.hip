@@ -1175,6 +1175,10 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
             pack_w(p, ws, W, o.w_layout, io.pack, st);
             compact_rows(p, ws, io, plan, st);
         }
+        if (clip) {
+            Span sp(ST_ESTIMATOR, st);
+            launch_clip_advantages(cl, st);
+        }
         const int cst = g_cached_step_tiles.load();
         const int64_t cstep = cst > 0 ? ((int64_t)cst * ROW_TILE < p.Rcap ? (int64_t)cst * ROW_TILE : p.Rcap) : p.Rcap;
         const int wst = g_cached_dw_step_tiles.load();
@@ -1301,6 +1305,7 @@ static int fused_call(const char* name, const void* hidden, const void* W, const
         // as the plan of run_forward has them
         cl.first_row = io.idle.idle ? at<int32_t>(ws, p.gen_row0) : at<int32_t>(ws, p.cu);
         cl.region = io.idle.idle ? p.Mmax_pad : INT64_MAX / 4; cl.row_counts = counts;
+        launch_clip_advantages(cl, st);
         launch_clip_generations(cl, nullptr, at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), st);
         launch_clip_finish(at<double>(ws, p.g64), at<double>(ws, p.tsum), at<double>(ws, p.tmax), N, counts, loss_out, clip->diag, st);
     } else {

@@ -149,7 +149,7 @@ struct ClipArgs {
     float eps_low, eps_high, kl_beta, loss_scale; int norm_mode;
     const float* rewards; const int32_t *group_ids, *runs; float adv_eps; int std_ddof;
     float* adv;                                      // [N]
-    double* adv64;                                   // NULL, or [N] scratch: the advantages are formed in a launch of their own
+    double* adv64;                                   // NULL, or [N] scratch: launch_clip_advantages forms the advantages
     // the generations' compact rows (as in RowsArgs), and dLoss/dlogp of the rows below row_counts[CNT_MR]
     const int32_t *first_row, *row_index, *row_counts; int64_t region;
     float* rowg;
@@ -158,8 +158,10 @@ struct ClipArgs {
 // Generations up to which each one looks through its group (or through the whole batch where some group lies scattered); above, a
 // launch does it per group, because all of them looking is quadratic work.  Steps (d = 16, V = 40) with each looking and with the launch:
 // 2048 x 8 positions in groups of four 200 and 203 us, as one group 212 and 207; 4096 x 4 206 and 210, 237 and 222, scattered 223 and 220;
-// 20 000 x 1 302 and 310, 794 and 374.
-constexpr int64_t CLIP_SCAN = 2048;
+// 8192 x 2 219 and 224, 285 and 249, scattered 266 and 253; 20 000 x 1 302 and 310, 794 and 374.
+constexpr int64_t CLIP_SCAN = 4096;
+// with adv64, once a call and behind its plan
+void launch_clip_advantages(const ClipArgs& a, hipStream_t st);
 // advantages, the rows' coefficients, and per generation (in gen_range): its share of the loss, its clipped tokens, the sum of
 // its tokens' KL estimates
 void launch_clip_generations(const ClipArgs& a, const int32_t* gen_range, double* loss_n, double* clipped_n, double* kl_n, hipStream_t st);

@@ -1311,10 +1311,10 @@ __device__ inline GroupStats group_stats(const ClipArgs& a, int32_t k, const Gro
 }
 
 // A block per group: the advantages of its generations, where there are too many generations for each to look for itself.
-__global__ __launch_bounds__(256) void clip_advantages_kernel(ClipArgs a, const int32_t* __restrict__ gen_range) {
+__global__ __launch_bounds__(256) void clip_advantages_kernel(ClipArgs a) {
     __shared__ double sm[16];
     const int32_t k = blockIdx.x;
-    const GroupScan s = group_scan(a, k, gen_range ? gen_range[0] : 0, gen_range ? gen_range[1] : a.N);
+    const GroupScan s = group_scan(a, k, 0, a.N);
     if (s.begin >= s.end) return;
     const GroupStats g = group_stats<false>(a, k, s, sm);
     for (int64_t n = s.begin + threadIdx.x; n < s.end; n += blockDim.x)
@@ -1398,8 +1398,10 @@ __global__ void clip_finish_kernel(const double* __restrict__ loss_n, const doub
 
 }  // namespace
 
+void launch_clip_advantages(const ClipArgs& a, hipStream_t st) {
+    if (a.adv64) clip_advantages_kernel<<<(unsigned)a.K, block_threads(a.N, 256), 0, st>>>(a);
+}
 void launch_clip_generations(const ClipArgs& a, const int32_t* gen_range, double* loss_n, double* clipped_n, double* kl_n, hipStream_t st) {
-    if (a.adv64) clip_advantages_kernel<<<(unsigned)a.K, block_threads(a.N, 256), 0, st>>>(a, gen_range);
     const unsigned threads = row_threads(a.T);
     (threads == WAVE ? &clip_generations_kernel<true> : &clip_generations_kernel<false>)<<<(unsigned)a.N + 1, threads, 0, st>>>(a, gen_range, loss_n, clipped_n, kl_n);
 }

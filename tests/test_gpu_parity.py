@@ -1250,10 +1250,10 @@ def test_clip_pg_special_cases_and_chunks(rb):
         _check_clip(rb, spec, w, out, ref, None)
 
 
-# up to 2048 generations each one works its group out by itself, above a launch does it per group; several waves per generation from
+# up to 4096 generations each one works its group out by itself, above a launch does it per group; several waves per generation from
 # 512 positions on
-@pytest.mark.parametrize("dtype,prompts,G,len_hi", [("f32", 6, 5, 24), ("f32", 4, 3, 600), ("f32", 512, 4, 2), ("f32", 683, 3, 2), ("bf16", 12, 4, 24),
-                                                    ("bf16", 683, 3, 2)])
+@pytest.mark.parametrize("dtype,prompts,G,len_hi", [("f32", 6, 5, 24), ("f32", 4, 3, 600), ("f32", 1024, 4, 2), ("f32", 1366, 3, 2), ("bf16", 12, 4, 24),
+                                                    ("bf16", 1366, 3, 2)])
 @pytest.mark.parametrize("groups", ["adjacent", "scattered", "one", "faulty"])
 def test_clip_pg_groups_anywhere(rb, dtype, prompts, G, len_hi, groups):
     """Groups that are one run of the batch, scattered ones, the whole batch as one group; "faulty": scattered, with group ids out of
